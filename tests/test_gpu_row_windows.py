@@ -1,0 +1,74 @@
+"""Rows of [B, D, n] that begin and end anywhere relative to the 16-byte boundaries: every length around the
+edges of a vector, a lane, a wave and a workgroup, pointers that start off a boundary together, few rows and
+many (the plan changes at 512), and the ranges in which a complex output is evaluated in float64."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2311_06281_amd import workloads
+
+import test_gpu_cross_product as cross
+from test_gpu_cross_product import gpu  # noqa: F401  (fixture)
+
+pytestmark = pytest.mark.gpu
+
+# (rows, n): one and several rows per wave, ends of lanes of 8, 16 and 32 steps, of waves and of tiles
+SHAPES = [(5, 1), (300, 2), (131, 3), (700, 7), (65, 9), (130, 13), (77, 31), (64, 33), (40, 63), (33, 101), (20, 129), (21, 249),
+          (9, 255), (600, 257), (3, 300), (530, 389), (520, 505), (515, 511), (6, 513), (70, 1017), (66, 1021), (65, 1025),
+          (65, 2041), (64, 2045), (3, 2047), (513, 2047), (514, 2500), (2, 4093), (513, 3001), (2, 8191), (514, 4097),
+          (2, 16382), (1, 16383), (1, 16385), (2, 24577)]
+
+
+@pytest.mark.parametrize("mode", list(cross.MODES))
+@pytest.mark.parametrize("bf16", [False, True])
+def test_rows_off_the_vector_boundaries(gpu, mode, bf16):
+    rng = np.random.default_rng(sum(map(ord, mode)) + int(bf16))
+    for i, (rows, n) in enumerate(SHAPES):
+        a, b, x0 = cross._inputs(rng, (1, rows, n), "BDN", mode)
+        if bf16:  # the bf16-rounded values are what is stored: they define the problem
+            a = workloads.bf16_bits_to_f32(workloads.f32_to_bf16_bits(a)).reshape(a.shape)
+            b = workloads.bf16_bits_to_f32(workloads.f32_to_bf16_bits(b)).reshape(b.shape)
+        for offset in ((0, 3) if i % 2 else (0, 4)):
+            print(f"[windows] {mode} bf16={bf16} rows={rows} n={n} offset={offset}", flush=True)
+            got = cross._run(gpu, a, b, x0, "BDN", cross.MODES[mode], bf16, offset_elems=offset)
+            cross._check(got, a, b, x0, "BDN", mode)
+
+
+# Positive numbers, so that nothing cancels and log x_t is as good as its largest term: every step of the
+# log-domain form rounds a logarithm of size at most L to L 2^-24 (base 2), and n such roundings of
+# random sign, five standard deviations of them, stay below 5 sqrt(n) L 2^-24 ln 2; 2e-6 for the
+# hardware logarithm and exponential.  The float64 form rounds once.
+@pytest.mark.parametrize("rows,n", [(60, 41), (20, 700), (12, 3001), (520, 1100)])
+def test_complex_output_in_and_out_of_the_float64_range(gpu, rows, n):
+    rng = np.random.default_rng(n)
+    a = rng.uniform(0.7, 1.3, (rows, n)).astype(np.float32)
+    b = rng.uniform(0.1, 1.0, (rows, n)).astype(np.float32)
+    x0 = rng.uniform(0.5, 2.0, rows).astype(np.float32)
+    at = n // 2
+    a[0, at] = 1e-9            # below 2^-18
+    a[1, at] = 1e4             # above 2^8
+    a[2, at] = 0.0             # restarts the row
+    b[3, at] = 1e-25           # below 2^-60
+    b[4, at] = 1e25            # above 2^60
+    b[5] = 0.0                 # only x_0
+    x0[6] = 0.0
+    x0[7], b[7] = 0.0, 0.0     # x = 0 throughout
+    a[8], b[8] = 3.0, 0.0      # leaves float64 where n is long enough
+    a[9], b[9] = 2.0 ** -7, 0.0
+    a[10], b[10] = 2.0 ** -17, 1.0
+    a[11, : at], a[11, at:], b[11] = 2.0 ** -9, 2.0 ** 7, 0.0
+    got = cross._run(gpu, a[None], b[None], x0, "BDN", cross.MODES["signed_clog"], False)[0]
+    for r in list(range(12)) + [rows - 1]:
+        # (the oracle's states leave float64 below 2^-1074: rows that only scale x_0 have a closed form)
+        if np.all(b[r] == 0.0):
+            with np.errstate(divide="ignore"):
+                ref = np.log(np.abs(np.float64(x0[r]))) + np.cumsum(np.log(a[r].astype(np.float64))) + 0j
+        else:
+            ref = oracle.seq_clog_scaled(a[r], b[r], x0[r])
+        re = got[r, :, 0].astype(np.float64)
+        zero = np.isneginf(ref.real)
+        assert np.array_equal(np.isneginf(re), zero), r
+        assert np.all(got[r, ~zero, 1] == 0.0), r
+        size = max(1.0, float(np.max(np.abs(ref.real[~zero]), initial=0.0)) / np.log(2.0))
+        err = np.max(np.abs(re[~zero] - ref.real[~zero]), initial=0.0)
+        assert err <= 5 * np.sqrt(n) * size * 2.0 ** -24 * np.log(2.0) + 2e-6, (r, err)
