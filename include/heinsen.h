@@ -128,8 +128,8 @@ int heinsen_scan(const void *a_or_log_a, const void *b_or_log_b, const void *x0,
  * never calls hipMalloc, hipFree or any allocating routine: the inter-tile carries live in a fixed
  * 48 MiB device array that is part of the library (each GPU the library runs on holds its own copy
  * until the process ends).  Results are those of heinsen_scan bit for bit, except for large [B, n, D]
- * shapes whose preferred (wider) tiles would not fit the array: those run with the narrower tiles, whose
- * float32 rounding differs in the last bits.
+ * shapes whose preferred (wider) tiles or carry records would not fit the array: those run with narrower
+ * tiles or fewer records, whose float32 rounding differs in the last bits.
  *
  *   limit   : shapes whose carries do not fit are refused with HEINSEN_ERR_SCRATCH_LIMIT and nothing is
  *             launched.  In records of 8 bytes, 256 + the following must stay within 6 * 2^20:

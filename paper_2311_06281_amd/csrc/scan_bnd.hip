@@ -16,9 +16,9 @@
 // another, and each die streams through a compact part of memory.
 //
 // Variations chosen on the host (make_plan): the tile shape; fewer waves per tile for short sequences, no
-// tickets at all when a column is one short tile; with few columns, longer groups and a second carry
-// level (SG); with fewer than 33 channels, several batch items side by side in the lanes of a column
-// (PACKB).
+// tickets at all when a column is one short tile; with few columns, a second carry level whose records the
+// waves of a tile share (TREE); where channels do not fill the lanes, columns of channels of several batch
+// items (DENSE).
 //
 // What is computed is Sec. 4's expression applied by parts (Sec. 1, footnote on associativity); the
 // arithmetic is in heinsen_math.hpp.
@@ -37,10 +37,9 @@ struct BndParams {
     int64_t D, n;
     int x0_stride;    // 0: one x0 for all, 1: x0[b*D + d]
     int cols_per_b;   // ceil(D / CH)
-    int ncols;        // B * cols_per_b; narrow rows (PACKB): ceil(B / bpack)
-    int64_t B;        // PACKB only below: batch items,
-    int dp_shift;     //   log2 of the lanes one batch item takes (the power of two >= D),
-    int bpack;        //   batch items per 64-lane column = 64 >> dp_shift
+    int ncols;        // B * cols_per_b; DENSE: ceil(B * D / lanes)
+    int64_t nchan;    // DENSE: B * D,
+    int lanes;        //   channels per column
     int nchunks;      // ceil(n / (NW*T))
     uint32_t ntiles;  // ncols * nchunks; tile id = chunk * ncols + col
     int nq;           // ticket queues in use (1 or 8); workgroup i draws from queue i mod nq
@@ -48,39 +47,43 @@ struct BndParams {
     uint32_t draws_per_q; // workgroups per queue = grid size / nq
     rec_t *header;    // scratch header (ticket queues); null when the launch needs no carries
     rec_t *agg;       // [ntiles][2][CH]  tile summaries: plane 0 = {A | signs}, plane 1 = {M}
+                      // (the last tile of a group has no use for its own: TREE: its group's is there instead)
     rec_t *state;     // [ngroups][ncols][2][CH] state at the start of a group: float64 log2|x| in two records
                       // (high word | sign, low word)
-                      // (SG > 0: [nsuper][ncols][2][CH], at the start of a super-group of SG groups)
-    rec_t *gagg;      // SG > 0: [ngroups][ncols][2][CH] group summaries, planes as in agg
+                      // (TREE: [nsuper][ncols][2][CH], at the start of a super-group of G groups)
     uint32_t spin_limit;
     uint32_t drop_tile;
     Timeline tl;
 };
 
-// every element is touched once: non-temporal accesses keep the stream out of the caches' way
-template <typename InT>
+// How a kernel touches memory; every element is used once.  (A compile-time choice: written as a run-time
+// branch the optimiser merges the two kinds of access into plain ones.)
+//   kKeepOut: inputs past the caches, output left in them for whoever consumes it next;
+//   kStream:  both past the caches: the output is larger than the last-level cache;
+//   kShared:  rows that do not keep to 128-byte lines: neighbouring columns (and neighbouring steps, where an
+//             item's channels are fewer than a line) read and write parts of the same lines, which stay in
+//             the die's L2 for that.
+enum Mem { kKeepOut, kStream, kShared };
+
+template <int MEM, typename InT>
 __device__ __forceinline__ float load_elem(const InT *p)
 {
-    return widen(__builtin_nontemporal_load(p));
+    return MEM == kShared ? widen(*p) : widen(__builtin_nontemporal_load(p));
 }
-
-// NT: the output is larger than the last-level cache and is written past it; otherwise it is written
-// normally and stays cached for whoever consumes it next.  (A compile-time choice: written as a run-time
-// branch the optimiser merges the two stores into one plain store.)
-template <bool NT>
+template <int MEM>
 __device__ __forceinline__ void store_elem(float *p, float v)
 {
-    if (NT)
+    if (MEM == kStream)
         __builtin_nontemporal_store(v, p);
     else
         *p = v;
 }
-template <bool NT>
+template <int MEM>
 __device__ __forceinline__ void store_pair(float *p, float re, float im)
 {
     typedef float vec_t __attribute__((ext_vector_type(2)));
     const vec_t x = {re, im};
-    if (NT)
+    if (MEM == kStream)
         __builtin_nontemporal_store(x, reinterpret_cast<vec_t *>(p));
     else
         *reinterpret_cast<vec_t *>(p) = x;
@@ -109,36 +112,42 @@ __device__ __forceinline__ void lds_await(volatile uint32_t *flag)
 
 // One tile.  The NW waves of the workgroup stand CG side by side along the channels and TS = NW / CG deep
 // along time; a lane owns one channel for T steps.  G tiles per group along time.  SB: keep the scheduler
-// from hoisting work across time steps (bounds register pressure).  PACKB: fewer than 64 channels -- the
-// 64 lanes of a column are the channels of several batch items side by side (same tiles, carries and
-// arithmetic; only the lane -> memory mapping differs, and a wave's accesses are then pieces of D
-// elements, one per batch item).  SG > 0: a second carry level for launches of few columns, where the
-// chain of group states would bound the launch: the last tile of a group also publishes the summary of
-// its group, states are handed on only from one super-group of SG groups to the next, and a tile folds
-// the summaries of the earlier groups of its super-group (a second round of record loads, into the
-// registers of the first).
+// from hoisting work across time steps (bounds register pressure).  DENSE: the lanes of a column are up to
+// 64 adjacent channels of all B * D, whatever batch items they belong to (same tiles, carries and
+// arithmetic; only the lane -> memory mapping differs: a wave's accesses are pieces of rows of one or more
+// batch items).  TREE: launches of few columns, where the chain of group states would bound the launch (2 x
+// 131072 x 96: 203 us, of which a tile waited 34 of its 43 us): the last tile of a group also publishes the
+// summary of its group, and states are handed on only from one super-group of G groups to the next.  A
+// tile then reads up to G - 1 tile summaries, G - 1 group summaries and one state; each of its waves fetches
+// and folds a part of them beside its own loads, and the first wave folds the parts.
 //
 // No wave waits for more than it needs.  The first wave along time of each 64-channel column fetches the
 // carry records, forms the state at the start of the tile and hands it to the waves behind it through
 // LDS; a later wave waits only for the summaries of the waves before it in its own column; the last wave
 // along time publishes the tile's summary (and, closing a group, the state for the next group).  `flags`
 // are TS*CG + CG words of LDS, zero when the tile begins.
-template <int DOM, bool LOG_IN, bool LOG_OUT, typename InT, int T, int NW, int G, bool SB, bool PACKB, int SG, int CG, bool NT>
+template <int DOM, bool LOG_IN, bool LOG_OUT, typename InT, int T, int NW, int G, bool SB, bool DENSE, bool TREE, int CG, int MEM>
 __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile, const uint32_t epoch, volatile uint32_t *flags)
 {
     constexpr bool SIGNED = DOM == kSigned;
     constexpr int CH = 64 * CG;  // channels of the tile
     constexpr int TS = NW / CG;  // waves one after the other along time
-    constexpr int GP = G > 1 ? G - 1 : 1;
+    constexpr int PT = TREE ? G / TS : (G > 1 ? G - 1 : 1); // summaries of each level a wave fetches
     static_assert(T <= 32, "one sign word per channel");
     static_assert(NW % CG == 0, "the waves form a CG x TS grid");
-    static_assert(!PACKB || CG == 1, "narrow rows are mapped one channel per lane");
-    static_assert(SG == 0 || (SG <= G && G > 1), "the second round of records reuses the registers of the first");
+    static_assert(!DENSE || CG == 1, "dense columns are mapped one channel per lane");
+    static_assert(!TREE || (CG == 1 && TS > 1 && G % TS == 0), "the waves of a tile share the summaries evenly");
     __shared__ float lds_A[TS][CH];
     __shared__ float lds_M[TS][CH];
     __shared__ uint32_t lds_S[SIGNED ? TS : 1][CH];
     __shared__ double lds_startL[CH]; // float64: the wave that closes a group hands it on as it is
     __shared__ uint32_t lds_startS[CH];
+    // TREE: every wave's fold of its part of the tile summaries [0] and of the group summaries [1]
+    __shared__ float lds_partA[TREE ? 2 : 1][TREE ? TS : 1][CH], lds_partM[TREE ? 2 : 1][TREE ? TS : 1][CH];
+    __shared__ uint32_t lds_partS[TREE ? 2 : 1][TREE ? TS : 1][CH];
+    // and, while the records are waited for, the wave's fold of the waves before it (registers are full)
+    __shared__ float lds_preA[TREE ? TS : 1][CH], lds_preM[TREE ? TS : 1][CH];
+    __shared__ uint32_t lds_preS[TREE ? TS : 1][CH];
 
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); // wave-uniform, kept in an SGPR
@@ -147,6 +156,7 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     const int wc = w % CG, ts = w / CG;
     volatile uint32_t *flag_run = flags;              // [TS][CG]: the wave's summary is in LDS
     volatile uint32_t *flag_start = flags + TS * CG;  // [CG]: the column's start state is in LDS
+    volatile uint32_t *flag_part = flags + TS * CG + CG; // TREE: [2][TS]: the wave's folds are in LDS
 
     const int chunk = (int)(tile / (uint32_t)p.ncols);
     const int col = (int)(tile % (uint32_t)p.ncols);
@@ -163,14 +173,13 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     bool chan_ok;    // the lane has a channel
     int64_t ubase;   // wave-uniform part of the addresses
     int64_t x0_at;   // the channel's place in x0
-    if constexpr (PACKB) {
-        const int bb = lane >> p.dp_shift;               // batch item inside the column
-        const int d = lane & ((1 << p.dp_shift) - 1);    // channel
-        const int64_t b = (int64_t)col * p.bpack + bb;
-        chan_ok = d < p.D && b < p.B;
-        moff = (uint32_t)(bb * (int)(p.n * p.D) + d);    // the host checks that this fits 31 bits
-        ubase = ((int64_t)col * p.bpack * p.n + t0) * p.D;
-        x0_at = b * p.D + d;
+    if constexpr (DENSE) {
+        const uint32_t D = (uint32_t)p.D, first_chan = (uint32_t)col * (uint32_t)p.lanes, chan = first_chan + (uint32_t)lane;
+        const uint32_t b0 = first_chan / D, bb = chan / D;   // batch items of the column's first lane and of this one
+        chan_ok = lane < p.lanes && chan < p.nchan;
+        moff = (bb - b0) * (uint32_t)(p.n * p.D) + (chan - bb * D); // the host checks that this fits 31 bits
+        ubase = ((int64_t)b0 * p.n + t0) * p.D;
+        x0_at = chan;
     } else {
         const int64_t d0 = (int64_t)cg * CH + c;
         chan_ok = d0 < p.D;
@@ -185,36 +194,56 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     //      flight: once the kernel is past its first round the earlier tiles of the group have usually
     //      published, and the records then arrive ahead of the tile's own loads at no cost in latency ---
     const bool first = ts == 0; // wave-uniform
-    rec_t rA[GP], rM[GP], rS = 0, rS2 = 0;
-    const int q = SG > 0 ? g / (SG > 0 ? SG : 1) : 0;  // super-group, and the group's place in it
-    const int gi = SG > 0 ? g % (SG > 0 ? SG : 1) : 0;
+    const bool fetches = TREE || first;
+    rec_t rA[PT], rM[PT], gA[TREE ? PT : 1], gM[TREE ? PT : 1], rS = 0, rS2 = 0;
+    const int q = TREE ? g / G : g;   // TREE: super-group, and the group's place in it
+    const int gi = TREE ? g % G : 0;
+    const bool has_state = first && q > 0;
+    const int j0 = TREE ? ts * PT : 0; // first of the summaries this wave fetches
+    bool want_state = has_state, want_tiles = true, want_groups = true; // TREE: still missing (wave-uniform)
     auto issue_records = [&]() {
-        if (SG == 0 && g > 0) {
-            const rec_t *sp = p.state + ((size_t)g * p.ncols + col) * (2 * CH) + c;
+        if (want_state) {
+            const rec_t *sp = p.state + ((size_t)q * p.ncols + col) * (2 * CH) + c;
             rS = rec_get(sp);
             rS2 = rec_get(sp + CH);
         }
 #pragma unroll
-        for (int j = 0; j < G - 1; ++j) {
-            if (j < r) {
-                const rec_t *tp = p.agg + ((size_t)(g * G + j) * p.ncols + col) * (2 * CH) + c;
+        for (int j = 0; j < (TREE ? PT : G - 1); ++j) {
+            if (want_tiles && j0 + j < r) {
+                const rec_t *tp = p.agg + ((size_t)(g * G + j0 + j) * p.ncols + col) * (2 * CH) + c;
                 rA[j] = rec_get(tp);
                 rM[j] = rec_get(tp + CH);
             }
+            if (TREE && want_groups && j0 + j < gi) {
+                const rec_t *gp = p.agg + ((size_t)((q * G + j0 + j) * G + G - 1) * p.ncols + col) * (2 * CH) + c;
+                gA[TREE ? j : 0] = rec_get(gp);
+                gM[TREE ? j : 0] = rec_get(gp + CH);
+            }
         }
     };
-    auto records_in = [&]() -> bool { // this lane's records carry the launch's tag
+    auto tiles_in = [&]() -> bool { // the tile summaries of this lane carry the launch's tag
         bool ok = true;
-        if (SG == 0 && g > 0) ok = rec_ok(rS, epoch) && rec_ok(rS2, epoch);
 #pragma unroll
-        for (int j = 0; j < G - 1; ++j) {
-            if (j < r) ok = ok && rec_ok(rA[j], epoch) && rec_ok(rM[j], epoch);
+        for (int j = 0; j < (TREE ? PT : G - 1); ++j) {
+            if (j0 + j < r) ok = ok && rec_ok(rA[j], epoch) && rec_ok(rM[j], epoch);
         }
         return ok;
     };
+    auto groups_in = [&]() -> bool { // TREE: the group summaries do
+        bool ok = true;
+        if constexpr (TREE) {
+#pragma unroll
+            for (int j = 0; j < PT; ++j) {
+                if (j0 + j < gi) ok = ok && rec_ok(gA[j], epoch) && rec_ok(gM[j], epoch);
+            }
+        }
+        return ok;
+    };
+    auto state_in = [&]() -> bool { return !has_state || (rec_ok(rS, epoch) && rec_ok(rS2, epoch)); };
+    auto records_in = [&]() -> bool { return tiles_in() && state_in() && groups_in(); }; // all of this lane's records do
     auto wave_all = [](bool ok) -> bool { return __builtin_amdgcn_ballot_w64(!ok) == 0ull; };
     bool have_records = false;
-    if (first) issue_records();
+    if (fetches) issue_records();
 
     // ---- load: the lane's T inputs ---------------------------------------------------------------
     float Av[T], Mv[T];
@@ -224,8 +253,8 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
         const InT *arow = ap, *brow = bp; // wave-uniform row pointers
 #pragma unroll
         for (int k = 0; k < T; ++k) {
-            Av[k] = load_elem<InT>(arow + moff);
-            Mv[k] = load_elem<InT>(brow + moff);
+            Av[k] = load_elem<MEM, InT>(arow + moff);
+            Mv[k] = load_elem<MEM, InT>(brow + moff);
             arow += p.D;
             brow += p.D;
         }
@@ -233,8 +262,8 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
 #pragma unroll
         for (int k = 0; k < T; ++k) {
             if (chan_ok && t0 + k < p.n) {
-                Av[k] = load_elem<InT>(ap + (int64_t)k * p.D + moff);
-                Mv[k] = load_elem<InT>(bp + (int64_t)k * p.D + moff);
+                Av[k] = load_elem<MEM, InT>(ap + (int64_t)k * p.D + moff);
+                Mv[k] = load_elem<MEM, InT>(bp + (int64_t)k * p.D + moff);
             } else {
                 Av[k] = id_a;
                 Mv[k] = id_b;
@@ -242,7 +271,7 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
         }
     }
 
-    if (first) have_records = wave_all(records_in()); // first look: answered while the tile's loads were in flight
+    if (!TREE && first) have_records = wave_all(records_in()); // first look: answered while the tile's loads were in flight
 
     // ---- encode + serial scan in each lane; Av/Mv become the per-element records (see stash) --------
     uint32_t sw = 0u, sm = 0u;
@@ -264,6 +293,52 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     }
     p.tl.mark(tile, 3);
 
+    // ---- a later wave: the fold of the waves before it in its column, in wave order; the last one along
+    //      time closes the tile: its fold with its own summary is the tile's -------------------------------
+    Seg pre = seg_identity<DOM>(), total = seg_identity<DOM>();
+    const bool closing = TS > 1 && ts == TS - 1; // wave-uniform
+    if (!first) {
+#pragma unroll
+        for (int j = 0; j < TS - 1; ++j) {
+            if (j < ts) {
+                lds_await(&flag_run[j * CG + wc]);
+                Seg h;
+                h.A = lds_A[j][c];
+                h.M = lds_M[j][c];
+                h.sA = h.sM = 0u;
+                if (SIGNED) unpack_signs(lds_S[j][c], h);
+                pre = (j == 0) ? h : seg_combine<DOM>(pre, h);
+            }
+        }
+        if (closing && more) {
+            total = seg_combine<DOM>(pre, run);
+            if (r < G - 1 && tile != p.drop_tile) {
+                rec_t *tp = p.agg + (size_t)tile * (2 * CH) + c;
+                seg_put<DOM>(tp, tp + CH, total, epoch);
+            }
+        }
+        if constexpr (TREE) {
+            lds_preA[ts][c] = pre.A;
+            lds_preM[ts][c] = pre.M;
+            if (SIGNED) lds_preS[ts][c] = pack_signs(pre);
+            if (closing) { // its slot among the waves' summaries is free
+                lds_A[TS - 1][c] = total.A;
+                lds_M[TS - 1][c] = total.M;
+                if (SIGNED) lds_S[TS - 1][c] = pack_signs(total);
+            }
+            asm volatile("" ::: "memory");
+        }
+    }
+    auto get_total = [&]() -> Seg { // closing wave
+        if constexpr (!TREE) return total;
+        Seg g2;
+        g2.A = lds_A[TS - 1][c];
+        g2.M = lds_M[TS - 1][c];
+        g2.sA = g2.sM = 0u;
+        if (SIGNED) unpack_signs(lds_S[TS - 1][c], g2);
+        return g2;
+    };
+
     State st;                // state at the wave's first step
     State64 st64{0.0, 0u};   // the same in float64, along the chain of tiles
     auto state_from_x0 = [&]() {
@@ -272,11 +347,91 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
         encode<DOM, LOG_IN>(x0v, lx, st64.s);
         st64.lx = (double)lx;
     };
-    if (first) {
+    if constexpr (TREE) {
+        // ---- every wave folds its part of the records: the tile summaries as soon as they are in, since the
+        //      tile that closes a group owes the later groups their sum, whatever else is on its way ----
+        auto put_part = [&](int level, const Seg &g2) {
+            lds_partA[level][ts][c] = g2.A;
+            lds_partM[level][ts][c] = g2.M;
+            lds_partS[level][ts][c] = pack_signs(g2);
+            lds_signal(&flag_part[level * TS + ts]);
+        };
+        auto get_part = [&](int level, int j) -> Seg {
+            lds_await(&flag_part[level * TS + j]);
+            Seg g2;
+            g2.A = lds_partA[level][j][c];
+            g2.M = lds_partM[level][j][c];
+            g2.sA = g2.sM = 0u;
+            if (SIGNED) unpack_signs(lds_partS[level][j][c], g2);
+            return g2;
+        };
+        bool lost = false, tiles_done = false; // lost: this lane's records never came
+        uint32_t polls = 0;
+        for (;;) {
+            want_tiles = want_tiles && !wave_all(tiles_in());
+            want_groups = want_groups && !wave_all(groups_in());
+            want_state = want_state && !wave_all(state_in());
+            have_records = !want_tiles && !want_groups && !want_state;
+            if (!have_records && ++polls > p.spin_limit) {
+                // give up: go on as if everything were in, with NaN for what is missing
+                lost = true;
+                note_wait_gave_up(p.header);
+            }
+            if (!tiles_done && (!want_tiles || lost)) {
+                tiles_done = true;
+                Seg part = seg_identity<DOM>();
+#pragma unroll
+                for (int j = 0; j < PT; ++j) {
+                    if (j0 + j < r) part = seg_combine<DOM>(part, seg_from<DOM>(rA[j], rM[j]));
+                }
+                if (!tiles_in()) part.M = __builtin_nanf("");
+                put_part(0, part);
+                if (closing && more && r == G - 1 && gi < G - 1) {
+                    // the last tile of a group owes the later groups the summary of its group
+                    part = get_part(0, 0);
+#pragma unroll 1
+                    for (int j = 1; j < TS; ++j) part = seg_combine<DOM>(part, get_part(0, j));
+                    rec_t *gp = p.agg + (size_t)tile * (2 * CH) + c;
+                    seg_put<DOM>(gp, gp + CH, seg_combine<DOM>(part, get_total()), epoch);
+                }
+            }
+            if (have_records || lost) break;
+            __builtin_amdgcn_s_sleep(2);
+            issue_records();
+        }
+        {
+            Seg part = seg_identity<DOM>();
+#pragma unroll
+            for (int j = 0; j < PT; ++j) {
+                if (j0 + j < gi) part = seg_combine<DOM>(part, seg_from<DOM>(gA[j], gM[j]));
+            }
+            if (!groups_in()) part.M = __builtin_nanf("");
+            put_part(1, part);
+        }
+        p.tl.mark(tile, 4);
+        if (first) {
+            if (q == 0) state_from_x0();
+            else st64 = state64_from(rS, rS2, SIGNED);
+#pragma unroll 1
+            for (int j = 0; j < TS; ++j) {
+                if (j * PT < gi) st64 = seg_apply64<DOM>(st64, get_part(1, j));
+            }
+#pragma unroll 1
+            for (int j = 0; j < TS; ++j) {
+                if (j * PT < r) st64 = seg_apply64<DOM>(st64, get_part(0, j));
+            }
+            if (!state_in()) st64.lx = __builtin_nan("");
+            st.lx = (float)st64.lx;
+            st.s = st64.s;
+            lds_startL[c] = st64.lx;
+            lds_startS[c] = st64.s;
+            lds_signal(&flag_start[wc]);
+        }
+    } else if (first) {
         // ---- obtain the state at the start of the tile ------------------------------------------
-        if (!have_records) issue_records();
         bool lost = false; // this lane's records never came
         if (!have_records) {
+            issue_records();
             uint32_t polls = 0;
             for (;;) {
                 const bool ok = records_in();
@@ -290,175 +445,54 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
             }
         }
         p.tl.mark(tile, 4);
-        if constexpr (SG > 0) {
-            // the earlier tiles of the group as one summary, kept for the group's summary below
-            Seg grp = seg_identity<DOM>();
-#pragma unroll
-            for (int j = 0; j < G - 1; ++j) {
-                if (j < r) grp = seg_combine<DOM>(grp, seg_from<DOM>(rA[j], rM[j]));
-            }
-            if (lost) grp.M = __builtin_nanf("");
-            // second round: the state at the start of the super-group and the earlier groups of it
-            auto issue2 = [&]() {
-                if (q > 0) {
-                    const rec_t *sp = p.state + ((size_t)q * p.ncols + col) * (2 * CH) + c;
-                    rS = rec_get(sp);
-                    rS2 = rec_get(sp + CH);
-                }
-#pragma unroll
-                for (int j = 0; j < SG - 1; ++j) {
-                    if (j < gi) {
-                        const rec_t *gp = p.gagg + ((size_t)(q * SG + j) * p.ncols + col) * (2 * CH) + c;
-                        rA[j] = rec_get(gp);
-                        rM[j] = rec_get(gp + CH);
-                    }
-                }
-            };
-            auto in2 = [&]() -> bool {
-                bool ok = true;
-                if (q > 0) ok = rec_ok(rS, epoch) && rec_ok(rS2, epoch);
-#pragma unroll
-                for (int j = 0; j < SG - 1; ++j) {
-                    if (j < gi) ok = ok && rec_ok(rA[j], epoch) && rec_ok(rM[j], epoch);
-                }
-                return ok;
-            };
-            issue2();
-            {
-                uint32_t polls = 0;
-                for (;;) {
-                    const bool ok = in2();
-                    if (wave_all(ok)) break;
-                    if (++polls > p.spin_limit) {
-                        lost = lost || !ok;
-                        break;
-                    }
-                    __builtin_amdgcn_s_sleep(2);
-                    issue2();
-                }
-            }
-            if (q == 0) {
-                state_from_x0();
-            } else {
-                st64 = state64_from(rS, rS2, SIGNED);
-            }
-#pragma unroll
-            for (int j = 0; j < SG - 1; ++j) {
-                if (j < gi) st64 = seg_apply64<DOM>(st64, seg_from<DOM>(rA[j], rM[j]));
-            }
-            st64 = seg_apply64<DOM>(st64, grp);
-            if (lost) {
-                st64.lx = __builtin_nan("");
-                note_wait_gave_up(p.header);
-            }
-            st.lx = (float)st64.lx;
-            st.s = st64.s;
-            if (TS > 1) {
-                lds_startL[c] = st64.lx;
-                lds_startS[c] = st64.s;
-                // the wave that closes the tile also needs the fold of the earlier tiles of the group (the
-                // last slot of the summaries is free: the closing wave never writes its own there)
-                lds_A[TS - 1][c] = grp.A;
-                lds_M[TS - 1][c] = grp.M;
-                if (SIGNED) lds_S[TS - 1][c] = pack_signs(grp);
-                lds_signal(&flag_start[wc]);
-            }
-            if (TS == 1) { // a single wave along time closes the tile itself
-                if (more && r < G - 1 && tile != p.drop_tile) {
-                    rec_t *tp = p.agg + (size_t)tile * (2 * CH) + c;
-                    seg_put<DOM>(tp, tp + CH, run, epoch);
-                }
-                if (more && r == G - 1 && gi < SG - 1) {
-                    rec_t *gp = p.gagg + ((size_t)g * p.ncols + col) * (2 * CH) + c;
-                    seg_put<DOM>(gp, gp + CH, seg_combine<DOM>(grp, run), epoch);
-                }
-                if (more && r == G - 1 && gi == SG - 1) {
-                    rec_t *sp = p.state + ((size_t)(q + 1) * p.ncols + col) * (2 * CH) + c;
-                    state64_put(sp, sp + CH, seg_apply64<DOM>(st64, run), epoch, SIGNED);
-                }
-            }
+        if (g == 0) {
+            state_from_x0();
         } else {
-            if (g == 0) {
-                state_from_x0();
-            } else {
-                st64 = state64_from(rS, rS2, SIGNED);
-            }
-            // fold the earlier tiles of the group in tile order
-#pragma unroll
-            for (int j = 0; j < G - 1; ++j) {
-                if (j < r) st64 = seg_apply64<DOM>(st64, seg_from<DOM>(rA[j], rM[j]));
-            }
-            if (lost) {
-                st64.lx = __builtin_nan("");
-                note_wait_gave_up(p.header);
-            }
-            st.lx = (float)st64.lx;
-            st.s = st64.s;
-            if (TS > 1) {
-                lds_startL[c] = st64.lx;
-                lds_startS[c] = st64.s;
-                lds_signal(&flag_start[wc]);
-            } else {
-                // a single wave along time closes the tile itself
-                if (more && r < G - 1 && tile != p.drop_tile) {
-                    rec_t *tp = p.agg + (size_t)tile * (2 * CH) + c;
-                    seg_put<DOM>(tp, tp + CH, run, epoch);
-                }
-                if (more && r == G - 1) {
-                    rec_t *sp = p.state + ((size_t)(g + 1) * p.ncols + col) * (2 * CH) + c;
-                    state64_put(sp, sp + CH, seg_apply64<DOM>(st64, run), epoch, SIGNED);
-                }
-            }
+            st64 = state64_from(rS, rS2, SIGNED);
         }
-    } else {
-        // ---- a later wave: the fold of the waves before it in its column, in wave order ------------
-        Seg pre;
+        // fold the earlier tiles of the group in tile order
 #pragma unroll
-        for (int j = 0; j < TS - 1; ++j) {
-            if (j < ts) {
-                lds_await(&flag_run[j * CG + wc]);
-                Seg h;
-                h.A = lds_A[j][c];
-                h.M = lds_M[j][c];
-                h.sA = h.sM = 0u;
-                if (SIGNED) unpack_signs(lds_S[j][c], h);
-                pre = (j == 0) ? h : seg_combine<DOM>(pre, h);
-            }
+        for (int j = 0; j < G - 1; ++j) {
+            if (j < r) st64 = seg_apply64<DOM>(st64, seg_from<DOM>(rA[TREE ? 0 : j], rM[TREE ? 0 : j]));
         }
-        // the last wave along time closes the tile: its fold with its own summary is the tile's
-        const bool closing = ts == TS - 1; // wave-uniform
-        Seg total = seg_identity<DOM>();
-        if (closing && more) {
-            total = seg_combine<DOM>(pre, run);
-            if (r < G - 1 && tile != p.drop_tile) {
+        if (lost) {
+            st64.lx = __builtin_nan("");
+            note_wait_gave_up(p.header);
+        }
+        st.lx = (float)st64.lx;
+        st.s = st64.s;
+        if (TS > 1) {
+            lds_startL[c] = st64.lx;
+            lds_startS[c] = st64.s;
+            lds_signal(&flag_start[wc]);
+        } else {
+            // a single wave along time closes the tile itself
+            if (more && r < G - 1 && tile != p.drop_tile) {
                 rec_t *tp = p.agg + (size_t)tile * (2 * CH) + c;
-                seg_put<DOM>(tp, tp + CH, total, epoch);
+                seg_put<DOM>(tp, tp + CH, run, epoch);
+            }
+            if (more && r == G - 1) {
+                rec_t *sp = p.state + ((size_t)(g + 1) * p.ncols + col) * (2 * CH) + c;
+                state64_put(sp, sp + CH, seg_apply64<DOM>(st64, run), epoch, SIGNED);
             }
         }
+    }
+    if (!first) {
         lds_await(&flag_start[wc]);
         st64.lx = lds_startL[c];
         st64.s = lds_startS[c];
         st.lx = (float)st64.lx;
         st.s = st64.s;
-        if (closing && more && r == G - 1) {
-            if constexpr (SG > 0) {
-                Seg grp;
-                grp.A = lds_A[TS - 1][c];
-                grp.M = lds_M[TS - 1][c];
-                grp.sA = grp.sM = 0u;
-                if (SIGNED) unpack_signs(lds_S[TS - 1][c], grp);
-                if (gi < SG - 1) {
-                    rec_t *gp = p.gagg + ((size_t)g * p.ncols + col) * (2 * CH) + c;
-                    seg_put<DOM>(gp, gp + CH, seg_combine<DOM>(grp, total), epoch);
-                } else {
-                    rec_t *sp = p.state + ((size_t)(q + 1) * p.ncols + col) * (2 * CH) + c;
-                    state64_put(sp, sp + CH, seg_apply64<DOM>(st64, total), epoch, SIGNED);
-                }
-            } else {
-                // last tile of a group: the state after this tile starts the next group
-                rec_t *sp = p.state + ((size_t)(g + 1) * p.ncols + col) * (2 * CH) + c;
-                state64_put(sp, sp + CH, seg_apply64<DOM>(st64, total), epoch, SIGNED);
-            }
+        if (closing && more && r == G - 1 && (!TREE || gi == G - 1)) {
+            // last tile of a group (TREE: of a super-group): the state after this tile starts the next one
+            rec_t *sp = p.state + ((size_t)(q + 1) * p.ncols + col) * (2 * CH) + c;
+            state64_put(sp, sp + CH, seg_apply64<DOM>(st64, get_total()), epoch, SIGNED);
+        }
+        if constexpr (TREE) {
+            pre.A = lds_preA[ts][c];
+            pre.M = lds_preM[ts][c];
+            pre.sA = pre.sM = 0u;
+            if (SIGNED) unpack_signs(lds_preS[ts][c], pre);
         }
         st = seg_apply<DOM>(st, pre);
     }
@@ -474,10 +508,10 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
             // complex output: (re, im) pairs, two floats per element
             float re, im;
             emit_clog(st, Av[k], Mv[k], swx, sm, k, re, im);
-            if (wanted) store_pair<NT>(op + 2 * ((int64_t)k * p.D + moff), re, im);
+            if (wanted) store_pair<MEM>(op + 2 * ((int64_t)k * p.D + moff), re, im);
         } else {
             const float o = emit<DOM, LOG_OUT>(st, Av[k], Mv[k], swx, k);
-            if (wanted) store_elem<NT>(op + (int64_t)k * p.D + moff, o);
+            if (wanted) store_elem<MEM>(op + (int64_t)k * p.D + moff, o);
         }
     };
     if (full) {
@@ -487,9 +521,9 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
             if constexpr (SIGNED && LOG_OUT) {
                 float re, im;
                 emit_clog(st, Av[k], Mv[k], swx, sm, k, re, im);
-                store_pair<NT>(orow + 2 * (size_t)moff, re, im);
+                store_pair<MEM>(orow + 2 * (size_t)moff, re, im);
             } else {
-                store_elem<NT>(orow + moff, emit<DOM, LOG_OUT>(st, Av[k], Mv[k], swx, k));
+                store_elem<MEM>(orow + moff, emit<DOM, LOG_OUT>(st, Av[k], Mv[k], swx, k));
             }
             orow += OW * p.D;
             if (SB) __builtin_amdgcn_sched_barrier(0);
@@ -504,14 +538,15 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     p.tl.mark(tile, 6);
 }
 
-template <int DOM, bool LOG_IN, bool LOG_OUT, typename InT, int T, int NW, int G, int MINW, bool SB, bool PACKB = false, int SG = 0, int CG = 1, bool NT = false>
+template <int DOM, bool LOG_IN, bool LOG_OUT, typename InT, int T, int NW, int G, int MINW, bool SB, bool DENSE, bool TREE, int CG, int MEM>
 __global__ __launch_bounds__(NW * 64, MINW) void heinsen_scan_bnd(BndParams p)
 {
     __shared__ uint32_t s_tile, s_epoch, s_flag;
-    __shared__ uint32_t s_flags[NW + CG];
+    constexpr int NFLAGS = NW + CG + (TREE ? 2 * NW : 0);
+    __shared__ uint32_t s_flags[NFLAGS];
     const unsigned long long t_begin = p.tl.stamps != nullptr ? wall_clock64() : 0ull;
     uint32_t tile, epoch = 0u;
-    if (threadIdx.x < NW + CG) s_flags[threadIdx.x] = 0u;
+    if (threadIdx.x < NFLAGS) s_flags[threadIdx.x] = 0u;
     if (p.header == nullptr) {
         // A launch whose columns are one short tile long (at most 64 steps) has nothing to wait for and
         // comes without tickets: there the draw's round trip would be a large part of a tile's life.
@@ -546,7 +581,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void heinsen_scan_bnd(BndParams p)
     if (tile < p.ntiles) {
         p.tl.mark_at(tile, 0, t_begin);
         p.tl.mark(tile, 1);
-        bnd_tile<DOM, LOG_IN, LOG_OUT, InT, T, NW, G, SB, PACKB, SG, CG, NT>(p, tile, epoch, s_flags);
+        bnd_tile<DOM, LOG_IN, LOG_OUT, InT, T, NW, G, SB, DENSE, TREE, CG, MEM>(p, tile, epoch, s_flags);
         p.tl.mark(tile, 7);
     }
     if (p.header != nullptr) end_of_workgroup(p.header, epoch, &s_flag);
@@ -558,25 +593,36 @@ __global__ __launch_bounds__(NW * 64, MINW) void heinsen_scan_bnd(BndParams p)
 constexpr int64_t kLastLevelCacheBytes = 192ll << 20;
 
 // Ticket queues: as many (up to one per compute die) as leave every queue this many columns.  The tiles
-// of a column start that many tickets apart, so a tile usually finds the tiles before it done; the wide
-// tiles, whose rows are requested by two waves at a time, want the queues longer still (measured).
-constexpr int kMinColsPerQueue = 16, kMinColsPerQueueWide = 128;
+// of a column start that many tickets apart, so a tile usually finds the tiles before it done; eight queues
+// also keep neighbouring columns on one die, which then reads the lines they share once (6 x 3001 x 770, 73
+// columns: 50.5 us with 16 per queue, 48 with 8).  The wide tiles, whose rows are requested by two waves at a time, want the queues longer still (measured).
+constexpr int kMinColsPerQueue = 8, kMinColsPerQueueWide = 128;
 
 struct BndPlan {
     int cg, T, NW, G, CH;
     bool ticketless;
-    int dp_shift, bpack; // bpack > 1: narrow rows, the channels of bpack batch items share a 64-lane column
+    bool dense;          // columns of adjacent channels of all B * D (see bnd_tile),
+    int lanes;           // this many
     int cols_per_b, ncols, nchunks, ngroups;
     uint32_t ntiles;
     int nq, cols_per_q;
     uint32_t grid;
-    int SG;             // > 0: groups per super-group (second carry level)
-    size_t off_agg, off_gagg, off_state, records; // in records, relative to kRecordBase
+    bool tree;          // second carry level, the waves of a tile share the record loads
+    size_t off_agg, off_state, records; // in records, relative to kRecordBase
 };
 
-BndPlan make_plan(const ScanCall &c, bool allow_wide = true)
+// TREE: tiles per group and groups per super-group, and the number of columns below which it is used.
+// Without it a link of the chain of group states takes 1.2-1.4 us and a group of four tiles is 786 KB per
+// column, 0.12 us of memory traffic: up to about 12 columns the chain is the slower of the two.  Measured with
+// and without: 3 columns of 131072 steps 75 and 176 us, 1 of 400000 109 and 479, 16 of 131072 283 and 279, 32 of
+// 32768 147 and 144 (the record loads).  Groups of 16 tiles instead of 8 cost registers (spills) and twice the
+// record loads: 106 us for the 3 columns.
+constexpr int kTreeGroup = 8;
+constexpr int kTreeBelow = 16;
+
+BndPlan make_plan(const ScanCall &c, bool allow_wide = true, bool want_tree = false)
 {
-    BndPlan pl;
+    BndPlan pl = {};
     // Default tile: 64 channels x 256 steps (8 waves one after the other along time, 32 steps each;
     // <= 128 VGPRs, two workgroups per CU).  With many wide rows the tile is 128 channels x 128 steps
     // instead (two waves side by side): the rows a workgroup touches are then 512 contiguous bytes, which
@@ -602,43 +648,33 @@ BndPlan make_plan(const ScanCall &c, bool allow_wide = true)
     pl.cols_per_b = (int)ceil_div(c.D, pl.CH);
     pl.ncols = (int)(c.B * pl.cols_per_b);
 
-    pl.dp_shift = 6;
-    pl.bpack = 1;
-    if (c.D <= 32 && c.B > 1) {
-        int sh = 0;
-        while ((1 << sh) < c.D) ++sh;
-        // a lane's offset from its column's base must fit a 32-bit byte offset
-        if ((int64_t)(64 >> sh) * c.n * c.D < ((int64_t)1 << 29)) {
-            pl.dp_shift = sh;
-            pl.bpack = 64 >> sh;
-            pl.ncols = (int)ceil_div(c.B, pl.bpack);
+    // Channels that do not fill their columns.  Up to 32 per batch item: a column takes whole items, 64 over the
+    // power of two at or above D of them.  (Items cut by the ends of columns read the lines at the cut
+    // twice: 256 x 4096 x 19 85 us, whole items 76; more and narrower pieces per access cost more than they fill:
+    // 999 x 4096 x 5 157 us with twelve items, 146 with eight.)  More channels: columns of 64 regardless of items
+    // where that saves a sixteenth of them (2 x 131072 x 96: three columns instead of four).  A lane's offset
+    // from its column's base -- it may lie some items further on -- has to fit 31 bits.
+    pl.lanes = 64;
+    if (pl.cg == 1) {
+        int64_t items = 1;
+        while (2 * items * c.D <= 64 && (items < 2 || 64 / (2 * items) >= c.D)) items *= 2;
+        const int64_t lanes = c.D <= 32 ? items * c.D : 64;
+        const int64_t cols = ceil_div(c.B * c.D, lanes), further = c.D <= 32 ? items - 1 : (c.D + 62) / c.D;
+        pl.dense = (c.D <= 32 ? cols : cols + cols / 16) < pl.ncols && c.B * c.D < ((int64_t)1 << 31) &&
+                   further * c.n * c.D + c.D < ((int64_t)1 << 31);
+        if (pl.dense) {
+            pl.lanes = (int)lanes;
+            pl.ncols = (int)cols;
         }
     }
-    // Few columns: the states handed from group to group (0.9 us per link) bound the launch, not the
-    // memory.  Below 64 columns the groups are eight tiles long (half the links); up to 8 columns a second
-    // carry level hands states on only between super-groups (4 x 4 tiles: n / 4096 links, no spills; one
-    // or two columns: 8 x 8 tiles, n / 16384 links, at the price of some spilled registers).  With many
-    // columns the longer folds and the second round of record loads would cost a few percent.  Not for the
-    // modes whose kernels are short of registers already.
-    pl.SG = 0;
-    if (pl.cg == 1 && pl.NW == 8 && pl.T == 32 && !(c.log_in && c.log_out)) {
-        if (pl.ncols <= 2) {
-            pl.G = 8;
-            pl.SG = 8;
-        } else if (pl.ncols <= 8) {
-            pl.G = 4;
-            pl.SG = 4;
-        } else if (pl.ncols < 64) {
-            pl.G = 8;
-        }
-    }
+    pl.tree = pl.cg == 1 && pl.NW == 8 && pl.T == 32 && (pl.ncols < kTreeBelow || want_tree) && c.n > 4 * pl.NW * pl.T;
+    if (pl.tree) pl.G = kTreeGroup;
     pl.nchunks = (int)ceil_div(c.n, (int64_t)(pl.NW / pl.cg) * pl.T);
     pl.ngroups = (int)ceil_div(pl.nchunks, pl.G);
     pl.ntiles = (uint32_t)pl.ncols * (uint32_t)pl.nchunks;
     pl.off_agg = 0;
-    pl.off_gagg = (size_t)pl.ntiles * 2 * pl.CH;
-    pl.off_state = pl.off_gagg + (pl.SG ? (size_t)pl.ngroups * pl.ncols * 2 * pl.CH : 0);
-    pl.records = pl.off_state + (size_t)(pl.SG ? ceil_div(pl.ngroups, pl.SG) + 1 : pl.ngroups) * pl.ncols * 2 * pl.CH;
+    pl.off_state = (size_t)pl.ntiles * 2 * pl.CH;
+    pl.records = pl.off_state + (size_t)(pl.tree ? ceil_div(pl.ngroups, pl.G) + 1 : pl.ngroups) * pl.ncols * 2 * pl.CH;
     pl.ticketless = pl.nchunks == 1 && c.n <= 64; // short single-tile columns: no records, no tickets
     // A queue's workgroups that find no tile behind their ticket (uneven deal) end at once.
     pl.nq = kQueues;
@@ -650,8 +686,15 @@ BndPlan make_plan(const ScanCall &c, bool allow_wide = true)
     } else {
         pl.grid = (uint32_t)pl.nq * (uint32_t)pl.cols_per_q * (uint32_t)pl.nchunks;
     }
-    // the wide tiles take twice the records: a caller with a fixed scratch buffer may have to do without them
-    if (pl.cg > 1 && c.scratch_budget != 0 && kRecordBase + pl.records > c.scratch_budget) return make_plan(c, false);
+    // A caller with a fixed scratch buffer may have to do without the wide tiles, which take twice the records,
+    // and with the second carry level, whose states are fewer.
+    if (c.scratch_budget != 0 && kRecordBase + pl.records > c.scratch_budget) {
+        if (pl.cg > 1) return make_plan(c, false);
+        if (!want_tree && pl.ncols < 64) {
+            const BndPlan t = make_plan(c, false, true);
+            if (t.tree) return t;
+        }
+    }
     return pl;
 }
 
@@ -668,12 +711,19 @@ hipError_t launch_mode(const ScanCall &c, const BndPlan &pl, const LaunchCtx &ct
     p.D = c.D;
     p.n = c.n;
     p.x0_stride = c.x0_scalar ? 0 : 1;
-    // the output does not fit the last-level cache: write it non-temporally (shapes with a kernel for it)
-    const bool nt_out = c.B * c.D * c.n * ((SIGNED && LOG_OUT) ? 8 : 4) > kLastLevelCacheBytes;
+    // see Mem.  kShared from the size on at which it wins however the caller goes through its buffers: while
+    // the outputs of the last few calls fit the memory-side cache, kKeepOut finds some of their lines there (6 x 3001 x
+    // 1111 float32, 240 MB: kKeepOut 59 us over three sets of buffers and 72 over six, kShared 64; 16 x 4096 x 301
+    // bf16, 316 MB: 108 and 82; 8 x 8000 x 1501, 2.3 GB: 658 and 490).  With items narrower than half a column the
+    // lines are shared by successive steps of one lane's wave as well (256 x 4096 x 19, 239 MB: 76 and 68).
+    const int64_t elements = c.B * c.D * c.n;
+    const int64_t out_bytes = elements * ((SIGNED && LOG_OUT) ? 8 : 4);
+    const bool large_out = out_bytes > kLastLevelCacheBytes;
+    const bool shares_lines = c.D * (int64_t)sizeof(InT) % 128 != 0 && out_bytes + 2 * elements * (int64_t)sizeof(InT) > (c.D <= 32 ? kLastLevelCacheBytes : kLastLevelCacheBytes * 3 / 2);
+    const int mem = shares_lines ? kShared : (large_out ? kStream : kKeepOut);
     p.cols_per_b = pl.cols_per_b;
-    p.B = c.B;
-    p.dp_shift = pl.dp_shift;
-    p.bpack = pl.bpack;
+    p.nchan = c.B * c.D;
+    p.lanes = pl.lanes;
     p.ncols = pl.ncols;
     p.nchunks = pl.nchunks;
     p.ntiles = pl.ntiles;
@@ -683,62 +733,51 @@ hipError_t launch_mode(const ScanCall &c, const BndPlan &pl, const LaunchCtx &ct
     p.header = records; // null when the launch needs no carries
     p.agg = records ? records + kRecordBase + pl.off_agg : nullptr;
     p.state = records ? records + kRecordBase + pl.off_state : nullptr;
-    p.gagg = records ? records + kRecordBase + pl.off_gagg : nullptr;
     p.spin_limit = ctx.spin_limit;
     p.drop_tile = ctx.drop_tile;
     p.tl.stamps = ctx.timeline;
     p.tl.tiles = ctx.timeline_tiles;
     if (!pl.ticketless && records == nullptr) return hipErrorInvalidValue;
-    dim3 grid(pl.grid), block(pl.NW * 64);
+    // The plan's shape and the kernel's must be the same one: a wave that is not there would be waited for.
+#define HS_BND(T_, NW_, G_, DENSE_, TREE_, CG_, MEM_)                                                              \
+    do {                                                                                                           \
+        if (pl.T != T_ || pl.NW != NW_ || pl.G != G_ || pl.cg != CG_ || pl.tree != TREE_ || pl.dense != DENSE_)    \
+            return hipErrorInvalidValue;                                                                           \
+        hipLaunchKernelGGL((heinsen_scan_bnd<DOM, LOG_IN, LOG_OUT, InT, T_, NW_, G_, 4, true, DENSE_, TREE_, CG_, MEM_>), \
+                           dim3(pl.grid), dim3(NW_ * 64), 0, c.stream, p);                                         \
+    } while (0)
+#define HS_BND_MEM(T_, NW_, G_, DENSE_, TREE_)                                \
+    do {                                                                      \
+        if (mem == kShared) HS_BND(T_, NW_, G_, DENSE_, TREE_, 1, kShared);      \
+        else if (mem == kStream) HS_BND(T_, NW_, G_, DENSE_, TREE_, 1, kStream); \
+        else HS_BND(T_, NW_, G_, DENSE_, TREE_, 1, kKeepOut);                    \
+    } while (0)
+#define HS_BND_ANY(T_, NW_, G_, TREE_)                     \
+    do {                                                   \
+        if (pl.dense) HS_BND_MEM(T_, NW_, G_, true, TREE_);   \
+        else HS_BND_MEM(T_, NW_, G_, false, TREE_);           \
+    } while (0)
     if constexpr (SIGNED && LOG_OUT) {
-        if (pl.bpack > 1)
-            hipLaunchKernelGGL((heinsen_scan_bnd<DOM, LOG_IN, LOG_OUT, InT, 16, 16, 4, 4, true, true>), grid, block, 0, c.stream, p);
-        else if (nt_out)
-            hipLaunchKernelGGL((heinsen_scan_bnd<DOM, LOG_IN, LOG_OUT, InT, 16, 16, 4, 4, true, false, 0, 1, true>), grid, block, 0, c.stream, p);
-        else
-            hipLaunchKernelGGL((heinsen_scan_bnd<DOM, LOG_IN, LOG_OUT, InT, 16, 16, 4, 4, true>), grid, block, 0, c.stream, p);
+        HS_BND_ANY(16, 16, 4, false);
+    } else if (pl.cg == 2) {
+        if (mem == kStream) HS_BND(32, 8, 4, false, false, 2, kStream);
+        else HS_BND(32, 8, 4, false, false, 2, kKeepOut);
+    } else if (pl.tree) {
+        HS_BND_ANY(32, 8, kTreeGroup, true);
+    } else if (pl.NW == 8) {
+        HS_BND_ANY(32, 8, 4, false);
+    } else if (pl.dense) { // short sequences
+        if (pl.NW == 1) HS_BND(32, 1, 4, true, false, 1, kKeepOut);
+        else if (pl.NW == 2) HS_BND(32, 2, 4, true, false, 1, kKeepOut);
+        else HS_BND(32, 4, 4, true, false, 1, kKeepOut);
     } else {
-        if (pl.cg == 2) {
-            if (nt_out)
-                hipLaunchKernelGGL((heinsen_scan_bnd<DOM, LOG_IN, LOG_OUT, InT, 32, 8, 4, 4, true, false, 0, 2, true>), grid, block, 0, c.stream, p);
-            else
-                hipLaunchKernelGGL((heinsen_scan_bnd<DOM, LOG_IN, LOG_OUT, InT, 32, 8, 4, 4, true, false, 0, 2, false>), grid, block, 0, c.stream, p);
-            return hipGetLastError();
-        }
-#define HS_BND(NW_, PACKB_) \
-    hipLaunchKernelGGL((heinsen_scan_bnd<DOM, LOG_IN, LOG_OUT, InT, 32, NW_, 4, 4, true, PACKB_>), grid, block, 0, c.stream, p)
-        if constexpr (!(LOG_IN && LOG_OUT)) {
-            if (pl.G == 8 || pl.SG > 0) {
-#define HS_BND_CARRY(G_, SG_, PACKB_) \
-    hipLaunchKernelGGL((heinsen_scan_bnd<DOM, LOG_IN, LOG_OUT, InT, 32, 8, G_, 4, true, PACKB_, SG_>), grid, block, 0, c.stream, p)
-                if (pl.bpack > 1) {
-                    if (pl.SG == 8) HS_BND_CARRY(8, 8, true);
-                    else if (pl.SG == 4) HS_BND_CARRY(4, 4, true);
-                    else HS_BND_CARRY(8, 0, true);
-                } else {
-                    if (pl.SG == 8) HS_BND_CARRY(8, 8, false);
-                    else if (pl.SG == 4) HS_BND_CARRY(4, 4, false);
-                    else HS_BND_CARRY(8, 0, false);
-                }
-#undef HS_BND_CARRY
-                return hipGetLastError();
-            }
-        }
-        if (pl.bpack > 1) {
-            if (pl.NW == 1) HS_BND(1, true);
-            else if (pl.NW == 2) HS_BND(2, true);
-            else if (pl.NW == 4) HS_BND(4, true);
-            else HS_BND(8, true);
-        } else {
-            if (pl.NW == 1) HS_BND(1, false);
-            else if (pl.NW == 2) HS_BND(2, false);
-            else if (pl.NW == 4) HS_BND(4, false);
-            else if (nt_out)
-                hipLaunchKernelGGL((heinsen_scan_bnd<DOM, LOG_IN, LOG_OUT, InT, 32, 8, 4, 4, true, false, 0, 1, true>), grid, block, 0, c.stream, p);
-            else HS_BND(8, false);
-        }
-#undef HS_BND
+        if (pl.NW == 1) HS_BND(32, 1, 4, false, false, 1, kKeepOut);
+        else if (pl.NW == 2) HS_BND(32, 2, 4, false, false, 1, kKeepOut);
+        else HS_BND(32, 4, 4, false, false, 1, kKeepOut);
     }
+#undef HS_BND_ANY
+#undef HS_BND_MEM
+#undef HS_BND
     return hipGetLastError();
 }
 
@@ -766,7 +805,7 @@ const char *bnd_kernel_name(const ScanCall &) { return "heinsen_scan_bnd"; }
 void bnd_tile_shape(const ScanCall &c, int &channels, int64_t &steps)
 {
     const BndPlan pl = make_plan(c);
-    channels = pl.bpack > 1 ? (int)c.D : pl.CH; // narrow rows: the channels of pl.bpack batch items side by side
+    channels = pl.dense && c.D < pl.CH ? (int)c.D : pl.CH; // narrow rows: the channels of several batch items side by side
     steps = (int64_t)(pl.NW / pl.cg) * pl.T;
 }
 

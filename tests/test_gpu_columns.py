@@ -1,0 +1,77 @@
+"""[B, n, D] with columns of channels that do not fill the lanes (whole narrow items, or 64 channels whatever item
+they belong to), rows that do not keep to 128-byte lines with few and many tiles, and few columns of many tiles:
+two carry levels of eight, whose records the waves of a tile share."""
+import numpy as np
+import pytest
+
+from paper_2311_06281_amd import workloads
+
+import test_gpu_cross_product as cross
+from test_gpu_cross_product import gpu  # noqa: F401  (fixture)
+
+pytestmark = pytest.mark.gpu
+
+# (B, n, D)
+SHAPES = [
+    (2, 300, 96), (3, 700, 65), (5, 65, 33), (4, 129, 100), (2, 33, 48), (7, 1100, 40), (3, 257, 1000 - 25),  # dense columns
+    (9, 513, 19), (13, 70, 5), (3, 300, 31), (6, 2000, 21),                                                    # whole items
+    (4, 16001, 70), (2, 100003, 20), (70, 3000, 13), (40, 2900, 37),                                           # shared lines
+    # few columns: one tile more than a group (8 tiles of 256 steps), than a super-group (64), than several
+    (1, 1025, 64), (1, 2049, 66), (2, 256 * 9 + 3, 96), (1, 256 * 64 + 1, 128), (1, 256 * 65, 2), (3, 256 * 72 + 5, 65),
+    (2, 256 * 200 + 77, 48), (1, 256 * 512, 5), (15, 256 * 17, 64), (14, 256 * 16 + 255, 64),
+]
+
+
+@pytest.mark.parametrize("mode", list(cross.MODES))
+@pytest.mark.parametrize("bf16", [False, True])
+def test_columns_and_carry_levels(gpu, mode, bf16):
+    rng = np.random.default_rng(sum(map(ord, mode)) + 7 * int(bf16))
+    for shape in SHAPES:
+        a, b, x0 = cross._inputs(rng, shape, "BND", mode)
+        if bf16:  # the bf16-rounded values are what is stored: they define the problem
+            a = workloads.bf16_bits_to_f32(workloads.f32_to_bf16_bits(a)).reshape(a.shape)
+            b = workloads.bf16_bits_to_f32(workloads.f32_to_bf16_bits(b)).reshape(b.shape)
+        for offset in (0, 1):
+            print(f"[columns] {mode} bf16={bf16} shape={shape} offset={offset}", flush=True)
+            got = cross._run(gpu, a, b, x0, "BND", cross.MODES[mode], bf16, offset_elems=offset)
+            cross._check(got, a, b, x0, "BND", mode)
+
+
+def test_fewer_records_where_the_fixed_scratch_is_short(gpu):
+    """40 columns of 1000 tiles need 6.4e6 records with one carry level, 5.2e6 with two; the fixed array holds 6.29e6.
+    The values are x_t = 1 for a = 1/2, b = 1/2, x_0 = 1."""
+    torch, hb = gpu
+    B, n, D = 40, 256 * 1000, 64
+    a = torch.full((B, n, D), 0.5, dtype=torch.bfloat16, device="cuda")
+    x0 = torch.ones(1, dtype=torch.float32, device="cuda")
+    out = torch.empty((B, n, D), dtype=torch.float32, device="cuda")
+    flags = hb.HEINSEN_IN_BF16 | hb.HEINSEN_X0_SCALAR
+    for call in (hb.heinsen_scan_static, hb.heinsen_scan):
+        out.fill_(float("nan"))
+        call(a, a, x0, out, B, D, n, hb.HEINSEN_LAYOUT_BND, flags, torch.cuda.current_stream())
+        assert hb.heinsen_check(torch.cuda.current_stream()) == hb.HEINSEN_OK
+        assert float((out - 1.0).abs().max()) <= 1e-5
+
+
+def test_a_tile_that_never_publishes_ends_in_nan_with_two_carry_levels(gpu):
+    torch, hb = gpu
+    B, n, D = 1, 256 * 100, 128  # two columns
+    a = torch.full((B, n, D), 0.5, device="cuda")
+    x0 = torch.ones(D, device="cuda")
+    out = torch.empty((B, n, D), device="cuda")
+    args = (a, a, x0, out, B, D, n, hb.HEINSEN_LAYOUT_BND, 0, torch.cuda.current_stream())
+    hb.heinsen_scan(*args)
+    torch.cuda.synchronize()
+    drop = 2 * 10  # chunk 10 of column 0
+    try:
+        hb.heinsen_test_carry(spin_limit=200, drop_tile=drop)
+        out.fill_(0.0)
+        hb.heinsen_scan(*args)
+        assert hb.heinsen_check(torch.cuda.current_stream()) == hb.HEINSEN_ERR_CARRY_LOST
+    finally:
+        hb.heinsen_test_carry()
+    assert torch.isnan(out[0, 256 * 11:, :64]).all()
+    assert (out[0, : 256 * 11, :64] - 1).abs().max() <= 1e-5 and (out[0, :, 64:] - 1).abs().max() <= 1e-5
+    hb.heinsen_scan(*args)
+    assert hb.heinsen_check(torch.cuda.current_stream()) == hb.HEINSEN_OK
+    assert (out - 1).abs().max() <= 1e-5
