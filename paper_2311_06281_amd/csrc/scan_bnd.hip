@@ -587,6 +587,62 @@ __global__ __launch_bounds__(NW * 64, MINW) void heinsen_scan_bnd(BndParams p)
     if (p.header != nullptr) end_of_workgroup(p.header, epoch, &s_flag);
 }
 
+// ---- a few steps of many channels ---------------------------------------------------------------------
+//
+// A model that generates one token after the other calls the scan with a handful of steps.  Such a call is
+// bound by how fast the chip starts waves: as a tile of 32 steps with the others masked, one step of 64 x 4096
+// channels took 4096 waves and 7.2 us for 4 MB (a first call 22.9 us from call to result, 19.7 now).  Here a thread takes VEC adjacent channels (16 bytes of
+// float32 per access), asks for all of their steps at once and evaluates the definition (Sec. 3), x_t =
+// a_t x_{t-1} + b_t, in float64, so that as in the log domain no state on the way leaves the range: eight
+// float32 factors stay within 2^1024.  Subnormal float32 counts as 0, in and out.
+struct StepsParams {
+    const void *a;
+    const void *b;
+    const float *x0;
+    float *out;
+    uint32_t nchan, D; // B * D; the host checks that it fits
+    int n;
+    int x0_stride;
+};
+constexpr int kMaxSteps = 8;
+
+__device__ __forceinline__ float flush_subnormal(float v) { return fabsf(v) < 0x1p-126f ? 0.0f : v; }
+
+template <typename InT, int VEC>
+__global__ __launch_bounds__(256) void heinsen_scan_steps(StepsParams p)
+{
+    typedef InT in_t __attribute__((ext_vector_type(VEC)));
+    typedef float out_t __attribute__((ext_vector_type(VEC)));
+    const uint32_t chan = (blockIdx.x * 256u + threadIdx.x) * (uint32_t)VEC;
+    if (chan >= p.nchan) return;
+    const uint32_t b = chan / p.D, d = chan - b * p.D; // VEC divides D: the channels are of one batch item
+    const int64_t base = (int64_t)b * p.n * p.D + d;
+    in_t av[kMaxSteps], bv[kMaxSteps];
+#pragma unroll
+    for (int t = 0; t < kMaxSteps; ++t) {
+        if (t < p.n) { // wave-uniform
+            const int64_t at = base + (int64_t)t * p.D;
+            av[t] = __builtin_nontemporal_load(reinterpret_cast<const in_t *>(reinterpret_cast<const InT *>(p.a) + at));
+            bv[t] = __builtin_nontemporal_load(reinterpret_cast<const in_t *>(reinterpret_cast<const InT *>(p.b) + at));
+        }
+    }
+    double x[VEC];
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) x[i] = (double)flush_subnormal(p.x0[p.x0_stride ? chan + i : 0]);
+#pragma unroll
+    for (int t = 0; t < kMaxSteps; ++t) {
+        if (t < p.n) {
+            out_t o;
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) {
+                x[i] = fma((double)flush_subnormal(widen(av[t][i])), x[i], (double)flush_subnormal(widen(bv[t][i])));
+                o[i] = flush_subnormal((float)x[i]);
+            }
+            *reinterpret_cast<out_t *>(p.out + base + (int64_t)t * p.D) = o;
+        }
+    }
+}
+
 // ---- host side ------------------------------------------------------------------------------------
 
 // MI355X: 256 MB of memory-side cache; an output up to three quarters of it is left to be cached
@@ -781,6 +837,24 @@ hipError_t launch_mode(const ScanCall &c, const BndPlan &pl, const LaunchCtx &ct
     return hipGetLastError();
 }
 
+// Plain numbers in and out, at most kMaxSteps of them per channel.  (Logarithms keep to the log domain.)
+bool is_steps(const ScanCall &c)
+{
+    return !c.linear && !c.log_in && !c.log_out && c.n <= kMaxSteps && c.B * c.D < ((int64_t)1 << 31);
+}
+
+template <typename InT>
+hipError_t launch_steps(const ScanCall &c)
+{
+    const StepsParams p{c.a, c.b, c.x0, c.out, (uint32_t)(c.B * c.D), (uint32_t)c.D, (int)c.n, c.x0_scalar ? 0 : 1};
+    auto on = [](const void *ptr, size_t bytes) { return reinterpret_cast<uintptr_t>(ptr) % bytes == 0; };
+    const bool vec = c.D % 4 == 0 && on(c.a, 4 * sizeof(InT)) && on(c.b, 4 * sizeof(InT)) && on(c.out, 16);
+    const dim3 grid((unsigned)ceil_div(c.B * c.D, vec ? 1024 : 256)), block(256);
+    if (vec) hipLaunchKernelGGL((heinsen_scan_steps<InT, 4>), grid, block, 0, c.stream, p);
+    else hipLaunchKernelGGL((heinsen_scan_steps<InT, 1>), grid, block, 0, c.stream, p);
+    return hipGetLastError();
+}
+
 hipError_t launch_dispatch(const ScanCall &c, const BndPlan &pl, const LaunchCtx &ctx)
 {
     HS_DISPATCH_MODE(c, launch_mode, c, pl, ctx);
@@ -790,20 +864,27 @@ hipError_t launch_dispatch(const ScanCall &c, const BndPlan &pl, const LaunchCtx
 
 ScratchNeed bnd_scratch(const ScanCall &c)
 {
+    if (is_steps(c)) return ScratchNeed{0};
     BndPlan pl = make_plan(c);
     return ScratchNeed{pl.records};
 }
 
 hipError_t bnd_launch(const ScanCall &c, const LaunchCtx &ctx)
 {
+    if (is_steps(c)) return c.bf16 ? launch_steps<uint16_t>(c) : launch_steps<float>(c);
     BndPlan pl = make_plan(c);
     return launch_dispatch(c, pl, ctx);
 }
 
-const char *bnd_kernel_name(const ScanCall &) { return "heinsen_scan_bnd"; }
+const char *bnd_kernel_name(const ScanCall &c) { return is_steps(c) ? "heinsen_scan_steps" : "heinsen_scan_bnd"; }
 
 void bnd_tile_shape(const ScanCall &c, int &channels, int64_t &steps)
 {
+    if (is_steps(c)) {
+        channels = c.D % 4 == 0 ? 1024 : 256;
+        steps = c.n;
+        return;
+    }
     const BndPlan pl = make_plan(c);
     channels = pl.dense && c.D < pl.CH ? (int)c.D : pl.CH; // narrow rows: the channels of several batch items side by side
     steps = (int64_t)(pl.NW / pl.cg) * pl.T;

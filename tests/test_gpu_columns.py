@@ -75,3 +75,33 @@ def test_a_tile_that_never_publishes_ends_in_nan_with_two_carry_levels(gpu):
     hb.heinsen_scan(*args)
     assert hb.heinsen_check(torch.cuda.current_stream()) == hb.HEINSEN_OK
     assert (out - 1).abs().max() <= 1e-5
+
+
+# a few steps: four channels per thread and one, the ends of a workgroup, the last length of the kernel and the next
+@pytest.mark.parametrize("mode", ["signed", "positive"])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_a_few_steps(gpu, mode, bf16):
+    rng = np.random.default_rng(91 + int(bf16))
+    for shape in [(1, 1, 2), (2, 1, 4), (64, 1, 1024), (3, 2, 341), (5, 3, 205), (1, 7, 1028), (2, 8, 260), (7, 8, 37), (2, 9, 260)]:
+        a, b, x0 = cross._inputs(rng, shape, "BND", mode)
+        if bf16:  # the bf16-rounded values are what is stored: they define the problem
+            a = workloads.bf16_bits_to_f32(workloads.f32_to_bf16_bits(a)).reshape(a.shape)
+            b = workloads.bf16_bits_to_f32(workloads.f32_to_bf16_bits(b)).reshape(b.shape)
+        for offset in (0, 1, 4):
+            print(f"[steps] {mode} bf16={bf16} shape={shape} offset={offset}", flush=True)
+            got = cross._run(gpu, a, b, x0, "BND", cross.MODES[mode], bf16, offset_elems=offset)
+            cross._check(got, a, b, x0, "BND", mode)
+
+
+def test_a_few_steps_out_of_range_and_back(gpu):
+    """States beyond float32 between outputs, zeros, infinities and NaN: as the definition has them."""
+    # all factors and float32 outputs are normal numbers (at least 2^-126 = 1.18e-38) except x_0 = 1e-39, which counts as 0
+    a = np.tile(np.array([1e30, 1e30, 1e-30, 1e-37], np.float32)[None, :, None], (1, 1, 8))
+    b = np.zeros_like(a)
+    x0 = np.array([1.0, -1.0, 0.0, np.inf, np.nan, 1e-30, 1e-39, 2.0], np.float32)
+    a[0, 1, 7], b[0, 1, 7] = 0.0, 3.0
+    got = cross._run(gpu, a, b, x0, "BND", (), False)[0]
+    inf = np.inf
+    want = np.array([[1e30, -1e30, 0, inf, np.nan, 1.0, 0, 2e30], [inf, -inf, 0, inf, np.nan, 1e30, 0, 3.0],
+                     [1e30, -1e30, 0, inf, np.nan, 1.0, 0, 3e-30], [1e-7, -1e-7, 0, inf, np.nan, 1e-37, 0, 0]])
+    assert np.allclose(got, want, rtol=1e-6, atol=0, equal_nan=True)
