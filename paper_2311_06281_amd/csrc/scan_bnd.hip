@@ -125,7 +125,7 @@ __device__ __forceinline__ void lds_await(volatile uint32_t *flag)
 // carry records, forms the state at the start of the tile and hands it to the waves behind it through
 // LDS; a later wave waits only for the summaries of the waves before it in its own column; the last wave
 // along time publishes the tile's summary (and, closing a group, the state for the next group).  `flags`
-// are TS*CG + CG words of LDS, zero when the tile begins.
+// are TS*CG + CG words of LDS (TREE: 2*TS more), zero when the tile begins.
 template <int DOM, bool LOG_IN, bool LOG_OUT, typename InT, int T, int NW, int G, bool SB, bool DENSE, bool TREE, int CG, int MEM>
 __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile, const uint32_t epoch, volatile uint32_t *flags)
 {
