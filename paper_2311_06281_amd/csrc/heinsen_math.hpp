@@ -117,27 +117,54 @@ struct State64 {
     uint32_t s;
 };
 
-// seg_apply with the state kept in float64: only the (small) correction log2(1 +- 2^-|t|) is formed in
+// slae with its terms and result in float64: only the (small) correction log2(1 +- 2^-|t|) is formed in
 // float32.
-template <int DOM>
-__device__ __forceinline__ State64 seg_apply64(const State64 &x, const Seg &g)
+template <bool SIGNED>
+__device__ __forceinline__ void slae64(double p, uint32_t sp, double q, uint32_t sq, double &r, uint32_t &sr)
 {
-    constexpr bool SIGNED = DOM == kSigned;
-    if (DOM == kLinear) return State64{x.lx * (double)g.A + (double)g.M, 0u};
-    const double p = x.lx + (double)g.A;
-    const double q = (double)g.M;
-    const uint32_t sp = SIGNED ? (x.s ^ g.sA) : 0u;
     const double m = fmax(p, q);
     float t = (float)(p - q);
     t = (p == q) ? 0.0f : t;
     float e = exp2_hw(-fabsf(t));
-    State64 r;
-    r.s = 0u;
+    sr = 0u;
     if (SIGNED) {
-        e = u2f(f2u(e) ^ ((sp ^ g.sM) & kSignBit));
-        r.s = (t >= 0.0f) ? sp : g.sM;
+        e = u2f(f2u(e) ^ ((sp ^ sq) & kSignBit));
+        sr = (t >= 0.0f) ? sp : sq;
     }
-    r.lx = m + (double)log2_hw(1.0f + e);
+    const float u = 1.0f + e;
+    r = m + (double)fmaf((e - (u - 1.0f)) * kLog2e, __builtin_amdgcn_rcpf(u), log2_hw(u));
+}
+
+// A summary of many tiles, which a chain hands on like a state, keeps its two sums in float64 too: folded in
+// float32 the eight tiles of a group would round their sum of logarithms once per tile, and every state
+// behind them would carry that.
+struct Seg64 {
+    double A, M;
+    uint32_t sA, sM;
+};
+__device__ __forceinline__ Seg64 seg64(const Seg &g) { return Seg64{(double)g.A, (double)g.M, g.sA, g.sM}; }
+
+// g1 and the steps of g2 behind it.
+template <int DOM>
+__device__ __forceinline__ Seg64 seg_append64(const Seg64 &g1, const Seg &g2)
+{
+    constexpr bool SIGNED = DOM == kSigned;
+    if (DOM == kLinear) return Seg64{g1.A * (double)g2.A, g1.M * (double)g2.A + (double)g2.M, 0u, 0u};
+    Seg64 r;
+    r.A = g1.A + (double)g2.A;
+    r.sA = SIGNED ? (g1.sA ^ g2.sA) : 0u;
+    slae64<SIGNED>(g1.M + (double)g2.A, SIGNED ? (g1.sM ^ g2.sA) : 0u, (double)g2.M, g2.sM, r.M, r.sM);
+    return r;
+}
+
+// seg_apply with the state kept in float64; SEG: Seg or Seg64.
+template <int DOM, typename SEG>
+__device__ __forceinline__ State64 seg_apply64(const State64 &x, const SEG &g)
+{
+    constexpr bool SIGNED = DOM == kSigned;
+    if (DOM == kLinear) return State64{x.lx * (double)g.A + (double)g.M, 0u};
+    State64 r;
+    slae64<SIGNED>(x.lx + (double)g.A, SIGNED ? (x.s ^ g.sA) : 0u, (double)g.M, g.sM, r.lx, r.s);
     return r;
 }
 
@@ -460,20 +487,26 @@ __device__ __forceinline__ bool rec_ok(rec_t r, uint32_t epoch) { return ((uint3
 __device__ __forceinline__ uint32_t rec_payload(rec_t r) { return (uint32_t)r; }
 __device__ __forceinline__ uint32_t rec_bits(rec_t r) { return (uint32_t)(r >> 32) & 3u; }
 
-// A float64 state travels as two records: the high and low word of the double; the sign rides in the user
-// bits of the first.
+// A float64 number travels as two records: its high and low word.
+__device__ __forceinline__ void double_put(rec_t *p_hi, rec_t *p_lo, double v, uint32_t epoch, uint32_t bits)
+{
+    const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+    rec_put(p_hi, (uint32_t)(u >> 32), epoch, bits);
+    rec_put(p_lo, (uint32_t)u, epoch, 0u);
+}
+__device__ __forceinline__ double double_from(rec_t r_hi, rec_t r_lo)
+{
+    return __longlong_as_double((long long)(((unsigned long long)rec_payload(r_hi) << 32) | rec_payload(r_lo)));
+}
+
+// A float64 state: the sign rides in the user bits of the first record.
 __device__ __forceinline__ void state64_put(rec_t *p_hi, rec_t *p_lo, const State64 &x, uint32_t epoch, bool with_sign)
 {
-    const unsigned long long bits = (unsigned long long)__double_as_longlong(x.lx);
-    rec_put(p_hi, (uint32_t)(bits >> 32), epoch, with_sign ? (x.s >> 31) : 0u);
-    rec_put(p_lo, (uint32_t)bits, epoch, 0u);
+    double_put(p_hi, p_lo, x.lx, epoch, with_sign ? (x.s >> 31) : 0u);
 }
 __device__ __forceinline__ State64 state64_from(rec_t r_hi, rec_t r_lo, bool with_sign)
 {
-    State64 x;
-    x.lx = __longlong_as_double((long long)(((unsigned long long)rec_payload(r_hi) << 32) | rec_payload(r_lo)));
-    x.s = with_sign ? (rec_bits(r_hi) << 31) : 0u;
-    return x;
+    return State64{double_from(r_hi, r_lo), with_sign ? (rec_bits(r_hi) << 31) : 0u};
 }
 
 // A segment summary is two records: {A, tag | sA, sM} and {M, tag}.
@@ -494,6 +527,22 @@ __device__ __forceinline__ Seg seg_from(rec_t ra, rec_t rm)
     g.sA = SIGNED ? (rec_bits(ra) << 31) : 0u;
     g.sM = SIGNED ? (rec_bits(ra) << 30) : 0u;
     return g;
+}
+
+// A float64 summary is four: high and low word of A (the first with the signs), of M.
+template <int DOM>
+__device__ __forceinline__ void seg64_put(rec_t *pa, rec_t *pm, int plane, const Seg64 &g, uint32_t epoch)
+{
+    constexpr bool SIGNED = DOM == kSigned;
+    double_put(pa, pa + plane, g.A, epoch, SIGNED ? ((g.sA >> 31) | ((g.sM >> 31) << 1)) : 0u);
+    double_put(pm, pm + plane, g.M, epoch, 0u);
+}
+template <int DOM>
+__device__ __forceinline__ Seg64 seg64_from(const rec_t (&r)[4])
+{
+    constexpr bool SIGNED = DOM == kSigned;
+    return Seg64{double_from(r[0], r[1]), double_from(r[2], r[3]), SIGNED ? (rec_bits(r[0]) << 31) : 0u,
+                 SIGNED ? (rec_bits(r[0]) << 30) : 0u};
 }
 
 } // namespace hs

@@ -47,10 +47,11 @@ struct BndParams {
     uint32_t draws_per_q; // workgroups per queue = grid size / nq
     rec_t *header;    // scratch header (ticket queues); null when the launch needs no carries
     rec_t *agg;       // [ntiles][2][CH]  tile summaries: plane 0 = {A | signs}, plane 1 = {M}
-                      // (the last tile of a group has no use for its own: TREE: its group's is there instead)
+                      // (the last tile of a group has no use for its own.  TREE: A of its group's summary is
+                      // there instead, float64 in two records, and behind the last group of a super-group the
+                      // state at the start of the next one)
     rec_t *state;     // [ngroups][ncols][2][CH] state at the start of a group: float64 log2|x| in two records
-                      // (high word | sign, low word)
-                      // (TREE: [nsuper][ncols][2][CH], at the start of a super-group of G groups)
+                      // (high word | sign, low word).  TREE: M of the group's summary
     uint32_t spin_limit;
     uint32_t drop_tile;
     Timeline tl;
@@ -119,7 +120,8 @@ __device__ __forceinline__ void lds_await(volatile uint32_t *flag)
 // 131072 x 96: 203 us, of which a tile waited 34 of its 43 us): the last tile of a group also publishes the
 // summary of its group, and states are handed on only from one super-group of G groups to the next.  A
 // tile then reads up to G - 1 tile summaries, G - 1 group summaries and one state; each of its waves fetches
-// and folds a part of them beside its own loads, and the first wave folds the parts.
+// one of each level beside its own loads, and the first wave folds them.  Whatever is folded beyond a tile is
+// folded in float64, as the chain of states is.
 //
 // No wave waits for more than it needs.  The first wave along time of each 64-channel column fetches the
 // carry records, forms the state at the start of the tile and hands it to the waves behind it through
@@ -132,19 +134,20 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     constexpr bool SIGNED = DOM == kSigned;
     constexpr int CH = 64 * CG;  // channels of the tile
     constexpr int TS = NW / CG;  // waves one after the other along time
-    constexpr int PT = TREE ? G / TS : (G > 1 ? G - 1 : 1); // summaries of each level a wave fetches
+    constexpr int PT = TREE ? 1 : (G > 1 ? G - 1 : 1); // tile summaries a wave fetches
     static_assert(T <= 32, "one sign word per channel");
     static_assert(NW % CG == 0, "the waves form a CG x TS grid");
     static_assert(!DENSE || CG == 1, "dense columns are mapped one channel per lane");
-    static_assert(!TREE || (CG == 1 && TS > 1 && G % TS == 0), "the waves of a tile share the summaries evenly");
+    static_assert(!TREE || (CG == 1 && TS > 1 && G == TS), "every wave of a tile takes one summary of each level");
     __shared__ float lds_A[TS][CH];
     __shared__ float lds_M[TS][CH];
     __shared__ uint32_t lds_S[SIGNED ? TS : 1][CH];
     __shared__ double lds_startL[CH]; // float64: the wave that closes a group hands it on as it is
     __shared__ uint32_t lds_startS[CH];
-    // TREE: every wave's fold of its part of the tile summaries [0] and of the group summaries [1]
-    __shared__ float lds_partA[TREE ? 2 : 1][TREE ? TS : 1][CH], lds_partM[TREE ? 2 : 1][TREE ? TS : 1][CH];
-    __shared__ uint32_t lds_partS[TREE ? 2 : 1][TREE ? TS : 1][CH];
+    // TREE: every wave's tile summary and its group summary
+    __shared__ float lds_tileA[TREE ? TS : 1][CH], lds_tileM[TREE ? TS : 1][CH];
+    __shared__ double lds_groupA[TREE ? TS : 1][CH], lds_groupM[TREE ? TS : 1][CH];
+    __shared__ uint32_t lds_tileS[TREE ? TS : 1][CH], lds_groupS[TREE ? TS : 1][CH];
     // and, while the records are waited for, the wave's fold of the waves before it (registers are full)
     __shared__ float lds_preA[TREE ? TS : 1][CH], lds_preM[TREE ? TS : 1][CH];
     __shared__ uint32_t lds_preS[TREE ? TS : 1][CH];
@@ -156,7 +159,7 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     const int wc = w % CG, ts = w / CG;
     volatile uint32_t *flag_run = flags;              // [TS][CG]: the wave's summary is in LDS
     volatile uint32_t *flag_start = flags + TS * CG;  // [CG]: the column's start state is in LDS
-    volatile uint32_t *flag_part = flags + TS * CG + CG; // TREE: [2][TS]: the wave's folds are in LDS
+    volatile uint32_t *flag_part = flags + TS * CG + CG; // TREE: [2][TS]: the wave's summaries are in LDS
 
     const int chunk = (int)(tile / (uint32_t)p.ncols);
     const int col = (int)(tile % (uint32_t)p.ncols);
@@ -195,52 +198,50 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     //      published, and the records then arrive ahead of the tile's own loads at no cost in latency ---
     const bool first = ts == 0; // wave-uniform
     const bool fetches = TREE || first;
-    rec_t rA[PT], rM[PT], gA[TREE ? PT : 1], gM[TREE ? PT : 1], rS = 0, rS2 = 0;
+    rec_t rA[PT], rM[PT], rG[4] = {}, rS = 0, rS2 = 0;
     const int q = TREE ? g / G : g;   // TREE: super-group, and the group's place in it
     const int gi = TREE ? g % G : 0;
     const bool has_state = first && q > 0;
-    const int j0 = TREE ? ts * PT : 0; // first of the summaries this wave fetches
-    bool want_state = has_state, want_tiles = true, want_groups = true; // TREE: still missing (wave-uniform)
+    const int j0 = TREE ? ts : 0;             // first of the tile summaries this wave fetches,
+    const bool has_group = TREE && ts < gi;   // and whether it has a group's to fetch
+    bool want_state = has_state, want_tiles = true, want_group = has_group; // TREE: still missing (wave-uniform)
     auto issue_records = [&]() {
         if (want_state) {
-            const rec_t *sp = p.state + ((size_t)q * p.ncols + col) * (2 * CH) + c;
+            const rec_t *sp = (TREE ? p.agg + ((size_t)(q * G * G - 1) * p.ncols + col) * (2 * CH)
+                                    : p.state + ((size_t)q * p.ncols + col) * (2 * CH)) + c;
             rS = rec_get(sp);
             rS2 = rec_get(sp + CH);
         }
 #pragma unroll
-        for (int j = 0; j < (TREE ? PT : G - 1); ++j) {
+        for (int j = 0; j < (TREE ? 1 : G - 1); ++j) {
             if (want_tiles && j0 + j < r) {
                 const rec_t *tp = p.agg + ((size_t)(g * G + j0 + j) * p.ncols + col) * (2 * CH) + c;
                 rA[j] = rec_get(tp);
                 rM[j] = rec_get(tp + CH);
             }
-            if (TREE && want_groups && j0 + j < gi) {
-                const rec_t *gp = p.agg + ((size_t)((q * G + j0 + j) * G + G - 1) * p.ncols + col) * (2 * CH) + c;
-                gA[TREE ? j : 0] = rec_get(gp);
-                gM[TREE ? j : 0] = rec_get(gp + CH);
-            }
+        }
+        if (TREE && want_group) {
+            const rec_t *gp = p.agg + ((size_t)((q * G + ts) * G + G - 1) * p.ncols + col) * (2 * CH) + c;
+            const rec_t *mp = p.state + ((size_t)(q * G + ts) * p.ncols + col) * (2 * CH) + c;
+            rG[0] = rec_get(gp);
+            rG[1] = rec_get(gp + CH);
+            rG[2] = rec_get(mp);
+            rG[3] = rec_get(mp + CH);
         }
     };
     auto tiles_in = [&]() -> bool { // the tile summaries of this lane carry the launch's tag
         bool ok = true;
 #pragma unroll
-        for (int j = 0; j < (TREE ? PT : G - 1); ++j) {
+        for (int j = 0; j < (TREE ? 1 : G - 1); ++j) {
             if (j0 + j < r) ok = ok && rec_ok(rA[j], epoch) && rec_ok(rM[j], epoch);
         }
         return ok;
     };
-    auto groups_in = [&]() -> bool { // TREE: the group summaries do
-        bool ok = true;
-        if constexpr (TREE) {
-#pragma unroll
-            for (int j = 0; j < PT; ++j) {
-                if (j0 + j < gi) ok = ok && rec_ok(gA[j], epoch) && rec_ok(gM[j], epoch);
-            }
-        }
-        return ok;
+    auto group_in = [&]() -> bool { // TREE: the group summary does
+        return !has_group || (rec_ok(rG[0], epoch) && rec_ok(rG[1], epoch) && rec_ok(rG[2], epoch) && rec_ok(rG[3], epoch));
     };
     auto state_in = [&]() -> bool { return !has_state || (rec_ok(rS, epoch) && rec_ok(rS2, epoch)); };
-    auto records_in = [&]() -> bool { return tiles_in() && state_in() && groups_in(); }; // all of this lane's records do
+    auto records_in = [&]() -> bool { return tiles_in() && state_in() && group_in(); }; // all of this lane's records do
     auto wave_all = [](bool ok) -> bool { return __builtin_amdgcn_ballot_w64(!ok) == 0ull; };
     bool have_records = false;
     if (fetches) issue_records();
@@ -348,78 +349,69 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
         st64.lx = (double)lx;
     };
     if constexpr (TREE) {
-        // ---- every wave folds its part of the records: the tile summaries as soon as they are in, since the
-        //      tile that closes a group owes the later groups their sum, whatever else is on its way ----
-        auto put_part = [&](int level, const Seg &g2) {
-            lds_partA[level][ts][c] = g2.A;
-            lds_partM[level][ts][c] = g2.M;
-            lds_partS[level][ts][c] = pack_signs(g2);
-            lds_signal(&flag_part[level * TS + ts]);
-        };
-        auto get_part = [&](int level, int j) -> Seg {
-            lds_await(&flag_part[level * TS + j]);
+        // ---- every wave passes on its summaries: the tile's as soon as it is in, since the tile that closes
+        //      a group owes the later groups their sum, whatever else is on its way -------------------------
+        auto get_tile = [&](int j) -> Seg {
+            lds_await(&flag_part[j]);
             Seg g2;
-            g2.A = lds_partA[level][j][c];
-            g2.M = lds_partM[level][j][c];
+            g2.A = lds_tileA[j][c];
+            g2.M = lds_tileM[j][c];
             g2.sA = g2.sM = 0u;
-            if (SIGNED) unpack_signs(lds_partS[level][j][c], g2);
+            if (SIGNED) unpack_signs(lds_tileS[j][c], g2);
             return g2;
         };
-        bool lost = false, tiles_done = false; // lost: this lane's records never came
+        bool lost = false, tile_done = false; // lost: this lane's records never came
         uint32_t polls = 0;
         for (;;) {
             want_tiles = want_tiles && !wave_all(tiles_in());
-            want_groups = want_groups && !wave_all(groups_in());
+            want_group = want_group && !wave_all(group_in());
             want_state = want_state && !wave_all(state_in());
-            have_records = !want_tiles && !want_groups && !want_state;
+            have_records = !want_tiles && !want_group && !want_state;
             if (!have_records && ++polls > p.spin_limit) {
                 // give up: go on as if everything were in, with NaN for what is missing
                 lost = true;
                 note_wait_gave_up(p.header);
             }
-            if (!tiles_done && (!want_tiles || lost)) {
-                tiles_done = true;
-                Seg part = seg_identity<DOM>();
-#pragma unroll
-                for (int j = 0; j < PT; ++j) {
-                    if (j0 + j < r) part = seg_combine<DOM>(part, seg_from<DOM>(rA[j], rM[j]));
-                }
+            if (!tile_done && (!want_tiles || lost)) {
+                tile_done = true;
+                Seg part = ts < r ? seg_from<DOM>(rA[0], rM[0]) : seg_identity<DOM>();
                 if (!tiles_in()) part.M = __builtin_nanf("");
-                put_part(0, part);
+                lds_tileA[ts][c] = part.A;
+                lds_tileM[ts][c] = part.M;
+                lds_tileS[ts][c] = pack_signs(part);
+                lds_signal(&flag_part[ts]);
                 if (closing && more && r == G - 1 && gi < G - 1) {
                     // the last tile of a group owes the later groups the summary of its group
-                    part = get_part(0, 0);
+                    Seg64 sum = seg64(get_tile(0));
 #pragma unroll 1
-                    for (int j = 1; j < TS; ++j) part = seg_combine<DOM>(part, get_part(0, j));
-                    rec_t *gp = p.agg + (size_t)tile * (2 * CH) + c;
-                    seg_put<DOM>(gp, gp + CH, seg_combine<DOM>(part, get_total()), epoch);
+                    for (int j = 1; j < G - 1; ++j) sum = seg_append64<DOM>(sum, get_tile(j));
+                    seg64_put<DOM>(p.agg + (size_t)tile * (2 * CH) + c, p.state + ((size_t)g * p.ncols + col) * (2 * CH) + c, CH,
+                                   seg_append64<DOM>(sum, get_total()), epoch);
                 }
             }
             if (have_records || lost) break;
             __builtin_amdgcn_s_sleep(2);
             issue_records();
         }
-        {
-            Seg part = seg_identity<DOM>();
-#pragma unroll
-            for (int j = 0; j < PT; ++j) {
-                if (j0 + j < gi) part = seg_combine<DOM>(part, seg_from<DOM>(gA[j], gM[j]));
-            }
-            if (!groups_in()) part.M = __builtin_nanf("");
-            put_part(1, part);
+        if (has_group) {
+            const Seg64 sum = seg64_from<DOM>(rG);
+            lds_groupA[ts][c] = sum.A;
+            lds_groupM[ts][c] = group_in() ? sum.M : __builtin_nan("");
+            lds_groupS[ts][c] = (sum.sA >> 31) | ((sum.sM >> 31) << 1);
+            lds_signal(&flag_part[TS + ts]);
         }
         p.tl.mark(tile, 4);
         if (first) {
             if (q == 0) state_from_x0();
             else st64 = state64_from(rS, rS2, SIGNED);
 #pragma unroll 1
-            for (int j = 0; j < TS; ++j) {
-                if (j * PT < gi) st64 = seg_apply64<DOM>(st64, get_part(1, j));
+            for (int j = 0; j < gi; ++j) {
+                lds_await(&flag_part[TS + j]);
+                const uint32_t s = SIGNED ? lds_groupS[j][c] : 0u;
+                st64 = seg_apply64<DOM>(st64, Seg64{lds_groupA[j][c], lds_groupM[j][c], s << 31, s << 30});
             }
 #pragma unroll 1
-            for (int j = 0; j < TS; ++j) {
-                if (j * PT < r) st64 = seg_apply64<DOM>(st64, get_part(0, j));
-            }
+            for (int j = 0; j < r; ++j) st64 = seg_apply64<DOM>(st64, get_tile(j));
             if (!state_in()) st64.lx = __builtin_nan("");
             st.lx = (float)st64.lx;
             st.s = st64.s;
@@ -485,7 +477,7 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
         st.s = st64.s;
         if (closing && more && r == G - 1 && (!TREE || gi == G - 1)) {
             // last tile of a group (TREE: of a super-group): the state after this tile starts the next one
-            rec_t *sp = p.state + ((size_t)(q + 1) * p.ncols + col) * (2 * CH) + c;
+            rec_t *sp = (TREE ? p.agg + (size_t)tile * (2 * CH) : p.state + ((size_t)(q + 1) * p.ncols + col) * (2 * CH)) + c;
             state64_put(sp, sp + CH, seg_apply64<DOM>(st64, get_total()), epoch, SIGNED);
         }
         if constexpr (TREE) {
@@ -730,7 +722,7 @@ BndPlan make_plan(const ScanCall &c, bool allow_wide = true, bool want_tree = fa
     pl.ntiles = (uint32_t)pl.ncols * (uint32_t)pl.nchunks;
     pl.off_agg = 0;
     pl.off_state = (size_t)pl.ntiles * 2 * pl.CH;
-    pl.records = pl.off_state + (size_t)(pl.tree ? ceil_div(pl.ngroups, pl.G) + 1 : pl.ngroups) * pl.ncols * 2 * pl.CH;
+    pl.records = pl.off_state + (size_t)pl.ngroups * pl.ncols * 2 * pl.CH;
     pl.ticketless = pl.nchunks == 1 && c.n <= 64; // short single-tile columns: no records, no tickets
     // A queue's workgroups that find no tile behind their ticket (uneven deal) end at once.
     pl.nq = kQueues;
@@ -743,7 +735,7 @@ BndPlan make_plan(const ScanCall &c, bool allow_wide = true, bool want_tree = fa
         pl.grid = (uint32_t)pl.nq * (uint32_t)pl.cols_per_q * (uint32_t)pl.nchunks;
     }
     // A caller with a fixed scratch buffer may have to do without the wide tiles, which take twice the records,
-    // and with the second carry level, whose states are fewer.
+    // and with the second carry level, whose groups are longer.
     if (c.scratch_budget != 0 && kRecordBase + pl.records > c.scratch_budget) {
         if (pl.cg > 1) return make_plan(c, false);
         if (!want_tree && pl.ncols < 64) {

@@ -4,6 +4,7 @@ two carry levels of eight, whose records the waves of a tile share."""
 import numpy as np
 import pytest
 
+import oracle
 from paper_2311_06281_amd import workloads
 
 import test_gpu_cross_product as cross
@@ -75,6 +76,25 @@ def test_a_tile_that_never_publishes_ends_in_nan_with_two_carry_levels(gpu):
     hb.heinsen_scan(*args)
     assert hb.heinsen_check(torch.cuda.current_stream()) == hb.HEINSEN_OK
     assert (out - 1).abs().max() <= 1e-5
+
+
+# Slow decay (a within 1e-4 of one, x close to 1), log domain throughout: the error of the states that travel between
+# tiles, since the steps inside a tile add little.  A fold of eight tile summaries in float32 rounds a term of size 1 to
+# 2^-24 (6e-8) up to eight times over; in float64 what is left is the outputs' own rounding and that of one tile.
+# Measured relative rms over the steps behind the first super-group, 4 and 12 columns: 1.0e-7 and 1.1e-7 with the
+# levels above a tile in float64, 1.5e-7 with them in float32.
+@pytest.mark.parametrize("columns", [4, 12])
+def test_summaries_of_many_tiles_keep_float64(gpu, columns):
+    rng = np.random.default_rng(1)
+    shape = (1, 256 * 150 + 17, 64 * columns)
+    a = np.exp(-1e-4 * rng.uniform(0.5, 1.5, shape)).astype(np.float32)
+    b = ((1 - a.astype(np.float64)) * rng.uniform(0.9, 1.1, shape)).astype(np.float32)
+    a, b, x0 = np.log(a), np.log(b), np.zeros(shape[2], np.float32)
+    got = cross._run(gpu, a, b, x0, "BND", cross.MODES["log_logout"], False)
+    behind = slice(256 * 64, None)
+    err = got[:, behind].astype(np.float64) - oracle.sequential_log(a, b, x0, layout=oracle.LAYOUT_BND)[:, behind]
+    rms = float(np.sqrt(np.mean(err * err)))  # of log x, which is the relative error of x
+    assert rms <= 1.25e-7, rms
 
 
 # a few steps: four channels per thread and one, the ends of a workgroup, the last length of the kernel and the next
