@@ -755,6 +755,15 @@ __device__ __forceinline__ Lin lin_packed_inclusive_scan(Lin g, int lane, int po
     return g;
 }
 
+__device__ __forceinline__ int packed_inclusive_sum(int v, int lane, int pos, int group)
+{
+    packed_scan_steps([&](auto ctrl, bool ok) {
+        const int before = (int)dpp_u<decltype(ctrl)::ctrl, decltype(ctrl)::mask>(0u, (uint32_t)v);
+        v += ok ? before : 0;
+    }, lane, pos, group);
+    return v;
+}
+
 template <int DOM, bool LOG_IN, bool LOG_OUT, typename InT, int ITEMS, bool VECIO>
 __global__ __launch_bounds__(256, 4) void heinsen_scan_rows_packed(PackedParams p)
 {
@@ -838,22 +847,32 @@ __global__ __launch_bounds__(256, 4) void heinsen_scan_rows_packed(PackedParams 
             }
             wave_lds_order();
         };
-        bool done = false; // wave-uniform
+        // Every row of the wave decides for itself, so that what becomes of a row does not depend on its
+        // neighbours' numbers.
         Lin g;
         int up;
-        if (wave_all(lin_summary<ITEMS>(get, g, up)) && wave_sum(up) <= kLinUp) {
-            g = lin_dpp<0x138, 0xf>(lin_packed_inclusive_scan(g, lane, pos, p.group));
-            if (pos == 0) g = Lin{1.0, 0.0}; // first lane of a row
-            const double x = fma(g.P, lin_x0(x0), g.Z);
-            done = wave_all(lin_state_ok(x, pos == 0) || !row_ok);
-            if (done) lin_emit<ITEMS>(x, get, put);
-        }
-        if (!done) {
+        bool ok = lin_summary<ITEMS>(get, g, up);
+        up = packed_inclusive_sum(up, lane, pos, p.group); // of the whole row in its last lane
+        g = lin_dpp<0x138, 0xf>(lin_packed_inclusive_scan(g, lane, pos, p.group));
+        if (pos == 0) g = Lin{1.0, 0.0}; // first lane of a row
+        const double x = fma(g.P, lin_x0(x0), g.Z);
+        ok = (ok && up <= kLinUp && lin_state_ok(x, pos == 0)) || !row_ok;
+        const uint64_t bad = __builtin_amdgcn_ballot_w64(!ok);
+        if (bad == 0ull) {
+            lin_emit<ITEMS>(x, get, put);
+        } else {
+            const uint64_t row_lanes = (~0ull >> (64 - p.group)) << (r * p.group);
             Seg excl = wave_shift_up<DOM>(packed_inclusive_scan<DOM>(log_summary<ITEMS>(get), lane, pos, p.group));
             if (pos == 0) excl = seg_identity<DOM>();
             State st;
             encode<DOM, LOG_IN>(x0, st.lx, st.s);
-            log_emit<ITEMS>(seg_apply<DOM>(st, excl), get, put);
+            st = seg_apply<DOM>(st, excl);
+            // The two kinds of rows take their second passes one after the other: the quad in which a row
+            // begins may by then hold outputs of the row that ends in it.
+            const Quads head = get(0);
+            auto get_after = [&](int q) -> Quads { return q == 0 ? head : get(q); };
+            if ((bad & row_lanes) == 0ull) lin_emit<ITEMS>(x, get_after, put);
+            else log_emit<ITEMS>(st, get_after, put);
         }
         if (late) write_own(0, late_re, late_im);
         wave_lds_order();

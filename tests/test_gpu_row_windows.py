@@ -72,3 +72,27 @@ def test_complex_output_in_and_out_of_the_float64_range(gpu, rows, n):
         size = max(1.0, float(np.max(np.abs(ref.real[~zero]), initial=0.0)) / np.log(2.0))
         err = np.max(np.abs(re[~zero] - ref.real[~zero]), initial=0.0)
         assert err <= 5 * np.sqrt(n) * size * 2.0 ** -24 * np.log(2.0) + 2e-6, (r, err)
+
+
+# A row's result is its own: with and without neighbours that need the log-domain steps, bit for bit.  Several rows per
+# wave, with the ends of rows inside a vector (41, 7, 301), on vectors (40, 300) and many rows that share one (1, 2).
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("rows,n", [(130, 41), (130, 40), (200, 7), (700, 301), (700, 300), (600, 1), (600, 2), (90, 100)])
+def test_complex_rows_do_not_depend_on_their_neighbours(gpu, rows, n, bf16):
+    rng = np.random.default_rng(rows + n)
+    a, b, x0 = cross._inputs(rng, (1, rows, n), "BDN", "signed_clog")
+    a = np.where(np.abs(a) < 1e-3, np.float32(0.25), a)  # in range everywhere
+    b = np.where(np.abs(b) < 1e-3, np.float32(0.25), b)
+    if bf16:
+        a = workloads.bf16_bits_to_f32(workloads.f32_to_bf16_bits(a)).reshape(a.shape)
+        b = workloads.bf16_bits_to_f32(workloads.f32_to_bf16_bits(b)).reshape(b.shape)
+    alone = cross._run(gpu, a, b, x0, "BDN", cross.MODES["signed_clog"], bf16)
+    a2, b2, x2 = a.copy(), b.copy(), x0.copy()
+    changed = np.arange(1, rows, 3)
+    a2[0, changed, n // 2] = np.resize(np.array([2.0 ** 40, 2.0 ** -50, np.nan, np.inf], np.float32), len(changed))
+    x2[changed[::5]] = 1e-38
+    got = cross._run(gpu, a2, b2, x2, "BDN", cross.MODES["signed_clog"], bf16)
+    kept = np.setdiff1d(np.arange(rows), changed)
+    assert np.array_equal(got[0, kept].view(np.uint32), alone[0, kept].view(np.uint32))
+    finite = changed[np.isfinite(a2[0, changed, n // 2])]
+    cross._check(got[:, finite], a2[:, finite], b2[:, finite], x2[finite], "BDN", "signed_clog")
