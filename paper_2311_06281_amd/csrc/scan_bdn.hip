@@ -55,10 +55,10 @@ constexpr bool complex_output()
 // in two passes over the lane's inputs: from 0 for the lane's summary (P, Z), x_e = P x_s + Z, which is
 // composed across the lanes as it is, then from the lane's start state for the outputs, one logarithm per
 // element.  Log-domain steps cannot leave their range, these can, so a wave takes them only if
-//     |a| in [2^-18, 2^8], b = 0 or |b| in [2^-60, 2^60] for every element,
+//     a = 0 or |a| in [2^-36, 2^16], b = 0 or |b| in [2^-60, 2^60] for every element,
 //     the lanes' products P that are above 1 multiply to at most 2^600 over the wave,
 //     every lane's start state is in [2^-360, 2^600] (or is the row's x_0 = 0).
-// The at most 32 steps of a lane then multiply any number by 2^-576 to 2^256, so no state inside it reaches
+// The at most 16 steps of a lane then multiply any number by 0 or by 2^-576 to 2^256, so no state inside it reaches
 // 2^-1022 or 2^1023, and neither does a Z (at most 2^(600 + 256 + 60) times the number of steps).  A term that
 // underflows between lanes is below 2^-1022, grows by 2^600 at most, and is less than 2^-60 of any start state.
 //
@@ -87,8 +87,9 @@ struct Quads {
 template <int ITEMS, typename GET>
 __device__ __forceinline__ bool lin_summary(GET &&get, Lin &g, int &up)
 {
-    float alo = 1.0f, ahi = 1.0f, bhi = 0.0f;
-    uint32_t blo = 0xffffffffu; // of 2|b| - 1 as an integer, which puts 0 above everything else
+    static_assert(ITEMS <= 16, "the bounds are for 16 steps per lane");
+    float ahi = 1.0f, bhi = 0.0f;
+    uint32_t alo = 0xffffffffu, blo = 0xffffffffu; // of 2|v| - 1 as an integer, which puts 0 above everything else
     g = Lin{1.0, 0.0};
 #pragma unroll 2
     for (int q = 0; q < ITEMS / 4; ++q) {
@@ -96,16 +97,16 @@ __device__ __forceinline__ bool lin_summary(GET &&get, Lin &g, int &up)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             g = lin_combine(g, Lin{(double)v.a[i], (double)v.b[i]});
-            alo = fminf(alo, fabsf(v.a[i]));
             ahi = fmaxf(ahi, fabsf(v.a[i]));
             bhi = fmaxf(bhi, fabsf(v.b[i]));
-            const uint32_t z = (f2u(v.b[i]) << 1) - 1u;
+            const uint32_t y = (f2u(v.a[i]) << 1) - 1u, z = (f2u(v.b[i]) << 1) - 1u;
+            alo = y < alo ? y : alo;
             blo = z < blo ? z : blo;
         }
     }
     up = __builtin_amdgcn_frexp_exp(g.P);
     up = up > 0 ? up : 0;
-    return alo >= 0x1p-18f && ahi <= 0x1p8f && bhi <= 0x1p60f && blo >= ((127u - 60u) << 24) - 1u;
+    return alo >= ((127u - 36u) << 24) - 1u && ahi <= 0x1p16f && bhi <= 0x1p60f && blo >= ((127u - 60u) << 24) - 1u;
 }
 
 // Pass 2 in float64.
@@ -127,50 +128,52 @@ __device__ __forceinline__ void lin_emit(double x, GET &&get, PUT &&put)
     }
 }
 
-// The same passes by log-domain steps (see seg_step, emit_clog).
-template <int ITEMS, typename VISIT>
-__device__ __forceinline__ Seg log_steps(VISIT &&visit)
+// The same passes by log-domain steps.  Pass 1 leaves every element's record (A_k, M_k) where a and b were
+// (keep(q, A, M)), with its signs in sw and sm (see stash), so that pass 2 costs one log-add-exp per element.
+template <int ITEMS, typename GET, typename KEEP>
+__device__ __forceinline__ Seg log_summary(GET &&get, KEEP &&keep, uint32_t &sw, uint32_t &sm)
 {
+    static_assert(ITEMS <= 32, "sign bits are kept in one word");
     Seg run = seg_identity<kSigned>();
+    sw = sm = 0u;
 #pragma unroll 1
-    for (int q = 0; q < ITEMS / 4; ++q) visit(q, run);
+    for (int q = 0; q < ITEMS / 4; ++q) {
+        const Quads v = get(q);
+        f32x4 A, M;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float la, lb;
+            uint32_t sa, sb;
+            encode<kSigned, false>(v.a[i], la, sa);
+            encode<kSigned, false>(v.b[i], lb, sb);
+            if (q == 0 && i == 0) run = Seg{la, lb, sa, sb};
+            else seg_step<kSigned>(run, la, sa, lb, sb);
+            A[i] = run.A;
+            M[i] = run.M;
+            sw |= (run.sA >> 31) << (4 * q + i);
+            sm |= (run.sM >> 31) << (4 * q + i);
+        }
+        keep(q, A, M);
+    }
     return run;
 }
-__device__ __forceinline__ void log_step(Seg &run, bool first, float a, float b)
-{
-    float la, lb;
-    uint32_t sa, sb;
-    encode<kSigned, false>(a, la, sa);
-    encode<kSigned, false>(b, lb, sb);
-    if (first) run = Seg{la, lb, sa, sb};
-    else seg_step<kSigned>(run, la, sa, lb, sb);
-}
-template <int ITEMS, typename GET>
-__device__ __forceinline__ Seg log_summary(GET &&get)
-{
-    return log_steps<ITEMS>([&](int q, Seg &run) {
-        const Quads v = get(q);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) log_step(run, q == 0 && i == 0, v.a[i], v.b[i]);
-    });
-}
 template <int ITEMS, typename GET, typename PUT>
-__device__ __forceinline__ void log_emit(const State &st, GET &&get, PUT &&put)
+__device__ __forceinline__ void log_emit(const State &st, uint32_t sw, uint32_t sm, GET &&get, PUT &&put)
 {
-    (void)log_steps<ITEMS>([&](int q, Seg &run) {
-        const Quads v = get(q);
+    const uint32_t swx = fold_state_sign<kSigned>(sw, st);
+#pragma unroll 1
+    for (int q = 0; q < ITEMS / 4; ++q) {
+        const Quads v = get(q); // the records
         f32x4 re, im;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            log_step(run, q == 0 && i == 0, v.a[i], v.b[i]);
-            float r;
-            uint32_t sr;
-            slae<true>(st.lx + run.A, st.s ^ run.sA, run.M, run.sM, r, sr);
-            re[i] = r * kLn2;
-            im[i] = (sr & kSignBit) ? kPi : 0.0f;
+            float re_i, im_i;
+            emit_clog(st, v.a[i], v.b[i], swx, sm, 4 * q + i, re_i, im_i);
+            re[i] = re_i;
+            im[i] = im_i;
         }
         put(q, re, im);
-    });
+    }
 }
 
 // Start state of a lane: in range for lin_emit?  `exact_zero`: a zero is x_0 itself.
@@ -599,6 +602,11 @@ struct OwnQuads {
         const u32x4 a = lds[2 * q], b = lds[2 * q + 1];
         return Quads{f32x4{u2f(a[0]), u2f(a[1]), u2f(a[2]), u2f(a[3])}, f32x4{u2f(b[0]), u2f(b[1]), u2f(b[2]), u2f(b[3])}};
     }
+    __device__ __forceinline__ void keep(int q, f32x4 A, f32x4 M) const // in the place of a and b
+    {
+        lds[2 * q] = u32x4{f2u(A[0]), f2u(A[1]), f2u(A[2]), f2u(A[3])};
+        lds[2 * q + 1] = u32x4{f2u(M[0]), f2u(M[1]), f2u(M[2]), f2u(M[3])};
+    }
     __device__ __forceinline__ void operator()(int q, f32x4 re, f32x4 im) const
     {
         lds[2 * q] = u32x4{f2u(re[0]), f2u(im[0]), f2u(re[1]), f2u(im[1])};
@@ -646,10 +654,12 @@ __global__ __launch_bounds__(256, VECIO ? 4 : 1) void heinsen_scan_rows_wave(Row
             if (done) lin_emit<ITEMS>(x, own, own);
         }
         if (!done) {
-            const Seg excl = wave_shift_up<DOM>(wave_inclusive_scan<DOM>(log_summary<ITEMS>(own)));
+            uint32_t sw, sm;
+            auto keep = [&](int q, f32x4 A, f32x4 M) { own.keep(q, A, M); };
+            const Seg excl = wave_shift_up<DOM>(wave_inclusive_scan<DOM>(log_summary<ITEMS>(own, keep, sw, sm)));
             State st;
             encode<DOM, LOG_IN>(x0, st.lx, st.s);
-            log_emit<ITEMS>(seg_apply<DOM>(st, excl), own, own);
+            log_emit<ITEMS>(seg_apply<DOM>(st, excl), sw, sm, own, own);
         }
         wave_lds_order();
         if (VECIO) wave_unstage_span<ITEMS / 2, 1>(orow - OW * h, OW * sp.lo, OW * sp.hi, region, lane, 0);
@@ -852,7 +862,7 @@ __global__ __launch_bounds__(256, 4) void heinsen_scan_rows_packed(PackedParams 
         Lin g;
         int up;
         bool ok = lin_summary<ITEMS>(get, g, up);
-        up = packed_inclusive_sum(up, lane, pos, p.group); // of the whole row in its last lane
+        if (!wave_all(up * p.group <= kLinUp)) up = packed_inclusive_sum(up, lane, pos, p.group); // of the whole row in its last lane
         g = lin_dpp<0x138, 0xf>(lin_packed_inclusive_scan(g, lane, pos, p.group));
         if (pos == 0) g = Lin{1.0, 0.0}; // first lane of a row
         const double x = fma(g.P, lin_x0(x0), g.Z);
@@ -861,8 +871,20 @@ __global__ __launch_bounds__(256, 4) void heinsen_scan_rows_packed(PackedParams 
         if (bad == 0ull) {
             lin_emit<ITEMS>(x, get, put);
         } else {
-            const uint64_t row_lanes = (~0ull >> (64 - p.group)) << (r * p.group);
-            Seg excl = wave_shift_up<DOM>(packed_inclusive_scan<DOM>(log_summary<ITEMS>(get), lane, pos, p.group));
+            const bool by_steps = (bad & (~0ull >> (64 - p.group)) << (r * p.group)) != 0ull;
+            uint32_t sw, sm;
+            auto keep = [&](int q, f32x4 A, f32x4 M) { // rows that share a quad keep their own elements of it
+                if (!by_steps) return;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (start + 4 * q + i >= h && 4 * q + i < end) {
+                        reinterpret_cast<float *>(region + clog_slot<ITEMS>(at / 4 + q, 0))[i] = A[i];
+                        reinterpret_cast<float *>(region + clog_slot<ITEMS>(at / 4 + q, 1))[i] = M[i];
+                    }
+                }
+                wave_lds_order();
+            };
+            Seg excl = wave_shift_up<DOM>(packed_inclusive_scan<DOM>(log_summary<ITEMS>(get, keep, sw, sm), lane, pos, p.group));
             if (pos == 0) excl = seg_identity<DOM>();
             State st;
             encode<DOM, LOG_IN>(x0, st.lx, st.s);
@@ -871,8 +893,8 @@ __global__ __launch_bounds__(256, 4) void heinsen_scan_rows_packed(PackedParams 
             // begins may by then hold outputs of the row that ends in it.
             const Quads head = get(0);
             auto get_after = [&](int q) -> Quads { return q == 0 ? head : get(q); };
-            if ((bad & row_lanes) == 0ull) lin_emit<ITEMS>(x, get_after, put);
-            else log_emit<ITEMS>(st, get_after, put);
+            if (by_steps) log_emit<ITEMS>(st, sw, sm, get_after, put);
+            else lin_emit<ITEMS>(x, get_after, put);
         }
         if (late) write_own(0, late_re, late_im);
         wave_lds_order();
@@ -1136,7 +1158,9 @@ __device__ __forceinline__ void tiles_tile(const TileParams &p, const uint32_t t
             lin_emit<ITEMS>(x, own, own);
         } else {
             // one wave of the row is out of range: the whole row by log-domain steps
-            const Seg incl = wave_inclusive_scan<DOM>(log_summary<ITEMS>(own));
+            uint32_t sw, sm;
+            auto keep = [&](int q, f32x4 A, f32x4 M) { own.keep(q, A, M); };
+            const Seg incl = wave_inclusive_scan<DOM>(log_summary<ITEMS>(own, keep, sw, sm));
             if (lane == 63) {
                 lds_A[w] = incl.A;
                 lds_M[w] = incl.M;
@@ -1151,7 +1175,7 @@ __device__ __forceinline__ void tiles_tile(const TileParams &p, const uint32_t t
             }
             State st;
             encode<DOM, LOG_IN>(x0, st.lx, st.s);
-            log_emit<ITEMS>(seg_apply<DOM>(st, seg_combine<DOM>(before, excl)), own, own);
+            log_emit<ITEMS>(seg_apply<DOM>(st, seg_combine<DOM>(before, excl)), sw, sm, own, own);
         }
         wave_lds_order();
         if (VECIO) wave_unstage_span<ITEMS / 2, 1>(orow + OW * (wstart - h), OW * sp.lo, OW * sp.hi, region, lane, 0);

@@ -45,8 +45,8 @@ def test_complex_output_in_and_out_of_the_float64_range(gpu, rows, n):
     b = rng.uniform(0.1, 1.0, (rows, n)).astype(np.float32)
     x0 = rng.uniform(0.5, 2.0, rows).astype(np.float32)
     at = n // 2
-    a[0, at] = 1e-9            # below 2^-18
-    a[1, at] = 1e4             # above 2^8
+    a[0, at] = 1e-12           # below 2^-36
+    a[1, at] = 1e6             # above 2^16
     a[2, at] = 0.0             # restarts the row
     b[3, at] = 1e-25           # below 2^-60
     b[4, at] = 1e25            # above 2^60
@@ -55,7 +55,7 @@ def test_complex_output_in_and_out_of_the_float64_range(gpu, rows, n):
     x0[7], b[7] = 0.0, 0.0     # x = 0 throughout
     a[8], b[8] = 3.0, 0.0      # leaves float64 where n is long enough
     a[9], b[9] = 2.0 ** -7, 0.0
-    a[10], b[10] = 2.0 ** -17, 1.0
+    a[10], b[10] = 2.0 ** -36, 1.0
     a[11, : at], a[11, at:], b[11] = 2.0 ** -9, 2.0 ** 7, 0.0
     got = cross._run(gpu, a[None], b[None], x0, "BDN", cross.MODES["signed_clog"], False)[0]
     for r in list(range(12)) + [rows - 1]:
@@ -96,3 +96,26 @@ def test_complex_rows_do_not_depend_on_their_neighbours(gpu, rows, n, bf16):
     assert np.array_equal(got[0, kept].view(np.uint32), alone[0, kept].view(np.uint32))
     finite = changed[np.isfinite(a2[0, changed, n // 2])]
     cross._check(got[:, finite], a2[:, finite], b2[:, finite], x2[finite], "BDN", "signed_clog")
+
+
+# In range, with resets and small coefficients in every row: the float64 path, in each of the three kernels.  What it
+# rounds is the number to float32 (2^-25 of it), its mantissa's logarithm (2^-24) and the sum with the exponent
+# (2^-24 of log2 x, of the result): 2^-23 (1 + |re|) leaves a factor of two.  Log-domain steps round a logarithm per step:
+# 3e-7 to 6e-7 on these rows.
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("rows,n", [(600, 300), (600, 257), (520, 700), (520, 1001), (520, 3001), (12, 5000)])
+def test_complex_output_in_range_is_evaluated_in_float64(gpu, rows, n, bf16):
+    rng = np.random.default_rng(rows * n)
+    a = rng.uniform(0.7, 1.3, (rows, n)).astype(np.float32)
+    b = rng.uniform(0.1, 1.0, (rows, n)).astype(np.float32)
+    x0 = rng.uniform(0.5, 2.0, rows).astype(np.float32)
+    a[:, n // 3], a[:, n // 5], a[::2, n // 4] = 0.0, 2.0 ** -36, 2.0 ** 16
+    if bf16:
+        a = workloads.bf16_bits_to_f32(workloads.f32_to_bf16_bits(a)).reshape(a.shape)
+        b = workloads.bf16_bits_to_f32(workloads.f32_to_bf16_bits(b)).reshape(b.shape)
+    got = cross._run(gpu, a[None], b[None], x0, "BDN", cross.MODES["signed_clog"], bf16)[0]
+    ref = np.log(oracle.sequential(a[None], b[None], x0, layout=oracle.LAYOUT_BDN)[0])
+    assert np.all(got[..., 1] == 0.0)
+    err = np.abs(got[..., 0] - ref) / (1.0 + np.abs(ref))
+    print(f"[float64] {rows} x {n} bf16={bf16}: {err.max():.2e}", flush=True)
+    assert err.max() <= 2.0 ** -23
