@@ -132,7 +132,7 @@ __device__ __forceinline__ void slae64(double p, uint32_t sp, double q, uint32_t
         sr = (t >= 0.0f) ? sp : sq;
     }
     const float u = 1.0f + e;
-    r = m + (double)fmaf((e - (u - 1.0f)) * kLog2e, __builtin_amdgcn_rcpf(u), log2_hw(u));
+    r = m + (double)fmaf(e - (u - 1.0f), kLog2e, log2_hw(u)); // what 1 + e rounds off shows where u is close to 1
 }
 
 // A summary of many tiles, which a chain hands on like a state, keeps its two sums in float64 too: folded in

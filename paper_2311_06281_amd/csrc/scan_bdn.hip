@@ -230,6 +230,7 @@ struct RowsParams {
     int64_t rows, n;
     int x0_stride;
     int phase; // elements from the last 16-byte boundary to the first element of a and b (VECIO)
+    bool both; // ask for a and b together
 };
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -250,6 +251,7 @@ __device__ __forceinline__ void wave_lds_order() { asm volatile("" ::: "memory")
 // before (64 x 1024 rows of bf16: 2041 steps 596 -> 189 us, 300 steps of 64 x 4000 rows 251 -> 114 us).
 struct Span {
     int lo, hi;
+    __device__ __forceinline__ bool cut(int vl) const { return ((lo | hi) % vl) != 0; } // some vector is not whole (wave-uniform)
 };
 __device__ __forceinline__ Span wave_span(int64_t lo, int64_t hi, int cap)
 {
@@ -267,7 +269,6 @@ __device__ __forceinline__ bool edge_element(int lo, int hi, int lane, int &e)
     e = lane < VL ? ((lo + VL - 1) / VL - 1) * VL + lane : hi / VL * VL + lane - VL;
     return lane < 2 * VL && e >= lo && e < hi;
 }
-
 // Global (striped, coalesced) -> the wave's LDS region: window vector c to slot c + c/NV.
 template <typename InT, int NV>
 __device__ __forceinline__ void wave_stage_span(const InT *win, Span sp, u32x4 fill, u32x4 *lds, int lane)
@@ -277,7 +278,7 @@ __device__ __forceinline__ void wave_stage_span(const InT *win, Span sp, u32x4 f
     const int c_lo = (sp.lo + VL - 1) / VL;
     const int whole = sp.hi / VL - c_lo;
     const uint32_t count = whole > 0 ? (uint32_t)whole : 0u;
-    const bool cut = ((sp.lo | sp.hi) % VL) != 0; // wave-uniform
+    const bool cut = sp.cut(VL);
     u32x4 t[NV];
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
@@ -304,14 +305,75 @@ __device__ __forceinline__ void wave_stage_span(const InT *win, Span sp, u32x4 f
     wave_lds_order();
 }
 
-// Global (striped, coalesced) -> lanes (blocked): elements of the window outside [lo, hi) become `fill`.
+// The same in two parts, for a and b to be in flight together.  (Where they are not, the parts cost a launch that fills
+// the chip 5 to 10 % over the whole: 32768 rows of 200 steps 15.6 and 14.7 us.)
 template <typename InT, int NV>
-__device__ __forceinline__ void wave_load_span(const InT *win, Span sp, u32x4 fill, u32x4 *lds, int lane, u32x4 (&v)[NV])
+__device__ __forceinline__ void span_fetch(const InT *win, Span sp, u32x4 fill, int lane, u32x4 (&t)[NV], InT &x)
 {
-    wave_stage_span<InT, NV>(win, sp, fill, lds, lane);
+    constexpr int VL = 16 / (int)sizeof(InT);
+    const u32x4 *wv = reinterpret_cast<const u32x4 *>(win);
+    const int c_lo = (sp.lo + VL - 1) / VL;
+    const int whole = sp.hi / VL - c_lo;
+    const uint32_t count = whole > 0 ? (uint32_t)whole : 0u;
 #pragma unroll
-    for (int q = 0; q < NV; ++q) v[q] = lds[lane * (NV + 1) + q];
+    for (int j = 0; j < NV; ++j) {
+        const int c = j * 64 + lane;
+        t[j] = ((uint32_t)(c - c_lo) < count) ? __builtin_nontemporal_load(wv + c) : fill;
+    }
+    x = 0;
+    if (sp.cut(VL)) {
+        int e;
+        if (edge_element<VL>(sp.lo, sp.hi, lane, e)) x = win[e];
+    }
+}
+template <typename InT, int NV>
+__device__ __forceinline__ void span_stage(Span sp, const u32x4 (&t)[NV], InT x, u32x4 *lds, int lane)
+{
+    constexpr int VL = 16 / (int)sizeof(InT);
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+        const int c = j * 64 + lane;
+        lds[c + c / NV] = t[j];
+    }
+    if (sp.cut(VL)) {
+        wave_lds_order();
+        int e;
+        if (edge_element<VL>(sp.lo, sp.hi, lane, e)) reinterpret_cast<InT *>(lds + (e / VL + e / VL / NV))[e % VL] = x;
+    }
     wave_lds_order();
+}
+
+// Global (striped, coalesced) -> lanes (blocked), a and b.  Elements of the window outside [lo, hi) become fa, fb.
+// `both`: both are asked for before either is waited for.
+template <typename InT, int NV>
+__device__ __forceinline__ void wave_load_spans(const InT *wa, const InT *wb, Span sp, u32x4 fa, u32x4 fb, bool both, u32x4 *lds,
+                                                int lane, u32x4 (&va)[NV], u32x4 (&vb)[NV])
+{
+    auto pick = [&](u32x4 (&v)[NV]) {
+#pragma unroll
+        for (int q = 0; q < NV; ++q) v[q] = lds[lane * (NV + 1) + q];
+        wave_lds_order();
+    };
+    if (!both) {
+        wave_stage_span<InT, NV>(wa, sp, fa, lds, lane);
+        pick(va);
+        wave_stage_span<InT, NV>(wb, sp, fb, lds, lane);
+        pick(vb);
+        return;
+    }
+    u32x4 ta[NV], tb[NV];
+    InT xa, xb;
+    span_fetch<InT, NV>(wa, sp, fa, lane, ta, xa);
+    span_fetch<InT, NV>(wb, sp, fb, lane, tb, xb);
+    if (NV == 1 && !sp.cut(16 / (int)sizeof(InT))) { // one vector per lane is where it belongs
+        va[0] = ta[0];
+        vb[0] = tb[0];
+        return;
+    }
+    span_stage<InT, NV>(sp, ta, xa, lds, lane);
+    pick(va);
+    span_stage<InT, NV>(sp, tb, xb, lds, lane);
+    pick(vb);
 }
 
 // The wave's LDS region -> global (striped, coalesced): floats [lo, hi) of the window are written.  A lane
@@ -511,7 +573,7 @@ __device__ __forceinline__ void clog_stage_span(const InT *wa, const InT *wb, Sp
     const int c_lo = (sp.lo + VL - 1) / VL;
     const int whole = sp.hi / VL - c_lo;
     const uint32_t count = whole > 0 ? (uint32_t)whole : 0u;
-    const bool cut = ((sp.lo | sp.hi) % VL) != 0; // wave-uniform
+    const bool cut = sp.cut(VL);
     const uint32_t one = sizeof(InT) == 4 ? 0x3f800000u : 0x3f803f80u;
     u32x4 ta[NV], tb[NV];
 #pragma unroll
@@ -636,7 +698,7 @@ __global__ __launch_bounds__(256, VECIO ? 4 : 1) void heinsen_scan_rows_wave(Row
     int h = 0; // elements of the window before the row
     if (VECIO) {
         h = (int)((row * p.n + p.phase) & (16 / (int)sizeof(InT) - 1));
-        sp = wave_span(h, h + p.n, 64 * ITEMS);
+        sp = Span{h, h + (int)p.n}; // the row fits the window
     }
     if constexpr (CLOG) {
         u32x4 *const region = stage[w];
@@ -678,8 +740,8 @@ __global__ __launch_bounds__(256, VECIO ? 4 : 1) void heinsen_scan_rows_wave(Row
         const uint32_t ninf = sizeof(InT) == 4 ? 0xff800000u : 0xff80ff80u;
         const uint32_t fa = LOG_IN ? 0u : one, fb = LOG_IN ? ninf : 0u;
         u32x4 va[NVI], vb[NVI];
-        wave_load_span<InT, NVI>(arow - h, sp, u32x4{fa, fa, fa, fa}, stage[w], lane, va);
-        wave_load_span<InT, NVI>(brow - h, sp, u32x4{fb, fb, fb, fb}, stage[w], lane, vb);
+        wave_load_spans<InT, NVI>(arow - h, brow - h, sp, u32x4{fa, fa, fa, fa}, u32x4{fb, fb, fb, fb},
+                                      p.both || NVI == 1, stage[w], lane, va, vb);
         unpack_inputs<InT, NVI, ITEMS>(va, Av);
         unpack_inputs<InT, NVI, ITEMS>(vb, Mv);
     } else {
@@ -917,10 +979,28 @@ __global__ __launch_bounds__(256, 4) void heinsen_scan_rows_packed(PackedParams 
             }
             wave_lds_order();
         };
-        wave_stage_span<InT, NV>(abase - h0, sp, fill, stage[w], lane);
-        pick(va);
-        wave_stage_span<InT, NV>(bbase - h0, sp, fill, stage[w], lane);
-        pick(vb);
+        // Few rows wait for one load, not two; with 16 steps per lane the launch is large, and the registers are
+        // worth more (32768 rows of 200 steps 14.7 us, with both in flight 15.9).
+        if constexpr (ITEMS > 8) {
+            wave_stage_span<InT, NV>(abase - h0, sp, fill, stage[w], lane);
+            pick(va);
+            wave_stage_span<InT, NV>(bbase - h0, sp, fill, stage[w], lane);
+            pick(vb);
+        } else {
+            u32x4 ta[NV], tb[NV];
+            InT xa, xb;
+            span_fetch<InT, NV>(abase - h0, sp, fill, lane, ta, xa);
+            span_fetch<InT, NV>(bbase - h0, sp, fill, lane, tb, xb);
+            if (NV == 1 && n == p.group * ITEMS && !sp.cut(VL)) { // one vector per lane is where it belongs
+                va[0] = ta[0];
+                vb[0] = tb[0];
+            } else {
+                span_stage<InT, NV>(sp, ta, xa, stage[w], lane);
+                pick(va);
+                span_stage<InT, NV>(sp, tb, xb, stage[w], lane);
+                pick(vb);
+            }
+        }
         unpack_inputs<InT, NV, ITEMS>(va, Av);
         unpack_inputs<InT, NV, ITEMS>(vb, Mv);
         if (((p.phase | n) & (VL - 1)) != 0) { // rows that start inside a vector
@@ -1191,8 +1271,8 @@ __device__ __forceinline__ void tiles_tile(const TileParams &p, const uint32_t t
         const uint32_t ninf = sizeof(InT) == 4 ? 0xff800000u : 0xff80ff80u;
         const uint32_t fa = LOG_IN ? 0u : one, fb = LOG_IN ? ninf : 0u;
         u32x4 va[NVI], vb[NVI];
-        wave_load_span<InT, NVI>(arow - h + wstart, sp, u32x4{fa, fa, fa, fa}, region, lane, va);
-        wave_load_span<InT, NVI>(brow - h + wstart, sp, u32x4{fb, fb, fb, fb}, region, lane, vb);
+        wave_load_spans<InT, NVI>(arow - h + wstart, brow - h + wstart, sp, u32x4{fa, fa, fa, fa}, u32x4{fb, fb, fb, fb}, !MULTI,
+                                  region, lane, va, vb);
         unpack_inputs<InT, NVI, ITEMS>(va, Av);
         unpack_inputs<InT, NVI, ITEMS>(vb, Mv);
     } else {
@@ -1214,9 +1294,7 @@ __device__ __forceinline__ void tiles_tile(const TileParams &p, const uint32_t t
     // summary of the waves before this one, and (wave 0) of the whole tile, in wave order
     Seg wave_excl = seg_identity<DOM>();
     Seg total = seg_identity<DOM>();
-#pragma unroll
-    for (int j = 0; j < NW; ++j) {
-        if (!MULTI && j + 1 >= nw) break; // rows of one tile: nobody needs the last wave's
+    auto fold = [&](int j) {
         Seg g2;
         g2.A = lds_A[j];
         g2.M = lds_M[j];
@@ -1224,6 +1302,12 @@ __device__ __forceinline__ void tiles_tile(const TileParams &p, const uint32_t t
         g2.sM = SIGNED ? (lds_S[j] << 30) : 0u;
         total = (j == 0) ? g2 : seg_combine<DOM>(total, g2);
         if (j + 1 == w) wave_excl = total;
+    };
+    if (MULTI || nw == NW) { // all asked for at once
+#pragma unroll
+        for (int j = 0; j < NW; ++j) fold(j);
+    } else { // rows of one tile: nobody needs the last wave's
+        for (int j = 0; j + 1 < nw; ++j) fold(j);
     }
 
     if (w == 0) {
@@ -1363,9 +1447,34 @@ struct BdnPlan {
 
 // Rows of one tile: with at least this many rows the chip is full whatever a row's workgroup looks like, and
 // the fewest, fullest waves win (a lane's serial steps cost far less than its share of the scans across
-// lanes and waves): 8192 rows of 3001 steps, complex output, took 147 us on eight waves of eight steps.  With
-// fewer rows a call is bound by the latency of one row, which all eight waves share.
+// lanes and waves): 8192 rows of 3001 steps, complex output, took 147 us on eight waves of eight steps; 700 rows of 2500
+// float32 steps 7.8 us on eight, 6.9 on three of 16.  With fewer rows a call is bound by the latency of one row, which
+// all eight waves share (256 rows 5.5 us on eight waves, 5.6 and 6.2 on fewer).
 constexpr int64_t kManyRows = 512;
+
+// Rows of up to 512 steps: do several share a wave, on how many lanes each and of how many steps?
+//   Steps per lane: eight as long as the launch does not fill the chip twice over anyhow (about 3 * 2^20 elements),
+// since a lane's steps are one after the other (100 steps: 16384 rows 5.9 us with eight, 6.3 with 16; 32768 8.5 and
+// 8.3; 131072 30.4 and 29.4), and beyond that where they fill the lanes better by more than a quarter.
+//   Rows of more than 256 steps have a wave of eight steps per lane to themselves unless three fit one of 16 (300 steps,
+// 4096 rows: 5.2 us alone, 6.3 shared; 32768: 25 and 22), or two and the launch is large (400 steps, 16384 rows: 16.1 and
+// 14.7; from about 450 steps on nothing is gained).  bf16, whose loads are half as many, shares later.
+//   Up to 1024 rows, one wave per SIMD, every row has its own: fewer steps of the scan across lanes do not make up
+// for the rearrangement (200 steps, 512 rows: 3.0 us alone, 3.3 shared, 3.9 with 16 steps).
+bool shares_waves(const ScanCall &c, int64_t lead, bool clog, bool vecio, int &items, int &group)
+{
+    const int64_t rows = c.B * c.D, elements = rows * c.n, before = clog && !vecio ? 3 : lead; // a complex output works on quads in any case
+    const int g16 = (int)ceil_div(c.n + before, 16), g8 = (int)ceil_div(c.n + before, 8);
+    if (rows <= 1024 && (c.n >= 64 || rows == 1)) return false;
+    if (c.n <= 256) {
+        items = elements <= (3ll << 20) || 8 * (64 / g8) > 5 * (64 / g16) ? 8 : 16;
+    } else {
+        items = 16;
+        if (!(64 / g16 >= 3 && elements > (2ll << 20)) && !(c.n <= 448 && elements > (3ll << 20)) && !(c.bf16 && elements > (9ll << 19))) return false;
+    }
+    group = items == 16 ? g16 : g8;
+    return true;
+}
 
 BdnPlan make_plan(const ScanCall &c)
 {
@@ -1385,20 +1494,18 @@ BdnPlan make_plan(const ScanCall &c)
         lead = 0;
     };
     if (!pl.vecio) element_wise();
-    // a complex output keeps at most 16 steps per lane (see inputs_in_lds)
+    // A float32 row that its lead would push to twice the steps per lane: element by element it is the faster one (1022
+    // steps, 600 rows 4.9 and 5.3 us, 4096 rows 9.2 and 10.7; bf16, two bytes per load: 9.0 and 4.9).  A few complex
+    // rows, whose moves are a small part of them, keep the vectors.
     const bool clog = c.is_signed && c.log_out;
+    if (!c.bf16 && ((c.n <= 512 && c.n + lead > 512) || (c.n <= 1024 && c.n + lead > 1024)) && pl.rows >= (clog ? kManyRows : c.n > 512 ? 64 : 1))
+        element_wise();
+    // a complex output keeps at most 16 steps per lane (see inputs_in_lds)
     pl.wave_kernel = c.n + lead <= (clog ? kRowsWaveMax / 2 : kRowsWaveMax) && !(pl.rows < 64 && c.n > 512);
     if (pl.wave_kernel) {
         pl.phase = pl.vecio ? (int)at_a : 0;
+        if (c.n + std::max<int64_t>(lead, clog ? 3 : 0) <= 512 && shares_waves(c, lead, clog, pl.vecio, pl.items, pl.group)) return pl;
         pl.items = c.n + lead > 1024 ? 32 : (c.n + lead > 512 ? 16 : 8);
-        // Rows that leave room for another in a wave share it: 16 steps per lane, or 8 where that fills the
-        // lanes better by more than a quarter (shorter rows).  A few longer rows keep a wave each.
-        if (c.n + std::max<int64_t>(lead, clog ? 3 : 0) <= 512 && pl.rows > (c.n <= 256 ? 1 : kManyRows)) {
-            const int64_t before = clog && !pl.vecio ? 3 : lead; // a complex output works on quads in any case
-            const int g16 = (int)ceil_div(c.n + before, 16), g8 = (int)ceil_div(c.n + before, 8);
-            pl.items = 8 * (64 / g8) > 5 * (64 / g16) ? 8 : 16;
-            pl.group = pl.items == 16 ? g16 : g8;
-        }
         return pl;
     }
     // a row of one tile is bound by latency: spread it over all waves of the workgroup
@@ -1409,9 +1516,14 @@ BdnPlan make_plan(const ScanCall &c)
     if (c.n <= kTile) {
         if (pl.rows >= kManyRows) {
             const int64_t w32 = ceil_div(c.n + lead, 64 * 32), w16 = ceil_div(c.n + lead, 64 * 16);
-            const bool finer = clog ? w16 <= kLdsTileWaves : (w16 <= kTileWaves && 8 * w16 < 7 * 2 * w32); // fills its lanes better by an eighth
-            pl.tile_items = finer ? 16 : 32;
-            pl.waves = (int)(finer ? w16 : w32);
+            // 16 steps where they fill their lanes better by an eighth, and while there are not two or three waves
+            // per SIMD even so (4096 steps, logarithms, 512 rows: 8.3 -> 7.0 us)
+            const bool finer = clog ? w16 <= kLdsTileWaves : (w16 <= kTileWaves && (8 * w16 < 7 * 2 * w32 || pl.rows * w32 <= 2400));
+            // five waves and more share a CU no better than all eight (12000 steps, 2048 rows: 55 us, eight waves 53)
+            if (finer || w32 <= 4 || pl.rows * w32 <= 4096) {
+                pl.tile_items = finer ? 16 : 32;
+                pl.waves = (int)(finer ? w16 : w32);
+            }
         }
     } else {
         if (pl.rows * ceil_div(c.n, kTile / 2) <= kHalfTilesUpTo) pl.tile_items = kTileItems / 2;
@@ -1472,6 +1584,9 @@ hipError_t launch_mode(const ScanCall &c, const BdnPlan &pl, const LaunchCtx &ct
         p.n = c.n;
         p.x0_stride = c.x0_scalar ? 0 : 1;
         p.phase = pl.phase;
+        // A launch of few waves waits for its loads once instead of twice (600 rows of 1021 steps 4.8 -> 4.5 us); one
+        // that fills the chip does better with one array of a row after the other (4096 rows 8.8, together 9.3).
+        p.both = pl.rows * c.n <= (3ll << 20);
         dim3 grid((unsigned)ceil_div(pl.rows, 4)), block(256);
 #define HS_ROWS(ITEMS_, VEC_)                                                                            \
     hipLaunchKernelGGL((heinsen_scan_rows_wave<DOM, LOG_IN, LOG_OUT, InT, ITEMS_, VEC_>), grid, block, 0, \

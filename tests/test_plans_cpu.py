@@ -1,0 +1,29 @@
+"""Which kernel and tile a call takes, on the side of each rule where a slower one was taken before.  No GPU: the
+plan is asked for through heinsen_kernel_name and heinsen_tile_shape."""
+import pytest
+
+from paper_2311_06281_amd import binding as hb
+
+BDN, BND = hb.HEINSEN_LAYOUT_BDN, hb.HEINSEN_LAYOUT_BND
+LOGS = hb.HEINSEN_LOG_INPUTS | hb.HEINSEN_LOG_OUTPUT
+CLOG = hb.HEINSEN_LOG_OUTPUT | hb.HEINSEN_OUT_COMPLEX
+
+
+# rows, n, flags -> kernel, rows per workgroup, steps (four waves per workgroup)
+@pytest.mark.parametrize("rows,n,flags,kernel,tile", [
+    (512, 200, 0, "rows_wave", (4, 200)),              # one wave per SIMD: a row each
+    (4096, 100, 0, "rows_packed", (4 * 4, 100)),       # eight steps per lane: 13 lanes per row
+    (131072, 100, 0, "rows_packed", (4 * 9, 100)),     # the chip is full: 16 steps, 7 lanes
+    (4096, 300, 0, "rows_wave", (4, 300)),
+    (32768, 300, 0, "rows_packed", (4 * 3, 300)),
+    (16384, 508, 0, "rows_wave", (4, 508)),
+    (63, 16, CLOG, "rows_packed", (4 * 32, 16)),       # two lanes of eight steps
+    (512, 4096, LOGS, "tiles", (1, 4 * 64 * 16)),
+    (2048, 4096, 0, "tiles", (1, 2 * 64 * 32)),
+    (2048, 12000, 0, "tiles", (1, 8 * 64 * 32)),
+    (600, 12000, 0, "tiles", (1, 6 * 64 * 32)),
+    (600, 1022, 0, "rows_wave", (4, 1022)),
+])
+def test_plans_of_rows(rows, n, flags, kernel, tile):
+    assert hb.heinsen_kernel_name(1, rows, n, BDN, flags) == "heinsen_scan_" + kernel
+    assert hb.heinsen_tile_shape(1, rows, n, BDN, flags) == tile
