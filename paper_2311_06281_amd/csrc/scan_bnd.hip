@@ -521,6 +521,10 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
             if (SB) __builtin_amdgcn_sched_barrier(0);
         }
     } else {
+        // Every store below is a block of its own, and the compiler, which cannot tell there whether a record it did not
+        // need is still on its way, would wait in each for all that is, the store before it included (1 x 3000 x
+        // 512: 15.3 us, 13.7 with one wait here).
+        __builtin_amdgcn_s_waitcnt(0x0f70); // vmcnt(0)
 #pragma unroll
         for (int k = 0; k < T; ++k) {
             emit_store(k, chan_ok && t0 + k < p.n);
