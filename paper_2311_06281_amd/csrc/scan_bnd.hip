@@ -671,6 +671,30 @@ struct BndPlan {
 // record loads: 106 us for the 3 columns.
 constexpr int kTreeGroup = 8;
 constexpr int kTreeBelow = 16;
+// From nine columns on a sequence of two groups of eight has one link and no use for a second level (12 columns of 4096
+// steps: 15.5 us with it, 14.7 with groups of eight alone, 15.8 with groups of four; bf16, three groups: 21.7 and 19.3).
+constexpr int kTreeAlways = 9;
+
+// Workgroups of eight waves that the chip holds at a time.
+constexpr int kPlaces = 512;
+
+// Channels that do not fill 64 lanes per batch item (D > 32): columns of 64 channels of whatever items?  Where
+// that saves a sixteenth of the columns, and
+//   - D is a multiple of 16: pieces of rows begin on 64 bytes (2 x 131072 x 96: three columns instead of four); or
+//   - the sequence is one tile, with logarithms, or with an eighth of the columns saved (3226 x 20 x 65: 13.7 us,
+//     with columns of their own 18.1; 139 x 100 x 301, a twentieth saved: 14.5 and 13.8); or
+//   - the tiles take fewer rounds of the chip, with logarithms (215 x 300 x 65 complex: 25 and 41), or, where memory is
+//     what bounds them, from three rounds on and with a fifth of the columns saved (860 x 300 x 65: 50 and 68 us).
+// Otherwise fewer tiles only mean fewer loads in flight (63 x 2000 x 33: 24.9 us, 18.9 with columns of their own).
+bool columns_across_items(const ScanCall &c, int64_t own, int64_t shared, int64_t steps, int waves)
+{
+    if (shared + shared / 16 >= own) return false;
+    if (c.D % 16 == 0) return true;
+    const bool logs = c.log_in || c.log_out;
+    if (c.n <= 128) return logs || 8 * shared <= 7 * own;
+    const int64_t chunks = ceil_div(c.n, steps), places = waves > 8 ? kPlaces / 2 : kPlaces;
+    return ceil_div(shared * chunks, places) < ceil_div(own * chunks, places) && (logs || (own * chunks > 2 * places && 5 * shared <= 4 * own));
+}
 
 BndPlan make_plan(const ScanCall &c, bool allow_wide = true, bool want_tree = false)
 {
@@ -703,24 +727,27 @@ BndPlan make_plan(const ScanCall &c, bool allow_wide = true, bool want_tree = fa
     // Channels that do not fill their columns.  Up to 32 per batch item: a column takes whole items, 64 over the
     // power of two at or above D of them.  (Items cut by the ends of columns read the lines at the cut
     // twice: 256 x 4096 x 19 85 us, whole items 76; more and narrower pieces per access cost more than they fill:
-    // 999 x 4096 x 5 157 us with twelve items, 146 with eight.)  More channels: columns of 64 regardless of items
-    // where that saves a sixteenth of them (2 x 131072 x 96: three columns instead of four).  A lane's offset
-    // from its column's base -- it may lie some items further on -- has to fit 31 bits.
+    // 999 x 4096 x 5 157 us with twelve items, 146 with eight.)  More channels: see columns_across_items.  A lane's
+    // offset from its column's base -- it may lie some items further on -- has to fit 31 bits.
     pl.lanes = 64;
     if (pl.cg == 1) {
         int64_t items = 1;
         while (2 * items * c.D <= 64 && (items < 2 || 64 / (2 * items) >= c.D)) items *= 2;
         const int64_t lanes = c.D <= 32 ? items * c.D : 64;
         const int64_t cols = ceil_div(c.B * c.D, lanes), further = c.D <= 32 ? items - 1 : (c.D + 62) / c.D;
-        pl.dense = (c.D <= 32 ? cols : cols + cols / 16) < pl.ncols && c.B * c.D < ((int64_t)1 << 31) &&
+        pl.dense = (c.D <= 32 ? cols < pl.ncols : columns_across_items(c, pl.ncols, cols, (int64_t)pl.NW * pl.T, pl.NW)) && c.B * c.D < ((int64_t)1 << 31) &&
                    further * c.n * c.D + c.D < ((int64_t)1 << 31);
         if (pl.dense) {
             pl.lanes = (int)lanes;
             pl.ncols = (int)cols;
         }
     }
-    pl.tree = pl.cg == 1 && pl.NW == 8 && pl.T == 32 && (pl.ncols < kTreeBelow || want_tree) && c.n > 4 * pl.NW * pl.T;
+    const bool tiles8 = pl.cg == 1 && pl.NW == 8 && pl.T == 32 && c.n > 4 * pl.NW * pl.T;
+    pl.tree = tiles8 && (pl.ncols < kTreeBelow || want_tree);
     if (pl.tree) pl.G = kTreeGroup;
+    if (pl.tree && pl.ncols >= kTreeAlways && pl.ncols < kTreeBelow && c.n > kTreeGroup * pl.NW * pl.T &&
+        c.n <= (c.bf16 ? 3 : 2) * kTreeGroup * pl.NW * pl.T)
+        pl.tree = false; // (its groups stay)
     pl.nchunks = (int)ceil_div(c.n, (int64_t)(pl.NW / pl.cg) * pl.T);
     pl.ngroups = (int)ceil_div(pl.nchunks, pl.G);
     pl.ntiles = (uint32_t)pl.ncols * (uint32_t)pl.nchunks;
@@ -731,6 +758,13 @@ BndPlan make_plan(const ScanCall &c, bool allow_wide = true, bool want_tree = fa
     // A queue's workgroups that find no tile behind their ticket (uneven deal) end at once.
     pl.nq = kQueues;
     while (pl.nq > 1 && pl.ncols < pl.nq * (pl.cg > 1 ? kMinColsPerQueueWide : kMinColsPerQueue)) pl.nq /= 2;
+    // Eight queues of fewer than 16 columns are for lines that columns share and for short sequences.  Long ones
+    // wait for their predecessors less in four (80 columns of 16384 steps: 169 and 174 us), and an uneven deal may be
+    // what makes a launch that fits the chip take a second round on one die (100 columns of 1100 steps, bf16: 18.3 and
+    // 21.9 us).
+    if (pl.cg == 1 && pl.nq == kQueues && pl.ncols < 2 * kMinColsPerQueue * kQueues && c.D * (c.bf16 ? 2 : 4) % 128 == 0 &&
+        (c.n >= 4096 || (pl.ntiles <= (uint32_t)kPlaces && ceil_div(pl.ncols, kQueues) * pl.nchunks > kPlaces / kQueues)))
+        pl.nq /= 2;
     pl.cols_per_q = (int)ceil_div(pl.ncols, pl.nq);
     pl.grid = pl.ntiles;
     if (pl.ticketless) {
@@ -816,6 +850,9 @@ hipError_t launch_mode(const ScanCall &c, const BndPlan &pl, const LaunchCtx &ct
         else HS_BND(32, 8, 4, false, false, 2, kKeepOut);
     } else if (pl.tree) {
         HS_BND_ANY(32, 8, kTreeGroup, true);
+    } else if (pl.G == kTreeGroup) { // few short columns: nothing that would not stay in the caches
+        if (pl.dense) HS_BND(32, 8, kTreeGroup, true, false, 1, kKeepOut);
+        else HS_BND(32, 8, kTreeGroup, false, false, 1, kKeepOut);
     } else if (pl.NW == 8) {
         HS_BND_ANY(32, 8, 4, false);
     } else if (pl.dense) { // short sequences

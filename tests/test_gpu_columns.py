@@ -15,10 +15,12 @@ pytestmark = pytest.mark.gpu
 # (B, n, D)
 SHAPES = [
     (2, 300, 96), (3, 700, 65), (5, 65, 33), (4, 129, 100), (2, 33, 48), (7, 1100, 40), (3, 257, 1000 - 25),  # dense columns
+    (130, 2100, 33), (8, 1100, 96),                                                                            # the same, several tiles
     (9, 513, 19), (13, 70, 5), (3, 300, 31), (6, 2000, 21),                                                    # whole items
     (4, 16001, 70), (2, 100003, 20), (70, 3000, 13), (40, 2900, 37),                                           # shared lines
     # few columns: one tile more than a group (8 tiles of 256 steps), than a super-group (64), than several
     (1, 1025, 64), (1, 2049, 66), (2, 256 * 9 + 3, 96), (1, 256 * 64 + 1, 128), (1, 256 * 65, 2), (3, 256 * 72 + 5, 65),
+    (9, 256 * 8 + 1, 64), (12, 256 * 16, 64), (15, 256 * 24, 64), (100, 256 * 4 + 9, 64),  # groups of eight, uneven queues
     (2, 256 * 200 + 77, 48), (1, 256 * 512, 5), (15, 256 * 17, 64), (14, 256 * 16 + 255, 64),
 ]
 
