@@ -37,8 +37,9 @@ struct BndParams {
     int64_t D, n;
     int x0_stride;    // 0: one x0 for all, 1: x0[b*D + d]
     int cols_per_b;   // ceil(D / CH)
-    int ncols;        // B * cols_per_b; DENSE: ceil(B * D / lanes)
-    int64_t nchan;    // DENSE: B * D,
+    int ncols;        // B * cols_per_b; DENSE: ceil(B / items per column), D > 32: ceil(B * D / 64)
+    int64_t places;   // DENSE: B * pad (TREE: B * D),
+    uint32_t pad;     //   lanes an item takes,
     int lanes;        //   channels per column
     int nchunks;      // ceil(n / (NW*T))
     uint32_t ntiles;  // ncols * nchunks; tile id = chunk * ncols + col
@@ -177,12 +178,15 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     int64_t ubase;   // wave-uniform part of the addresses
     int64_t x0_at;   // the channel's place in x0
     if constexpr (DENSE) {
-        const uint32_t D = (uint32_t)p.D, first_chan = (uint32_t)col * (uint32_t)p.lanes, chan = first_chan + (uint32_t)lane;
-        const uint32_t b0 = first_chan / D, bb = chan / D;   // batch items of the column's first lane and of this one
-        chan_ok = lane < p.lanes && chan < p.nchan;
-        moff = (bb - b0) * (uint32_t)(p.n * p.D) + (chan - bb * D); // the host checks that this fits 31 bits
+        // An item takes `pad` of the column's lanes (see make_plan).
+        const uint32_t pad = TREE ? (uint32_t)p.D : p.pad;
+        const uint32_t first = (uint32_t)col * (TREE ? (uint32_t)p.lanes : 64u), place = first + (uint32_t)lane;
+        const uint32_t b0 = first / pad, bb = place / pad;   // batch items of the column's first lane and of this one
+        const uint32_t at = place - bb * pad;                // the lane's channel in its item
+        chan_ok = (TREE ? lane < p.lanes : at < (uint32_t)p.D) && place < p.places;
+        moff = (bb - b0) * (uint32_t)(p.n * p.D) + at; // the host checks that this fits 31 bits
         ubase = ((int64_t)b0 * p.n + t0) * p.D;
-        x0_at = chan;
+        x0_at = TREE ? place : bb * (uint32_t)p.D + at;
     } else {
         const int64_t d0 = (int64_t)cg * CH + c;
         chan_ok = d0 < p.D;
@@ -655,6 +659,7 @@ struct BndPlan {
     bool ticketless;
     bool dense;          // columns of adjacent channels of all B * D (see bnd_tile),
     int lanes;           // this many
+    int pad;             // lanes an item takes: D, or the power of two at or above it
     int cols_per_b, ncols, nchunks, ngroups;
     uint32_t ntiles;
     int nq, cols_per_q;
@@ -724,21 +729,23 @@ BndPlan make_plan(const ScanCall &c, bool allow_wide = true, bool want_tree = fa
     pl.cols_per_b = (int)ceil_div(c.D, pl.CH);
     pl.ncols = (int)(c.B * pl.cols_per_b);
 
-    // Channels that do not fill their columns.  Up to 32 per batch item: a column takes whole items, 64 over the
-    // power of two at or above D of them.  (Items cut by the ends of columns read the lines at the cut
-    // twice: 256 x 4096 x 19 85 us, whole items 76; more and narrower pieces per access cost more than they fill:
-    // 999 x 4096 x 5 157 us with twelve items, 146 with eight.)  More channels: see columns_across_items.  A lane's
-    // offset from its column's base -- it may lie some items further on -- has to fit 31 bits.
+    // Channels that do not fill their columns.  Up to 32 per batch item: a column takes as many whole items as lanes
+    // of the next power of two fit.  (Items cut by the ends of columns read the lines at the cut twice: 256 x 4096 x 19
+    // 85 us, whole items 76.)  Each begins on such a lane: without lanes between them 419 x 2000 x 5 takes 41 us
+    // instead of 36.  Two carry levels, where few tiles are waited for rather than memory, go without them.  More
+    // channels: see columns_across_items.  A lane's offset from its column's base -- it may lie some items further on
+    // -- has to fit 31 bits.
     pl.lanes = 64;
+    pl.pad = 64;
+    int64_t pad = c.D;
     if (pl.cg == 1) {
-        int64_t items = 1;
-        while (2 * items * c.D <= 64 && (items < 2 || 64 / (2 * items) >= c.D)) items *= 2;
-        const int64_t lanes = c.D <= 32 ? items * c.D : 64;
-        const int64_t cols = ceil_div(c.B * c.D, lanes), further = c.D <= 32 ? items - 1 : (c.D + 62) / c.D;
-        pl.dense = (c.D <= 32 ? cols < pl.ncols : columns_across_items(c, pl.ncols, cols, (int64_t)pl.NW * pl.T, pl.NW)) && c.B * c.D < ((int64_t)1 << 31) &&
+        if (c.D <= 32)
+            for (pad = 2; pad < c.D;) pad *= 2;
+        const int64_t items = c.D <= 32 ? 64 / pad : 1, cols = ceil_div(c.B * pad, 64), further = c.D <= 32 ? items - 1 : (c.D + 62) / c.D;
+        pl.dense = (c.D <= 32 ? cols < pl.ncols : columns_across_items(c, pl.ncols, cols, (int64_t)pl.NW * pl.T, pl.NW)) && c.B * pad < ((int64_t)1 << 31) &&
                    further * c.n * c.D + c.D < ((int64_t)1 << 31);
         if (pl.dense) {
-            pl.lanes = (int)lanes;
+            if (c.D <= 32) pl.lanes = (int)(items * c.D);
             pl.ncols = (int)cols;
         }
     }
@@ -748,6 +755,7 @@ BndPlan make_plan(const ScanCall &c, bool allow_wide = true, bool want_tree = fa
     if (pl.tree && pl.ncols >= kTreeAlways && pl.ncols < kTreeBelow && c.n > kTreeGroup * pl.NW * pl.T &&
         c.n <= (c.bf16 ? 3 : 2) * kTreeGroup * pl.NW * pl.T)
         pl.tree = false; // (its groups stay)
+    if (pl.dense) pl.pad = (int)(pl.tree ? c.D : pad);
     pl.nchunks = (int)ceil_div(c.n, (int64_t)(pl.NW / pl.cg) * pl.T);
     pl.ngroups = (int)ceil_div(pl.nchunks, pl.G);
     pl.ntiles = (uint32_t)pl.ncols * (uint32_t)pl.nchunks;
@@ -808,7 +816,8 @@ hipError_t launch_mode(const ScanCall &c, const BndPlan &pl, const LaunchCtx &ct
     const bool shares_lines = c.D * (int64_t)sizeof(InT) % 128 != 0 && out_bytes + 2 * elements * (int64_t)sizeof(InT) > (c.D <= 32 ? kLastLevelCacheBytes : kLastLevelCacheBytes * 3 / 2);
     const int mem = shares_lines ? kShared : (large_out ? kStream : kKeepOut);
     p.cols_per_b = pl.cols_per_b;
-    p.nchan = c.B * c.D;
+    p.pad = (uint32_t)pl.pad;
+    p.places = c.B * pl.pad;
     p.lanes = pl.lanes;
     p.ncols = pl.ncols;
     p.nchunks = pl.nchunks;
