@@ -90,6 +90,8 @@ def _addr(x) -> int:
     """Device address of a tensor-like object (anything with data_ptr()) or a plain integer."""
     if x is None:
         return 0
+    if x.__class__ is int:
+        return x
     if hasattr(x, "data_ptr"):
         return int(x.data_ptr())
     return int(x)
@@ -98,6 +100,8 @@ def _addr(x) -> int:
 def _stream_handle(stream) -> int:
     if stream is None:
         return 0
+    if stream.__class__ is int:
+        return stream
     if hasattr(stream, "cuda_stream"):  # torch.cuda.Stream
         return int(stream.cuda_stream)
     return int(stream)
@@ -145,13 +149,16 @@ def heinsen_tile_shape(B: int, D: int, n: int, layout: int, flags: int):
 
 def _scan_call(fn, a, b, x0, out, B, D, n, layout, flags, stream) -> int:
     """Calls a scan entry point.  The smallest calls are bound by the host (4.4 us in the launch, 1.1 in ctypes), so
-    tensors, plain integers and a torch stream go straight through, 1.6 us where converting every argument took 2.6.
-    Whatever is not of these types fails before the library is entered and is converted then."""
-    try:
-        return fn(a.data_ptr(), b.data_ptr(), x0.data_ptr(), out.data_ptr(), B, D, n, layout, flags, stream.cuda_stream)
-    except (AttributeError, TypeError, ctypes.ArgumentError):
-        return int(fn(_addr(a), _addr(b), _addr(x0), _addr(out), int(B), int(D), int(n), int(layout), int(flags),
-                      _stream_handle(stream)))
+    tensors, plain integers and a torch stream go straight through, 1.6 us where converting every argument takes 2.1.
+    Addresses and streams that are integers, or no stream, are known as such at once; whatever else is not of these
+    types fails before the library is entered and is converted then."""
+    if stream is not None and stream.__class__ is not int and a.__class__ is not int:
+        try:
+            return fn(a.data_ptr(), b.data_ptr(), x0.data_ptr(), out.data_ptr(), B, D, n, layout, flags, stream.cuda_stream)
+        except (AttributeError, TypeError, ctypes.ArgumentError):
+            pass
+    return int(fn(_addr(a), _addr(b), _addr(x0), _addr(out), int(B), int(D), int(n), int(layout), int(flags),
+                  _stream_handle(stream)))
 
 
 def heinsen_scan_status(a, b, x0, out, B: int, D: int, n: int, layout: int, flags: int, stream=None) -> int:

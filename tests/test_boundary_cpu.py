@@ -100,3 +100,29 @@ def test_bench_refuses_more_than_one_gpu():
     r = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"], capture_output=True, text=True, timeout=120)
     assert r.returncode != 0
     assert "ONE GPU" in r.stderr and r.stdout.strip() == ""
+
+
+class _Tensor:
+    def __init__(self, at):
+        self.at, self.asked = at, 0
+
+    def data_ptr(self):
+        self.asked += 1
+        return self.at
+
+
+class _Stream:
+    cuda_stream = 0
+
+
+@pytest.mark.parametrize("a", [_Tensor(P), P])
+@pytest.mark.parametrize("stream", [_Stream(), None, 0])
+@pytest.mark.parametrize("number", [int, float])
+def test_every_form_of_the_arguments_arrives(a, stream, number):
+    """Tensors or addresses, a stream object, its handle or none, integers or what converts to them.  No form is tried
+    in vain first: each tensor is asked for its address once (twice where a number had to be converted)."""
+    rest = [_Tensor(P) for _ in range(3)]
+    assert hb.heinsen_scan_status(a, *rest, number(1), 1, 0, 0, 0, stream) == hb.HEINSEN_ERR_INVALID_ARG  # n = 0
+    assert hb.heinsen_scan_status(a, rest[0], None, rest[2], 1, 1, 8, 0, 0, stream) == hb.HEINSEN_ERR_INVALID_ARG  # null x0
+    fast = isinstance(a, _Tensor) and stream is not None and stream != 0
+    assert rest[1].asked == (2 if fast and number is float else 1)
