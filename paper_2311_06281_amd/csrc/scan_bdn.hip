@@ -1214,12 +1214,15 @@ __device__ __forceinline__ void tiles_tile(const TileParams &p, const uint32_t t
         const bool in_range = wave_all(lin_summary<ITEMS>(own, g, up));
         up = in_range ? wave_sum(up) : kLinUp + 1;
         g = lin_wave_inclusive_scan(g);
+        p.tl.mark(tile, 2);
         if (lane == 63) {
             lds_P[w] = g.P;
             lds_Z[w] = g.Z;
             lds_up[w] = up;
         }
         __syncthreads();
+        p.tl.mark(tile, 3);
+        p.tl.mark(tile, 4); // no records
         // the row's states at the waves up to this one and at its lanes
         double x = lin_x0(x0);
         bool ok = up <= kLinUp;
@@ -1234,6 +1237,7 @@ __device__ __forceinline__ void tiles_tile(const TileParams &p, const uint32_t t
         __syncthreads();
         int bad = 0;
         for (int j = 0; j < nw; ++j) bad |= lds_bad[j];
+        p.tl.mark(tile, 5);
         if (bad == 0) {
             lin_emit<ITEMS>(x, own, own);
         } else {
@@ -1260,6 +1264,7 @@ __device__ __forceinline__ void tiles_tile(const TileParams &p, const uint32_t t
         wave_lds_order();
         if (VECIO) wave_unstage_span<ITEMS / 2, 1>(orow + OW * (wstart - h), OW * sp.lo, OW * sp.hi, region, lane, 0);
         else clog_unstage_elems<ITEMS>(orow + OW * wstart, p.n - wstart, region, lane);
+        p.tl.mark(tile, 6);
         return;
     }
     float Av[ITEMS], Mv[ITEMS];

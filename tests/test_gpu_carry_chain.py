@@ -118,6 +118,24 @@ def test_per_tile_time_stamps(gpu):
     assert int(stamps.abs().sum().item()) == 0  # switched off again
 
 
+def test_time_stamps_of_rows_whose_inputs_stay_in_lds(gpu):
+    """Complex rows of one tile take every stamp too."""
+    torch, hb = gpu
+    rows, n = 600, 3001
+    a, b = torch.full((rows, n), 0.5, device="cuda:0"), torch.ones((rows, n), device="cuda:0")
+    x0, out = torch.ones(rows, device="cuda:0"), torch.empty((rows, n, 2), device="cuda:0")
+    stamps = torch.zeros(rows * 8, dtype=torch.int64, device="cuda:0")
+    hb.heinsen_set_timeline(stamps, rows)
+    try:
+        hb.heinsen_scan(a, b, x0, out, 1, rows, n, hb.HEINSEN_LAYOUT_BDN, hb.HEINSEN_LOG_OUTPUT | hb.HEINSEN_OUT_COMPLEX,
+                        torch.cuda.current_stream())
+        torch.cuda.synchronize()
+    finally:
+        hb.heinsen_set_timeline(None, 0)
+    t = stamps.cpu().numpy().reshape(rows, 8)
+    assert (t[:, 0] > 0).all() and (np.diff(t, axis=1) >= 0).all()
+
+
 def test_stream_probe_adds(gpu):
     """The yardstick kernels compute out = a + b for every pattern that applies to the shape."""
     torch, hb = gpu
