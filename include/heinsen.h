@@ -173,10 +173,13 @@ int heinsen_release_scratch(void);
 
 /* Name of the kernel heinsen_scan would launch for these arguments (for profilers), written as a
  * NUL-terminated string into buf (at most buflen bytes).  Launches nothing.  Returns a
- * heinsen_status_t from the same validation heinsen_scan performs (pointers are not checked). */
-/* The piece of the problem one workgroup of that kernel takes ("tile"): `sequences` adjacent sequences
- * (channels of [B, n, D], rows of [B, D, n]) for `steps` consecutive steps (the last tile of a sequence may
- * be shorter).  For profilers and for reading the tile ids of heinsen_set_timeline.  Launches nothing.
+ * heinsen_status_t from the same validation heinsen_scan performs (pointers are not checked).  This and the
+ * next function assume that a, b and out start on 16-byte boundaries; a call whose pointers do not may take
+ * another kernel for rows of [B, D, n], and fewer channels per workgroup for up to 8 steps of [B, n, D]. */
+/* The piece of the problem one workgroup of that kernel takes ("tile"): up to `sequences` adjacent sequences
+ * (channels of [B, n, D] -- of one batch item, or of several where an item's do not fill a tile -- rows of
+ * [B, D, n]) for `steps` consecutive steps (the last tile of a sequence may be shorter).  For profilers and
+ * for reading the tile ids of heinsen_set_timeline.  Launches nothing.
  * Returns a heinsen_status_t from the same validation heinsen_scan performs (pointers are not checked). */
 int heinsen_tile_shape(int64_t B, int64_t D, int64_t n, int layout, uint32_t flags, int *sequences,
                        int64_t *steps);

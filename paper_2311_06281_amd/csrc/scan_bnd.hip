@@ -805,15 +805,19 @@ hipError_t launch_mode(const ScanCall &c, const BndPlan &pl, const LaunchCtx &ct
     p.D = c.D;
     p.n = c.n;
     p.x0_stride = c.x0_scalar ? 0 : 1;
-    // see Mem.  kShared from the size on at which it wins however the caller goes through its buffers: while
-    // the outputs of the last few calls fit the memory-side cache, kKeepOut finds some of their lines there (6 x 3001 x
-    // 1111 float32, 240 MB: kKeepOut 59 us over three sets of buffers and 72 over six, kShared 64; 16 x 4096 x 301
-    // bf16, 316 MB: 108 and 82; 8 x 8000 x 1501, 2.3 GB: 658 and 490).  With items narrower than half a column the
-    // lines are shared by successive steps of one lane's wave as well (256 x 4096 x 19, 239 MB: 76 and 68).
+    // see Mem.  kShared where it wins however the caller goes through its buffers.  float32, more than 32 channels: in
+    // place of kStream only, since kKeepOut finds lines of the last calls' outputs in the memory-side cache as long as
+    // few sets of buffers take turns (8 x 3001 x 1111, 320 MB a call: kKeepOut 70 us over two sets, 76 over three, 78
+    // over five, kShared 78, 79, 78; 8 x 8000 x 1501, 1.2 GB: kStream 658, kShared 490).  bf16, whose pieces of 64 channels
+    // are one line long and touch two: from the size of that cache on (16 x 8192 x 301, 316 MB: kKeepOut 84 us over one
+    // set, 97 over two, 109 over five, kShared 77, 83, 84).  Items narrower than half a column, whose lines successive
+    // steps of one wave share as well: likewise (256 x 4096 x 19, 239 MB: 75 over one set and over five, kShared 53 and 69).
     const int64_t elements = c.B * c.D * c.n;
     const int64_t out_bytes = elements * ((SIGNED && LOG_OUT) ? 8 : 4);
     const bool large_out = out_bytes > kLastLevelCacheBytes;
-    const bool shares_lines = c.D * (int64_t)sizeof(InT) % 128 != 0 && out_bytes + 2 * elements * (int64_t)sizeof(InT) > (c.D <= 32 ? kLastLevelCacheBytes : kLastLevelCacheBytes * 3 / 2);
+    const int64_t bytes = out_bytes + 2 * elements * (int64_t)sizeof(InT);
+    const bool shares_lines = c.D * (int64_t)sizeof(InT) % 128 != 0 &&
+                              (c.D <= 32 ? bytes > kLastLevelCacheBytes : (c.bf16 ? bytes > kLastLevelCacheBytes * 3 / 2 : large_out));
     const int mem = shares_lines ? kShared : (large_out ? kStream : kKeepOut);
     p.cols_per_b = pl.cols_per_b;
     p.pad = (uint32_t)pl.pad;
@@ -879,10 +883,12 @@ hipError_t launch_mode(const ScanCall &c, const BndPlan &pl, const LaunchCtx &ct
     return hipGetLastError();
 }
 
-// Plain numbers in and out, at most kMaxSteps of them per channel.  (Logarithms keep to the log domain.)
+// Plain numbers in and out, at most kMaxSteps of them per channel.  (Logarithms keep to the log domain.)  Large
+// calls of a few channels for more than four steps are left to the tiles, which read such pieces of lines in fewer
+// instructions (2796202 x 8 x 3 bf16: 410 us here, 364 as tiles; 43690 x 8 x 3 5.1 and 7.8).
 bool is_steps(const ScanCall &c)
 {
-    return !c.linear && !c.log_in && !c.log_out && c.n <= kMaxSteps && c.B * c.D < ((int64_t)1 << 31);
+    return !c.linear && !c.log_in && !c.log_out && c.n <= kMaxSteps && (c.n <= 4 || c.D >= 8 || c.B * c.D * c.n < (1ll << 25)) && c.B * c.D < ((int64_t)1 << 31);
 }
 
 template <typename InT>
@@ -928,7 +934,7 @@ void bnd_tile_shape(const ScanCall &c, int &channels, int64_t &steps)
         return;
     }
     const BndPlan pl = make_plan(c);
-    channels = pl.dense && c.D < pl.CH ? (int)c.D : pl.CH; // narrow rows: the channels of several batch items side by side
+    channels = pl.dense ? pl.lanes : pl.CH;
     steps = (int64_t)(pl.NW / pl.cg) * pl.T;
 }
 

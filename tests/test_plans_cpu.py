@@ -27,3 +27,17 @@ CLOG = hb.HEINSEN_LOG_OUTPUT | hb.HEINSEN_OUT_COMPLEX
 def test_plans_of_rows(rows, n, flags, kernel, tile):
     assert hb.heinsen_kernel_name(1, rows, n, BDN, flags) == "heinsen_scan_" + kernel
     assert hb.heinsen_tile_shape(1, rows, n, BDN, flags) == tile
+
+
+# B, n, D -> channels a tile takes: of several items where an item's do not fill it
+@pytest.mark.parametrize("B,n,D,channels", [
+    (1, 300, 5, 64), (13, 300, 5, 40), (256, 4096, 19, 38), (256, 4096, 16, 64), (7, 300, 40, 64), (3, 300, 1024, 64),
+])
+def test_channels_of_a_tile(B, n, D, channels):
+    assert hb.heinsen_tile_shape(B, D, n, BND, 0) == (channels, 256)
+
+
+# B, n, D -> kernel for a few steps
+@pytest.mark.parametrize("B,n,D,kernel", [(64, 1, 4096, "steps"), (64, 8, 8, "steps"), (64, 4, 3, "steps"), (64, 8, 3, "steps"), (1 << 21, 8, 3, "bnd"), (64, 9, 4096, "bnd")])
+def test_kernel_of_a_few_steps(B, n, D, kernel):
+    assert hb.heinsen_kernel_name(B, D, n, BND, 0) == "heinsen_scan_" + kernel
