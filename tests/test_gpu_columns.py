@@ -17,7 +17,7 @@ SHAPES = [
     (2, 300, 96), (3, 700, 65), (5, 65, 33), (4, 129, 100), (2, 33, 48), (7, 1100, 40), (3, 257, 1000 - 25),  # dense columns
     (130, 2100, 33), (8, 1100, 96),                                                                            # the same, several tiles
     (9, 513, 19), (13, 70, 5), (3, 300, 31), (6, 2000, 21),                                                    # whole items
-    (4, 16001, 70), (2, 100003, 20), (70, 3000, 13), (40, 2900, 37),                                           # shared lines
+    (4, 16001, 70), (2, 100003, 20), (70, 3000, 13), (40, 2900, 37),
     # few columns: one tile more than a group (8 tiles of 256 steps), than a super-group (64), than several
     (1, 1025, 64), (1, 2049, 66), (2, 256 * 9 + 3, 96), (1, 256 * 64 + 1, 128), (1, 256 * 65, 2), (3, 256 * 72 + 5, 65),
     (9, 256 * 8 + 1, 64), (12, 256 * 16, 64), (15, 256 * 24, 64), (100, 256 * 4 + 9, 64),  # groups of eight, uneven queues
@@ -78,6 +78,36 @@ def test_a_tile_that_never_publishes_ends_in_nan_with_two_carry_levels(gpu):
     hb.heinsen_scan(*args)
     assert hb.heinsen_check(torch.cuda.current_stream()) == hb.HEINSEN_OK
     assert (out - 1).abs().max() <= 1e-5
+
+
+# Calls large enough to go through the L2 (rows that do not keep to 128-byte lines) or past the caches with columns
+# across items: one batch item against the oracle, the others bit for bit the same (a channel's arithmetic does not depend
+# on where it lies).  More than 192 MiB of output; bf16 288 MiB, narrow items 192 MiB of input and output.
+@pytest.mark.parametrize("mode,bf16,shape", [
+    ("signed", False, (8, 5000, 1501)), ("log_logout", False, (12, 6000, 770)), ("signed", True, (16, 8192, 301)),
+    ("log", True, (16, 8192, 301)), ("signed_clog", False, (20, 4500, 301)), ("signed_clog", True, (32, 4500, 200)),
+    ("positive", False, (130, 6300, 65)), ("signed", False, (256, 4096, 19)), ("signed", True, (300, 4100, 30)),
+    ("signed", False, (260, 2048, 96)), ("linear", False, (8, 5000, 1501)),
+])
+def test_large_calls_item_by_item(gpu, mode, bf16, shape):
+    torch, hb = gpu
+    B, n, D = shape
+    print(f"[large] {mode} bf16={bf16} shape={shape}", flush=True)
+    rng = np.random.default_rng(B * D + int(bf16))
+    a, b, x0 = cross._inputs(rng, (1, n, D), "BND", mode)
+    if bf16:
+        a = workloads.bf16_bits_to_f32(workloads.f32_to_bf16_bits(a)).reshape(a.shape)
+        b = workloads.bf16_bits_to_f32(workloads.f32_to_bf16_bits(b)).reshape(b.shape)
+    kind = torch.bfloat16 if bf16 else torch.float32
+    ta, tb = (torch.from_numpy(v).cuda().to(kind).expand(B, n, D).contiguous() for v in (a, b))
+    tx = torch.from_numpy(x0).cuda().repeat(B)
+    out = torch.full((B, n, D) + ((2,) if mode == "signed_clog" else ()), float("nan"), device="cuda")
+    flags = hb.flags_from_names(cross.MODES[mode]) | (hb.HEINSEN_IN_BF16 if bf16 else 0)
+    hb.heinsen_scan(ta, tb, tx, out, B, D, n, hb.HEINSEN_LAYOUT_BND, flags, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    first = out[:1]
+    assert all(torch.equal(out[i].view(torch.int32), first[0].view(torch.int32)) for i in range(1, B))
+    cross._check(first.cpu().numpy(), a, b, x0, "BND", mode)
 
 
 # Slow decay (a within 1e-4 of one, x close to 1), log domain throughout: the error of the states that travel between

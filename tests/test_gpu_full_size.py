@@ -139,8 +139,8 @@ def test_full_size_other_outputs(gpu, idx, mode):
 @pytest.mark.parametrize("D,n", [(256, 1 << 19), (64, 1 << 20), (1024, 1 << 16)])
 def test_long_sequences_of_few_columns(gpu, D, n):
     """[B,n,D] with 4, 1 and 16 columns of 64 channels and thousands of tiles along time: the launches whose
-    carry structure has longer groups and (for 4 and 1 columns) a second level, at a length where every
-    level is many records deep.  Configuration 2's distribution, generated and checked in full."""
+    carry structure has a second level for 4 and 1 columns and none for 16, at a length where every level
+    is many records deep.  Configuration 2's distribution, generated and checked in full."""
     torch, hb = gpu
     import bench
 
@@ -161,9 +161,8 @@ def test_long_sequences_of_few_columns(gpu, D, n):
 def test_long_slowly_decaying_sequences_channel_contiguous(gpu, B, D, n):
     """[B,n,D] with coefficients within 1e-4 of 1 (configuration 3's distribution) over millions of steps,
     held to the positive tolerance of the definition (1e-4 relative): the state that travels from one group
-    of tiles to the next goes through n/1024 .. n/16384 links (one column: two carry levels of 8 x 8 tiles;
-    four columns: 4 x 4; narrow channels packed side by side; 32 columns: plain groups of eight) and has to
-    be carried in float64 to stay inside the bound.  Generated and checked in full against the float64
+    of tiles to the next goes through n/1024 .. n/16384 links (one and four columns, and narrow channels
+    side by side: two carry levels of 8 x 8 tiles; 32 columns: plain groups of four) and has to be carried in float64 to stay inside the bound.  Generated and checked in full against the float64
     sequential oracle."""
     torch, hb = gpu
     import bench

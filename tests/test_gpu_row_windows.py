@@ -119,3 +119,44 @@ def test_complex_output_in_range_is_evaluated_in_float64(gpu, rows, n, bf16):
     err = np.abs(got[..., 0] - ref) / (1.0 + np.abs(ref))
     print(f"[float64] {rows} x {n} bf16={bf16}: {err.max():.2e}", flush=True)
     assert err.max() <= 2.0 ** -23
+
+
+# Complex rows on nine to 16 waves (up to 1024 threads and 147 KB of LDS): 512 rows of four kinds, the last of which leaves
+# the float64 range at one step.  Bounds as above.
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("n,offset", [(8193, 0), (12000, 0), (12000, 1), (16381, 1), (16384, 0)])
+def test_complex_rows_on_up_to_sixteen_waves(gpu, n, offset, bf16):
+    torch, hb = gpu
+    rng = np.random.default_rng(n + offset)
+    rows = 512
+    a = rng.uniform(0.7, 1.3, (4, n)).astype(np.float32)
+    b = rng.uniform(0.1, 1.0, (4, n)).astype(np.float32)
+    x0 = rng.uniform(0.5, 2.0, 4).astype(np.float32)
+    a[:3, n // 3], a[3, n // 2] = 0.0, 2.0 ** 20
+    if bf16:
+        a = workloads.bf16_bits_to_f32(workloads.f32_to_bf16_bits(a)).reshape(a.shape)
+        b = workloads.bf16_bits_to_f32(workloads.f32_to_bf16_bits(b)).reshape(b.shape)
+    kind = torch.bfloat16 if bf16 else torch.float32
+
+    def device(v):
+        buf = torch.zeros(rows * n + 8, dtype=kind, device="cuda")
+        buf[offset:offset + rows * n] = torch.from_numpy(v).cuda().to(kind).repeat(rows // 4, 1).reshape(-1)
+        return buf, buf[offset:]
+
+    keep_a, ta = device(a)
+    keep_b, tb = device(b)
+    tx = torch.from_numpy(x0).cuda().repeat(rows // 4)
+    keep = torch.full((2 * (rows * n + 8),), float("nan"), device="cuda")
+    out = keep[2 * offset:2 * (offset + rows * n)]
+    print(f"[waves] n={n} offset={offset} bf16={bf16}", flush=True)
+    hb.heinsen_scan(ta, tb, tx, out, 1, rows, n, hb.HEINSEN_LAYOUT_BDN, hb.flags_from_names(cross.MODES["signed_clog"]) |
+                    (hb.HEINSEN_IN_BF16 if bf16 else 0), torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    assert torch.isnan(keep[:2 * offset]).all() and torch.isnan(keep[2 * (offset + rows * n):]).all()
+    ref = np.log(oracle.sequential(a[None], b[None], x0, layout=oracle.LAYOUT_BDN)[0])
+    got = out.reshape(rows // 4, 4, n, 2)
+    assert (got[..., 1] == 0).all()
+    err = (got[..., 0].double() - torch.from_numpy(ref).cuda()).abs().amax(0).cpu().numpy()  # worst of the rows of a kind
+    assert np.all(err[:3] <= 2.0 ** -23 * (1.0 + np.abs(ref[:3])))
+    size = max(1.0, float(np.max(np.abs(ref[3]))) / np.log(2.0))
+    assert np.max(err[3]) <= 5 * np.sqrt(n) * size * 2.0 ** -24 * np.log(2.0) + 2e-6
