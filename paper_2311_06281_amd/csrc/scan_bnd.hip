@@ -26,6 +26,8 @@
 #include "heinsen_math.hpp"
 #include "heinsen_tickets.hpp"
 
+#include <algorithm>
+
 namespace hs {
 namespace {
 
@@ -38,9 +40,12 @@ struct BndParams {
     int x0_stride;    // 0: one x0 for all, 1: x0[b*D + d]
     int cols_per_b;   // ceil(D / CH)
     int ncols;        // B * cols_per_b; DENSE: ceil(B / items per column), D > 32: ceil(B * D / 64)
-    int64_t places;   // DENSE: B * pad (TREE: B * D),
+    int64_t places;   // DENSE: B * pad (TREE, RUNS: B * D),
     uint32_t pad;     //   lanes an item takes,
     int lanes;        //   channels per column
+    int B;            // RUNS: batch items,
+    uint32_t inv_in, inv_out;     //   ceil(2^20 / vectors of an item's run (of half of it, see run_rounds)),
+    uint32_t pitch_in, pitch_out; //   16-byte slots from one item's run (half of it) to the next in LDS
     int nchunks;      // ceil(n / (NW*T))
     uint32_t ntiles;  // ncols * nchunks; tile id = chunk * ncols + col
     int nq;           // ticket queues in use (1 or 8); workgroup i draws from queue i mod nq
@@ -112,6 +117,51 @@ __device__ __forceinline__ void lds_await(volatile uint32_t *flag)
     asm volatile("" ::: "memory");
 }
 
+// ---- items of fewer than 32 channels: whole runs of memory ------------------------------------------------
+//
+// T steps of an item of few channels are one contiguous run of memory, T * D elements, and a column's items are
+// as many such runs.  Taken step by step a wave's accesses are pieces of D elements, and the pieces are what bounds it:
+// out = a + b in them reaches 3.9 TB/s for 256 x 4096 x 19 and 1.4 for 900 x 4096 x 3.  Here they are the runs' 16-byte
+// vectors, consecutive lanes consecutive vectors, which every wave deals out to its lanes through LDS of its own; what is
+// left is the wait for predecessors and, below two rounds of tiles, ramp and drain.  Before and after: 256 x 4096 x 16
+// 51 and 48 us, x 19 67 and 56, 512 x 4096 x 8 71 and 49, 900 x 4096 x 3 116 and 35, 64 x 16384 x 5 47 and 25, bf16
+// 719 x 3461 x 9 107 and 49, 256 x 4096 x 16 46 and 36.  A run begins wherever its item does: the vectors are aligned
+// as elements are, which global accesses of four words may be.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef u32x4 u32x4_at2 __attribute__((aligned(2)));
+typedef u32x4 u32x4_at4 __attribute__((aligned(4)));
+__device__ __forceinline__ u32x4 load_run(const float *p) { return __builtin_nontemporal_load(reinterpret_cast<const u32x4_at4 *>(p)); }
+__device__ __forceinline__ u32x4 load_run(const uint16_t *p) { return __builtin_nontemporal_load(reinterpret_cast<const u32x4_at2 *>(p)); }
+template <bool STREAM>
+__device__ __forceinline__ void store_run(float *p, u32x4 v)
+{
+    if (STREAM)
+        __builtin_nontemporal_store(v, reinterpret_cast<u32x4_at4 *>(p));
+    else
+        *reinterpret_cast<u32x4_at4 *>(p) = v;
+}
+
+// Slots of 16 bytes per wave: an item's run is T * D / 4 of them in float32, and up to 15 between items keep the lanes,
+// which pick up step k of their channels all at once, on different banks (run_pitch).  TREE, which needs much of the
+// LDS itself, and groups of eight tiles, whose records leave fewer registers, deal the runs out in two halves.
+constexpr int run_rounds(int G) { return G > 4 ? 2 : 1; }
+constexpr int run_slots(int rounds) { return 544 / rounds; }
+
+// Which item and which vector of its run the wave's vector g is.
+struct RunAt {
+    uint32_t item, v;
+};
+__device__ __forceinline__ RunAt run_at(uint32_t g, uint32_t per_item, uint32_t inv)
+{
+    const uint32_t item = (g * inv) >> 20; // g < 1024, per_item >= 8: exact
+    return RunAt{item, g - item * per_item};
+}
+__device__ __forceinline__ void wave_lds_order()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // One tile.  The NW waves of the workgroup stand CG side by side along the channels and TS = NW / CG deep
 // along time; a lane owns one channel for T steps.  G tiles per group along time.  SB: keep the scheduler
 // from hoisting work across time steps (bounds register pressure).  DENSE: the lanes of a column are up to
@@ -129,7 +179,7 @@ __device__ __forceinline__ void lds_await(volatile uint32_t *flag)
 // LDS; a later wave waits only for the summaries of the waves before it in its own column; the last wave
 // along time publishes the tile's summary (and, closing a group, the state for the next group).  `flags`
 // are TS*CG + CG words of LDS (TREE: 2*TS more), zero when the tile begins.
-template <int DOM, bool LOG_IN, bool LOG_OUT, typename InT, int T, int NW, int G, bool SB, bool DENSE, bool TREE, int CG, int MEM>
+template <int DOM, bool LOG_IN, bool LOG_OUT, typename InT, int T, int NW, int G, bool SB, bool DENSE, bool TREE, bool RUNS, int CG, int MEM>
 __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile, const uint32_t epoch, volatile uint32_t *flags)
 {
     constexpr bool SIGNED = DOM == kSigned;
@@ -139,6 +189,7 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     static_assert(T <= 32, "one sign word per channel");
     static_assert(NW % CG == 0, "the waves form a CG x TS grid");
     static_assert(!DENSE || CG == 1, "dense columns are mapped one channel per lane");
+    static_assert(!RUNS || (DENSE && NW > 1 && !(SIGNED && LOG_OUT)), "runs are of columns of whole items");
     static_assert(!TREE || (CG == 1 && TS > 1 && G == TS), "every wave of a tile takes one summary of each level");
     __shared__ float lds_A[TS][CH];
     __shared__ float lds_M[TS][CH];
@@ -152,6 +203,9 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     // and, while the records are waited for, the wave's fold of the waves before it (registers are full)
     __shared__ float lds_preA[TREE ? TS : 1][CH], lds_preM[TREE ? TS : 1][CH];
     __shared__ uint32_t lds_preS[TREE ? TS : 1][CH];
+
+    constexpr int ROUNDS = run_rounds(G);
+    __shared__ u32x4 lds_runs[RUNS ? NW : 1][RUNS ? run_slots(ROUNDS) : 1];
 
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); // wave-uniform, kept in an SGPR
@@ -179,14 +233,15 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     int64_t x0_at;   // the channel's place in x0
     if constexpr (DENSE) {
         // An item takes `pad` of the column's lanes (see make_plan).
-        const uint32_t pad = TREE ? (uint32_t)p.D : p.pad;
-        const uint32_t first = (uint32_t)col * (TREE ? (uint32_t)p.lanes : 64u), place = first + (uint32_t)lane;
+        constexpr bool CLOSE = TREE || RUNS; // the items of a column stand close together
+        const uint32_t pad = CLOSE ? (uint32_t)p.D : p.pad;
+        const uint32_t first = (uint32_t)col * (CLOSE ? (uint32_t)p.lanes : 64u), place = first + (uint32_t)lane;
         const uint32_t b0 = first / pad, bb = place / pad;   // batch items of the column's first lane and of this one
         const uint32_t at = place - bb * pad;                // the lane's channel in its item
-        chan_ok = (TREE ? lane < p.lanes : at < (uint32_t)p.D) && place < p.places;
+        chan_ok = (CLOSE ? lane < p.lanes : at < (uint32_t)p.D) && place < p.places;
         moff = (bb - b0) * (uint32_t)(p.n * p.D) + at; // the host checks that this fits 31 bits
         ubase = ((int64_t)b0 * p.n + t0) * p.D;
-        x0_at = TREE ? place : bb * (uint32_t)p.D + at;
+        x0_at = CLOSE ? place : bb * (uint32_t)p.D + at;
     } else {
         const int64_t d0 = (int64_t)cg * CH + c;
         chan_ok = d0 < p.D;
@@ -254,7 +309,50 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     float Av[T], Mv[T];
     const float id_a = LOG_IN ? 0.0f : 1.0f; // a = 1, b = 0 leave the state unchanged
     const float id_b = LOG_IN ? -INFINITY : 0.0f;
-    if (chan_ok && t0 + T <= p.n) {
+    // RUNS: the part of the wave's LDS region that its lane reads and writes (elements from one step to the next: D)
+    const bool whole = RUNS && t0 + T <= p.n; // wave-uniform: the last steps of a sequence go one by one
+    const uint32_t D32 = (uint32_t)p.D, run_item = RUNS && chan_ok ? (uint32_t)lane / D32 : 0u;
+    const uint32_t run_ch = RUNS && chan_ok ? (uint32_t)lane - run_item * D32 : 0u;
+    uint32_t run_n = 0; // items of this column (wave-uniform)
+    if constexpr (RUNS) {
+        const uint32_t items = (uint32_t)p.lanes / D32, left = (uint32_t)p.B - (uint32_t)col * items;
+        run_n = items < left ? items : left;
+    }
+    if (RUNS && whole) {
+        constexpr int VL = 16 / (int)sizeof(InT), NV = T / VL / ROUNDS, TR = T / ROUNDS;
+        const uint32_t per = (uint32_t)(TR / VL) * D32, all = run_n * per;
+        const uint32_t to_next = (uint32_t)(p.n * p.D);
+        auto ask = [&](const InT *from, u32x4(&t)[ROUNDS * NV]) { // lanes without a vector take the first
+#pragma unroll
+            for (int j = 0; j < ROUNDS * NV; ++j) {
+                const uint32_t g = (uint32_t)(j % NV * 64 + lane);
+                const RunAt r2 = run_at(g < all ? g : 0u, per, p.inv_in);
+                t[j] = load_run(from + (r2.item * to_next + ((uint32_t)(j / NV) * per + r2.v) * VL));
+            }
+        };
+        auto deal = [&](const u32x4(&t)[ROUNDS * NV], float(&x)[T]) {
+            const InT *mine = reinterpret_cast<const InT *>(&lds_runs[w][run_item * p.pitch_in]) + run_ch;
+#pragma unroll
+            for (int h = 0; h < ROUNDS; ++h) {
+#pragma unroll
+                for (int j = 0; j < NV; ++j) {
+                    const uint32_t g = (uint32_t)(j * 64 + lane);
+                    const RunAt r2 = run_at(g, per, p.inv_in);
+                    if (g < all) lds_runs[w][r2.item * p.pitch_in + r2.v] = t[h * NV + j];
+                }
+                wave_lds_order();
+#pragma unroll
+                for (int k = 0; k < TR; ++k) x[h * TR + k] = widen(mine[(uint32_t)k * D32]);
+                wave_lds_order();
+            }
+        };
+        u32x4 ta[ROUNDS * NV], tb[ROUNDS * NV];
+        ask(ap, ta);
+        if (ROUNDS == 1) ask(bp, tb); // both at once, where there are registers for it
+        deal(ta, Av);
+        if (ROUNDS > 1) ask(bp, tb);
+        deal(tb, Mv);
+    } else if (chan_ok && t0 + T <= p.n) {
         const InT *arow = ap, *brow = bp; // wave-uniform row pointers
 #pragma unroll
         for (int k = 0; k < T; ++k) {
@@ -510,7 +608,31 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
             if (wanted) store_elem<MEM>(op + (int64_t)k * p.D + moff, o);
         }
     };
-    if (full) {
+    if (RUNS && whole) {
+        constexpr int NV = T / 4 / ROUNDS, TR = T / ROUNDS;
+        const uint32_t per = (uint32_t)(TR / 4) * D32, all = run_n * per;
+        const uint32_t to_next = (uint32_t)(p.n * p.D);
+        float *mine = reinterpret_cast<float *>(&lds_runs[w][run_item * p.pitch_out]) + run_ch;
+        __builtin_amdgcn_s_waitcnt(0x0f70); // vmcnt(0), as below
+#pragma unroll
+        for (int h = 0; h < ROUNDS; ++h) {
+            if (chan_ok) {
+#pragma unroll
+                for (int k = 0; k < TR; ++k) mine[(uint32_t)k * D32] = emit<DOM, LOG_OUT>(st, Av[h * TR + k], Mv[h * TR + k], swx, h * TR + k);
+            }
+            wave_lds_order();
+#pragma unroll
+            for (int j = 0; j < NV; ++j) {
+                const uint32_t g = (uint32_t)(j * 64 + lane);
+                const RunAt r2 = run_at(g, per, p.inv_out);
+                if (g < all) {
+                    const u32x4 o = lds_runs[w][r2.item * p.pitch_out + r2.v];
+                    store_run<MEM == kStream>(op + (r2.item * to_next + ((uint32_t)h * per + r2.v) * 4), o);
+                }
+            }
+            wave_lds_order();
+        }
+    } else if (full) {
         float *orow = op; // wave-uniform row pointer
 #pragma unroll
         for (int k = 0; k < T; ++k) {
@@ -538,7 +660,7 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     p.tl.mark(tile, 6);
 }
 
-template <int DOM, bool LOG_IN, bool LOG_OUT, typename InT, int T, int NW, int G, int MINW, bool SB, bool DENSE, bool TREE, int CG, int MEM>
+template <int DOM, bool LOG_IN, bool LOG_OUT, typename InT, int T, int NW, int G, int MINW, bool SB, bool DENSE, bool TREE, bool RUNS, int CG, int MEM>
 __global__ __launch_bounds__(NW * 64, MINW) void heinsen_scan_bnd(BndParams p)
 {
     __shared__ uint32_t s_tile, s_epoch, s_flag;
@@ -581,7 +703,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void heinsen_scan_bnd(BndParams p)
     if (tile < p.ntiles) {
         p.tl.mark_at(tile, 0, t_begin);
         p.tl.mark(tile, 1);
-        bnd_tile<DOM, LOG_IN, LOG_OUT, InT, T, NW, G, SB, DENSE, TREE, CG, MEM>(p, tile, epoch, s_flags);
+        bnd_tile<DOM, LOG_IN, LOG_OUT, InT, T, NW, G, SB, DENSE, TREE, RUNS, CG, MEM>(p, tile, epoch, s_flags);
         p.tl.mark(tile, 7);
     }
     if (p.header != nullptr) end_of_workgroup(p.header, epoch, &s_flag);
@@ -660,6 +782,8 @@ struct BndPlan {
     bool dense;          // columns of adjacent channels of all B * D (see bnd_tile),
     int lanes;           // this many
     int pad;             // lanes an item takes: D, or the power of two at or above it
+    bool runs;           // whole runs of memory (D <= 32, see bnd_tile)
+    int pitch_in, pitch_out;
     int cols_per_b, ncols, nchunks, ngroups;
     uint32_t ntiles;
     int nq, cols_per_q;
@@ -700,6 +824,41 @@ bool columns_across_items(const ScanCall &c, int64_t own, int64_t shared, int64_
     const int64_t chunks = ceil_div(c.n, steps), places = waves > 8 ? kPlaces / 2 : kPlaces;
     return ceil_div(shared * chunks, places) < ceil_div(own * chunks, places) && (logs || (own * chunks > 2 * places && 5 * shared <= 4 * own));
 }
+
+// RUNS: distance, in 16-byte slots, from one item's run to the next in LDS, for D channels per item whose runs are
+// `vectors` slots.  The lanes pick up words 4 * i * pitch + d of items i and channels d at once (bf16: half-words): the
+// pitch is the smallest of those that put fewest of them on one of the 64 banks.
+constexpr int run_pitch(int D, bool halves, int vectors, int slots)
+{
+    const int items = 64 / D, words = halves ? (D + 1) / 2 : D;
+    int best = vectors, fewest = 1 << 30;
+    for (int pitch = vectors; pitch < vectors + 16 && items * pitch <= slots; ++pitch) {
+        int on[64] = {}, most = 0;
+        for (int i = 0; i < items; ++i)
+            for (int d = 0; d < words; ++d) {
+                const int n = ++on[(4 * i * pitch + d) % 64];
+                most = n > most ? n : most;
+            }
+        if (most < fewest) {
+            fewest = most;
+            best = pitch;
+        }
+    }
+    return best;
+}
+struct RunPitches {
+    int of[2][2][33] = {}; // [float32, bf16][whole runs, halves of them][D]
+    constexpr RunPitches()
+    {
+        for (int D = 2; D <= 32; ++D)
+            for (int h = 0; h < 2; ++h) {
+                const int slots = run_slots(1 + h);
+                of[0][h][D] = run_pitch(D, false, 8 * D >> h, slots);
+                of[1][h][D] = run_pitch(D, true, 4 * D >> h, slots);
+            }
+    }
+};
+constexpr RunPitches kRunPitches;
 
 BndPlan make_plan(const ScanCall &c, bool allow_wide = true, bool want_tree = false)
 {
@@ -749,13 +908,36 @@ BndPlan make_plan(const ScanCall &c, bool allow_wide = true, bool want_tree = fa
             pl.ncols = (int)cols;
         }
     }
+    // Fewer than 32 channels move as whole runs.  (The pieces of 32 are lines or halves of lines as they are: 24 x 16384 x
+    // 32 40.5 us, as runs 43.)  An item's place in a column need not begin anywhere in particular then, and a column
+    // may take as many items as lanes hold instead of as many of the next power of two.  That pays where it saves a
+    // quarter of the columns of a launch that does not fit the chip: 719 x 3461 x 9 bf16 58 and 49 us, 544 x 1294 x 19 41.2
+    // and 36.9; a launch that fits waits less in shorter columns (300 x 700 x 20 16.6 and 17.4), and from four rounds of
+    // tiles on float32 is bound by memory either way (256 x 4096 x 19 55.8 and 55.5).
+    pl.runs = c.D < 32 && pl.cg == 1 && pl.NW == 8 && pl.T == 32;
+    if (pl.runs) {
+        for (pad = 2; pad < c.D;) pad *= 2;
+        int64_t items = std::min(64 / pad, c.B);
+        const int64_t own = ceil_div(c.B, items), close = ceil_div(c.B, 64 / c.D), tiles = own * ceil_div(c.n, (int64_t)pl.NW * pl.T);
+        if (4 * close <= 3 * own && tiles > kPlaces && (c.bf16 || tiles < 4 * kPlaces)) items = 64 / c.D;
+        pl.runs = items * c.n * c.D < ((int64_t)1 << 31) && ceil_div(c.B, items) * items * c.D < ((int64_t)1 << 31);
+        if (pl.runs) {
+            pl.dense = true;
+            pl.lanes = (int)(items * c.D);
+            pl.ncols = (int)ceil_div(c.B, items);
+        }
+    }
     const bool tiles8 = pl.cg == 1 && pl.NW == 8 && pl.T == 32 && c.n > 4 * pl.NW * pl.T;
     pl.tree = tiles8 && (pl.ncols < kTreeBelow || want_tree);
     if (pl.tree) pl.G = kTreeGroup;
     if (pl.tree && pl.ncols >= kTreeAlways && pl.ncols < kTreeBelow && c.n > kTreeGroup * pl.NW * pl.T &&
         c.n <= (c.bf16 ? 3 : 2) * kTreeGroup * pl.NW * pl.T)
         pl.tree = false; // (its groups stay)
-    if (pl.dense) pl.pad = (int)(pl.tree ? c.D : pad);
+    if (pl.dense) pl.pad = (int)(pl.tree || pl.runs ? c.D : pad);
+    if (pl.runs) {
+        pl.pitch_out = kRunPitches.of[0][run_rounds(pl.G) - 1][c.D];
+        pl.pitch_in = kRunPitches.of[c.bf16][run_rounds(pl.G) - 1][c.D];
+    }
     pl.nchunks = (int)ceil_div(c.n, (int64_t)(pl.NW / pl.cg) * pl.T);
     pl.ngroups = (int)ceil_div(pl.nchunks, pl.G);
     pl.ntiles = (uint32_t)pl.ncols * (uint32_t)pl.nchunks;
@@ -818,11 +1000,17 @@ hipError_t launch_mode(const ScanCall &c, const BndPlan &pl, const LaunchCtx &ct
     const int64_t bytes = out_bytes + 2 * elements * (int64_t)sizeof(InT);
     const bool shares_lines = c.D * (int64_t)sizeof(InT) % 128 != 0 &&
                               (c.D <= 32 ? bytes > kLastLevelCacheBytes : (c.bf16 ? bytes > kLastLevelCacheBytes * 3 / 2 : large_out));
-    const int mem = shares_lines ? kShared : (large_out ? kStream : kKeepOut);
+    const int mem = shares_lines && !pl.runs ? kShared : (large_out ? kStream : kKeepOut);
     p.cols_per_b = pl.cols_per_b;
     p.pad = (uint32_t)pl.pad;
     p.places = c.B * pl.pad;
     p.lanes = pl.lanes;
+    p.B = (int)c.B;
+    const uint32_t run = 8u / (uint32_t)run_rounds(pl.G) * (uint32_t)(pl.runs ? c.D : 2), run_in = c.bf16 ? run / 2 : run;
+    p.inv_in = ((1u << 20) + run_in - 1) / run_in;
+    p.inv_out = ((1u << 20) + run - 1) / run;
+    p.pitch_in = (uint32_t)pl.pitch_in;
+    p.pitch_out = (uint32_t)pl.pitch_out;
     p.ncols = pl.ncols;
     p.nchunks = pl.nchunks;
     p.ntiles = pl.ntiles;
@@ -838,46 +1026,56 @@ hipError_t launch_mode(const ScanCall &c, const BndPlan &pl, const LaunchCtx &ct
     p.tl.tiles = ctx.timeline_tiles;
     if (!pl.ticketless && records == nullptr) return hipErrorInvalidValue;
     // The plan's shape and the kernel's must be the same one: a wave that is not there would be waited for.
-#define HS_BND(T_, NW_, G_, DENSE_, TREE_, CG_, MEM_)                                                              \
+#define HS_BND(T_, NW_, G_, DENSE_, TREE_, RUNS_, CG_, MEM_)                                                              \
     do {                                                                                                           \
-        if (pl.T != T_ || pl.NW != NW_ || pl.G != G_ || pl.cg != CG_ || pl.tree != TREE_ || pl.dense != DENSE_)    \
+        if (pl.T != T_ || pl.NW != NW_ || pl.G != G_ || pl.cg != CG_ || pl.tree != TREE_ || pl.dense != DENSE_ || pl.runs != RUNS_) \
             return hipErrorInvalidValue;                                                                           \
-        hipLaunchKernelGGL((heinsen_scan_bnd<DOM, LOG_IN, LOG_OUT, InT, T_, NW_, G_, 4, true, DENSE_, TREE_, CG_, MEM_>), \
+        hipLaunchKernelGGL((heinsen_scan_bnd<DOM, LOG_IN, LOG_OUT, InT, T_, NW_, G_, 4, true, DENSE_, TREE_, RUNS_, CG_, MEM_>), \
                            dim3(pl.grid), dim3(NW_ * 64), 0, c.stream, p);                                         \
     } while (0)
 #define HS_BND_MEM(T_, NW_, G_, DENSE_, TREE_)                                \
     do {                                                                      \
-        if (mem == kShared) HS_BND(T_, NW_, G_, DENSE_, TREE_, 1, kShared);      \
-        else if (mem == kStream) HS_BND(T_, NW_, G_, DENSE_, TREE_, 1, kStream); \
-        else HS_BND(T_, NW_, G_, DENSE_, TREE_, 1, kKeepOut);                    \
+        if (mem == kShared) HS_BND(T_, NW_, G_, DENSE_, TREE_, false, 1, kShared);      \
+        else if (mem == kStream) HS_BND(T_, NW_, G_, DENSE_, TREE_, false, 1, kStream); \
+        else HS_BND(T_, NW_, G_, DENSE_, TREE_, false, 1, kKeepOut);                    \
+    } while (0)
+#define HS_BND_RUNS(T_, NW_, G_, TREE_)                                       \
+    do {                                                                      \
+        if constexpr (T_ == 32) {                                             \
+            if (mem == kStream) HS_BND(T_, NW_, G_, true, TREE_, true, 1, kStream); \
+            else HS_BND(T_, NW_, G_, true, TREE_, true, 1, kKeepOut);         \
+        }                                                                     \
     } while (0)
 #define HS_BND_ANY(T_, NW_, G_, TREE_)                     \
     do {                                                   \
-        if (pl.dense) HS_BND_MEM(T_, NW_, G_, true, TREE_);   \
+        if (pl.runs) HS_BND_RUNS(T_, NW_, G_, TREE_);         \
+        else if (pl.dense) HS_BND_MEM(T_, NW_, G_, true, TREE_); \
         else HS_BND_MEM(T_, NW_, G_, false, TREE_);           \
     } while (0)
     if constexpr (SIGNED && LOG_OUT) {
         HS_BND_ANY(16, 16, 4, false);
     } else if (pl.cg == 2) {
-        if (mem == kStream) HS_BND(32, 8, 4, false, false, 2, kStream);
-        else HS_BND(32, 8, 4, false, false, 2, kKeepOut);
+        if (mem == kStream) HS_BND(32, 8, 4, false, false, false, 2, kStream);
+        else HS_BND(32, 8, 4, false, false, false, 2, kKeepOut);
     } else if (pl.tree) {
         HS_BND_ANY(32, 8, kTreeGroup, true);
     } else if (pl.G == kTreeGroup) { // few short columns: nothing that would not stay in the caches
-        if (pl.dense) HS_BND(32, 8, kTreeGroup, true, false, 1, kKeepOut);
-        else HS_BND(32, 8, kTreeGroup, false, false, 1, kKeepOut);
+        if (pl.runs) HS_BND(32, 8, kTreeGroup, true, false, true, 1, kKeepOut);
+        else if (pl.dense) HS_BND(32, 8, kTreeGroup, true, false, false, 1, kKeepOut);
+        else HS_BND(32, 8, kTreeGroup, false, false, false, 1, kKeepOut);
     } else if (pl.NW == 8) {
         HS_BND_ANY(32, 8, 4, false);
     } else if (pl.dense) { // short sequences
-        if (pl.NW == 1) HS_BND(32, 1, 4, true, false, 1, kKeepOut);
-        else if (pl.NW == 2) HS_BND(32, 2, 4, true, false, 1, kKeepOut);
-        else HS_BND(32, 4, 4, true, false, 1, kKeepOut);
+        if (pl.NW == 1) HS_BND(32, 1, 4, true, false, false, 1, kKeepOut);
+        else if (pl.NW == 2) HS_BND(32, 2, 4, true, false, false, 1, kKeepOut);
+        else HS_BND(32, 4, 4, true, false, false, 1, kKeepOut);
     } else {
-        if (pl.NW == 1) HS_BND(32, 1, 4, false, false, 1, kKeepOut);
-        else if (pl.NW == 2) HS_BND(32, 2, 4, false, false, 1, kKeepOut);
-        else HS_BND(32, 4, 4, false, false, 1, kKeepOut);
+        if (pl.NW == 1) HS_BND(32, 1, 4, false, false, false, 1, kKeepOut);
+        else if (pl.NW == 2) HS_BND(32, 2, 4, false, false, false, 1, kKeepOut);
+        else HS_BND(32, 4, 4, false, false, false, 1, kKeepOut);
     }
 #undef HS_BND_ANY
+#undef HS_BND_RUNS
 #undef HS_BND_MEM
 #undef HS_BND
     return hipGetLastError();
@@ -934,7 +1132,7 @@ void bnd_tile_shape(const ScanCall &c, int &channels, int64_t &steps)
         return;
     }
     const BndPlan pl = make_plan(c);
-    channels = pl.dense ? pl.lanes : pl.CH;
+    channels = pl.dense && pl.lanes > c.D ? pl.lanes : pl.CH; // (an item alone in its column has it to itself)
     steps = (int64_t)(pl.NW / pl.cg) * pl.T;
 }
 

@@ -40,6 +40,28 @@ def test_columns_and_carry_levels(gpu, mode, bf16):
             cross._check(got, a, b, x0, "BND", mode)
 
 
+# Items of fewer than 32 channels, whose runs are dealt out through LDS: one wave's worth of steps more than the short
+# kernels take, tiles that end in the middle of a wave and of a vector, runs that begin on any element (odd n * D), the
+# last column with fewer items than the others, one item alone, one more item than a column, both numbers of items per
+# column, groups of four and of eight tiles with one and two carry levels (whole runs and halves).
+@pytest.mark.parametrize("mode", ["signed", "log_logout", "linear"])
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("shape", [
+    (1, 129, 2), (33, 160, 2), (22, 257, 3), (17, 288, 4), (70, 511, 5), (1, 1024, 31), (3, 1025, 31), (5, 300, 16), (64, 255, 9),
+    (800, 333, 9), (700, 300, 19), (200, 1100, 13), (3, 2049, 23), (25, 2304, 31), (19, 3001, 30), (2, 20001, 7), (40, 1055, 1 + 16),
+])
+def test_runs_of_narrow_items(gpu, mode, bf16, shape):
+    rng = np.random.default_rng(sum(shape) + int(bf16))
+    a, b, x0 = cross._inputs(rng, shape, "BND", mode)
+    if bf16:  # the bf16-rounded values are what is stored: they define the problem
+        a = workloads.bf16_bits_to_f32(workloads.f32_to_bf16_bits(a)).reshape(a.shape)
+        b = workloads.bf16_bits_to_f32(workloads.f32_to_bf16_bits(b)).reshape(b.shape)
+    for offset in (0, 1, 3):
+        print(f"[runs] {mode} bf16={bf16} shape={shape} offset={offset}", flush=True)
+        got = cross._run(gpu, a, b, x0, "BND", cross.MODES[mode], bf16, offset_elems=offset)
+        cross._check(got, a, b, x0, "BND", mode)
+
+
 def test_fewer_records_where_the_fixed_scratch_is_short(gpu):
     """40 columns of 1000 tiles need 6.4e6 records with one carry level, 5.2e6 with two; the fixed array holds 6.29e6.
     The values are x_t = 1 for a = 1/2, b = 1/2, x_0 = 1."""
