@@ -63,6 +63,9 @@ struct BndParams {
     Timeline tl;
 };
 
+// MI355X: 256 MB of memory-side cache; an output up to three quarters of it is left to be cached
+constexpr int64_t kLastLevelCacheBytes = 192ll << 20;
+
 // How a kernel touches memory; every element is used once.  (A compile-time choice: written as a run-time
 // branch the optimiser merges the two kinds of access into plain ones.)
 //   kKeepOut: inputs past the caches, output left in them for whoever consumes it next;
@@ -70,7 +73,10 @@ struct BndParams {
 //   kShared:  rows that do not keep to 128-byte lines: neighbouring columns (and neighbouring steps, where an
 //             item's channels are fewer than a line) read and write parts of the same lines, which stay in
 //             the die's L2 for that.
-enum Mem { kKeepOut, kStream, kShared };
+//   kThrough: kKeepOut where waves write whole lines: written through the die's L2 at once instead of back at some
+//             time later, and at the end of the launch what is left, up to 4 MB per die.  The output is in the memory-side
+//             cache either way.
+enum Mem { kKeepOut, kStream, kShared, kThrough };
 
 template <int MEM, typename InT>
 __device__ __forceinline__ float load_elem(const InT *p)
@@ -82,6 +88,8 @@ __device__ __forceinline__ void store_elem(float *p, float v)
 {
     if (MEM == kStream)
         __builtin_nontemporal_store(v, p);
+    else if (MEM == kThrough)
+        __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     else
         *p = v;
 }
@@ -92,6 +100,8 @@ __device__ __forceinline__ void store_pair(float *p, float re, float im)
     const vec_t x = {re, im};
     if (MEM == kStream)
         __builtin_nontemporal_store(x, reinterpret_cast<vec_t *>(p));
+    else if (MEM == kThrough)
+        __hip_atomic_store(reinterpret_cast<rec_t *>(p), ((rec_t)f2u(im) << 32) | f2u(re), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     else
         *reinterpret_cast<vec_t *>(p) = x;
 }
@@ -132,13 +142,18 @@ typedef u32x4 u32x4_at2 __attribute__((aligned(2)));
 typedef u32x4 u32x4_at4 __attribute__((aligned(4)));
 __device__ __forceinline__ u32x4 load_run(const float *p) { return __builtin_nontemporal_load(reinterpret_cast<const u32x4_at4 *>(p)); }
 __device__ __forceinline__ u32x4 load_run(const uint16_t *p) { return __builtin_nontemporal_load(reinterpret_cast<const u32x4_at2 *>(p)); }
-template <bool STREAM>
-__device__ __forceinline__ void store_run(float *p, u32x4 v)
+// Vector at byte `at` of the wave's output; kThrough is for outputs of up to kLastLevelCacheBytes.  (An atomic store,
+// which is how single words are written through, has 64 bits at most.)
+template <int MEM>
+__device__ __forceinline__ void store_run(float *out, uint32_t at, u32x4 v)
 {
-    if (STREAM)
-        __builtin_nontemporal_store(v, reinterpret_cast<u32x4_at4 *>(p));
+    u32x4_at4 *p = reinterpret_cast<u32x4_at4 *>(out + at);
+    if (MEM == kStream)
+        __builtin_nontemporal_store(v, p);
+    else if (MEM == kThrough)
+        __builtin_amdgcn_raw_buffer_store_b128(v, __builtin_amdgcn_make_buffer_rsrc(out, 0, (int)kLastLevelCacheBytes, 0x00027000), (int)(4u * at), 0, 16); // sc1
     else
-        *reinterpret_cast<u32x4_at4 *>(p) = v;
+        *p = v;
 }
 
 // Slots of 16 bytes per wave: an item's run is T * D / 4 of them in float32, and up to 15 between items keep the lanes,
@@ -627,7 +642,7 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
                 const RunAt r2 = run_at(g, per, p.inv_out);
                 if (g < all) {
                     const u32x4 o = lds_runs[w][r2.item * p.pitch_out + r2.v];
-                    store_run<MEM == kStream>(op + (r2.item * to_next + ((uint32_t)h * per + r2.v) * 4), o);
+                    store_run<MEM>(op, r2.item * to_next + ((uint32_t)h * per + r2.v) * 4, o);
                 }
             }
             wave_lds_order();
@@ -766,9 +781,6 @@ __global__ __launch_bounds__(256) void heinsen_scan_steps(StepsParams p)
 }
 
 // ---- host side ------------------------------------------------------------------------------------
-
-// MI355X: 256 MB of memory-side cache; an output up to three quarters of it is left to be cached
-constexpr int64_t kLastLevelCacheBytes = 192ll << 20;
 
 // Ticket queues: as many (up to one per compute die) as leave every queue this many columns.  The tiles
 // of a column start that many tickets apart, so a tile usually finds the tiles before it done; eight queues
@@ -1000,7 +1012,13 @@ hipError_t launch_mode(const ScanCall &c, const BndPlan &pl, const LaunchCtx &ct
     const int64_t bytes = out_bytes + 2 * elements * (int64_t)sizeof(InT);
     const bool shares_lines = c.D * (int64_t)sizeof(InT) % 128 != 0 &&
                               (c.D <= 32 ? bytes > kLastLevelCacheBytes : (c.bf16 ? bytes > kLastLevelCacheBytes * 3 / 2 : large_out));
-    const int mem = shares_lines && !pl.runs ? kShared : (large_out ? kStream : kKeepOut);
+    // Lines that a wave writes whole gain nothing from waiting in the L2: written through, 8 x 4096 x 1024 takes 77.8 us
+    // instead of 79.1, 32 x 1024 x 1024 76.1 and 80.2, 16 x 1024 x 256 12.0 and 13.9, runs (256 x 4096 x 16) 45.3 and 47.9,
+    // and a kernel that reads the output next is no slower (out = a + b in these pieces and a pass over out, 8 x 4096
+    // x 1024: 96 us, 99.6 with ordinary stores, 102 past the caches).  Lines that columns share do (6 x 3001 x 770: 48.7
+    // and 45.4, 9 x 20000 x 48 39.1 and 38.4).
+    const bool whole_lines = pl.runs || (c.D % 32 == 0 && reinterpret_cast<uintptr_t>(c.out) % 128 == 0);
+    const int mem = shares_lines && !pl.runs ? kShared : (large_out ? kStream : (whole_lines ? kThrough : kKeepOut));
     p.cols_per_b = pl.cols_per_b;
     p.pad = (uint32_t)pl.pad;
     p.places = c.B * pl.pad;
@@ -1033,9 +1051,15 @@ hipError_t launch_mode(const ScanCall &c, const BndPlan &pl, const LaunchCtx &ct
         hipLaunchKernelGGL((heinsen_scan_bnd<DOM, LOG_IN, LOG_OUT, InT, T_, NW_, G_, 4, true, DENSE_, TREE_, RUNS_, CG_, MEM_>), \
                            dim3(pl.grid), dim3(NW_ * 64), 0, c.stream, p);                                         \
     } while (0)
+#define HS_BND_SHORT(NW_, DENSE_)                                             \
+    do {                                                                      \
+        if (mem == kThrough) HS_BND(32, NW_, 4, DENSE_, false, false, 1, kThrough); \
+        else HS_BND(32, NW_, 4, DENSE_, false, false, 1, kKeepOut);           \
+    } while (0)
 #define HS_BND_MEM(T_, NW_, G_, DENSE_, TREE_)                                \
     do {                                                                      \
         if (mem == kShared) HS_BND(T_, NW_, G_, DENSE_, TREE_, false, 1, kShared);      \
+        else if (mem == kThrough) HS_BND(T_, NW_, G_, DENSE_, TREE_, false, 1, kThrough);      \
         else if (mem == kStream) HS_BND(T_, NW_, G_, DENSE_, TREE_, false, 1, kStream); \
         else HS_BND(T_, NW_, G_, DENSE_, TREE_, false, 1, kKeepOut);                    \
     } while (0)
@@ -1043,7 +1067,7 @@ hipError_t launch_mode(const ScanCall &c, const BndPlan &pl, const LaunchCtx &ct
     do {                                                                      \
         if constexpr (T_ == 32) {                                             \
             if (mem == kStream) HS_BND(T_, NW_, G_, true, TREE_, true, 1, kStream); \
-            else HS_BND(T_, NW_, G_, true, TREE_, true, 1, kKeepOut);         \
+            else HS_BND(T_, NW_, G_, true, TREE_, true, 1, kThrough);         \
         }                                                                     \
     } while (0)
 #define HS_BND_ANY(T_, NW_, G_, TREE_)                     \
@@ -1056,26 +1080,28 @@ hipError_t launch_mode(const ScanCall &c, const BndPlan &pl, const LaunchCtx &ct
         HS_BND_ANY(16, 16, 4, false);
     } else if (pl.cg == 2) {
         if (mem == kStream) HS_BND(32, 8, 4, false, false, false, 2, kStream);
+        else if (mem == kThrough) HS_BND(32, 8, 4, false, false, false, 2, kThrough);
         else HS_BND(32, 8, 4, false, false, false, 2, kKeepOut);
     } else if (pl.tree) {
         HS_BND_ANY(32, 8, kTreeGroup, true);
     } else if (pl.G == kTreeGroup) { // few short columns: nothing that would not stay in the caches
-        if (pl.runs) HS_BND(32, 8, kTreeGroup, true, false, true, 1, kKeepOut);
+        if (pl.runs) HS_BND(32, 8, kTreeGroup, true, false, true, 1, kThrough);
         else if (pl.dense) HS_BND(32, 8, kTreeGroup, true, false, false, 1, kKeepOut);
         else HS_BND(32, 8, kTreeGroup, false, false, false, 1, kKeepOut);
     } else if (pl.NW == 8) {
         HS_BND_ANY(32, 8, 4, false);
     } else if (pl.dense) { // short sequences
-        if (pl.NW == 1) HS_BND(32, 1, 4, true, false, false, 1, kKeepOut);
-        else if (pl.NW == 2) HS_BND(32, 2, 4, true, false, false, 1, kKeepOut);
-        else HS_BND(32, 4, 4, true, false, false, 1, kKeepOut);
+        if (pl.NW == 1) HS_BND_SHORT(1, true);
+        else if (pl.NW == 2) HS_BND_SHORT(2, true);
+        else HS_BND_SHORT(4, true);
     } else {
-        if (pl.NW == 1) HS_BND(32, 1, 4, false, false, false, 1, kKeepOut);
-        else if (pl.NW == 2) HS_BND(32, 2, 4, false, false, false, 1, kKeepOut);
-        else HS_BND(32, 4, 4, false, false, false, 1, kKeepOut);
+        if (pl.NW == 1) HS_BND_SHORT(1, false);
+        else if (pl.NW == 2) HS_BND_SHORT(2, false);
+        else HS_BND_SHORT(4, false);
     }
 #undef HS_BND_ANY
 #undef HS_BND_RUNS
+#undef HS_BND_SHORT
 #undef HS_BND_MEM
 #undef HS_BND
     return hipGetLastError();

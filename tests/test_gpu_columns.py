@@ -62,6 +62,22 @@ def test_runs_of_narrow_items(gpu, mode, bf16, shape):
         cross._check(got, a, b, x0, "BND", mode)
 
 
+# Output that a wave writes in whole lines goes through the L2 at once: rows of a multiple of 32 channels from an address
+# that is one of 128 bytes (offsets 0 and 32; offset 1: any other), one wave to eight per tile, one tile and several,
+# columns across items, wide tiles, single values and pairs.
+@pytest.mark.parametrize("mode", ["signed", "log_logout", "signed_clog"])
+@pytest.mark.parametrize("shape", [
+    (2, 17, 32), (2, 40, 64), (3, 100, 96), (3, 300, 64), (1, 2500, 160), (2, 700, 1024), (9, 513, 32), (128, 1030, 256),
+])
+def test_output_written_through(gpu, mode, shape):
+    rng = np.random.default_rng(sum(shape))
+    a, b, x0 = cross._inputs(rng, shape, "BND", mode)
+    for offset in (0, 32, 1):
+        print(f"[through] {mode} shape={shape} offset={offset}", flush=True)
+        got = cross._run(gpu, a, b, x0, "BND", cross.MODES[mode], False, offset_elems=offset)
+        cross._check(got, a, b, x0, "BND", mode)
+
+
 def test_fewer_records_where_the_fixed_scratch_is_short(gpu):
     """40 columns of 1000 tiles need 6.4e6 records with one carry level, 5.2e6 with two; the fixed array holds 6.29e6.
     The values are x_t = 1 for a = 1/2, b = 1/2, x_0 = 1."""
