@@ -620,7 +620,8 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
             if (wanted) store_pair<MEM>(op + 2 * ((int64_t)k * p.D + moff), re, im);
         } else {
             const float o = emit<DOM, LOG_OUT>(st, Av[k], Mv[k], swx, k);
-            if (wanted) store_elem<MEM>(op + (int64_t)k * p.D + moff, o);
+            // the last steps of runs, in pieces of D: lines are put together in the L2
+            if (wanted) store_elem<RUNS && MEM == kThrough ? kKeepOut : MEM>(op + (int64_t)k * p.D + moff, o);
         }
     };
     if (RUNS && whole) {
@@ -1016,8 +1017,12 @@ hipError_t launch_mode(const ScanCall &c, const BndPlan &pl, const LaunchCtx &ct
     // instead of 79.1, 32 x 1024 x 1024 76.1 and 80.2, 16 x 1024 x 256 12.0 and 13.9, runs (256 x 4096 x 16) 45.3 and 47.9,
     // and a kernel that reads the output next is no slower (out = a + b in these pieces and a pass over out, 8 x 4096
     // x 1024: 96 us, 99.6 with ordinary stores, 102 past the caches).  Lines that columns share do (6 x 3001 x 770: 48.7
-    // and 45.4, 9 x 20000 x 48 39.1 and 38.4).
-    const bool whole_lines = pl.runs || (c.D % 32 == 0 && reinterpret_cast<uintptr_t>(c.out) % 128 == 0);
+    // and 45.4, 9 x 20000 x 48 39.1 and 38.4).  The runs of 32 steps are whole lines where items begin on lines; where not,
+    // the lines at their ends are parts, which is as well as long as everything fits half the memory-side cache (300 x 3000 x
+    // 7, 76 MB, 21.3 and 23.0; 81 x 8716 x 18 bf16, 102 MB, 35.7 and 36.7), but not beyond (544 x 1294 x 19, 161 MB, 38.4
+    // and 36.9; 962 x 3401 x 7, 275 MB, 78 and 67).
+    const bool on_line = reinterpret_cast<uintptr_t>(c.out) % 128 == 0;
+    const bool whole_lines = pl.runs ? (on_line && (c.B == 1 || c.n * c.D % 32 == 0)) || bytes <= ((int64_t)128 << 20) : on_line && c.D % 32 == 0;
     const int mem = shares_lines && !pl.runs ? kShared : (large_out ? kStream : (whole_lines ? kThrough : kKeepOut));
     p.cols_per_b = pl.cols_per_b;
     p.pad = (uint32_t)pl.pad;
@@ -1067,7 +1072,8 @@ hipError_t launch_mode(const ScanCall &c, const BndPlan &pl, const LaunchCtx &ct
     do {                                                                      \
         if constexpr (T_ == 32) {                                             \
             if (mem == kStream) HS_BND(T_, NW_, G_, true, TREE_, true, 1, kStream); \
-            else HS_BND(T_, NW_, G_, true, TREE_, true, 1, kThrough);         \
+            else if (mem == kThrough) HS_BND(T_, NW_, G_, true, TREE_, true, 1, kThrough); \
+            else HS_BND(T_, NW_, G_, true, TREE_, true, 1, kKeepOut);         \
         }                                                                     \
     } while (0)
 #define HS_BND_ANY(T_, NW_, G_, TREE_)                     \
