@@ -39,6 +39,13 @@ __device__ __forceinline__ Draw draw_ticket(rec_t *header, int queue, uint32_t d
     return d;
 }
 
+// Holds the calling thread, which has just drawn its workgroup's ticket, back for `ns` nanoseconds (see kPaceNs).
+__device__ __forceinline__ void pace_start(uint32_t ns)
+{
+    const unsigned long long until = wall_clock64() + ns / 10u; // a 100 MHz clock
+    while (wall_clock64() < until) __builtin_amdgcn_s_sleep(1);
+}
+
 // Last action of every workgroup of a launch that drew tickets (all threads call it).  Only the launch that
 // carries the last epoch does anything here: once all of its workgroups have ended, the last one clears
 // the records, so that no tag of this cycle of epochs can be taken for one of the next cycle.

@@ -6,7 +6,7 @@ import pytest
 
 from paper_2311_06281_amd import workloads
 
-from parity import to_device
+from parity import reference, to_device, violations
 
 pytestmark = pytest.mark.gpu
 
@@ -93,6 +93,21 @@ def test_lost_carry_ends_in_nan_and_a_report(gpu, cfg, drop, bad_from_tile):
         assert np.isnan(g[first_bad:]).all()
     again = _run(cfg, dev, torch, hb)
     assert np.array_equal(again.view(np.uint32), want.view(np.uint32))
+
+
+# the first tiles of a launch that fills the chip start one after the other: one tile fewer than that, as many, more, in one
+# row and in rows of the fewest tiles that are paced; float32 and bf16 storage
+@pytest.mark.parametrize("cfg", [
+    workloads.CONFIGS[3].scaled(n=16384 * 510 + 5), workloads.CONFIGS[3].scaled(n=16384 * 511 + 5), workloads.CONFIGS[3].scaled(n=16384 * 700),
+    workloads.CONFIGS[4].scaled(B=2, D=100, n=16384 * 2 + 9), workloads.CONFIGS[4].scaled(B=1, D=9, n=16384 * 63 + 1),
+], ids=lambda c: "x".join(map(str, c.shape())))
+def test_paced_tiles(gpu, cfg):
+    torch, hb = gpu
+    print(f"[paced] {cfg.shape()}", flush=True)
+    batch = workloads.generate(cfg)
+    got = _run(cfg, to_device(batch, cfg, torch), torch, hb)
+    nbad, worst = violations(cfg, got, reference(cfg, batch))
+    assert nbad == 0, worst
 
 
 def test_per_tile_time_stamps(gpu):
