@@ -40,6 +40,7 @@ EXPORTS = ("heinsen_scan", "heinsen_scan_static", "heinsen_status_string", "hein
            "heinsen_set_timeline", "heinsen_test_carry", "heinsen_stream_probe")
 
 _lib = None
+_call = None  # the scan entry points without ctypes (csrc/call.c), once the library is loaded
 
 
 class HeinsenError(RuntimeError):
@@ -50,10 +51,14 @@ class HeinsenError(RuntimeError):
 
 def load() -> ctypes.CDLL:
     """Load the shared library built by paper_2311_06281_amd.build (raises if it is missing)."""
-    global _lib
+    global _lib, _call
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise ImportError(f"{LIB_PATH} not found: build it with `python -m paper_2311_06281_amd.build`")
+        try:
+            from . import _call as call
+        except ImportError as e:
+            raise ImportError(f"the call module of {LIB_PATH} is missing: build it with `python -m paper_2311_06281_amd.build`") from e
         lib = ctypes.CDLL(LIB_PATH)
         vp, i64, ci, u32 = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int, ctypes.c_uint32
         lib.heinsen_scan.argtypes = [vp, vp, vp, vp, i64, i64, i64, ci, u32, vp]
@@ -82,8 +87,15 @@ def load() -> ctypes.CDLL:
         lib.heinsen_stream_probe.restype = ci
         lib.heinsen_sequential.argtypes = [vp, vp, vp, vp, i64, vp]
         lib.heinsen_sequential.restype = ci
+        call.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.heinsen_scan, lib.heinsen_scan_static)))
+        _call = call
         _lib = lib
     return _lib
+
+
+def _native():
+    load()
+    return _call
 
 
 def _addr(x) -> int:
@@ -147,30 +159,28 @@ def heinsen_tile_shape(B: int, D: int, n: int, layout: int, flags: int):
     return seqs.value, steps.value
 
 
-def _scan_call(fn, a, b, x0, out, B, D, n, layout, flags, stream) -> int:
-    """Calls a scan entry point.  The smallest calls are bound by the host (4.4 us in the launch, 1.1 in ctypes), so
-    tensors, plain integers and a torch stream go straight through, 1.6 us where converting every argument takes 2.1.
-    Addresses and streams that are integers, or no stream, are known as such at once; whatever else is not of these
-    types fails before the library is entered and is converted then."""
-    if stream is not None and stream.__class__ is not int and a.__class__ is not int:
-        try:
-            return fn(a.data_ptr(), b.data_ptr(), x0.data_ptr(), out.data_ptr(), B, D, n, layout, flags, stream.cuda_stream)
-        except (AttributeError, TypeError, ctypes.ArgumentError):
-            pass
+def _convert_and_call(fn, a, b, x0, out, B, D, n, layout, flags, stream) -> int:
+    """Calls a scan entry point with arguments of any kind.  Tensors, plain integers and a torch stream do not come here:
+    the smallest calls are bound by the host, and csrc/call.c hands those over in 0.4 us where this takes 1.5."""
     return int(fn(_addr(a), _addr(b), _addr(x0), _addr(out), int(B), int(D), int(n), int(layout), int(flags),
                   _stream_handle(stream)))
 
 
 def heinsen_scan_status(a, b, x0, out, B: int, D: int, n: int, layout: int, flags: int, stream=None) -> int:
     """Raw call: returns the heinsen_status_t instead of raising."""
-    return _scan_call((_lib or load()).heinsen_scan, a, b, x0, out, B, D, n, layout, flags, stream)
+    st = (_call or _native()).scan(a, b, x0, out, B, D, n, layout, flags, stream)
+    if st is NotImplemented:
+        st = _convert_and_call(_lib.heinsen_scan, a, b, x0, out, B, D, n, layout, flags, stream)
+    return st
 
 
 def heinsen_scan(a, b, x0, out, B: int, D: int, n: int, layout: int, flags: int, stream=None) -> None:
     """x_t = a_t x_{t-1} + b_t for B*D sequences; see include/heinsen.h.  Asynchronous on `stream`.
 
     a, b, x0, out: device tensors (anything with data_ptr()) or integer device addresses."""
-    st = _scan_call((_lib or load()).heinsen_scan, a, b, x0, out, B, D, n, layout, flags, stream)
+    st = (_call or _native()).scan(a, b, x0, out, B, D, n, layout, flags, stream)
+    if st is NotImplemented:
+        st = _convert_and_call(_lib.heinsen_scan, a, b, x0, out, B, D, n, layout, flags, stream)
     if st != HEINSEN_OK:
         msg = heinsen_status_string(st)
         if st in (HEINSEN_ERR_HIP, HEINSEN_ERR_ALLOC):
@@ -180,12 +190,17 @@ def heinsen_scan(a, b, x0, out, B: int, D: int, n: int, layout: int, flags: int,
 
 def heinsen_scan_static_status(a, b, x0, out, B: int, D: int, n: int, layout: int, flags: int, stream=None) -> int:
     """Raw call of the allocation-free variant: returns the heinsen_status_t instead of raising."""
-    return _scan_call((_lib or load()).heinsen_scan_static, a, b, x0, out, B, D, n, layout, flags, stream)
+    st = (_call or _native()).scan_static(a, b, x0, out, B, D, n, layout, flags, stream)
+    if st is NotImplemented:
+        st = _convert_and_call(_lib.heinsen_scan_static, a, b, x0, out, B, D, n, layout, flags, stream)
+    return st
 
 
 def heinsen_scan_static(a, b, x0, out, B: int, D: int, n: int, layout: int, flags: int, stream=None) -> None:
     """heinsen_scan without any device allocation (fixed scratch inside the library); see include/heinsen.h."""
-    st = _scan_call((_lib or load()).heinsen_scan_static, a, b, x0, out, B, D, n, layout, flags, stream)
+    st = (_call or _native()).scan_static(a, b, x0, out, B, D, n, layout, flags, stream)
+    if st is NotImplemented:
+        st = _convert_and_call(_lib.heinsen_scan_static, a, b, x0, out, B, D, n, layout, flags, stream)
     if st != HEINSEN_OK:
         msg = heinsen_status_string(st)
         if st == HEINSEN_ERR_HIP:

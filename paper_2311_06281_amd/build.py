@@ -4,6 +4,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -11,6 +12,8 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libheinsen.so")
 SOURCES = ["heinsen_api.hip", "scan_bnd.hip", "scan_bdn.hip", "sequential_ref.hip", "stream_probe.hip"]
 HEADERS = ["heinsen_internal.hpp", "heinsen_math.hpp", "heinsen_tickets.hpp", os.path.join("..", "..", "include", "heinsen.h")]
+CALL_SOURCE = "call.c"  # the Python side of the scan entry points
+CALL = os.path.join(HERE, "_call" + sysconfig.get_config_var("EXT_SUFFIX"))
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-command-line-argument",
          # packed-FP32 instructions are kept out of the generated code
@@ -31,11 +34,18 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _compile_call() -> None:
+    cmd = ["gcc", "-O2", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, CALL_SOURCE), "-o", CALL]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"gcc failed on {CALL_SOURCE}:\n{r.stderr}")
+
+
 def needs_build() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(CALL):
         return True
-    t = os.path.getmtime(LIB)
-    deps = [os.path.join(CSRC, s) for s in SOURCES + HEADERS]
+    t = min(os.path.getmtime(LIB), os.path.getmtime(CALL))
+    deps = [os.path.join(CSRC, s) for s in SOURCES + HEADERS + [CALL_SOURCE]]
     return any(os.path.getmtime(d) > t for d in deps)
 
 
@@ -43,6 +53,7 @@ def build(force: bool = True) -> str:
     """Compile every translation unit and link the shared library. Returns its path."""
     if not force and not needs_build():
         return LIB
+    _compile_call()
     with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
         objs = list(ex.map(_compile, SOURCES))
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]

@@ -3,6 +3,7 @@ declares, and rejects bad arguments on the host before any GPU work."""
 import os
 import re
 
+import numpy as np
 import pytest
 
 from paper_2311_06281_amd import binding as hb
@@ -126,3 +127,32 @@ def test_every_form_of_the_arguments_arrives(a, stream, number):
     assert hb.heinsen_scan_status(a, rest[0], None, rest[2], 1, 1, 8, 0, 0, stream) == hb.HEINSEN_ERR_INVALID_ARG  # null x0
     fast = isinstance(a, _Tensor) and stream is not None and stream != 0
     assert rest[1].asked == (2 if fast and number is float else 1)
+
+
+# The direct call and the converting one take the same arguments the same way.  All are refused before anything touches
+# a GPU: by a null pointer (1), a misaligned one (1), a layout or flags that do not exist (1), an unsupported mode (2).
+@pytest.mark.parametrize("pointers,rest,status", [
+    ((0, 16, 16, 16), (1, 1, 1, 0, 0), 1), ((16, 16, None, 16), (1, 1, 1, 0, 0), 1), ((17, 16, 16, 16), (1, 1, 1, 0, 0), 1),
+    ((16, 16, 16, 16), (1, 1, 1, 7, 0), 1), ((16, 16, 16, 16), (1, 1, 1, 0, 1 << 20), 1), ((16, 16, 16, 16), (1, 1, 1, 0, -1), 1),
+    ((16, 16, 16, 16), (0, 1, 1, 0, 0), 1), ((16, 16, 16, 16), (1, 1, True, 1, 2), 2), ((16, 16, 16, 16), (1 << 40, 1 << 40, 1, 0, 0), 1),
+    ((16, 16, 16, 16), (np.int64(1), 1, 1, 0, 2), 2), ((16, 16, 16, 16), (1.0, 1, 1, 0, 2), 2),
+])
+def test_arguments_of_every_kind(pointers, rest, status):
+    lib = hb.load()
+    for wrap in (lambda p: p, lambda p: p if p is None else _Tensor(p)):
+        args = [wrap(p) for p in pointers]
+        for stream in (None, 0, _Stream()):
+            assert hb._convert_and_call(lib.heinsen_scan, *args, *rest, stream) == status
+            assert hb.heinsen_scan_status(*args, *rest, stream) == status
+            assert hb.heinsen_scan_static_status(*args, *rest, stream) == status
+            with pytest.raises(hb.HeinsenError):
+                hb.heinsen_scan(*args, *rest, stream=stream)
+            with pytest.raises(hb.HeinsenError):
+                hb.heinsen_scan_static(*args, *rest, stream=stream)
+
+
+@pytest.mark.parametrize("bad,error", [("x", ValueError), (object(), TypeError), (_Tensor("x"), ValueError), (_Tensor(None), TypeError)])
+def test_arguments_of_no_kind(bad, error):
+    for call in (hb.heinsen_scan, hb.heinsen_scan_static):
+        with pytest.raises(error):
+            call(bad, 16, 16, 16, 1, 1, 1, 0, 0)
