@@ -959,8 +959,15 @@ BndPlan make_plan(const ScanCall &c, bool allow_wide = true, bool want_tree = fa
     pl.records = pl.off_state + (size_t)pl.ngroups * pl.ncols * 2 * pl.CH;
     pl.ticketless = pl.nchunks == 1 && c.n <= 64; // short single-tile columns: no records, no tickets
     // A queue's workgroups that find no tile behind their ticket (uneven deal) end at once.
+    // Wide tiles of items a power of two apart: the items lie on the same memory channels, and dies that share a queue ask for
+    // the same rows of several at about the same time.  A queue per die, each with its own items, is the better there
+    // as long as the dies stay together (16 x 4096 x 2048 288 and 272 us, 32 x 2048 x 1024 152 and 140, bf16 64 x 2048 x 1024
+    // 228 and 192, 8 x 4096 x 4096 277.6 and 278.6; but 32 x 8192 x 1024 541 and 616, and other distances, 28 x 2944 x 1792
+    // bf16 212 and 219).
+    const int64_t item = c.n * c.D;
+    const bool queue_per_die = pl.cg > 1 && (item & (item - 1)) == 0 && c.n <= 4096;
     pl.nq = kQueues;
-    while (pl.nq > 1 && pl.ncols < pl.nq * (pl.cg > 1 ? kMinColsPerQueueWide : kMinColsPerQueue)) pl.nq /= 2;
+    while (pl.nq > 1 && !queue_per_die && pl.ncols < pl.nq * (pl.cg > 1 ? kMinColsPerQueueWide : kMinColsPerQueue)) pl.nq /= 2;
     // Eight queues of fewer than 16 columns are for lines that columns share and for short sequences.  Long ones
     // wait for their predecessors less in four (80 columns of 16384 steps: 169 and 174 us), and an uneven deal may be
     // what makes a launch that fits the chip take a second round on one die (100 columns of 1100 steps, bf16: 18.3 and
