@@ -41,11 +41,9 @@ struct BndParams {
     int cols_per_b;   // ceil(D / CH)
     int ncols;        // B * cols_per_b; DENSE: ceil(B / items per column), D > 32: ceil(B * D / 64)
     int64_t places;   // DENSE: B * pad (TREE, RUNS: B * D),
-    uint32_t pad;     //   lanes an item takes,
+    uint32_t pad;     //   lanes an item takes (RUNS: 16-byte slots from one item's run, or half of it, to the next in LDS, of
+                      //   the inputs in the low half of the word, of the output in the high half),
     int lanes;        //   channels per column
-    int B;            // RUNS: batch items,
-    uint32_t inv_in, inv_out;     //   ceil(2^20 / vectors of an item's run (of half of it, see run_rounds)),
-    uint32_t pitch_in, pitch_out; //   16-byte slots from one item's run (half of it) to the next in LDS
     int nchunks;      // ceil(n / (NW*T))
     uint32_t ntiles;  // ncols * nchunks; tile id = chunk * ncols + col
     int nq;           // ticket queues in use (1 or 8); workgroup i draws from queue i mod nq
@@ -166,9 +164,10 @@ constexpr int run_slots(int rounds) { return 544 / rounds; }
 struct RunAt {
     uint32_t item, v;
 };
+__device__ __forceinline__ uint32_t run_inverse(uint32_t per_item) { return ((1u << 20) + per_item - 1u) / per_item; }
 __device__ __forceinline__ RunAt run_at(uint32_t g, uint32_t per_item, uint32_t inv)
 {
-    const uint32_t item = (g * inv) >> 20; // g < 1024, per_item >= 8: exact
+    const uint32_t item = (g * inv) >> 20; // g < 512, per_item of 4 to 256: exact
     return RunAt{item, g - item * per_item};
 }
 __device__ __forceinline__ void wave_lds_order()
@@ -329,31 +328,32 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     const uint32_t D32 = (uint32_t)p.D, run_item = RUNS && chan_ok ? (uint32_t)lane / D32 : 0u;
     const uint32_t run_ch = RUNS && chan_ok ? (uint32_t)lane - run_item * D32 : 0u;
     uint32_t run_n = 0; // items of this column (wave-uniform)
+    const uint32_t pitch_in = p.pad & 0xffffu, pitch_out = p.pad >> 16;
     if constexpr (RUNS) {
-        const uint32_t items = (uint32_t)p.lanes / D32, left = (uint32_t)p.B - (uint32_t)col * items;
-        run_n = items < left ? items : left;
+        const uint32_t first_place = (uint32_t)col * (uint32_t)p.lanes, left = (uint32_t)p.places - first_place;
+        run_n = ((uint32_t)p.lanes < left ? (uint32_t)p.lanes : left) / D32;
     }
     if (RUNS && whole) {
         constexpr int VL = 16 / (int)sizeof(InT), NV = T / VL / ROUNDS, TR = T / ROUNDS;
-        const uint32_t per = (uint32_t)(TR / VL) * D32, all = run_n * per;
+        const uint32_t per = (uint32_t)(TR / VL) * D32, all = run_n * per, inv = run_inverse(per);
         const uint32_t to_next = (uint32_t)(p.n * p.D);
         auto ask = [&](const InT *from, u32x4(&t)[ROUNDS * NV]) { // lanes without a vector take the first
 #pragma unroll
             for (int j = 0; j < ROUNDS * NV; ++j) {
                 const uint32_t g = (uint32_t)(j % NV * 64 + lane);
-                const RunAt r2 = run_at(g < all ? g : 0u, per, p.inv_in);
+                const RunAt r2 = run_at(g < all ? g : 0u, per, inv);
                 t[j] = load_run(from + (r2.item * to_next + ((uint32_t)(j / NV) * per + r2.v) * VL));
             }
         };
         auto deal = [&](const u32x4(&t)[ROUNDS * NV], float(&x)[T]) {
-            const InT *mine = reinterpret_cast<const InT *>(&lds_runs[w][run_item * p.pitch_in]) + run_ch;
+            const InT *mine = reinterpret_cast<const InT *>(&lds_runs[w][run_item * pitch_in]) + run_ch;
 #pragma unroll
             for (int h = 0; h < ROUNDS; ++h) {
 #pragma unroll
                 for (int j = 0; j < NV; ++j) {
                     const uint32_t g = (uint32_t)(j * 64 + lane);
-                    const RunAt r2 = run_at(g, per, p.inv_in);
-                    if (g < all) lds_runs[w][r2.item * p.pitch_in + r2.v] = t[h * NV + j];
+                    const RunAt r2 = run_at(g, per, inv);
+                    if (g < all) lds_runs[w][r2.item * pitch_in + r2.v] = t[h * NV + j];
                 }
                 wave_lds_order();
 #pragma unroll
@@ -626,9 +626,9 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     };
     if (RUNS && whole) {
         constexpr int NV = T / 4 / ROUNDS, TR = T / ROUNDS;
-        const uint32_t per = (uint32_t)(TR / 4) * D32, all = run_n * per;
+        const uint32_t per = (uint32_t)(TR / 4) * D32, all = run_n * per, inv = run_inverse(per);
         const uint32_t to_next = (uint32_t)(p.n * p.D);
-        float *mine = reinterpret_cast<float *>(&lds_runs[w][run_item * p.pitch_out]) + run_ch;
+        float *mine = reinterpret_cast<float *>(&lds_runs[w][run_item * pitch_out]) + run_ch;
         __builtin_amdgcn_s_waitcnt(0x0f70); // vmcnt(0), as below
 #pragma unroll
         for (int h = 0; h < ROUNDS; ++h) {
@@ -640,9 +640,9 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
 #pragma unroll
             for (int j = 0; j < NV; ++j) {
                 const uint32_t g = (uint32_t)(j * 64 + lane);
-                const RunAt r2 = run_at(g, per, p.inv_out);
+                const RunAt r2 = run_at(g, per, inv);
                 if (g < all) {
-                    const u32x4 o = lds_runs[w][r2.item * p.pitch_out + r2.v];
+                    const u32x4 o = lds_runs[w][r2.item * pitch_out + r2.v];
                     store_run<MEM>(op, r2.item * to_next + ((uint32_t)h * per + r2.v) * 4, o);
                 }
             }
@@ -1030,17 +1030,14 @@ hipError_t launch_mode(const ScanCall &c, const BndPlan &pl, const LaunchCtx &ct
     // and 36.9; 962 x 3401 x 7, 275 MB, 78 and 67).
     const bool on_line = reinterpret_cast<uintptr_t>(c.out) % 128 == 0;
     const bool whole_lines = pl.runs ? (on_line && (c.B == 1 || c.n * c.D % 32 == 0)) || bytes <= ((int64_t)128 << 20) : on_line && c.D % 32 == 0;
-    const int mem = shares_lines && !pl.runs ? kShared : (large_out ? kStream : (whole_lines ? kThrough : kKeepOut));
+    // A launch of one round whose CUs hold two tiles, some of them a group ahead: the state that the later one waits for
+    // would queue with the output of all (60 columns of five tiles, 30 x 1152 x 128, 17.3 us and 16.0; 56 of six 18.2 and 16.9).
+    const bool waits_for_stores = !pl.tree && pl.ngroups > 1 && pl.ntiles > (uint32_t)kPlaces / 2 && pl.ntiles <= (uint32_t)kPlaces;
+    const int mem = shares_lines && !pl.runs ? kShared : (large_out ? kStream : (whole_lines && !waits_for_stores ? kThrough : kKeepOut));
     p.cols_per_b = pl.cols_per_b;
-    p.pad = (uint32_t)pl.pad;
+    p.pad = pl.runs ? (uint32_t)(pl.pitch_in | pl.pitch_out << 16) : (uint32_t)pl.pad;
     p.places = c.B * pl.pad;
     p.lanes = pl.lanes;
-    p.B = (int)c.B;
-    const uint32_t run = 8u / (uint32_t)run_rounds(pl.G) * (uint32_t)(pl.runs ? c.D : 2), run_in = c.bf16 ? run / 2 : run;
-    p.inv_in = ((1u << 20) + run_in - 1) / run_in;
-    p.inv_out = ((1u << 20) + run - 1) / run;
-    p.pitch_in = (uint32_t)pl.pitch_in;
-    p.pitch_out = (uint32_t)pl.pitch_out;
     p.ncols = pl.ncols;
     p.nchunks = pl.nchunks;
     p.ntiles = pl.ntiles;
