@@ -11,7 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libheinsen.so")
 SOURCES = ["heinsen_api.hip", "scan_bnd.hip", "scan_bdn.hip", "sequential_ref.hip", "stream_probe.hip"]
-HEADERS = ["heinsen_internal.hpp", "heinsen_math.hpp", "heinsen_tickets.hpp", os.path.join("..", "..", "include", "heinsen.h")]
+HEADERS = ["heinsen_internal.hpp", "heinsen_math.hpp", "heinsen_tickets.hpp", "scan_rules.hpp", os.path.join("..", "..", "include", "heinsen.h")]
 CALL_SOURCE = "call.c"  # the Python side of the scan entry points
 CALL = os.path.join(HERE, "_call" + sysconfig.get_config_var("EXT_SUFFIX"))
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

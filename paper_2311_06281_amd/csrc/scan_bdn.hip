@@ -17,6 +17,7 @@
 #include "heinsen_internal.hpp"
 #include "heinsen_math.hpp"
 #include "heinsen_tickets.hpp"
+#include "scan_rules.hpp"
 
 #include <algorithm>
 
@@ -1106,20 +1107,6 @@ constexpr int kTile = kTileWaves * 64 * kTileItems;
 // 9.5 against 10.1 us for 2^20 (128 half tiles), even at 2^21, slower beyond.
 constexpr int64_t kHalfTilesUpTo = 128;
 
-// A launch of rows of several tiles starts its first tiles one after the other, this many nanoseconds apart, which is
-// about as fast as memory takes their loads.  Started all at once they shared the memory evenly, had their inputs at about
-// the same time, waited for one another at the same time and wrote at the same time, and so did the tiles behind them:
-// at some times 39 of 512 tiles were loading, at others 488.  One after the other, a tile is waiting or writing while the
-// next ones load, from the first to the last.  Measured (none, 6, 9, 12, 15 ns): one row of 2^26 float32 154.1, 152.4,
-// 150.3, 149.0, 149.3 us; 700 rows of 40000 69.4, 68.1, 66.7, 66.4, 67.3; bf16, whose tiles are half the bytes, one row of
-// 4 * 10^7 81.4, 79.9, 79.5, 79.8, 81.3, 4 rows of 4 * 10^6 37.5, 36.6, 36.8, 39.0, 41.6.  A launch that fits the chip
-// has nothing behind its first tiles (4.2 * 10^6 steps 16.0, 16.0, 16.5, 17.3, 18.0); from one round on (8.5 * 10^6 steps)
-// it gains (32.1, 31.5, 31.3, 31.0, 31.5).  Of rows of two tiles only every other tile waits, and for one (3000 rows of
-// 17000 137.2, 12 ns 138.0).
-constexpr uint32_t kPaceNs = 12, kPaceNsBf16 = 8;
-constexpr uint32_t kPacedTiles = 512; // workgroups that the chip holds
-constexpr uint32_t kPacedTilesPerRow = 3;
-
 struct TileParams {
     const void *a;
     const void *b;
@@ -1430,7 +1417,7 @@ __global__ __launch_bounds__((inputs_in_lds<DOM, LOG_OUT, MULTI, ITEMS>() ? kLds
         // tickets: a tile only ever waits for tiles with smaller tickets, which are already running
         if (threadIdx.x == 0) {
             const Draw d = draw_ticket(p.header, 0, p.ntiles, 1);
-            if (p.pace_ns != 0 && d.ticket < kPacedTiles) pace_start(d.ticket * p.pace_ns);
+            if (paced_kernel(VECIO, complex_output<DOM, LOG_OUT>()) && p.pace_ns != 0 && d.ticket < kPacedTiles) pace_start(d.ticket * p.pace_ns);
             s_tile = d.ticket;
             s_epoch = d.epoch;
         }
@@ -1637,7 +1624,7 @@ hipError_t launch_mode(const ScanCall &c, const BdnPlan &pl, const LaunchCtx &ct
     p.x0_stride = c.x0_scalar ? 0 : 1;
     p.phase = pl.phase;
     p.waves = pl.waves;
-    p.pace_ns = pl.tpr >= kPacedTilesPerRow && pl.ntiles >= kPacedTiles ? (c.bf16 ? kPaceNsBf16 : kPaceNs) : 0;
+    p.pace_ns = pace_ns(pl.vecio, complex_output<DOM, LOG_OUT>(), c.bf16, pl.tpr, pl.ntiles);
     p.tpr = pl.tpr;
     p.ntiles = pl.ntiles;
     rec_t *records = pl.multi ? ctx.scratch : nullptr;

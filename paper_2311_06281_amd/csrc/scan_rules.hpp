@@ -1,0 +1,37 @@
+// Rules of a launch that follow from sizes and types alone (plain C++, which the tests compile by itself).
+#pragma once
+#include <stdint.h>
+
+namespace hs {
+
+// A launch of rows of several tiles starts its first tiles one after the other: each waits its ticket times this many
+// nanoseconds after it has drawn the ticket.  (The draws queue as well: in one row of 2^26 steps the 512th tile starts 8.5 us
+// after the first without the wait and 13.2 us with 12 ns, that is 26 ns a tile, at which their loads are 5.1 TB/s.
+// The spacing is the one measured best.)  Started all at once they shared the memory evenly, had their inputs at about
+// the same time, waited for one another at the same time and wrote at the same time, and so did the tiles behind them:
+// at some times 39 of 512 tiles were loading, at others 488.  One after the other, a tile is waiting or writing while the
+// next ones load, from the first to the last.  Measured (none, 6, 9, 12, 15 ns): one row of 2^26 float32 154.1, 152.4,
+// 150.3, 149.0, 149.3 us; 700 rows of 40000 69.4, 68.1, 66.7, 66.4, 67.3; bf16, whose tiles are half the bytes, one row of
+// 4 * 10^7 81.4, 79.9, 79.5, 79.8, 81.3, 4 rows of 4 * 10^6 37.5, 36.6, 36.8, 39.0, 41.6.  A launch that fits the chip
+// has nothing behind its first tiles (4.2 * 10^6 steps 16.0, 16.0, 16.5, 17.3, 18.0); from one round on (8.5 * 10^6 steps)
+// it gains (32.1, 31.5, 31.3, 31.0, 31.5).  Of rows of two tiles only every other tile waits, and for one (3000 rows of
+// 17000 137.2, 12 ns 138.0).
+//
+// That is for the tiles of which the chip holds kPacedTiles at a time, two workgroups per compute unit: real output moved
+// as vectors (114 to 128 registers).  Element by element (159 to 163 registers) and with complex output (178 to 208) a
+// workgroup has its compute unit to itself; tickets 256 and up are then drawn in the middle of the launch, where a wait only
+// leaves the unit empty.  Without and with it: 200 rows of 40000 whose pointers are not alike 35.2 and 41.3 us, bf16 104.5
+// and 108.9, one row of 1.25 * 10^7 such steps 43.3 and 47.9; complex output, 200 x 40000, 46.2 and 50.5.
+constexpr uint32_t kPaceNs = 12, kPaceNsBf16 = 8;
+constexpr uint32_t kPacedTiles = 512;
+constexpr uint32_t kPacedTilesPerRow = 3;
+
+// Whether the tiles kernel for such data may be paced, and the spacing for a launch (0: none).
+constexpr bool paced_kernel(bool vectors, bool complex_out) { return vectors && !complex_out; }
+constexpr uint32_t pace_ns(bool vectors, bool complex_out, bool bf16, uint32_t tiles_per_row, uint32_t tiles)
+{
+    if (!paced_kernel(vectors, complex_out) || tiles_per_row < kPacedTilesPerRow || tiles < kPacedTiles) return 0;
+    return bf16 ? kPaceNsBf16 : kPaceNs;
+}
+
+} // namespace hs

@@ -1,5 +1,9 @@
 """Which kernel and tile a call takes, on the side of each rule where a slower one was taken before.  No GPU: the
-plan is asked for through heinsen_kernel_name and heinsen_tile_shape."""
+plan is asked for through heinsen_kernel_name and heinsen_tile_shape; rules that do not show there stand in
+scan_rules.hpp and are compiled by themselves."""
+import os
+import subprocess
+
 import pytest
 
 from paper_2311_06281_amd import binding as hb
@@ -41,3 +45,26 @@ def test_channels_of_a_tile(B, n, D, channels):
 @pytest.mark.parametrize("B,n,D,kernel", [(64, 1, 4096, "steps"), (64, 8, 8, "steps"), (64, 4, 3, "steps"), (64, 8, 3, "steps"), (1 << 21, 8, 3, "bnd"), (64, 9, 4096, "bnd")])
 def test_kernel_of_a_few_steps(B, n, D, kernel):
     assert hb.heinsen_kernel_name(B, D, n, BND, 0) == "heinsen_scan_" + kernel
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    """Values of C++ expressions over scan_rules.hpp."""
+    folder = tmp_path_factory.mktemp("rules")
+    csrc = os.path.join(os.path.dirname(os.path.abspath(hb.__file__)), "csrc")
+
+    def values(expressions):
+        lines = "".join(f'    std::printf("%lld\\n", (long long)({e}));\n' for e in expressions)
+        (folder / "rules.cpp").write_text(f'#include "scan_rules.hpp"\n#include <cstdio>\nusing namespace hs;\nint main()\n{{\n{lines}}}\n')
+        subprocess.run(["g++", "-std=c++17", "-I", csrc, str(folder / "rules.cpp"), "-o", str(folder / "rules")], check=True)
+        return [int(v) for v in subprocess.run([str(folder / "rules")], check=True, capture_output=True, text=True).stdout.split()]
+
+    return values
+
+
+def test_only_tiles_that_share_a_compute_unit_are_paced(rules):
+    # moved as vectors, complex output, bf16, tiles per row, tiles
+    assert rules(["pace_ns(true, false, false, 5000, 5000)", "pace_ns(true, false, true, 5000, 5000)"]) == [12, 8]
+    assert rules([f"pace_ns({v}, {c}, {h}, {r}, {t})" for v, c in (("false", "false"), ("true", "true"), ("false", "true"))
+                  for h in ("false", "true") for r, t in ((3, 600), (5000, 5000), (16, 1024))]) == [0] * 18
+    assert rules(["pace_ns(true, false, false, 2, 5000)", "pace_ns(true, false, false, 100, 100)"]) == [0, 0]  # rows of two tiles; a launch that fits the chip
