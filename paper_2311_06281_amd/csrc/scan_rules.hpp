@@ -12,9 +12,11 @@ namespace hs {
 // at some times 39 of 512 tiles were loading, at others 488.  One after the other, a tile is waiting or writing while the
 // next ones load, from the first to the last.  Measured (none, 6, 9, 12, 15 ns): one row of 2^26 float32 154.1, 152.4,
 // 150.3, 149.0, 149.3 us; 700 rows of 40000 69.4, 68.1, 66.7, 66.4, 67.3; bf16, whose tiles are half the bytes, one row of
-// 4 * 10^7 81.4, 79.9, 79.5, 79.8, 81.3, 4 rows of 4 * 10^6 37.5, 36.6, 36.8, 39.0, 41.6.  A launch that fits the chip
-// has nothing behind its first tiles (4.2 * 10^6 steps 16.0, 16.0, 16.5, 17.3, 18.0); from one round on (8.5 * 10^6 steps)
-// it gains (32.1, 31.5, 31.3, 31.0, 31.5).  Of rows of two tiles only every other tile waits, and for one (3000 rows of
+// 4 * 10^7 81.4, 79.9, 79.5, 79.8, 81.3, 4 rows of 4 * 10^6 37.5, 36.6, 36.8, 39.0, 41.6.
+// That pays from the third round of tiles on.  A launch that fits the chip has nothing behind its first tiles (one row of
+// 2^23 steps, 512 tiles, 26.5 and with 12 ns 30.0 us), and with less than a second round behind them it comes out even or loses
+// (119 rows of 123464, 960 tiles, 42.5 and 43.6, bf16 33.5 and 36.7; 40 x 322896 without logarithms, bf16, 27.3 and 30.0;
+// one row of 1.25 * 10^7, 763 tiles, 41.5 and 38.8).  Of rows of two tiles only every other tile waits, and for one (3000 rows of
 // 17000 137.2, 12 ns 138.0).
 //
 // That is for the tiles of which the chip holds kPacedTiles at a time, two workgroups per compute unit: real output moved
@@ -30,7 +32,7 @@ constexpr uint32_t kPacedTilesPerRow = 3;
 constexpr bool paced_kernel(bool vectors, bool complex_out) { return vectors && !complex_out; }
 constexpr uint32_t pace_ns(bool vectors, bool complex_out, bool bf16, uint32_t tiles_per_row, uint32_t tiles)
 {
-    if (!paced_kernel(vectors, complex_out) || tiles_per_row < kPacedTilesPerRow || tiles < kPacedTiles) return 0;
+    if (!paced_kernel(vectors, complex_out) || tiles_per_row < kPacedTilesPerRow || tiles <= 2 * kPacedTiles) return 0;
     return bf16 ? kPaceNsBf16 : kPaceNs;
 }
 

@@ -68,3 +68,8 @@ def test_only_tiles_that_share_a_compute_unit_are_paced(rules):
     assert rules([f"pace_ns({v}, {c}, {h}, {r}, {t})" for v, c in (("false", "false"), ("true", "true"), ("false", "true"))
                   for h in ("false", "true") for r, t in ((3, 600), (5000, 5000), (16, 1024))]) == [0] * 18
     assert rules(["pace_ns(true, false, false, 2, 5000)", "pace_ns(true, false, false, 100, 100)"]) == [0, 0]  # rows of two tiles; a launch that fits the chip
+
+
+def test_launches_of_up_to_two_rounds_are_not_paced(rules):
+    for half, ns in (("false", 12), ("true", 8)):
+        assert rules([f"pace_ns(true, false, {half}, 16, {t})" for t in (511, 512, 513, 760, 960, 1024, 1025, 1600, 100000)]) == [0] * 6 + [ns] * 3
