@@ -25,6 +25,7 @@
 #include "heinsen_internal.hpp"
 #include "heinsen_math.hpp"
 #include "heinsen_tickets.hpp"
+#include "scan_rules.hpp"
 
 #include <algorithm>
 
@@ -783,12 +784,6 @@ __global__ __launch_bounds__(256) void heinsen_scan_steps(StepsParams p)
 
 // ---- host side ------------------------------------------------------------------------------------
 
-// Ticket queues: as many (up to one per compute die) as leave every queue this many columns.  The tiles
-// of a column start that many tickets apart, so a tile usually finds the tiles before it done; eight queues
-// also keep neighbouring columns on one die, which then reads the lines they share once (6 x 3001 x 770, 73
-// columns: 50.5 us with 16 per queue, 48 with 8).  The wide tiles, whose rows are requested by two waves at a time, want the queues longer still (measured).
-constexpr int kMinColsPerQueue = 8, kMinColsPerQueueWide = 128;
-
 struct BndPlan {
     int cg, T, NW, G, CH;
     bool ticketless;
@@ -959,15 +954,7 @@ BndPlan make_plan(const ScanCall &c, bool allow_wide = true, bool want_tree = fa
     pl.records = pl.off_state + (size_t)pl.ngroups * pl.ncols * 2 * pl.CH;
     pl.ticketless = pl.nchunks == 1 && c.n <= 64; // short single-tile columns: no records, no tickets
     // A queue's workgroups that find no tile behind their ticket (uneven deal) end at once.
-    // Wide tiles of items a power of two apart: the items lie on the same memory channels, and dies that share a queue ask for
-    // the same rows of several at about the same time.  A queue per die, each with its own items, is the better there
-    // as long as the dies stay together (16 x 4096 x 2048 288 and 272 us, 32 x 2048 x 1024 152 and 140, bf16 64 x 2048 x 1024
-    // 228 and 192, 8 x 4096 x 4096 277.6 and 278.6; but 32 x 8192 x 1024 541 and 616, and other distances, 28 x 2944 x 1792
-    // bf16 212 and 219).
-    const int64_t item = c.n * c.D;
-    const bool queue_per_die = pl.cg > 1 && (item & (item - 1)) == 0 && c.n <= 4096;
-    pl.nq = kQueues;
-    while (pl.nq > 1 && !queue_per_die && pl.ncols < pl.nq * (pl.cg > 1 ? kMinColsPerQueueWide : kMinColsPerQueue)) pl.nq /= 2;
+    pl.nq = ticket_queues(kQueues, pl.ncols, pl.cg > 1);
     // Eight queues of fewer than 16 columns are for lines that columns share and for short sequences.  Long ones
     // wait for their predecessors less in four (80 columns of 16384 steps: 169 and 174 us), and an uneven deal may be
     // what makes a launch that fits the chip take a second round on one die (100 columns of 1100 steps, bf16: 18.3 and

@@ -36,4 +36,19 @@ constexpr uint32_t pace_ns(bool vectors, bool complex_out, bool bf16, uint32_t t
     return bf16 ? kPaceNsBf16 : kPaceNs;
 }
 
+// [B, n, D].  Ticket queues: as many (up to one per compute die) as leave every queue this many columns.  The tiles
+// of a column start that many tickets apart, so a tile usually finds the tiles before it done; eight queues
+// also keep neighbouring columns on one die, which then reads the lines they share once (6 x 3001 x 770, 73
+// columns: 50.5 us with 16 per queue, 48 with 8).  The wide tiles, whose rows are requested by two waves at a time, want
+// the queues longer still.  (A queue per die where items lie a power of two apart gains and loses: 128 x 1024 x 512 168 and
+// 140 us, 16 x 4096 x 2048 283 and 268, but 64 x 4096 x 512 276 and 311, 64 x 4096 x 1024 627 and 705, 511 x 1024 x 128 147
+// and 172.)
+constexpr int kMinColsPerQueue = 8, kMinColsPerQueueWide = 128;
+constexpr int ticket_queues(int most, int64_t columns, bool wide)
+{
+    int queues = most;
+    while (queues > 1 && columns < queues * (wide ? kMinColsPerQueueWide : kMinColsPerQueue)) queues /= 2;
+    return queues;
+}
+
 } // namespace hs
