@@ -1017,11 +1017,7 @@ hipError_t launch_mode(const ScanCall &c, const BndPlan &pl, const LaunchCtx &ct
     // and 36.9; 962 x 3401 x 7, 275 MB, 78 and 67).
     const bool on_line = reinterpret_cast<uintptr_t>(c.out) % 128 == 0;
     const bool whole_lines = pl.runs ? (on_line && (c.B == 1 || c.n * c.D % 32 == 0)) || bytes <= ((int64_t)128 << 20) : on_line && c.D % 32 == 0;
-    // Between one tile and three per CU, most of the output is written while nothing is left to load, and tiles wait
-    // for states that would queue with it: 30 x 1152 x 128 (300 tiles) 17.3 us and 16.0, 3 x 576 x 3456 (486) 18.5 and 17.5,
-    // 2 x 2624 x 2048 (704) 29.2 and 28.8; 4 x 448 x 1152 (144) 9.2 and 10.4, 18 x 768 x 1792 (1512) 60.3 and 62.0.
-    const bool waits_for_stores = !pl.tree && !pl.runs && pl.ntiles > (uint32_t)kPlaces / 2 && pl.ntiles <= (uint32_t)kPlaces * 3 / 2;
-    const int mem = shares_lines && !pl.runs ? kShared : (large_out ? kStream : (whole_lines && !waits_for_stores ? kThrough : kKeepOut));
+    const int mem = shares_lines && !pl.runs ? kShared : (large_out ? kStream : (whole_lines && !waits_behind_stores(pl.NW, pl.nchunks, pl.ntiles, pl.tree, pl.runs) ? kThrough : kKeepOut));
     p.cols_per_b = pl.cols_per_b;
     p.pad = pl.runs ? (uint32_t)(pl.pitch_in | pl.pitch_out << 16) : (uint32_t)pl.pad;
     p.places = c.B * pl.pad;

@@ -51,4 +51,20 @@ constexpr int ticket_queues(int most, int64_t columns, bool wide)
     return queues;
 }
 
+// [B, n, D], output in whole lines.  It goes through the L2 at once unless the tiles wait for states that would queue with
+// it: tiles of eight waves with one carry level, between one and three per compute unit, where most of the output is
+// written while nothing is left to load.  Ordinary stores and through the L2 there: 15 x 1993 x 256 (480 tiles) 20.2 and
+// 22.6 us, 32 x 879 x 256 (512) 19.8 and 21.7, 43 x 1013 x 256 (688) 30.1 and 31.2 (long chains differ: 2 x 5593 x 512, 352
+// tiles, 22.5 and 21.2); below and above, 2 x 4075 x 512 (256) 15.6 and 14.2, 50 x 3972 x 64 (800) 35.5 and 34.8.
+// Sequences of one tile wait for nothing: in this range of tiles 270 x 209 x 64 bf16 17.6 and 16.2, 37 x 109 x 512 10.3 and 8.9,
+// 31 x 57 x 1024 7.1 and 5.7, 190 x 30 x 256 bf16 16.9 and 14.7, 18 x 227 x 1024 14.2 and 14.6.  (Over 700 sizes of up to 256
+// steps through the L2 takes 0.90 to 0.98 of the time in the mean, and 1.00, between 0.90 and 1.07, for 17 to 30 MB of
+// float32 output.)  Complex output, of whose tiles a compute unit holds one, is faster so as well: 8 x 1956 x 512 33.2 and
+// 30.5, 130 x 1013 x 64 39.7 and 36.3.  Narrow items as runs differ (266 x 704 x 27 bf16 15.2 and 12.8, 250 x 994 x 17 15.8 and
+// 14.9, 6000 x 238 x 5, whose runs cut lines, 20.8 and 25.0; 0.99 in the mean of 50 sizes).
+constexpr bool waits_behind_stores(int waves, int64_t chunks, int64_t tiles, bool two_levels, bool runs)
+{
+    return waves == 8 && chunks > 1 && !two_levels && !runs && tiles > 256 && tiles <= 768;
+}
+
 } // namespace hs

@@ -78,3 +78,10 @@ def test_launches_of_up_to_two_rounds_are_not_paced(rules):
 def test_ticket_queues_go_by_columns_alone(rules):
     assert rules([f"ticket_queues(8, {c}, true)" for c in (128, 255, 256, 511, 512, 1023, 1024, 4096)]) == [1, 1, 2, 2, 4, 4, 8, 8]
     assert rules([f"ticket_queues(8, {c}, false)" for c in (1, 15, 16, 31, 32, 63, 64, 1000)]) == [1, 1, 2, 2, 4, 4, 8, 8]
+
+
+def test_only_tiles_that_wait_keep_ordinary_stores(rules):
+    # waves of a tile, tiles of a sequence, tiles, second carry level, runs of narrow items
+    assert rules([f"waits_behind_stores(8, 4, {t}, false, false)" for t in (256, 257, 512, 768, 769)]) == [0, 1, 1, 1, 0]
+    assert rules([f"waits_behind_stores({w}, 1, 500, false, false)" for w in (1, 2, 4, 8)]) == [0] * 4  # one tile each
+    assert rules(["waits_behind_stores(16, 4, 500, false, false)", "waits_behind_stores(8, 4, 500, false, true)"]) == [0, 0]
