@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import threading
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libheinsen.so")
@@ -41,6 +42,7 @@ EXPORTS = ("heinsen_scan", "heinsen_scan_static", "heinsen_status_string", "hein
 
 _lib = None
 _call = None  # the scan entry points without ctypes (csrc/call.c), once the library is loaded
+_loading = threading.Lock()
 
 
 class HeinsenError(RuntimeError):
@@ -52,45 +54,52 @@ class HeinsenError(RuntimeError):
 def load() -> ctypes.CDLL:
     """Load the shared library built by paper_2311_06281_amd.build (raises if it is missing)."""
     global _lib, _call
-    if _lib is None:
-        if not os.path.exists(LIB_PATH):
-            raise ImportError(f"{LIB_PATH} not found: build it with `python -m paper_2311_06281_amd.build`")
-        try:
-            from . import _call as call
-        except ImportError as e:
-            raise ImportError(f"the call module of {LIB_PATH} is missing: build it with `python -m paper_2311_06281_amd.build`") from e
-        lib = ctypes.CDLL(LIB_PATH)
-        vp, i64, ci, u32 = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int, ctypes.c_uint32
-        lib.heinsen_scan.argtypes = [vp, vp, vp, vp, i64, i64, i64, ci, u32, vp]
-        lib.heinsen_scan.restype = ci
-        lib.heinsen_scan_static.argtypes = [vp, vp, vp, vp, i64, i64, i64, ci, u32, vp]
-        lib.heinsen_scan_static.restype = ci
-        lib.heinsen_status_string.argtypes = [ci]
-        lib.heinsen_status_string.restype = ctypes.c_char_p
-        lib.heinsen_last_hip_error.argtypes = []
-        lib.heinsen_last_hip_error.restype = ci
-        lib.heinsen_version.argtypes = []
-        lib.heinsen_version.restype = ci
-        lib.heinsen_release_scratch.argtypes = []
-        lib.heinsen_release_scratch.restype = ci
-        lib.heinsen_kernel_name.argtypes = [i64, i64, i64, ci, u32, ctypes.c_char_p, ci]
-        lib.heinsen_kernel_name.restype = ci
-        lib.heinsen_tile_shape.argtypes = [i64, i64, i64, ci, u32, ctypes.POINTER(ci), ctypes.POINTER(i64)]
-        lib.heinsen_tile_shape.restype = ci
-        lib.heinsen_check.argtypes = [vp]
-        lib.heinsen_check.restype = ci
-        lib.heinsen_set_timeline.argtypes = [vp, ctypes.c_uint64]
-        lib.heinsen_set_timeline.restype = ci
-        lib.heinsen_test_carry.argtypes = [u32, u32, u32, vp]
-        lib.heinsen_test_carry.restype = ci
-        lib.heinsen_stream_probe.argtypes = [vp, vp, vp, i64, i64, i64, ci, vp]
-        lib.heinsen_stream_probe.restype = ci
-        lib.heinsen_sequential.argtypes = [vp, vp, vp, vp, i64, vp]
-        lib.heinsen_sequential.restype = ci
-        call.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.heinsen_scan, lib.heinsen_scan_static)))
-        _call = call
-        _lib = lib
+    if _call is None:
+        with _loading:
+            if _call is None:
+                _lib, call = _open()
+                _call = call  # last: whoever finds it finds the library as well
     return _lib
+
+
+def _open():
+    """The library and the call module, bound to its entry points."""
+    if not os.path.exists(LIB_PATH):
+        raise ImportError(f"{LIB_PATH} not found: build it with `python -m paper_2311_06281_amd.build`")
+    try:
+        from . import _call as call
+    except ImportError as e:
+        raise ImportError(f"the call module of {LIB_PATH} cannot be imported ({e}): build it with `python -m paper_2311_06281_amd.build`") from e
+    lib = ctypes.CDLL(LIB_PATH)
+    vp, i64, ci, u32 = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int, ctypes.c_uint32
+    lib.heinsen_scan.argtypes = [vp, vp, vp, vp, i64, i64, i64, ci, u32, vp]
+    lib.heinsen_scan.restype = ci
+    lib.heinsen_scan_static.argtypes = [vp, vp, vp, vp, i64, i64, i64, ci, u32, vp]
+    lib.heinsen_scan_static.restype = ci
+    lib.heinsen_status_string.argtypes = [ci]
+    lib.heinsen_status_string.restype = ctypes.c_char_p
+    lib.heinsen_last_hip_error.argtypes = []
+    lib.heinsen_last_hip_error.restype = ci
+    lib.heinsen_version.argtypes = []
+    lib.heinsen_version.restype = ci
+    lib.heinsen_release_scratch.argtypes = []
+    lib.heinsen_release_scratch.restype = ci
+    lib.heinsen_kernel_name.argtypes = [i64, i64, i64, ci, u32, ctypes.c_char_p, ci]
+    lib.heinsen_kernel_name.restype = ci
+    lib.heinsen_tile_shape.argtypes = [i64, i64, i64, ci, u32, ctypes.POINTER(ci), ctypes.POINTER(i64)]
+    lib.heinsen_tile_shape.restype = ci
+    lib.heinsen_check.argtypes = [vp]
+    lib.heinsen_check.restype = ci
+    lib.heinsen_set_timeline.argtypes = [vp, ctypes.c_uint64]
+    lib.heinsen_set_timeline.restype = ci
+    lib.heinsen_test_carry.argtypes = [u32, u32, u32, vp]
+    lib.heinsen_test_carry.restype = ci
+    lib.heinsen_stream_probe.argtypes = [vp, vp, vp, i64, i64, i64, ci, vp]
+    lib.heinsen_stream_probe.restype = ci
+    lib.heinsen_sequential.argtypes = [vp, vp, vp, vp, i64, vp]
+    lib.heinsen_sequential.restype = ci
+    call.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.heinsen_scan, lib.heinsen_scan_static)))
+    return lib, call
 
 
 def _native():

@@ -2,6 +2,8 @@
 declares, and rejects bad arguments on the host before any GPU work."""
 import os
 import re
+import sys
+import threading
 
 import numpy as np
 import pytest
@@ -156,3 +158,34 @@ def test_arguments_of_no_kind(bad, error):
     for call in (hb.heinsen_scan, hb.heinsen_scan_static):
         with pytest.raises(error):
             call(bad, 16, 16, 16, 1, 1, 1, 0, 0)
+
+
+def test_a_call_while_another_thread_loads_the_library(monkeypatch):
+    """At every line of load() at which a part of it can be seen from outside, a second thread makes a call whose numbers
+    have to be converted."""
+    monkeypatch.setattr(hb, "_lib", None)
+    monkeypatch.setattr(hb, "_call", None)
+    results, threads = [], []
+
+    def call():
+        try:
+            results.append(hb.heinsen_scan_status(P, P, P, P, np.int64(1), 1, 0, 0, 0, 0))  # n = 0
+        except Exception as e:
+            results.append(e)
+
+    def trace(frame, event, arg):
+        if event == "line" and (hb._lib is None) != (hb._call is None):
+            threads.append(threading.Thread(target=call))
+            threads[-1].start()
+            threads[-1].join(0.2)
+        return trace if frame.f_code is hb.load.__code__ else None
+
+    old = sys.gettrace()
+    sys.settrace(trace)
+    try:
+        hb.load()
+    finally:
+        sys.settrace(old)
+    for t in threads:
+        t.join()
+    assert threads and results == [hb.HEINSEN_ERR_INVALID_ARG] * len(threads)
