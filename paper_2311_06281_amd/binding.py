@@ -63,13 +63,14 @@ def load() -> ctypes.CDLL:
 
 
 def _open():
-    """The library and the call module, bound to its entry points."""
+    """The library and the call module, bound to its entry points.  (Without the module, which only saves time, every call is
+    left to _convert_and_call.)"""
     if not os.path.exists(LIB_PATH):
         raise ImportError(f"{LIB_PATH} not found: build it with `python -m paper_2311_06281_amd.build`")
     try:
         from . import _call as call
-    except ImportError as e:
-        raise ImportError(f"the call module of {LIB_PATH} cannot be imported ({e}): build it with `python -m paper_2311_06281_amd.build`") from e
+    except ImportError:
+        call = _Converted
     lib = ctypes.CDLL(LIB_PATH)
     vp, i64, ci, u32 = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int, ctypes.c_uint32
     lib.heinsen_scan.argtypes = [vp, vp, vp, vp, i64, i64, i64, ci, u32, vp]
@@ -100,6 +101,20 @@ def _open():
     lib.heinsen_sequential.restype = ci
     call.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.heinsen_scan, lib.heinsen_scan_static)))
     return lib, call
+
+
+class _Converted:
+    """In the call module's place where it has not been built, or for another Python."""
+
+    @staticmethod
+    def bind(scan, scan_static):
+        pass
+
+    @staticmethod
+    def scan(*args):
+        return NotImplemented
+
+    scan_static = scan
 
 
 def _native():

@@ -8,7 +8,9 @@ import threading
 import numpy as np
 import pytest
 
+import paper_2311_06281_amd
 from paper_2311_06281_amd import binding as hb
+from paper_2311_06281_amd import build as hip_build
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HEADER = os.path.join(ROOT, "include", "heinsen.h")
@@ -189,3 +191,28 @@ def test_a_call_while_another_thread_loads_the_library(monkeypatch):
     for t in threads:
         t.join()
     assert threads and results == [hb.HEINSEN_ERR_INVALID_ARG] * len(threads)
+
+
+def test_calls_without_the_call_module(monkeypatch):
+    monkeypatch.setattr(hb, "_lib", None)
+    monkeypatch.setattr(hb, "_call", None)
+    monkeypatch.delattr(paper_2311_06281_amd, "_call", raising=False)
+    monkeypatch.setitem(sys.modules, "paper_2311_06281_amd._call", None)  # as if there were none
+    for at in (P, _Tensor(P)):
+        for call in (hb.heinsen_scan_status, hb.heinsen_scan_static_status):
+            assert call(at, at, at, at, 1, 1, 0, 0, 0, _Stream()) == hb.HEINSEN_ERR_INVALID_ARG
+            assert call(at, at, at, at, 1, 1, 8, 0, hb.HEINSEN_LOG_OUTPUT, 0) == hb.HEINSEN_ERR_UNSUPPORTED
+        for call in (hb.heinsen_scan, hb.heinsen_scan_static):
+            with pytest.raises(hb.HeinsenError):
+                call(at, at, at, at, 1, 1, 0, 0, 0)
+
+
+@pytest.mark.parametrize("compiler", [["/nowhere/cc"], ["false"]])
+def test_a_build_without_a_c_compiler_has_no_call_module(monkeypatch, tmp_path, capsys, compiler):
+    stale = tmp_path / "_call.so"
+    stale.write_bytes(b"of another build")
+    monkeypatch.setattr(hip_build, "CC", compiler, raising=False)
+    monkeypatch.setattr(hip_build, "CALL", str(stale))
+    monkeypatch.setattr(hip_build, "_older", lambda built, sources: built == str(stale), raising=False)
+    assert hip_build.build(force=False) == hip_build.LIB
+    assert not stale.exists() and "call.c" in capsys.readouterr().err
