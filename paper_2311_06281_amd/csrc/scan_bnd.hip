@@ -1017,7 +1017,8 @@ hipError_t launch_mode(const ScanCall &c, const BndPlan &pl, const LaunchCtx &ct
     // and 36.9; 962 x 3401 x 7, 275 MB, 78 and 67).
     const bool on_line = reinterpret_cast<uintptr_t>(c.out) % 128 == 0;
     const bool whole_lines = pl.runs ? (on_line && (c.B == 1 || c.n * c.D % 32 == 0)) || bytes <= ((int64_t)128 << 20) : on_line && c.D % 32 == 0;
-    const int mem = shares_lines && !pl.runs ? kShared : (large_out ? kStream : (whole_lines && !waits_behind_stores(pl.NW, pl.nchunks, pl.ntiles, pl.tree, pl.runs) ? kThrough : kKeepOut));
+    const bool through = whole_lines && !waits_behind_stores(pl.NW, pl.ncols, pl.nchunks, pl.tree, c.linear, pl.runs);
+    const int mem = shares_lines && !pl.runs ? kShared : (large_out ? kStream : (through ? kThrough : kKeepOut));
     p.cols_per_b = pl.cols_per_b;
     p.pad = pl.runs ? (uint32_t)(pl.pitch_in | pl.pitch_out << 16) : (uint32_t)pl.pad;
     p.places = c.B * pl.pad;

@@ -62,9 +62,15 @@ constexpr int ticket_queues(int most, int64_t columns, bool wide)
 // float32 output.)  Complex output, of whose tiles a compute unit holds one, is faster so as well: 8 x 1956 x 512 33.2 and
 // 30.5, 130 x 1013 x 64 39.7 and 36.3.  Narrow items as runs differ (266 x 704 x 27 bf16 15.2 and 12.8, 250 x 994 x 17 15.8 and
 // 14.9, 6000 x 238 x 5, whose runs cut lines, 20.8 and 25.0; 0.99 in the mean of 50 sizes).
-constexpr bool waits_behind_stores(int waves, int64_t chunks, int64_t tiles, bool two_levels, bool runs)
+// With two carry levels states come from farther back and seldom queue: 1 x 10625 x 384 (252 tiles) 17.0 and 15.8, 1 x 8677 x 704
+// (374) 22.2 and 21.3, bf16 1 x 8160 x 832 (416) 20.0 and 18.4, without logarithms up to seven columns 1 x 25584 x 192 (300) 19.6
+// and 18.5.  From eight columns on tiles without logarithms, which take the least time over their steps, do lose up to one
+// round of the chip (2 x 9437 x 256, 296 tiles, 19.3 and 20.6, 2 x 12276 x 320, 480, 23.8 and 25.1, 1 x 11391 x 768, 540, 31.9 and 31.5).
+constexpr bool waits_behind_stores(int waves, int64_t columns, int64_t chunks, bool two_levels, bool linear, bool runs)
 {
-    return waves == 8 && chunks > 1 && !two_levels && !runs && tiles > 256 && tiles <= 768;
+    const int64_t tiles = columns * chunks;
+    if (waves != 8 || chunks == 1 || runs || tiles <= 256) return false;
+    return two_levels ? linear && columns >= 8 && tiles <= 512 : tiles <= 768;
 }
 
 } // namespace hs

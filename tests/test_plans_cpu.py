@@ -81,7 +81,12 @@ def test_ticket_queues_go_by_columns_alone(rules):
 
 
 def test_only_tiles_that_wait_keep_ordinary_stores(rules):
-    # waves of a tile, tiles of a sequence, tiles, second carry level, runs of narrow items
-    assert rules([f"waits_behind_stores(8, 4, {t}, false, false)" for t in (256, 257, 512, 768, 769)]) == [0, 1, 1, 1, 0]
-    assert rules([f"waits_behind_stores({w}, 1, 500, false, false)" for w in (1, 2, 4, 8)]) == [0] * 4  # one tile each
-    assert rules(["waits_behind_stores(16, 4, 500, false, false)", "waits_behind_stores(8, 4, 500, false, true)"]) == [0, 0]
+    # waves of a tile, columns, tiles of a column, second carry level, without logarithms, runs of narrow items
+    assert rules([f"waits_behind_stores(8, {c}, {k}, false, false, false)" for c, k in ((64, 4), (257, 1), (129, 2), (128, 4), (96, 8), (769, 1), (385, 2))]) == [0, 0, 1, 1, 1, 0, 0]
+    assert rules([f"waits_behind_stores({w}, 500, 1, false, false, false)" for w in (1, 2, 4, 8)]) == [0] * 4  # one tile each
+    assert rules(["waits_behind_stores(16, 125, 4, false, false, false)", "waits_behind_stores(8, 125, 4, false, false, true)"]) == [0, 0]
+
+
+def test_two_carry_levels_keep_ordinary_stores_only_without_logarithms(rules):
+    assert rules([f"waits_behind_stores(8, {c}, {k}, true, false, false)" for c, k in ((8, 40), (15, 30), (3, 100), (12, 37))]) == [0] * 4
+    assert rules([f"waits_behind_stores(8, {c}, {k}, true, true, false)" for c, k in ((7, 60), (8, 32), (8, 33), (12, 37), (8, 64), (9, 57), (14, 60))]) == [0, 0, 1, 1, 1, 0, 0]
