@@ -119,13 +119,18 @@ def test_a_tile_that_never_publishes_ends_in_nan_with_two_carry_levels(gpu):
 
 
 # Calls large enough to go through the L2 (rows that do not keep to 128-byte lines) or past the caches with columns
-# across items: one batch item against the oracle, the others bit for bit the same (a channel's arithmetic does not depend
+# across items or narrow items as runs: one batch item against the oracle, the others bit for bit the same (a channel's arithmetic does not depend
 # on where it lies).  More than 192 MiB of output; bf16 288 MiB, narrow items 192 MiB of input and output.
 @pytest.mark.parametrize("mode,bf16,shape", [
     ("signed", False, (8, 5000, 1501)), ("log_logout", False, (12, 6000, 770)), ("signed", True, (16, 8192, 301)),
     ("log", True, (16, 8192, 301)), ("signed_clog", False, (20, 4500, 301)), ("signed_clog", True, (32, 4500, 200)),
     ("positive", False, (130, 6300, 65)), ("signed", False, (256, 4096, 19)), ("signed", True, (300, 4100, 30)),
     ("signed", False, (260, 2048, 96)), ("linear", False, (8, 5000, 1501)),
+    # narrow items as runs: past the caches, on lines and not, whole runs and halves (two carry levels), and with ordinary stores
+    ("signed", False, (700, 4099, 19)), ("log_logout", True, (700, 4099, 19)), ("linear", False, (512, 6400, 16)),
+    ("signed", False, (2, 2000003, 13)), ("signed", True, (2, 2000003, 13)), ("signed", False, (544, 1294, 19)),
+    # wide tiles whose items lie a power of two apart
+    ("signed", False, (16, 1024, 2048)), ("signed", True, (16, 2048, 2048)),
 ])
 def test_large_calls_item_by_item(gpu, mode, bf16, shape):
     torch, hb = gpu
