@@ -83,6 +83,11 @@ __device__ __forceinline__ float load_elem(const InT *p)
     return MEM == kShared ? widen(*p) : widen(__builtin_nontemporal_load(p));
 }
 template <int MEM>
+__device__ __forceinline__ uint32_t load_bits(const uint16_t *p)
+{
+    return MEM == kShared ? *p : __builtin_nontemporal_load(p);
+}
+template <int MEM>
 __device__ __forceinline__ void store_elem(float *p, float v)
 {
     if (MEM == kStream)
@@ -376,6 +381,25 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
             Mv[k] = load_elem<MEM, InT>(brow + moff);
             arow += p.D;
             brow += p.D;
+        }
+    } else if constexpr (sizeof(InT) == 2) {
+        // As stored until all are asked for: widened inside the branches, every step would be waited for before the next
+        // one is asked for.
+        uint32_t ra[T], rb[T]; // (1, 0 and -inf are exact in bf16)
+#pragma unroll
+        for (int k = 0; k < T; ++k) {
+            ra[k] = f2u(id_a) >> 16;
+            rb[k] = f2u(id_b) >> 16;
+            if (chan_ok && t0 + k < p.n) {
+                ra[k] = load_bits<MEM>(ap + (int64_t)k * p.D + moff);
+                rb[k] = load_bits<MEM>(bp + (int64_t)k * p.D + moff);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < T; ++k) {
+            asm("" : "+v"(ra[k]), "+v"(rb[k])); // keeps the shift out of the branches
+            Av[k] = u2f(ra[k] << 16);
+            Mv[k] = u2f(rb[k] << 16);
         }
     } else {
 #pragma unroll

@@ -62,6 +62,19 @@ def test_runs_of_narrow_items(gpu, mode, bf16, shape):
         cross._check(got, a, b, x0, "BND", mode)
 
 
+# The last steps of a sequence, fewer than a wave takes, are loaded one by one and in bf16 widened afterwards: every number of
+# them, in narrow items and wide rows, a wave each and several, identity elements of numbers (1, 0) and of logarithms (0, -inf).
+@pytest.mark.parametrize("mode", ["signed", "log_logout", "linear"])
+def test_last_steps_of_every_length_in_bf16(gpu, mode):
+    rng = np.random.default_rng(7)
+    for last in range(1, 32):
+        for shape in [(3, 128 + 32 * (last % 4) + last, 7), (2, 8 + last, 96), (2, 64 + last, 40), (1, 256 * (last % 3) + last + 160, 130)]:
+            a, b, x0 = cross._inputs(rng, shape, "BND", mode)
+            a, b = (workloads.bf16_bits_to_f32(workloads.f32_to_bf16_bits(v)).reshape(v.shape) for v in (a, b))
+            print(f"[last steps] {mode} shape={shape}", flush=True)
+            cross._check(cross._run(gpu, a, b, x0, "BND", cross.MODES[mode], True), a, b, x0, "BND", mode)
+
+
 # Output that a wave writes in whole lines goes through the L2 at once: rows of a multiple of 32 channels from an address
 # that is one of 128 bytes (offsets 0 and 32; offset 1: any other), one wave to eight per tile, one tile and several,
 # columns across items, wide tiles, single values and pairs.
