@@ -146,7 +146,7 @@ typedef u32x4 u32x4_at2 __attribute__((aligned(2)));
 typedef u32x4 u32x4_at4 __attribute__((aligned(4)));
 __device__ __forceinline__ u32x4 load_run(const float *p) { return __builtin_nontemporal_load(reinterpret_cast<const u32x4_at4 *>(p)); }
 __device__ __forceinline__ u32x4 load_run(const uint16_t *p) { return __builtin_nontemporal_load(reinterpret_cast<const u32x4_at2 *>(p)); }
-// Vector at byte `at` of the wave's output; kThrough is for outputs of up to kLastLevelCacheBytes.  (An atomic store,
+// Vector that begins at element `at` of the wave's output; kThrough is for outputs of up to kLastLevelCacheBytes.  (An atomic store,
 // which is how single words are written through, has 64 bits at most.)
 template <int MEM>
 __device__ __forceinline__ void store_run(float *out, uint32_t at, u32x4 v)
@@ -814,7 +814,7 @@ struct BndPlan {
     bool dense;          // columns of adjacent channels of all B * D (see bnd_tile),
     int lanes;           // this many
     int pad;             // lanes an item takes: D, or the power of two at or above it
-    bool runs;           // whole runs of memory (D <= 32, see bnd_tile)
+    bool runs;           // whole runs of memory (D < 32, see bnd_tile)
     int pitch_in, pitch_out;
     int cols_per_b, ncols, nchunks, ngroups;
     uint32_t ntiles;
@@ -1035,12 +1035,9 @@ hipError_t launch_mode(const ScanCall &c, const BndPlan &pl, const LaunchCtx &ct
     // instead of 79.1, 32 x 1024 x 1024 76.1 and 80.2, 16 x 1024 x 256 12.0 and 13.9, runs (256 x 4096 x 16) 45.3 and 47.9,
     // and a kernel that reads the output next is no slower (out = a + b in these pieces and a pass over out, 8 x 4096
     // x 1024: 96 us, 99.6 with ordinary stores, 102 past the caches).  Lines that columns share do (6 x 3001 x 770: 48.7
-    // and 45.4, 9 x 20000 x 48 39.1 and 38.4).  The runs of 32 steps are whole lines where items begin on lines; where not,
-    // the lines at their ends are parts, which is as well as long as everything fits half the memory-side cache (300 x 3000 x
-    // 7, 76 MB, 21.3 and 23.0; 81 x 8716 x 18 bf16, 102 MB, 35.7 and 36.7), but not beyond (544 x 1294 x 19, 161 MB, 38.4
-    // and 36.9; 962 x 3401 x 7, 275 MB, 78 and 67).
+    // and 45.4, 9 x 20000 x 48 39.1 and 38.4).  (Runs: see runs_in_lines.)
     const bool on_line = reinterpret_cast<uintptr_t>(c.out) % 128 == 0;
-    const bool whole_lines = pl.runs ? (on_line && (c.B == 1 || c.n * c.D % 32 == 0)) || bytes <= ((int64_t)128 << 20) : on_line && c.D % 32 == 0;
+    const bool whole_lines = pl.runs ? runs_in_lines(on_line, c.B, c.n * c.D, bytes) : on_line && c.D % 32 == 0;
     const bool through = whole_lines && !waits_behind_stores(pl.NW, pl.ncols, pl.nchunks, pl.tree, c.linear, pl.runs);
     const int mem = shares_lines && !pl.runs ? kShared : (large_out ? kStream : (through ? kThrough : kKeepOut));
     p.cols_per_b = pl.cols_per_b;

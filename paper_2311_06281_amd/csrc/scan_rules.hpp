@@ -56,21 +56,31 @@ constexpr int ticket_queues(int most, int64_t columns, bool wide)
 // written while nothing is left to load.  Ordinary stores and through the L2 there: 15 x 1993 x 256 (480 tiles) 20.2 and
 // 22.6 us, 32 x 879 x 256 (512) 19.8 and 21.7, 43 x 1013 x 256 (688) 30.1 and 31.2 (long chains differ: 2 x 5593 x 512, 352
 // tiles, 22.5 and 21.2); below and above, 2 x 4075 x 512 (256) 15.6 and 14.2, 50 x 3972 x 64 (800) 35.5 and 34.8.
-// Sequences of one tile wait for nothing: in this range of tiles 270 x 209 x 64 bf16 17.6 and 16.2, 37 x 109 x 512 10.3 and 8.9,
-// 31 x 57 x 1024 7.1 and 5.7, 190 x 30 x 256 bf16 16.9 and 14.7, 18 x 227 x 1024 14.2 and 14.6.  (Over 700 sizes of up to 256
+// Sequences of one tile wait for nothing: in this range of tiles 37 x 109 x 512 10.3 and 8.9, 31 x 57 x 1024 7.1 and 5.7,
+// 150 x 32 x 256 5.25 and 4.76, 360 x 160 x 64 11.2 and 11.1, 18 x 227 x 1024 14.2 and 14.6.  (Over 700 sizes of up to 256
 // steps through the L2 takes 0.90 to 0.98 of the time in the mean, and 1.00, between 0.90 and 1.07, for 17 to 30 MB of
 // float32 output.)  Complex output, of whose tiles a compute unit holds one, is faster so as well: 8 x 1956 x 512 33.2 and
-// 30.5, 130 x 1013 x 64 39.7 and 36.3.  Narrow items as runs differ (266 x 704 x 27 bf16 15.2 and 12.8, 250 x 994 x 17 15.8 and
-// 14.9, 6000 x 238 x 5, whose runs cut lines, 20.8 and 25.0; 0.99 in the mean of 50 sizes).
-// With two carry levels states come from farther back and seldom queue: 1 x 10625 x 384 (252 tiles) 17.0 and 15.8, 1 x 8677 x 704
-// (374) 22.2 and 21.3, bf16 1 x 8160 x 832 (416) 20.0 and 18.4, without logarithms up to seven columns 1 x 25584 x 192 (300) 19.6
-// and 18.5.  From eight columns on tiles without logarithms, which take the least time over their steps, do lose up to one
-// round of the chip (2 x 9437 x 256, 296 tiles, 19.3 and 20.6, 2 x 12276 x 320, 480, 23.8 and 25.1, 1 x 11391 x 768, 540, 31.9 and 31.5).
+// 30.5, 130 x 1013 x 64 39.7 and 36.3.  Narrow items as runs: see runs_in_lines.
+// With two carry levels states come from farther back and seldom queue: 1 x 10625 x 384 (252 tiles) 17.0 and 15.8, 1 x 8677 x
+// 704 (374) 22.2 and 21.3, bf16 1 x 8160 x 832 (416) 20.0 and 18.4, without logarithms up to seven columns 1 x 25584 x 192 (300)
+// 19.6 and 18.5.  From eight columns on tiles without logarithms, which take the least time over their steps, do lose up
+// to one round of the chip (2 x 9437 x 256, 296 tiles, 19.3 and 20.6, 2 x 12276 x 320, 480, 23.8 and 25.1; 1 x 11391 x 768, 540
+// tiles, 31.9 and 31.5).
 constexpr bool waits_behind_stores(int waves, int64_t columns, int64_t chunks, bool two_levels, bool linear, bool runs)
 {
     const int64_t tiles = columns * chunks;
     if (waves != 8 || chunks == 1 || runs || tiles <= 256) return false;
     return two_levels ? linear && columns >= 8 && tiles <= 512 : tiles <= 768;
+}
+
+// Narrow items as runs: 32 steps are whole lines where items begin on lines, and then go through the L2 at once (0.90 to 0.97
+// of the time with ordinary stores).  Where not, the lines at their ends are parts; that pays as long as inputs and output are
+// small: over 190 such sizes 0.92 to 0.98 of the time in the mean up to 96 MB, 1.01 up to 128, 1.04 up to 200 (ordinary stores and
+// through the L2: 250 x 994 x 17, 49 MB, 15.8 and 14.9 us; 300 x 3000 x 7, 76 MB, 23.0 and 21.3; 1525 x 253 x 25, 116 MB, 30.0 and
+// 31.4; 544 x 1294 x 19, 161 MB, 36.9 and 38.4; the other way 1360 x 1012 x 5, 83 MB, 20.9 and 25.1).
+constexpr bool runs_in_lines(bool out_on_line, int64_t items, int64_t item_elements, int64_t bytes)
+{
+    return (out_on_line && (items == 1 || item_elements % 32 == 0)) || bytes <= ((int64_t)96 << 20);
 }
 
 } // namespace hs

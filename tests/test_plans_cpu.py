@@ -90,3 +90,9 @@ def test_only_tiles_that_wait_keep_ordinary_stores(rules):
 def test_two_carry_levels_keep_ordinary_stores_only_without_logarithms(rules):
     assert rules([f"waits_behind_stores(8, {c}, {k}, true, false, false)" for c, k in ((8, 40), (15, 30), (3, 100), (12, 37))]) == [0] * 4
     assert rules([f"waits_behind_stores(8, {c}, {k}, true, true, false)" for c, k in ((7, 60), (8, 32), (8, 33), (12, 37), (8, 64), (9, 57), (14, 60))]) == [0, 0, 1, 1, 1, 0, 0]
+
+
+def test_runs_that_cut_lines_are_written_through_up_to_96_mb(rules):
+    mb = 1 << 20
+    assert rules([f"runs_in_lines(true, 250, 994 * 17, {m * mb})" for m in (49, 96, 97, 120)]) == [1, 1, 0, 0]
+    assert rules([f"runs_in_lines({o}, {b}, {e}, {200 * mb})" for o, b, e in (("true", 9, 4096 * 16), ("true", 1, 4097 * 13), ("false", 9, 4096 * 16), ("false", 1, 4096))]) == [1, 1, 0, 0]
