@@ -15,8 +15,11 @@ namespace hs {
 // 4 * 10^7 81.4, 79.9, 79.5, 79.8, 81.3, 4 rows of 4 * 10^6 37.5, 36.6, 36.8, 39.0, 41.6.
 // That pays from the third round of tiles on.  A launch that fits the chip has nothing behind its first tiles (one row of
 // 2^23 steps, 512 tiles, 26.5 and with 12 ns 30.0 us), and with less than a second round behind them it comes out even or loses
-// (119 rows of 123464, 960 tiles, 42.5 and 43.6, bf16 33.5 and 36.7; 40 x 322896 without logarithms, bf16, 27.3 and 30.0;
-// one row of 1.25 * 10^7, 763 tiles, 41.5 and 38.8).  Of rows of two tiles only every other tile waits, and for one (3000 rows of
+// (119 rows of 123464, 960 tiles, 42.5 and 43.6, bf16 33.5 and 36.7; 40 x 322896 without logarithms, bf16, 27.3 and 30.0),
+// but for float32 in rows so long that nearly all tiles in flight wait for one another, from a few tiles more than a round up to
+// 1.6 rounds (one row of 9 * 10^6 35.6 and 33.4, of 1.25 * 10^7 41.5 and 38.8, 9 rows of 1.31 * 10^6 0.96 of the time; without
+// logarithms one row 0.95 to 0.99 of the time, several 0.97 to 1.03; one row of 8.40 * 10^6, 513 tiles, 1.03 to 1.08, one of
+// 1.5 * 10^7, 1.8 rounds, 0.97 to 1.04).  Of rows of two tiles only every other tile waits, and for one (3000 rows of
 // 17000 137.2, 12 ns 138.0).
 //
 // That is for the tiles of which the chip holds kPacedTiles at a time, two workgroups per compute unit: real output moved
@@ -26,13 +29,15 @@ namespace hs {
 // and 108.9, one row of 1.25 * 10^7 such steps 43.3 and 47.9; complex output, 200 x 40000, 46.2 and 50.5.
 constexpr uint32_t kPaceNs = 12, kPaceNsBf16 = 8;
 constexpr uint32_t kPacedTiles = 512;
-constexpr uint32_t kPacedTilesPerRow = 3;
+constexpr uint32_t kPacedTilesPerRow = 3, kPacedTilesPerLongRow = 64;
 
 // Whether the tiles kernel for such data may be paced, and the spacing for a launch (0: none).
 constexpr bool paced_kernel(bool vectors, bool complex_out) { return vectors && !complex_out; }
 constexpr uint32_t pace_ns(bool vectors, bool complex_out, bool bf16, uint32_t tiles_per_row, uint32_t tiles)
 {
-    if (!paced_kernel(vectors, complex_out) || tiles_per_row < kPacedTilesPerRow || tiles <= 2 * kPacedTiles) return 0;
+    const bool many = tiles_per_row >= kPacedTilesPerRow && tiles > 2 * kPacedTiles;
+    const bool long_rows = !bf16 && tiles_per_row >= kPacedTilesPerLongRow && tiles >= kPacedTiles + 8 && tiles <= kPacedTiles * 8 / 5;
+    if (!paced_kernel(vectors, complex_out) || !(many || long_rows)) return 0;
     return bf16 ? kPaceNsBf16 : kPaceNs;
 }
 

@@ -95,8 +95,8 @@ def test_lost_carry_ends_in_nan_and_a_report(gpu, cfg, drop, bad_from_tile):
     assert np.array_equal(again.view(np.uint32), want.view(np.uint32))
 
 
-# the first tiles of a launch of more than two rounds start one after the other: one tile fewer than that, one more, many, in
-# one row and in rows of the fewest tiles that are paced; float32 and bf16 storage; launches of one round
+# the first tiles of a launch of more than two rounds start one after the other: as many tiles, one more, many, in one row and
+# in rows of the fewest tiles that are paced; float32 and bf16 storage; launches of one round and little more
 @pytest.mark.parametrize("cfg", [
     workloads.CONFIGS[3].scaled(n=16384 * 1023 + 5), workloads.CONFIGS[3].scaled(n=16384 * 1024 + 5), workloads.CONFIGS[3].scaled(n=16384 * 1300),
     workloads.CONFIGS[4].scaled(B=2, D=200, n=16384 * 2 + 9), workloads.CONFIGS[4].scaled(B=1, D=17, n=16384 * 63 + 1),
