@@ -137,9 +137,12 @@ __device__ __forceinline__ void lds_await(volatile uint32_t *flag)
 // as many such runs.  Taken step by step a wave's accesses are pieces of D elements, and the pieces are what bounds it:
 // out = a + b in them reaches 3.9 TB/s for 256 x 4096 x 19 and 1.4 for 900 x 4096 x 3.  Here they are the runs' 16-byte
 // vectors, consecutive lanes consecutive vectors, which every wave deals out to its lanes through LDS of its own; what is
-// left is the wait for predecessors and, below two rounds of tiles, ramp and drain.  Before and after: 256 x 4096 x 16
-// 51 and 48 us, x 19 67 and 56, 512 x 4096 x 8 71 and 49, 900 x 4096 x 3 116 and 35, 64 x 16384 x 5 47 and 25, bf16
-// 719 x 3461 x 9 107 and 49, 256 x 4096 x 16 46 and 36.  A run begins wherever its item does: the vectors are aligned
+// left is the wait for predecessors and, below two rounds of tiles, ramp and drain.  Before and now, the stores of
+// runs_in_lines included (five sets of buffers in turn): 256 x 4096 x 16 50.9 and 45.5 us, x 19 67.2 and 55.6, 512 x 4096 x 8
+// 71.2 and 46.4, 900 x 4096 x 3 115.6 and 33.1, 64 x 16384 x 5 47.3 and 24.4, bf16 719 x 3461 x 9 107.0 and 49.2, 256 x 4096 x 16
+// 45.1 and 34.0; with more than 192 MB of output 700 x 4099 x 19 166 and 148, 3000 x 4096 x 5 252 and 153.  The last steps of a
+// sequence, fewer than a wave takes, still go one by one; where they are most of a short one's time it may be 3 % slower
+// (8 x 156 x 10 without logarithms 6.4 and 6.6).  A run begins wherever its item does: the vectors are aligned
 // as elements are, which global accesses of four words may be.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef u32x4 u32x4_at2 __attribute__((aligned(2)));
@@ -162,7 +165,9 @@ __device__ __forceinline__ void store_run(float *out, uint32_t at, u32x4 v)
 
 // Slots of 16 bytes per wave: an item's run is T * D / 4 of them in float32, and up to 15 between items keep the lanes,
 // which pick up step k of their channels all at once, on different banks (run_pitch).  TREE, which needs much of the
-// LDS itself, and groups of eight tiles, whose records leave fewer registers, deal the runs out in two halves.
+// LDS itself, and groups of eight tiles, whose records leave fewer registers, deal the runs out in two halves.  (Registers
+// are short there all the same: the kernels of groups of eight keep up to 15 of float32 and 6 of bf16 in scratch, with two
+// carry levels 4 and 2.  Pieces and runs: 20 x 4000 x 31 18.1 and 16.3 us, 24 x 3000 x 20 16.1 and 15.0, 2 x 1500000 x 30 382 and 354.)
 constexpr int run_rounds(int G) { return G > 4 ? 2 : 1; }
 constexpr int run_slots(int rounds) { return 544 / rounds; }
 
@@ -384,7 +389,8 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
         }
     } else if constexpr (sizeof(InT) == 2) {
         // As stored until all are asked for: widened inside the branches, every step would be waited for before the next
-        // one is asked for.
+        // one is asked for, which is what bounds short and ragged calls (25 x 285 x 320 17.8 us so, 8.8 now; 52 x 183 x 13 10.6
+        // and 7.7; 36 x 702 x 1184, logarithms, 78.5 and 57.7).
         uint32_t ra[T], rb[T]; // (1, 0 and -inf are exact in bf16)
 #pragma unroll
         for (int k = 0; k < T; ++k) {
