@@ -1,4 +1,5 @@
-"""ctypes binding of libheinsen: same names as include/heinsen.h, argument marshalling only.
+"""Python binding of libheinsen: same names as include/heinsen.h, argument marshalling only (the scan entry points through
+csrc/call.c, the rest through ctypes).
 
 Every step of the computation runs in the HIP kernels of the shared library; nothing here (or
 anywhere in this package) falls back to the CPU.  If the library has not been built, importing the
