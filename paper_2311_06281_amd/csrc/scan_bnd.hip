@@ -120,14 +120,17 @@ __device__ __forceinline__ void unpack_signs(uint32_t s, Seg &g)
 // Hand-over between the waves of a workgroup through LDS without a barrier: the producer writes its data,
 // then the flag; the consumer polls the flag, then reads the data.  LDS operations of one wave are carried
 // out in order, so only the compiler has to be kept from moving them.
-__device__ __forceinline__ void lds_signal(volatile uint32_t *flag)
+// (The flags are pointed to as what they are, words of LDS: through generic pointers they became flat accesses, each of which waits
+// for all that the wave has in flight, its record and output stores included.  4 x 500 x 100 10.3 us so, 9.4 now.)
+typedef __attribute__((address_space(3))) volatile uint32_t lds_flag_t;
+__device__ __forceinline__ void lds_signal(lds_flag_t *flag)
 {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     *flag = 1u;
 }
-__device__ __forceinline__ void lds_await(volatile uint32_t *flag)
+__device__ __forceinline__ void lds_await(lds_flag_t *flag)
 {
-    while (*flag == 0u) __builtin_amdgcn_s_sleep(1);
+    while (__builtin_amdgcn_readfirstlane((int)*flag) == 0) __builtin_amdgcn_s_sleep(1);
     asm volatile("" ::: "memory");
 }
 
@@ -205,11 +208,16 @@ __device__ __forceinline__ void wave_lds_order()
 // along time publishes the tile's summary (and, closing a group, the state for the next group).  `flags`
 // are TS*CG + CG words of LDS (TREE: 2*TS more), zero when the tile begins.
 template <int DOM, bool LOG_IN, bool LOG_OUT, typename InT, int T, int NW, int G, bool SB, bool DENSE, bool TREE, bool RUNS, int CG, int MEM>
-__device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile, const uint32_t epoch, volatile uint32_t *flags)
+__device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile, const uint32_t epoch, lds_flag_t *flags)
 {
     constexpr bool SIGNED = DOM == kSigned;
     constexpr int CH = 64 * CG;  // channels of the tile
     constexpr int TS = NW / CG;  // waves one after the other along time
+    // Whether the scan stands behind each way to load.  One scan behind them all is one where the compiler, which cannot tell there
+    // what is still on its way, has the first step wait for the last input (6 x 3072 x 768 36.9 and 36.1 us, 4 x 1000 x 1000 14.0
+    // and 13.2).  Not for bf16 (8 x 8192 x 1536 151.0 and 152.1), whose loads are half as long, where lines are shared (8 x 8000 x
+    // 1501, logarithms, 252.5 and 254.5), for the wide tiles (16 x 16384 x 2048 1039 and 1042) and where registers are short.
+    constexpr bool EARLY = sizeof(InT) == 4 && !RUNS && !TREE && CG == 1 && G <= 4 && MEM != kShared;
     constexpr int PT = TREE ? 1 : (G > 1 ? G - 1 : 1); // tile summaries a wave fetches
     static_assert(T <= 32, "one sign word per channel");
     static_assert(NW % CG == 0, "the waves form a CG x TS grid");
@@ -237,9 +245,9 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     // The rows the workgroup reads and writes are runs of 256*CG contiguous bytes, requested by its CG
     // columns at about the same time, which is what the memory system wants to see.
     const int wc = w % CG, ts = w / CG;
-    volatile uint32_t *flag_run = flags;              // [TS][CG]: the wave's summary is in LDS
-    volatile uint32_t *flag_start = flags + TS * CG;  // [CG]: the column's start state is in LDS
-    volatile uint32_t *flag_part = flags + TS * CG + CG; // TREE: [2][TS]: the wave's summaries are in LDS
+    lds_flag_t *flag_run = flags;              // [TS][CG]: the wave's summary is in LDS
+    lds_flag_t *flag_start = flags + TS * CG;  // [CG]: the column's start state is in LDS
+    lds_flag_t *flag_part = flags + TS * CG + CG; // TREE: [2][TS]: the wave's summaries are in LDS
 
     const int chunk = (int)(tile / (uint32_t)p.ncols);
     const int col = (int)(tile % (uint32_t)p.ncols);
@@ -330,8 +338,19 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     bool have_records = false;
     if (fetches) issue_records();
 
-    // ---- load: the lane's T inputs ---------------------------------------------------------------
+    // ---- load the lane's T inputs, encode and scan them serially; Av/Mv become the per-element records (see stash).  Every way
+    //      to load has the scan behind it: with one scan behind them all the compiler, which cannot tell there what is still on
+    //      its way, would have the first step wait for the last input -----------------------------------------------
     float Av[T], Mv[T];
+    uint32_t sw = 0u, sm = 0u;
+    Seg run;
+    auto scan = [&]() {
+#pragma unroll
+        for (int k = 0; k < T; ++k) {
+            lane_step<DOM, LOG_IN, LOG_OUT>(k, run, Av[k], Mv[k], sw, sm);
+            if (SB) __builtin_amdgcn_sched_barrier(0);
+        }
+    };
     const float id_a = LOG_IN ? 0.0f : 1.0f; // a = 1, b = 0 leave the state unchanged
     const float id_b = LOG_IN ? -INFINITY : 0.0f;
     // RUNS: the part of the wave's LDS region that its lane reads and writes (elements from one step to the next: D)
@@ -378,15 +397,17 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
         deal(ta, Av);
         if (ROUNDS > 1) ask(bp, tb);
         deal(tb, Mv);
-    } else if (chan_ok && t0 + T <= p.n) {
-        const InT *arow = ap, *brow = bp; // wave-uniform row pointers
+    } else if ((EARLY || chan_ok) && t0 + T <= p.n) {
+        const InT *arow = ap, *brow = bp; // likewise: row pointers
+        const uint32_t off = !EARLY || chan_ok ? moff : 0u; // lanes without a channel take the first one's
 #pragma unroll
         for (int k = 0; k < T; ++k) {
-            Av[k] = load_elem<MEM, InT>(arow + moff);
-            Mv[k] = load_elem<MEM, InT>(brow + moff);
+            Av[k] = load_elem<MEM, InT>(arow + off);
+            Mv[k] = load_elem<MEM, InT>(brow + off);
             arow += p.D;
             brow += p.D;
         }
+        if (EARLY) scan();
     } else if constexpr (sizeof(InT) == 2) {
         // As stored until all are asked for: widened inside the branches, every step would be waited for before the next
         // one is asked for, which is what bounds short and ragged calls (25 x 285 x 320 17.8 us so, 8.8 now; 52 x 183 x 13 10.6
@@ -418,18 +439,14 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
                 Mv[k] = id_b;
             }
         }
-    }
-
-    if (!TREE && first) have_records = wave_all(records_in()); // first look: answered while the tile's loads were in flight
-
-    // ---- encode + serial scan in each lane; Av/Mv become the per-element records (see stash) --------
-    uint32_t sw = 0u, sm = 0u;
-    Seg run;
+        if (EARLY) {
 #pragma unroll
-    for (int k = 0; k < T; ++k) {
-        lane_step<DOM, LOG_IN, LOG_OUT>(k, run, Av[k], Mv[k], sw, sm);
-        if (SB) __builtin_amdgcn_sched_barrier(0);
+            for (int k = 0; k < T; ++k) asm volatile("" : "+v"(Av[k]), "+v"(Mv[k])); // all are asked for before the first is used
+            scan();
+        }
     }
+
+    if (!EARLY) scan();
     lane_close<DOM, LOG_IN, LOG_OUT>(run);
     p.tl.mark(tile, 2);
 
@@ -441,6 +458,7 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
         lds_signal(&flag_run[ts * CG + wc]);
     }
     p.tl.mark(tile, 3);
+    if (!TREE && first) have_records = wave_all(records_in()); // first look: answered ahead of the tile's loads
 
     // ---- a later wave: the fold of the waves before it in its column, in wave order; the last one along
     //      time closes the tile: its fold with its own summary is the tile's -------------------------------
@@ -750,7 +768,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void heinsen_scan_bnd(BndParams p)
     if (tile < p.ntiles) {
         p.tl.mark_at(tile, 0, t_begin);
         p.tl.mark(tile, 1);
-        bnd_tile<DOM, LOG_IN, LOG_OUT, InT, T, NW, G, SB, DENSE, TREE, RUNS, CG, MEM>(p, tile, epoch, s_flags);
+        bnd_tile<DOM, LOG_IN, LOG_OUT, InT, T, NW, G, SB, DENSE, TREE, RUNS, CG, MEM>(p, tile, epoch, (lds_flag_t *)s_flags);
         p.tl.mark(tile, 7);
     }
     if (p.header != nullptr) end_of_workgroup(p.header, epoch, &s_flag);
