@@ -144,9 +144,9 @@ struct Seg64 {
 };
 __device__ __forceinline__ Seg64 seg64(const Seg &g) { return Seg64{(double)g.A, (double)g.M, g.sA, g.sM}; }
 
-// g1 and the steps of g2 behind it.
-template <int DOM>
-__device__ __forceinline__ Seg64 seg_append64(const Seg64 &g1, const Seg &g2)
+// g1 and the steps of g2 behind it; SEG: Seg or Seg64.
+template <int DOM, typename SEG>
+__device__ __forceinline__ Seg64 seg_append64(const Seg64 &g1, const SEG &g2)
 {
     constexpr bool SIGNED = DOM == kSigned;
     if (DOM == kLinear) return Seg64{g1.A * (double)g2.A, g1.M * (double)g2.A + (double)g2.M, 0u, 0u};

@@ -128,9 +128,27 @@ __device__ __forceinline__ void lds_signal(lds_flag_t *flag)
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     *flag = 1u;
 }
+__device__ __forceinline__ bool lds_ready(lds_flag_t *flag)
+{
+    const bool ready = __builtin_amdgcn_readfirstlane((int)*flag) != 0;
+    asm volatile("" ::: "memory");
+    return ready;
+}
+// `count` flags one behind the other, at most 64
+__device__ __forceinline__ bool lds_ready_all(lds_flag_t *flags, int count)
+{
+    const int lane = threadIdx.x & 63;
+    const bool ready = lane >= count || flags[lane] != 0;
+    asm volatile("" ::: "memory");
+    return __builtin_amdgcn_ballot_w64(!ready) == 0ull;
+}
+__device__ __forceinline__ void lds_await_all(lds_flag_t *flags, int count)
+{
+    while (!lds_ready_all(flags, count)) __builtin_amdgcn_s_sleep(1);
+}
 __device__ __forceinline__ void lds_await(lds_flag_t *flag)
 {
-    while (__builtin_amdgcn_readfirstlane((int)*flag) == 0) __builtin_amdgcn_s_sleep(1);
+    while (!lds_ready(flag)) __builtin_amdgcn_s_sleep(1);
     asm volatile("" ::: "memory");
 }
 
@@ -174,6 +192,8 @@ __device__ __forceinline__ void store_run(float *out, uint32_t at, u32x4 v)
 constexpr int run_rounds(int G) { return G > 4 ? 2 : 1; }
 constexpr int run_slots(int rounds) { return 544 / rounds; }
 
+constexpr int kTreeBlock = 4; // TREE: summaries that one wave adds up for the others (see bnd_tile)
+
 // Which item and which vector of its run the wave's vector g is.
 struct RunAt {
     uint32_t item, v;
@@ -199,14 +219,18 @@ __device__ __forceinline__ void wave_lds_order()
 // 131072 x 96: 203 us, of which a tile waited 34 of its 43 us): the last tile of a group also publishes the
 // summary of its group, and states are handed on only from one super-group of G groups to the next.  A
 // tile then reads up to G - 1 tile summaries, G - 1 group summaries and one state; each of its waves fetches
-// one of each level beside its own loads, and the first wave folds them.  Whatever is folded beyond a tile is
-// folded in float64, as the chain of states is.
+// one of each level beside its own loads and passes it on through LDS, the last wave of every four adds up theirs, and
+// the first wave folds the sums.  Whatever is folded beyond a tile is folded in float64, as the chain of states is: some
+// 200 cycles each, which one after the other were half of what a tile waited.  Registers are full of the tile itself, so nothing
+// of this stays in them: records are looked at as soon as they are there and go to LDS, and addresses in LDS are formed anew in
+// every round of polling (kept, they pushed elements into scratch memory, whose loads wait for every store before them).  Before
+// and now: 2 x 131072 x 96 72.6 and 66.1 us, 1 x 1048576 x 64 248 and 168, 12 x 4096 x 64 14.4 and 12.7, 3 x 1100 x 64 9.2 and 8.9.
 //
 // No wave waits for more than it needs.  The first wave along time of each 64-channel column fetches the
 // carry records, forms the state at the start of the tile and hands it to the waves behind it through
 // LDS; a later wave waits only for the summaries of the waves before it in its own column; the last wave
 // along time publishes the tile's summary (and, closing a group, the state for the next group).  `flags`
-// are TS*CG + CG words of LDS (TREE: 2*TS more), zero when the tile begins.
+// are words of LDS, as many as the kernel says, zero when the tile begins.
 template <int DOM, bool LOG_IN, bool LOG_OUT, typename InT, int T, int NW, int G, bool SB, bool DENSE, bool TREE, bool RUNS, int CG, int MEM>
 __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile, const uint32_t epoch, lds_flag_t *flags)
 {
@@ -216,26 +240,36 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     // Whether the scan stands behind each way to load.  One scan behind them all is one where the compiler, which cannot tell there
     // what is still on its way, has the first step wait for the last input (6 x 3072 x 768 36.9 and 36.1 us, 4 x 1000 x 1000 14.0
     // and 13.2).  Not for bf16 (8 x 8192 x 1536 151.0 and 152.1), whose loads are half as long, where lines are shared (8 x 8000 x
-    // 1501, logarithms, 252.5 and 254.5), for the wide tiles (16 x 16384 x 2048 1039 and 1042) and where registers are short.
-    constexpr bool EARLY = sizeof(InT) == 4 && !RUNS && !TREE && CG == 1 && G <= 4 && MEM != kShared;
+    // 1501, logarithms, 252.5 and 254.5), for the wide tiles (16 x 16384 x 2048 1039 and 1042) and for runs, which leave no registers.
+    constexpr bool EARLY = sizeof(InT) == 4 && !RUNS && CG == 1 && MEM != kShared;
     constexpr int PT = TREE ? 1 : (G > 1 ? G - 1 : 1); // tile summaries a wave fetches
     static_assert(T <= 32, "one sign word per channel");
     static_assert(NW % CG == 0, "the waves form a CG x TS grid");
     static_assert(!DENSE || CG == 1, "dense columns are mapped one channel per lane");
     static_assert(!RUNS || (DENSE && NW > 1 && !(SIGNED && LOG_OUT)), "runs are of columns of whole items");
-    static_assert(!TREE || (CG == 1 && TS > 1 && G == TS), "every wave of a tile takes one summary of each level");
+    static_assert(!TREE || (CG == 1 && G == TS && TS % kTreeBlock == 0), "every wave of a tile takes one summary of each level");
     __shared__ float lds_A[TS][CH];
     __shared__ float lds_M[TS][CH];
     __shared__ uint32_t lds_S[SIGNED ? TS : 1][CH];
     __shared__ double lds_startL[CH]; // float64: the wave that closes a group hands it on as it is
     __shared__ uint32_t lds_startS[CH];
-    // TREE: every wave's tile summary and its group summary
-    __shared__ float lds_tileA[TREE ? TS : 1][CH], lds_tileM[TREE ? TS : 1][CH];
-    __shared__ double lds_groupA[TREE ? TS : 1][CH], lds_groupM[TREE ? TS : 1][CH];
-    __shared__ uint32_t lds_tileS[TREE ? TS : 1][CH], lds_groupS[TREE ? TS : 1][CH];
+    // TREE: every wave's tile summary and its group summary, and the sums of BL of them
+    constexpr int BL = kTreeBlock, NBL = TREE ? G / BL : 1;
+    __shared__ float lds_tileA[TREE ? G : 1][CH], lds_tileM[TREE ? G : 1][CH];
+    __shared__ double lds_groupA[TREE ? G : 1][CH], lds_groupM[TREE ? G : 1][CH];
+    __shared__ uint32_t lds_tileS[TREE ? G : 1][CH], lds_groupS[TREE ? G : 1][CH];
+    __shared__ double lds_sumA[2][NBL][CH], lds_sumM[2][NBL][CH]; // of tiles, of groups
+    __shared__ uint32_t lds_sumS[2][NBL][CH];
     // and, while the records are waited for, the wave's fold of the waves before it (registers are full)
     __shared__ float lds_preA[TREE ? TS : 1][CH], lds_preM[TREE ? TS : 1][CH];
     __shared__ uint32_t lds_preS[TREE ? TS : 1][CH];
+    __shared__ double lds_superL[TREE ? CH : 1]; // state at the start of the super-group
+    __shared__ uint32_t lds_superS[TREE ? CH : 1];
+    __shared__ double lds_restA[TREE ? CH : 1], lds_restM[TREE ? CH : 1]; // everything between there and the tile
+    __shared__ uint32_t lds_restS[TREE ? CH : 1];
+    // the folds of BL waves
+    __shared__ float lds_wavesA[NBL][CH], lds_wavesM[NBL][CH];
+    __shared__ uint32_t lds_wavesS[NBL][CH];
 
     constexpr int ROUNDS = run_rounds(G);
     __shared__ u32x4 lds_runs[RUNS ? NW : 1][RUNS ? run_slots(ROUNDS) : 1];
@@ -247,7 +281,8 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     const int wc = w % CG, ts = w / CG;
     lds_flag_t *flag_run = flags;              // [TS][CG]: the wave's summary is in LDS
     lds_flag_t *flag_start = flags + TS * CG;  // [CG]: the column's start state is in LDS
-    lds_flag_t *flag_part = flags + TS * CG + CG; // TREE: [2][TS]: the wave's summaries are in LDS
+    lds_flag_t *flag_part = flags + TS * CG + CG; // TREE: [2][TS]: the wave's summaries are in LDS,
+    lds_flag_t *flag_sum = flag_part + 2 * G;     //   [2][NBL]: the sums of BL of them, [1]: the super-group's state, [NBL]: of BL waves, [1]: what lies between
 
     const int chunk = (int)(tile / (uint32_t)p.ncols);
     const int col = (int)(tile % (uint32_t)p.ncols);
@@ -290,53 +325,93 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     //      published, and the records then arrive ahead of the tile's own loads at no cost in latency ---
     const bool first = ts == 0; // wave-uniform
     const bool fetches = TREE || first;
-    rec_t rA[PT], rM[PT], rG[4] = {}, rS = 0, rS2 = 0;
+    struct Recs {
+        rec_t A[PT], M[PT], Q[4], S, S2;
+    };
+    Recs recs = {};
     const int q = TREE ? g / G : g;   // TREE: super-group, and the group's place in it
     const int gi = TREE ? g % G : 0;
     const bool has_state = first && q > 0;
-    const int j0 = TREE ? ts : 0;             // first of the tile summaries this wave fetches,
-    const bool has_group = TREE && ts < gi;   // and whether it has a group's to fetch
-    bool want_state = has_state, want_tiles = true, want_group = has_group; // TREE: still missing (wave-uniform)
-    auto issue_records = [&]() {
+    bool want_state = has_state, want_tile = TREE && ts < r, want_group = TREE && ts < gi; // TREE: still missing (wave-uniform)
+    int cv = c; // TREE: renewed in every round of the loop below, so that no address that depends on it stays in a register
+    auto issue_records = [&](Recs &R) {
         if (want_state) {
             const rec_t *sp = (TREE ? p.agg + ((size_t)(q * G * G - 1) * p.ncols + col) * (2 * CH)
-                                    : p.state + ((size_t)q * p.ncols + col) * (2 * CH)) + c;
-            rS = rec_get(sp);
-            rS2 = rec_get(sp + CH);
+                                    : p.state + ((size_t)q * p.ncols + col) * (2 * CH)) + cv;
+            R.S = rec_get(sp);
+            R.S2 = rec_get(sp + CH);
         }
+        if constexpr (TREE) {
+            if (want_tile) {
+                const rec_t *tp = p.agg + ((size_t)(g * G + ts) * p.ncols + col) * (2 * CH) + cv;
+                R.A[0] = rec_get(tp);
+                R.M[0] = rec_get(tp + CH);
+            }
+            if (want_group) {
+                const rec_t *gp = p.agg + ((size_t)((q * G + ts) * G + G - 1) * p.ncols + col) * (2 * CH) + cv;
+                const rec_t *mp = p.state + ((size_t)(q * G + ts) * p.ncols + col) * (2 * CH) + cv;
+                R.Q[0] = rec_get(gp);
+                R.Q[1] = rec_get(gp + CH);
+                R.Q[2] = rec_get(mp);
+                R.Q[3] = rec_get(mp + CH);
+            }
+        } else {
 #pragma unroll
-        for (int j = 0; j < (TREE ? 1 : G - 1); ++j) {
-            if (want_tiles && j0 + j < r) {
-                const rec_t *tp = p.agg + ((size_t)(g * G + j0 + j) * p.ncols + col) * (2 * CH) + c;
-                rA[j] = rec_get(tp);
-                rM[j] = rec_get(tp + CH);
+            for (int j = 0; j < G - 1; ++j) {
+                if (j < r) {
+                    const rec_t *tp = p.agg + ((size_t)(g * G + j) * p.ncols + col) * (2 * CH) + cv;
+                    R.A[j] = rec_get(tp);
+                    R.M[j] = rec_get(tp + CH);
+                }
             }
         }
-        if (TREE && want_group) {
-            const rec_t *gp = p.agg + ((size_t)((q * G + ts) * G + G - 1) * p.ncols + col) * (2 * CH) + c;
-            const rec_t *mp = p.state + ((size_t)(q * G + ts) * p.ncols + col) * (2 * CH) + c;
-            rG[0] = rec_get(gp);
-            rG[1] = rec_get(gp + CH);
-            rG[2] = rec_get(mp);
-            rG[3] = rec_get(mp + CH);
-        }
     };
-    auto tiles_in = [&]() -> bool { // the tile summaries of this lane carry the launch's tag
-        bool ok = true;
+    auto tile_in = [&](const Recs &R, int j) -> bool { return rec_ok(R.A[j], epoch) && rec_ok(R.M[j], epoch); }; // of this lane
+    auto group_in = [&](const Recs &R) -> bool {
+        return rec_ok(R.Q[0], epoch) && rec_ok(R.Q[1], epoch) && rec_ok(R.Q[2], epoch) && rec_ok(R.Q[3], epoch);
+    };
+    auto state_in = [&](const Recs &R) -> bool { return !has_state || (rec_ok(R.S, epoch) && rec_ok(R.S2, epoch)); };
+    auto records_in = [&](const Recs &R) -> bool { // one carry level: all of this lane's
+        bool ok = state_in(R);
+        if constexpr (!TREE) {
 #pragma unroll
-        for (int j = 0; j < (TREE ? 1 : G - 1); ++j) {
-            if (j0 + j < r) ok = ok && rec_ok(rA[j], epoch) && rec_ok(rM[j], epoch);
+            for (int j = 0; j < G - 1; ++j)
+                if (j < r) ok = ok && tile_in(R, j);
         }
         return ok;
     };
-    auto group_in = [&]() -> bool { // TREE: the group summary does
-        return !has_group || (rec_ok(rG[0], epoch) && rec_ok(rG[1], epoch) && rec_ok(rG[2], epoch) && rec_ok(rG[3], epoch));
-    };
-    auto state_in = [&]() -> bool { return !has_state || (rec_ok(rS, epoch) && rec_ok(rS2, epoch)); };
-    auto records_in = [&]() -> bool { return tiles_in() && state_in() && group_in(); }; // all of this lane's records do
     auto wave_all = [](bool ok) -> bool { return __builtin_amdgcn_ballot_w64(!ok) == 0ull; };
     bool have_records = false;
-    if (fetches) issue_records();
+    if (fetches) issue_records(recs);
+    // TREE: what is in goes to LDS at once (and with `lost`, NaN for what never came): registers are full
+    auto pass_on = [&](const Recs &R, bool lost) {
+        if constexpr (TREE) {
+            if (want_tile && (lost || wave_all(tile_in(R, 0)))) {
+                want_tile = false;
+                Seg part = seg_from<DOM>(R.A[0], R.M[0]);
+                if (!tile_in(R, 0)) part.M = __builtin_nanf("");
+                lds_tileA[ts][cv] = part.A;
+                lds_tileM[ts][cv] = part.M;
+                if (SIGNED) lds_tileS[ts][cv] = pack_signs(part);
+                lds_signal(&flag_part[ts]);
+            }
+            if (want_group && (lost || wave_all(group_in(R)))) {
+                want_group = false;
+                const Seg64 part = seg64_from<DOM>(R.Q);
+                lds_groupA[ts][cv] = part.A;
+                lds_groupM[ts][cv] = group_in(R) ? part.M : __builtin_nan("");
+                if (SIGNED) lds_groupS[ts][cv] = (part.sA >> 31) | ((part.sM >> 31) << 1);
+                lds_signal(&flag_part[G + ts]);
+            }
+            if (want_state && (lost || wave_all(state_in(R)))) {
+                want_state = false;
+                const State64 x = state64_from(R.S, R.S2, SIGNED);
+                lds_superL[cv] = state_in(R) ? x.lx : __builtin_nan("");
+                lds_superS[cv] = x.s;
+                lds_signal(&flag_sum[2 * NBL]);
+            }
+        }
+    };
 
     // ---- load the lane's T inputs, encode and scan them serially; Av/Mv become the per-element records (see stash).  Every way
     //      to load has the scan behind it: with one scan behind them all the compiler, which cannot tell there what is still on
@@ -398,7 +473,7 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
         if (ROUNDS > 1) ask(bp, tb);
         deal(tb, Mv);
     } else if ((EARLY || chan_ok) && t0 + T <= p.n) {
-        const InT *arow = ap, *brow = bp; // likewise: row pointers
+        const InT *arow = ap, *brow = bp; // wave-uniform row pointers
         const uint32_t off = !EARLY || chan_ok ? moff : 0u; // lanes without a channel take the first one's
 #pragma unroll
         for (int k = 0; k < T; ++k) {
@@ -407,7 +482,10 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
             arow += p.D;
             brow += p.D;
         }
-        if (EARLY) scan();
+        if (EARLY) {
+            pass_on(recs, false);
+            scan();
+        }
     } else if constexpr (sizeof(InT) == 2) {
         // As stored until all are asked for: widened inside the branches, every step would be waited for before the next
         // one is asked for, which is what bounds short and ragged calls (25 x 285 x 320 17.8 us so, 8.8 now; 52 x 183 x 13 10.6
@@ -440,45 +518,83 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
             }
         }
         if (EARLY) {
+            pass_on(recs, false);
 #pragma unroll
             for (int k = 0; k < T; ++k) asm volatile("" : "+v"(Av[k]), "+v"(Mv[k])); // all are asked for before the first is used
             scan();
         }
     }
-
-    if (!EARLY) scan();
+    if (!EARLY) {
+        pass_on(recs, false);
+        scan();
+    }
     lane_close<DOM, LOG_IN, LOG_OUT>(run);
     p.tl.mark(tile, 2);
 
     // ---- the waves behind this one in the column need its summary --------------------------------
-    if (TS > 1 && ts < TS - 1) {
+    if (TS > 1 && (TREE || ts < TS - 1)) {
         lds_A[ts][c] = run.A;
         lds_M[ts][c] = run.M;
         if (SIGNED) lds_S[ts][c] = pack_signs(run);
         lds_signal(&flag_run[ts * CG + wc]);
     }
     p.tl.mark(tile, 3);
-    if (!TREE && first) have_records = wave_all(records_in()); // first look: answered ahead of the tile's loads
+    if (!TREE && first) have_records = wave_all(records_in(recs)); // first look: answered ahead of the tile's loads
 
     // ---- a later wave: the fold of the waves before it in its column, in wave order; the last one along
     //      time closes the tile: its fold with its own summary is the tile's -------------------------------
     Seg pre = seg_identity<DOM>(), total = seg_identity<DOM>();
     const bool closing = TS > 1 && ts == TS - 1; // wave-uniform
+    auto mine = [&]() -> Seg { // TREE: read back, registers are full
+        if constexpr (!TREE) return run;
+        Seg h;
+        h.A = lds_A[ts][c];
+        h.M = lds_M[ts][c];
+        h.sA = h.sM = 0u;
+        if (SIGNED) unpack_signs(lds_S[ts][c], h);
+        return h;
+    };
     if (!first) {
-#pragma unroll
-        for (int j = 0; j < TS - 1; ++j) {
-            if (j < ts) {
-                lds_await(&flag_run[j * CG + wc]);
-                Seg h;
-                h.A = lds_A[j][c];
-                h.M = lds_M[j][c];
-                h.sA = h.sM = 0u;
-                if (SIGNED) unpack_signs(lds_S[j][c], h);
-                pre = (j == 0) ? h : seg_combine<DOM>(pre, h);
+        auto get_run = [&](int j) -> Seg {
+            if (!TREE) lds_await(&flag_run[j * CG + wc]);
+            Seg h;
+            h.A = lds_A[j][c];
+            h.M = lds_M[j][c];
+            h.sA = h.sM = 0u;
+            if (SIGNED) unpack_signs(lds_S[j][c], h);
+            return h;
+        };
+        if constexpr (TREE) { // the waves before it in its block, which the block's last wave passes on, and the blocks before that
+            const int b0 = ts / BL;
+            lds_await_all(&flag_run[b0 * BL], ts - b0 * BL);
+#pragma unroll 1
+            for (int j = b0 * BL; j < ts; ++j) pre = seg_combine<DOM>(pre, get_run(j));
+            if (ts % BL == BL - 1 && !closing) {
+                const Seg sum = seg_combine<DOM>(pre, mine());
+                lds_wavesA[b0][c] = sum.A;
+                lds_wavesM[b0][c] = sum.M;
+                if (SIGNED) lds_wavesS[b0][c] = pack_signs(sum);
+                lds_signal(&flag_sum[2 * NBL + 1 + b0]);
             }
+            Seg before = seg_identity<DOM>();
+            lds_await_all(&flag_sum[2 * NBL + 1], b0);
+#pragma unroll 1
+            for (int j = 0; j < b0; ++j) {
+                Seg h;
+                h.A = lds_wavesA[j][c];
+                h.M = lds_wavesM[j][c];
+                h.sA = h.sM = 0u;
+                if (SIGNED) unpack_signs(lds_wavesS[j][c], h);
+                before = seg_combine<DOM>(before, h);
+            }
+            pre = seg_combine<DOM>(before, pre);
+        } else {
+#pragma unroll
+            for (int j = 0; j < TS - 1; ++j)
+                if (j < ts) pre = (j == 0) ? get_run(j) : seg_combine<DOM>(pre, get_run(j));
         }
         if (closing && more) {
-            total = seg_combine<DOM>(pre, run);
+            total = seg_combine<DOM>(pre, mine());
             if (r < G - 1 && tile != p.drop_tile) {
                 rec_t *tp = p.agg + (size_t)tile * (2 * CH) + c;
                 seg_put<DOM>(tp, tp + CH, total, epoch);
@@ -499,10 +615,10 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     auto get_total = [&]() -> Seg { // closing wave
         if constexpr (!TREE) return total;
         Seg g2;
-        g2.A = lds_A[TS - 1][c];
-        g2.M = lds_M[TS - 1][c];
+        g2.A = lds_A[TS - 1][cv];
+        g2.M = lds_M[TS - 1][cv];
         g2.sA = g2.sM = 0u;
-        if (SIGNED) unpack_signs(lds_S[TS - 1][c], g2);
+        if (SIGNED) unpack_signs(lds_S[TS - 1][cv], g2);
         return g2;
     };
 
@@ -510,75 +626,124 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     State64 st64{0.0, 0u};   // the same in float64, along the chain of tiles
     auto state_from_x0 = [&]() {
         float x0v = LOG_IN ? 0.0f : 1.0f, lx;
-        if (chan_ok) x0v = p.x0[p.x0_stride ? x0_at : 0];
+        int64_t at = x0_at;
+        if (TREE) { // formed here: registers are full
+            int l = threadIdx.x & 63;
+            asm volatile("" : "+v"(l));
+            at = DENSE ? (int64_t)col * p.lanes + l : (int64_t)bidx * p.D + (int64_t)cg * CH + l;
+        }
+        if (chan_ok) x0v = p.x0[p.x0_stride ? at : 0];
         encode<DOM, LOG_IN>(x0v, lx, st64.s);
         st64.lx = (double)lx;
     };
     if constexpr (TREE) {
-        // ---- every wave passes on its summaries: the tile's as soon as it is in, since the tile that closes
-        //      a group owes the later groups their sum, whatever else is on its way -------------------------
+        // ---- every wave passes on its summaries as soon as they are in, and the last wave of a block of BL the sum of the
+        //      block's: one after the other the 15 of a group are four microseconds of float64 in the way of every tile behind ---
         auto get_tile = [&](int j) -> Seg {
-            lds_await(&flag_part[j]);
             Seg g2;
-            g2.A = lds_tileA[j][c];
-            g2.M = lds_tileM[j][c];
+            g2.A = lds_tileA[j][cv];
+            g2.M = lds_tileM[j][cv];
             g2.sA = g2.sM = 0u;
-            if (SIGNED) unpack_signs(lds_tileS[j][c], g2);
+            if (SIGNED) unpack_signs(lds_tileS[j][cv], g2);
             return g2;
         };
-        bool lost = false, tile_done = false; // lost: this lane's records never came
+        auto get64 = [&](const double (&A)[CH], const double (&M)[CH], const uint32_t (&S)[CH]) -> Seg64 {
+            const uint32_t sg = SIGNED ? S[cv] : 0u;
+            return Seg64{A[cv], M[cv], sg << 31, sg << 30};
+        };
+        auto put64 = [&](double (&A)[CH], double (&M)[CH], uint32_t (&S)[CH], const Seg64 &v) {
+            A[cv] = v.A;
+            M[cv] = v.M;
+            if (SIGNED) S[cv] = (v.sA >> 31) | ((v.sM >> 31) << 1);
+        };
+        const int bl = ts / BL * BL;         // first of the wave's block
+        const bool sums = ts % BL == BL - 1; // it adds up the block's summaries, if there are as many
+        // Without logarithms only group by group: the products of a of two groups may leave float64, where those of one (eight
+        // tiles, in float32 each) cannot.
+        constexpr bool SUM_GROUPS = DOM != kLinear;
+        const int gi_sums = SUM_GROUPS ? gi / BL : 0; // blocks of groups
+        bool tile_sum = !(sums && bl + BL <= r), group_sum = !(sums && SUM_GROUPS && bl + BL <= gi);
+        bool owes = closing && more && r == G - 1 && gi < G - 1; // the last tile of a group owes the later groups its sum
         uint32_t polls = 0;
         for (;;) {
-            want_tiles = want_tiles && !wave_all(tiles_in());
-            want_group = want_group && !wave_all(group_in());
-            want_state = want_state && !wave_all(state_in());
-            have_records = !want_tiles && !want_group && !want_state;
-            if (!have_records && ++polls > p.spin_limit) {
-                // give up: go on as if everything were in, with NaN for what is missing
-                lost = true;
-                note_wait_gave_up(p.header);
+            asm volatile("" : "+v"(cv));
+            if (want_tile || want_group || want_state) {
+                Recs again = {};
+                issue_records(again);
+                if (++polls > p.spin_limit) note_wait_gave_up(p.header); // go on as if everything were in, with NaN for what is missing
+                pass_on(again, polls > p.spin_limit);
             }
-            if (!tile_done && (!want_tiles || lost)) {
-                tile_done = true;
-                Seg part = ts < r ? seg_from<DOM>(rA[0], rM[0]) : seg_identity<DOM>();
-                if (!tiles_in()) part.M = __builtin_nanf("");
-                lds_tileA[ts][c] = part.A;
-                lds_tileM[ts][c] = part.M;
-                lds_tileS[ts][c] = pack_signs(part);
-                lds_signal(&flag_part[ts]);
-                if (closing && more && r == G - 1 && gi < G - 1) {
-                    // the last tile of a group owes the later groups the summary of its group
-                    Seg64 sum = seg64(get_tile(0));
+            if (!tile_sum && lds_ready_all(&flag_part[bl], BL)) {
+                tile_sum = true;
+                Seg64 sum = seg64(get_tile(bl));
 #pragma unroll 1
-                    for (int j = 1; j < G - 1; ++j) sum = seg_append64<DOM>(sum, get_tile(j));
-                    seg64_put<DOM>(p.agg + (size_t)tile * (2 * CH) + c, p.state + ((size_t)g * p.ncols + col) * (2 * CH) + c, CH,
-                                   seg_append64<DOM>(sum, get_total()), epoch);
-                }
+                for (int j = bl + 1; j < bl + BL; ++j) sum = seg_append64<DOM>(sum, get_tile(j));
+                put64(lds_sumA[0][bl / BL], lds_sumM[0][bl / BL], lds_sumS[0][bl / BL], sum);
+                lds_signal(&flag_sum[bl / BL]);
             }
-            if (have_records || lost) break;
-            __builtin_amdgcn_s_sleep(2);
-            issue_records();
-        }
-        if (has_group) {
-            const Seg64 sum = seg64_from<DOM>(rG);
-            lds_groupA[ts][c] = sum.A;
-            lds_groupM[ts][c] = group_in() ? sum.M : __builtin_nan("");
-            lds_groupS[ts][c] = (sum.sA >> 31) | ((sum.sM >> 31) << 1);
-            lds_signal(&flag_part[TS + ts]);
+            if (!group_sum && lds_ready_all(&flag_part[G + bl], BL)) {
+                group_sum = true;
+                Seg64 sum = get64(lds_groupA[bl], lds_groupM[bl], lds_groupS[bl]);
+#pragma unroll 1
+                for (int j = bl + 1; j < bl + BL; ++j) sum = seg_append64<DOM>(sum, get64(lds_groupA[j], lds_groupM[j], lds_groupS[j]));
+                put64(lds_sumA[1][bl / BL], lds_sumM[1][bl / BL], lds_sumS[1][bl / BL], sum);
+                lds_signal(&flag_sum[NBL + bl / BL]);
+            }
+            if (owes && lds_ready_all(flag_sum, NBL - 1) && lds_ready_all(&flag_part[G - BL], BL - 1)) {
+                owes = false;
+                Seg64 sum = get64(lds_sumA[0][0], lds_sumM[0][0], lds_sumS[0][0]);
+#pragma unroll 1
+                for (int j = 1; j < NBL - 1; ++j) sum = seg_append64<DOM>(sum, get64(lds_sumA[0][j], lds_sumM[0][j], lds_sumS[0][j]));
+#pragma unroll 1
+                for (int j = G - BL; j < G - 1; ++j) sum = seg_append64<DOM>(sum, get_tile(j));
+                seg64_put<DOM>(p.agg + (size_t)tile * (2 * CH) + cv, p.state + ((size_t)g * p.ncols + col) * (2 * CH) + cv, CH,
+                               seg_append64<DOM>(sum, get_total()), epoch);
+            }
+            if (!want_tile && !want_group && !want_state && tile_sum && group_sum && !owes) break;
+            __builtin_amdgcn_s_sleep(1);
         }
         p.tl.mark(tile, 4);
-        if (first) {
-            if (q == 0) state_from_x0();
-            else st64 = state64_from(rS, rS2, SIGNED);
+        // what lies between the super-group's start and the tile, in order: the sums of whole blocks, then what is behind them
+        auto rest = [&](auto &&take) {
 #pragma unroll 1
-            for (int j = 0; j < gi; ++j) {
-                lds_await(&flag_part[TS + j]);
-                const uint32_t s = SIGNED ? lds_groupS[j][c] : 0u;
-                st64 = seg_apply64<DOM>(st64, Seg64{lds_groupA[j][c], lds_groupM[j][c], s << 31, s << 30});
+            for (int j = 0; j < gi_sums; ++j) {
+                lds_await(&flag_sum[NBL + j]);
+                take(get64(lds_sumA[1][j], lds_sumM[1][j], lds_sumS[1][j]));
             }
 #pragma unroll 1
-            for (int j = 0; j < r; ++j) st64 = seg_apply64<DOM>(st64, get_tile(j));
-            if (!state_in()) st64.lx = __builtin_nan("");
+            for (int j = gi_sums * BL; j < gi; ++j) {
+                lds_await(&flag_part[G + j]);
+                take(get64(lds_groupA[j], lds_groupM[j], lds_groupS[j]));
+            }
+#pragma unroll 1
+            for (int j = 0; j < r / BL; ++j) {
+                lds_await(&flag_sum[j]);
+                take(get64(lds_sumA[0][j], lds_sumM[0][j], lds_sumS[0][j]));
+            }
+#pragma unroll 1
+            for (int j = r / BL * BL; j < r; ++j) {
+                lds_await(&flag_part[j]);
+                take(get_tile(j));
+            }
+        };
+        lds_flag_t *flag_rest = &flag_sum[2 * NBL + 1 + NBL];
+        // Behind the first super-group the second wave adds it all up: a link of the chain of states is one step then, however late
+        // the state (one column of 400000 steps 89.7 and 75.9 us, of 1048576 206 and 168).
+        if (SUM_GROUPS && ts == 1 && q > 0) {
+            Seg64 sum{0.0, -INFINITY, 0u, 0u};
+            rest([&](const auto &part) { sum = seg_append64<DOM>(sum, part); });
+            put64(lds_restA, lds_restM, lds_restS, sum);
+            lds_signal(flag_rest);
+        }
+        if (first) {
+            if (q == 0) state_from_x0();
+            else st64 = State64{lds_superL[c], lds_superS[c]};
+            if (SUM_GROUPS && q > 0) {
+                lds_await(flag_rest);
+                st64 = seg_apply64<DOM>(st64, get64(lds_restA, lds_restM, lds_restS));
+            } else {
+                rest([&](const auto &part) { st64 = seg_apply64<DOM>(st64, part); });
+            }
             st.lx = (float)st64.lx;
             st.s = st64.s;
             lds_startL[c] = st64.lx;
@@ -589,29 +754,29 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
         // ---- obtain the state at the start of the tile ------------------------------------------
         bool lost = false; // this lane's records never came
         if (!have_records) {
-            issue_records();
+            issue_records(recs);
             uint32_t polls = 0;
             for (;;) {
-                const bool ok = records_in();
+                const bool ok = records_in(recs);
                 if (wave_all(ok)) break;
                 if (++polls > p.spin_limit) {
                     lost = !ok;
                     break;
                 }
                 __builtin_amdgcn_s_sleep(2);
-                issue_records();
+                issue_records(recs);
             }
         }
         p.tl.mark(tile, 4);
         if (g == 0) {
             state_from_x0();
         } else {
-            st64 = state64_from(rS, rS2, SIGNED);
+            st64 = state64_from(recs.S, recs.S2, SIGNED);
         }
         // fold the earlier tiles of the group in tile order
 #pragma unroll
         for (int j = 0; j < G - 1; ++j) {
-            if (j < r) st64 = seg_apply64<DOM>(st64, seg_from<DOM>(rA[TREE ? 0 : j], rM[TREE ? 0 : j]));
+            if (j < r) st64 = seg_apply64<DOM>(st64, seg_from<DOM>(recs.A[TREE ? 0 : j], recs.M[TREE ? 0 : j]));
         }
         if (lost) {
             st64.lx = __builtin_nan("");
@@ -729,7 +894,7 @@ template <int DOM, bool LOG_IN, bool LOG_OUT, typename InT, int T, int NW, int G
 __global__ __launch_bounds__(NW * 64, MINW) void heinsen_scan_bnd(BndParams p)
 {
     __shared__ uint32_t s_tile, s_epoch, s_flag;
-    constexpr int NFLAGS = NW + CG + (TREE ? 2 * NW : 0);
+    constexpr int NFLAGS = NW + CG + (TREE ? 2 * G + 3 * G / kTreeBlock + 2 : 0);
     __shared__ uint32_t s_flags[NFLAGS];
     const unsigned long long t_begin = p.tl.stamps != nullptr ? wall_clock64() : 0ull;
     uint32_t tile, epoch = 0u;
@@ -856,9 +1021,9 @@ struct BndPlan {
 // record loads: 106 us for the 3 columns.
 constexpr int kTreeGroup = 8;
 constexpr int kTreeBelow = 16;
-// From nine columns on a sequence of two groups of eight has one link and no use for a second level (12 columns of 4096
-// steps: 15.5 us with it, 14.7 with groups of eight alone, 15.8 with groups of four; bf16, three groups: 21.7 and 19.3).
-constexpr int kTreeAlways = 9;
+// Tall tiles (see tall_tiles): sixteen waves one after the other along time, and as many tiles per group and groups per
+// super-group.
+constexpr int kTallWaves = 16;
 
 // Workgroups of eight waves that the chip holds at a time.
 constexpr int kPlaces = 512;
@@ -986,9 +1151,10 @@ BndPlan make_plan(const ScanCall &c, bool allow_wide = true, bool want_tree = fa
     const bool tiles8 = pl.cg == 1 && pl.NW == 8 && pl.T == 32 && c.n > 4 * pl.NW * pl.T;
     pl.tree = tiles8 && (pl.ncols < kTreeBelow || want_tree);
     if (pl.tree) pl.G = kTreeGroup;
-    if (pl.tree && pl.ncols >= kTreeAlways && pl.ncols < kTreeBelow && c.n > kTreeGroup * pl.NW * pl.T &&
-        c.n <= (c.bf16 ? 3 : 2) * kTreeGroup * pl.NW * pl.T)
-        pl.tree = false; // (its groups stay)
+    if (tiles8 && !c.linear && tall_tiles(pl.ncols, ceil_div(c.n, (int64_t)kTallWaves * pl.T))) {
+        pl.tree = true;
+        pl.NW = pl.G = kTallWaves;
+    }
     if (pl.dense) pl.pad = (int)(pl.tree || pl.runs ? c.D : pad);
     if (pl.runs) {
         pl.pitch_out = kRunPitches.of[0][run_rounds(pl.G) - 1][c.D];
@@ -1122,12 +1288,11 @@ hipError_t launch_mode(const ScanCall &c, const BndPlan &pl, const LaunchCtx &ct
         if (mem == kStream) HS_BND(32, 8, 4, false, false, false, 2, kStream);
         else if (mem == kThrough) HS_BND(32, 8, 4, false, false, false, 2, kThrough);
         else HS_BND(32, 8, 4, false, false, false, 2, kKeepOut);
+    } else if (pl.tree && pl.NW == kTallWaves) {
+        if constexpr (DOM != kLinear) HS_BND_ANY(32, kTallWaves, kTallWaves, true);
+        else return hipErrorInvalidValue;
     } else if (pl.tree) {
         HS_BND_ANY(32, 8, kTreeGroup, true);
-    } else if (pl.G == kTreeGroup) { // few short columns: nothing that would not stay in the caches
-        if (pl.runs) HS_BND(32, 8, kTreeGroup, true, false, true, 1, kThrough);
-        else if (pl.dense) HS_BND(32, 8, kTreeGroup, true, false, false, 1, kKeepOut);
-        else HS_BND(32, 8, kTreeGroup, false, false, false, 1, kKeepOut);
     } else if (pl.NW == 8) {
         HS_BND_ANY(32, 8, 4, false);
     } else if (pl.dense) { // short sequences

@@ -56,6 +56,20 @@ constexpr int ticket_queues(int most, int64_t columns, bool wide)
     return queues;
 }
 
+// [B, n, D], few columns: tiles of sixteen waves (512 steps, one workgroup per compute unit) in two carry levels of sixteen, instead
+// of eight waves and levels of eight or four.  Half as many tiles lie behind one another in a column and 256 of them have their
+// states handed on without a chain, which is what the smaller ones wait for; but a compute unit has nothing to load while its one
+// workgroup waits.  So from half a round of the chip (below, a tile's own latency counts: 1 x 16384 x 64 12.6 us with eight waves,
+// 16.5 with sixteen) to three (eight and sixteen: one column of 131072 steps 35.8 and 24.7, of 262144 57.7 and 47.2, 4 x 65536 51.9 and
+// 45.6, 8 x 32768 51.4 and 44.7, 3 x 131072 70.9 and 67.6; four rounds, 4 x 131072, 90.0 and 91.2), and with more columns, whose tiles
+// wait less, to two and to one (16 x 8192 28.1 and 20.4, 24 x 8192 36.4 and 36.1, 32 x 4096 22.1 and 20.9; 24 x 16384 62.7 and
+// 68.1, 32 x 8192 43.1 and 45.8).
+constexpr bool tall_tiles(int64_t columns, int64_t chunks)
+{
+    const int64_t tiles = columns * chunks, places = 256;
+    return tiles > places / 2 && (columns < 16 ? tiles <= 3 * places : columns <= 24 ? tiles <= 2 * places : columns <= 32 && tiles <= places);
+}
+
 // [B, n, D], output in whole lines.  It goes through the L2 at once unless the tiles wait for states that would queue with
 // it: tiles of eight waves with one carry level, between one and three per compute unit, where most of the output is
 // written while nothing is left to load.  Ordinary stores and through the L2 there: 15 x 1993 x 256 (480 tiles) 20.2 and

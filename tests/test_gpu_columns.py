@@ -1,6 +1,6 @@
 """[B, n, D] with columns of channels that do not fill the lanes (whole narrow items, or 64 channels whatever item
 they belong to), rows that do not keep to 128-byte lines with few and many tiles, and few columns of many tiles:
-two carry levels of eight, whose records the waves of a tile share."""
+two carry levels of eight or sixteen, whose records the waves of a tile share."""
 import numpy as np
 import pytest
 
@@ -38,6 +38,60 @@ def test_columns_and_carry_levels(gpu, mode, bf16):
             print(f"[columns] {mode} bf16={bf16} shape={shape} offset={offset}", flush=True)
             got = cross._run(gpu, a, b, x0, "BND", cross.MODES[mode], bf16, offset_elems=offset)
             cross._check(got, a, b, x0, "BND", mode)
+
+
+# Few columns of tall tiles (sixteen waves, 512 steps; two carry levels of sixteen): just enough tiles, the last one a step long or
+# missing one, a group and one tile more, a super-group (256 tiles) and one tile more, whole items in their lanes and as runs,
+# columns of channels of two items, the most columns.
+@pytest.mark.parametrize("mode", ["signed", "log_logout", "positive"])
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("shape", [
+    (1, 512 * 128 + 1, 64), (1, 512 * 129 - 1, 64), (8, 512 * 17, 64), (8, 512 * 16 + 33, 64), (1, 512 * 256 + 1, 70), (1, 512 * 257, 33),
+    (3, 512 * 90 + 31, 96), (16, 512 * 16 + 5, 64), (24, 512 * 21, 64), (32, 512 * 8, 64), (5, 512 * 130 + 7, 32), (40, 512 * 45 + 3, 5), (9, 512 * 70 + 1, 30),
+])
+def test_tall_tiles(gpu, mode, bf16, shape):
+    torch, hb = gpu
+    B, n, D = shape
+    assert hb.heinsen_tile_shape(B, D, n, hb.HEINSEN_LAYOUT_BND, hb.flags_from_names(cross.MODES[mode]))[1] == 512
+    rng = np.random.default_rng(sum(shape) + int(bf16))
+    a, b, x0 = cross._inputs(rng, shape, "BND", mode)
+    if bf16:  # the bf16-rounded values are what is stored: they define the problem
+        a = workloads.bf16_bits_to_f32(workloads.f32_to_bf16_bits(a)).reshape(a.shape)
+        b = workloads.bf16_bits_to_f32(workloads.f32_to_bf16_bits(b)).reshape(b.shape)
+    print(f"[tall] {mode} bf16={bf16} shape={shape}", flush=True)
+    got = cross._run(gpu, a, b, x0, "BND", cross.MODES[mode], bf16, offset_elems=0)
+    cross._check(got, a, b, x0, "BND", mode)
+    for _ in range(3):  # whatever order the records come in
+        again = cross._run(gpu, a, b, x0, "BND", cross.MODES[mode], bf16, offset_elems=0)
+        assert np.array_equal(got.view(np.uint32), again.view(np.uint32))
+
+
+# Two carry levels, a tile whose summary never comes: its column is NaN from the next tile on, the others are as they were.
+@pytest.mark.parametrize("shape,drop", [((2, 256 * 70 + 9, 64), 4), ((2, 256 * 70 + 9, 64), 19), ((2, 512 * 66, 64), 6), ((2, 512 * 300 + 1, 64), 41)])
+def test_lost_summary_of_two_levels(gpu, shape, drop):
+    torch, hb = gpu
+    B, n, D = shape
+    steps = hb.heinsen_tile_shape(B, D, n, hb.HEINSEN_LAYOUT_BND, 0)[1]
+    rng = np.random.default_rng(n)
+    a, b, x0 = cross._inputs(rng, shape, "BND", "signed")
+    stream = torch.cuda.current_stream()
+    want = cross._run(gpu, a, b, x0, "BND", (), False)
+    assert hb.heinsen_check(stream) == hb.HEINSEN_OK
+    try:
+        hb.heinsen_test_carry(2000, drop, 0, stream)  # a few milliseconds of polling, then give up
+        print(f"[lost] {shape}: tile {drop} does not publish", flush=True)
+        got = cross._run(gpu, a, b, x0, "BND", (), False)
+    finally:
+        hb.heinsen_test_carry(0, 0xFFFFFFFF, 0, stream)
+    assert hb.heinsen_check(stream) == hb.HEINSEN_ERR_CARRY_LOST
+    assert hb.heinsen_check(stream) == hb.HEINSEN_OK
+    chunk, col = divmod(drop, B)  # a column is an item
+    first = (chunk + 1) * steps
+    assert np.array_equal(got[col, :first].view(np.uint32), want[col, :first].view(np.uint32))
+    assert np.isnan(got[col, first:]).all()
+    assert np.array_equal(got[1 - col].view(np.uint32), want[1 - col].view(np.uint32))
+    again = cross._run(gpu, a, b, x0, "BND", (), False)
+    assert np.array_equal(again.view(np.uint32), want.view(np.uint32))
 
 
 # Items of fewer than 32 channels, whose runs are dealt out through LDS: one wave's worth of steps more than the short

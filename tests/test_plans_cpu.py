@@ -99,3 +99,18 @@ def test_runs_that_cut_lines_are_written_through_up_to_96_mb(rules):
     mb = 1 << 20
     assert rules([f"runs_in_lines(true, 250, 994 * 17, {m * mb})" for m in (49, 96, 97, 120)]) == [1, 1, 0, 0]
     assert rules([f"runs_in_lines({o}, {b}, {e}, {200 * mb})" for o, b, e in (("true", 9, 4096 * 16), ("true", 1, 4097 * 13), ("false", 9, 4096 * 16), ("false", 1, 4096))]) == [1, 1, 0, 0]
+
+
+def test_tall_tiles_are_for_few_columns_and_few_rounds(rules):
+    # columns, tiles of 512 steps per column
+    assert rules([f"tall_tiles({c}, {k})" for c, k in ((1, 128), (1, 129), (1, 768), (1, 769), (3, 256), (3, 257), (15, 8), (15, 51), (15, 52))]) == [0, 1, 1, 0, 1, 0, 0, 1, 0]
+    assert rules([f"tall_tiles({c}, {k})" for c, k in ((16, 8), (16, 9), (16, 32), (16, 33), (24, 21), (24, 22), (25, 10), (25, 11), (32, 8), (33, 7))]) == [0, 1, 1, 0, 1, 0, 1, 0, 1, 0]
+
+
+# B, n, D, flags -> steps of a tile
+@pytest.mark.parametrize("B,n,D,flags,steps", [
+    (2, 131072, 96, 0, 512), (2, 131072, 96, hb.HEINSEN_LINEAR, 256), (2, 131072, 96, CLOG, 256), (1, 512 * 128, 64, 0, 256), (1, 512 * 129, 64, 0, 512),
+    (16, 8192, 64, LOGS, 512), (16, 16384 + 1, 64, LOGS, 256), (40, 512 * 45, 5, 0, 512),
+])
+def test_steps_of_a_tile(B, n, D, flags, steps):
+    assert hb.heinsen_tile_shape(B, D, n, BND, flags)[1] == steps
