@@ -1151,7 +1151,7 @@ BndPlan make_plan(const ScanCall &c, bool allow_wide = true, bool want_tree = fa
     const bool tiles8 = pl.cg == 1 && pl.NW == 8 && pl.T == 32 && c.n > 4 * pl.NW * pl.T;
     pl.tree = tiles8 && (pl.ncols < kTreeBelow || want_tree);
     if (pl.tree) pl.G = kTreeGroup;
-    if (tiles8 && !c.linear && tall_tiles(pl.ncols, ceil_div(c.n, (int64_t)kTallWaves * pl.T))) {
+    if (tiles8 && !c.linear && tall_tiles(pl.ncols, ceil_div(c.n, (int64_t)kTallWaves * pl.T), c.D, pl.runs, c.bf16, kQueues)) {
         pl.tree = true;
         pl.NW = pl.G = kTallWaves;
     }

@@ -61,13 +61,32 @@ constexpr int ticket_queues(int most, int64_t columns, bool wide)
 // states handed on without a chain, which is what the smaller ones wait for; but a compute unit has nothing to load while its one
 // workgroup waits.  So from half a round of the chip (below, a tile's own latency counts: 1 x 16384 x 64 12.6 us with eight waves,
 // 16.5 with sixteen) to three (eight and sixteen: one column of 131072 steps 35.8 and 24.7, of 262144 57.7 and 47.2, 4 x 65536 51.9 and
-// 45.6, 8 x 32768 51.4 and 44.7, 3 x 131072 70.9 and 67.6; four rounds, 4 x 131072, 90.0 and 91.2), and with more columns, whose tiles
-// wait less, to two and to one (16 x 8192 28.1 and 20.4, 24 x 8192 36.4 and 36.1, 32 x 4096 22.1 and 20.9; 24 x 16384 62.7 and
-// 68.1, 32 x 8192 43.1 and 45.8).
-constexpr bool tall_tiles(int64_t columns, int64_t chunks)
+// 45.6, 8 x 32768 51.4 and 44.7, 3 x 131072 70.9 and 67.6; four rounds, 4 x 131072, 90.0 and 91.2).  From 16 columns on a
+// round counts the tiles as the queues deal them: 19 columns of 26 are 494, but one of the two queues has 260 for the
+// 256 places of two turns (302 x 12838 x 3 41.9 and 52.0; 50 columns of five, 13 in a queue, 23.0 and 28.1).
+// One round: up to 32 columns always (16 x 8192 x 64 28.1 and 20.4, 32 x 4096 22.1 and 20.9), more as soon as a column is long enough
+// for its carries to cost something (36 columns of seven 20.3 and 18.5, 42 of four 16.7 and 15.9, 48 of three 13.7 and 17.5; where
+// lines are cut 34 of seven 23.5 and 21.0, 37 of four 18.1 and 19.4, bf16 37 of five 16.2 and 16.9; runs 39 of five 20.9 and 19.7, 41
+// of four 15.7 and 17.5, bf16 37 of five 18.0 and 18.9).  Two rounds: up to 24 columns (24 x 8192 x 64 36.4 and 36.1; as runs 24 of
+// 20 44.2 and 45.1), and more only where the memory is not what they wait for.  Columns that cut lines, from one and a half rounds on:
+// 6 x 3001 x 770 43.8 and 41.5, 4 x 7691 x 508 50.8 and 43.8, bf16 2 x 3840 x 1945 40.1 and 34.7 (78 of four 27.2 and 29.5, bf16
+// 72 of six 30.5 and 31.7).  Runs of up to 32 columns, if they nearly fill both: 512 x 8192 x 4 47.6 and 42.9, 128 x 8192 x 16 46.0 and
+// 41.9 (more columns gain less and lose: 432 x 4608 x 8 45.3 and 42.5, 45 of nine 36.2 and 36.4, 60 of seven 37.5 and 39.4, bf16 949 x
+// 3888 x 4 30.0 and 31.9; 64 of eight, 256 x 4096 x 16, 45.3 and 41.0, keep the tile that is promised for them).  Whole lines lose: 32 x 8192 x 64 43.1 and 45.8,
+// 6 x 3072 x 768 35.9 and 38.8.  Items of two channels, whose runs take the longest, gain below 16 columns alone (448 x 9179
+// x 2 44.1 and 38.3, 960 x 4059 34.6 and 37.5, 768 x 10203 58.4 and 78.8).
+constexpr bool tall_tiles(int64_t columns, int64_t chunks, int64_t channels, bool runs, bool bf16, int most_queues)
 {
     const int64_t tiles = columns * chunks, places = 256;
-    return tiles > places / 2 && (columns < 16 ? tiles <= 3 * places : columns <= 24 ? tiles <= 2 * places : columns <= 32 && tiles <= places);
+    if (tiles <= places / 2) return false;
+    if (columns < 16) return tiles <= 3 * places;
+    if (channels == 2) return false;
+    const int64_t queues = ticket_queues(most_queues, columns, false), dealt = (columns + queues - 1) / queues * queues * chunks;
+    const bool cut_lines = !runs && channels % 32 != 0;
+    if (dealt <= places) return columns <= 32 || (runs || cut_lines ? !bf16 && chunks >= 5 : chunks >= 4);
+    if (dealt > 2 * places) return false;
+    if (columns <= (runs ? 16 : 24)) return true;
+    return cut_lines ? chunks >= (bf16 ? 7 : 6) && 2 * tiles > 3 * places : runs && !bf16 && columns <= 32 && 5 * tiles > 9 * places;
 }
 
 // [B, n, D], output in whole lines.  It goes through the L2 at once unless the tiles wait for states that would queue with

@@ -42,17 +42,21 @@ def test_columns_and_carry_levels(gpu, mode, bf16):
 
 # Few columns of tall tiles (sixteen waves, 512 steps; two carry levels of sixteen): just enough tiles, the last one a step long or
 # missing one, a group and one tile more, a super-group (256 tiles) and one tile more, whole items in their lanes and as runs,
-# columns of channels of two items, the most columns.
+# columns of channels of two items, the most columns of
+# few.  One round of more columns; two rounds of columns that cut lines, and as runs.
 @pytest.mark.parametrize("mode", ["signed", "log_logout", "positive"])
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("shape", [
     (1, 512 * 128 + 1, 64), (1, 512 * 129 - 1, 64), (8, 512 * 17, 64), (8, 512 * 16 + 33, 64), (1, 512 * 256 + 1, 70), (1, 512 * 257, 33),
     (3, 512 * 90 + 31, 96), (16, 512 * 16 + 5, 64), (24, 512 * 21, 64), (32, 512 * 8, 64), (5, 512 * 130 + 7, 32), (40, 512 * 45 + 3, 5), (9, 512 * 70 + 1, 30),
+    (3, 512 * 6 - 5, 769), (16, 512 * 4, 256), (4, 512 * 5 - 511, 768), (5, 512 * 9 - 31, 611), (124, 512 * 15 + 1, 16), (154, 512 * 5 - 9, 16),
 ])
 def test_tall_tiles(gpu, mode, bf16, shape):
     torch, hb = gpu
     B, n, D = shape
-    assert hb.heinsen_tile_shape(B, D, n, hb.HEINSEN_LAYOUT_BND, hb.flags_from_names(cross.MODES[mode]))[1] == 512
+    flags = hb.flags_from_names(cross.MODES[mode]) | (hb.HEINSEN_IN_BF16 if bf16 else 0)
+    tall = n > 512 * 14 or (D % 32 == 0 or n > 512 * 8) or not bf16  # one round of bf16 that cuts lines keeps the small ones
+    assert hb.heinsen_tile_shape(B, D, n, hb.HEINSEN_LAYOUT_BND, flags)[1] == (512 if tall and not (bf16 and B == 124) else 256)
     rng = np.random.default_rng(sum(shape) + int(bf16))
     a, b, x0 = cross._inputs(rng, shape, "BND", mode)
     if bf16:  # the bf16-rounded values are what is stored: they define the problem

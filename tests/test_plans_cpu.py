@@ -102,15 +102,32 @@ def test_runs_that_cut_lines_are_written_through_up_to_96_mb(rules):
 
 
 def test_tall_tiles_are_for_few_columns_and_few_rounds(rules):
-    # columns, tiles of 512 steps per column
-    assert rules([f"tall_tiles({c}, {k})" for c, k in ((1, 128), (1, 129), (1, 768), (1, 769), (3, 256), (3, 257), (15, 8), (15, 51), (15, 52))]) == [0, 1, 1, 0, 1, 0, 0, 1, 0]
-    assert rules([f"tall_tiles({c}, {k})" for c, k in ((16, 8), (16, 9), (16, 32), (16, 33), (24, 21), (24, 22), (25, 10), (25, 11), (32, 8), (33, 7))]) == [0, 1, 1, 0, 1, 0, 1, 0, 1, 0]
+    def tall(pairs, channels=64, runs="false", bf16="false"):  # columns, tiles of 512 steps per column
+        return rules([f"tall_tiles({c}, {k}, {channels}, {runs}, {bf16}, 8)" for c, k in pairs])
+
+    few = ((1, 128), (1, 129), (1, 768), (1, 769), (3, 256), (3, 257), (15, 8), (15, 51), (15, 52))
+    assert tall(few) == tall(few, 2, "true", "true") == [0, 1, 1, 0, 1, 0, 0, 1, 0]
+    assert tall(((16, 8), (16, 9), (16, 32), (16, 33), (24, 21), (24, 22), (25, 10), (32, 8), (32, 9))) == [0, 1, 1, 0, 1, 0, 0, 1, 0]
+    assert tall(((16, 32), (19, 12), (19, 26), (24, 21), (32, 8)), 3, "true") == [1, 1, 0, 1, 1]
+    assert tall(((16, 32), (17, 15), (32, 8)), 2, "true") == [0] * 3
+    # one round of the chip, as the queues deal the columns (33 to 63 columns in four, from 64 in eight)
+    one = ((44, 5), (48, 5), (49, 5), (64, 4), (65, 4), (85, 3))
+    assert tall(one) == tall(one, bf16="true") == [1, 1, 0, 1, 0, 0]
+    assert tall(one, 65) == tall(one, 16, "true") == [1, 1, 0, 0, 0, 0]
+    assert tall(one, 65, bf16="true") == tall(one, 16, "true", "true") == [0] * 6
+    # two rounds
+    two = ((64, 8), (72, 7), (65, 7), (48, 9), (48, 8), (80, 6), (85, 5), (56, 9), (57, 9), (32, 16), (32, 12))
+    assert tall(two) == tall(two, 16, "true", "true") == [0] * len(two)
+    assert tall(two, 65) == [1, 1, 1, 1, 0, 1, 0, 1, 0, 1, 0]
+    assert tall(two, 65, bf16="true") == [1, 1, 1, 1, 0, 0, 0, 1, 0, 1, 0]
+    assert tall(two, 16, "true") == [0, 0, 0, 0, 0, 0, 0, 0, 0, 1, 0]
 
 
 # B, n, D, flags -> steps of a tile
 @pytest.mark.parametrize("B,n,D,flags,steps", [
     (2, 131072, 96, 0, 512), (2, 131072, 96, hb.HEINSEN_LINEAR, 256), (2, 131072, 96, CLOG, 256), (1, 512 * 128, 64, 0, 256), (1, 512 * 129, 64, 0, 512),
     (16, 8192, 64, LOGS, 512), (16, 16384 + 1, 64, LOGS, 256), (40, 512 * 45, 5, 0, 512),
+    (6, 3001, 770, 0, 512), (6, 3001, 768, 0, 256), (4, 1996, 896, 0, 512), (64, 4096, 64, 0, 256), (128, 8192, 16, 0, 512), (128, 8192, 16, hb.HEINSEN_LINEAR, 256),
 ])
 def test_steps_of_a_tile(B, n, D, flags, steps):
     assert hb.heinsen_tile_shape(B, D, n, BND, flags)[1] == steps
