@@ -185,12 +185,12 @@ __device__ __forceinline__ void store_run(float *out, uint32_t at, u32x4 v)
 }
 
 // Slots of 16 bytes per wave: an item's run is T * D / 4 of them in float32, and up to 15 between items keep the lanes,
-// which pick up step k of their channels all at once, on different banks (run_pitch).  TREE, which needs much of the
-// LDS itself, and groups of eight tiles, whose records leave fewer registers, deal the runs out in two halves.  (Registers
-// are short there all the same: the kernels of groups of eight keep up to 15 of float32 and 6 of bf16 in scratch, with two
-// carry levels 4 and 2.  Pieces and runs: 20 x 4000 x 31 18.1 and 16.3 us, 24 x 3000 x 20 16.1 and 15.0, 2 x 1500000 x 30 382 and 354.)
+// which pick up step k of their channels all at once, on different banks (run_pitch); halves of runs have a slot more per item
+// of two channels: without it their 32 items begin on four banks, and 355 x 5248 x 2 takes 34.7 us instead of 17.6, 256 x 32731
+// x 2 80.8 instead of 63.1.  TREE, which needs much of the LDS itself and whose records leave fewer registers, deals the runs out in two
+// halves.  (Pieces and runs: 20 x 4000 x 31 18.1 and 16.3 us, 24 x 3000 x 20 16.1 and 15.0, 2 x 1500000 x 30 382 and 354.)
 constexpr int run_rounds(int G) { return G > 4 ? 2 : 1; }
-constexpr int run_slots(int rounds) { return 544 / rounds; }
+constexpr int run_slots(int rounds) { return rounds == 1 ? 544 : 288; }
 
 constexpr int kTreeBlock = 4; // TREE: summaries that one wave adds up for the others (see bnd_tile)
 
@@ -1151,7 +1151,7 @@ BndPlan make_plan(const ScanCall &c, bool allow_wide = true, bool want_tree = fa
     const bool tiles8 = pl.cg == 1 && pl.NW == 8 && pl.T == 32 && c.n > 4 * pl.NW * pl.T;
     pl.tree = tiles8 && (pl.ncols < kTreeBelow || want_tree);
     if (pl.tree) pl.G = kTreeGroup;
-    if (tiles8 && !c.linear && tall_tiles(pl.ncols, ceil_div(c.n, (int64_t)kTallWaves * pl.T), c.D, pl.runs, c.bf16, kQueues)) {
+    if (tiles8 && !c.linear && tall_tiles(pl.ncols, ceil_div(c.n, (int64_t)pl.NW * pl.T), c.D, pl.runs, c.bf16, kQueues)) {
         pl.tree = true;
         pl.NW = pl.G = kTallWaves;
     }

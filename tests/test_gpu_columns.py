@@ -49,7 +49,7 @@ def test_columns_and_carry_levels(gpu, mode, bf16):
 @pytest.mark.parametrize("shape", [
     (1, 512 * 128 + 1, 64), (1, 512 * 129 - 1, 64), (8, 512 * 17, 64), (8, 512 * 16 + 33, 64), (1, 512 * 256 + 1, 70), (1, 512 * 257, 33),
     (3, 512 * 90 + 31, 96), (16, 512 * 16 + 5, 64), (24, 512 * 21, 64), (32, 512 * 8, 64), (5, 512 * 130 + 7, 32), (40, 512 * 45 + 3, 5), (9, 512 * 70 + 1, 30),
-    (3, 512 * 6 - 5, 769), (16, 512 * 4, 256), (4, 512 * 5 - 511, 768), (5, 512 * 9 - 31, 611), (124, 512 * 15 + 1, 16), (154, 512 * 5 - 9, 16),
+    (3, 512 * 6 - 5, 769), (16, 512 * 4, 256), (4, 512 * 5 - 511, 768), (5, 512 * 9 - 31, 611), (124, 512 * 15 + 1, 16), (154, 512 * 5 - 9, 16), (60, 512 * 65 + 7, 2), (611, 512 * 10 - 2, 2),
 ])
 def test_tall_tiles(gpu, mode, bf16, shape):
     torch, hb = gpu

@@ -102,14 +102,15 @@ def test_runs_that_cut_lines_are_written_through_up_to_96_mb(rules):
 
 
 def test_tall_tiles_are_for_few_columns_and_few_rounds(rules):
-    def tall(pairs, channels=64, runs="false", bf16="false"):  # columns, tiles of 512 steps per column
-        return rules([f"tall_tiles({c}, {k}, {channels}, {runs}, {bf16}, 8)" for c, k in pairs])
+    def tall(pairs, channels=64, runs="false", bf16="false", steps=512):  # columns, tiles of 512 steps per column (or one of 256 fewer)
+        return rules([f"tall_tiles({c}, {2 * k - (steps < 512)}, {channels}, {runs}, {bf16}, 8)" for c, k in pairs])
 
     few = ((1, 128), (1, 129), (1, 768), (1, 769), (3, 256), (3, 257), (15, 8), (15, 51), (15, 52))
-    assert tall(few) == tall(few, 2, "true", "true") == [0, 1, 1, 0, 1, 0, 0, 1, 0]
+    assert tall(few) == tall(few, 2, "true", "true") == tall(few, steps=256) == [0, 1, 1, 0, 1, 0, 0, 1, 0]
     assert tall(((16, 8), (16, 9), (16, 32), (16, 33), (24, 21), (24, 22), (25, 10), (32, 8), (32, 9))) == [0, 1, 1, 0, 1, 0, 0, 1, 0]
-    assert tall(((16, 32), (19, 12), (19, 26), (24, 21), (32, 8)), 3, "true") == [1, 1, 0, 1, 1]
-    assert tall(((16, 32), (17, 15), (32, 8)), 2, "true") == [0] * 3
+    assert tall(((16, 32), (19, 12), (19, 26), (24, 20), (24, 21), (32, 8)), 3, "true") == [1, 1, 0, 0, 1, 1]
+    assert tall(((28, 5), (29, 5), (16, 9)), steps=256) == [0, 1, 1]  # more than 256 tiles of 256 steps
+    assert tall(((16, 32), (17, 10), (20, 9), (32, 8), (17, 16)), 2, "true") == [0, 0, 1, 1, 0]
     # one round of the chip, as the queues deal the columns (33 to 63 columns in four, from 64 in eight)
     one = ((44, 5), (48, 5), (49, 5), (64, 4), (65, 4), (85, 3))
     assert tall(one) == tall(one, bf16="true") == [1, 1, 0, 1, 0, 0]
