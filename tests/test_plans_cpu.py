@@ -109,6 +109,7 @@ def test_tall_tiles_are_for_few_columns_and_few_rounds(rules):
     assert tall(few) == tall(few, 2, "true", "true") == tall(few, steps=256) == [0, 1, 1, 0, 1, 0, 0, 1, 0]
     assert tall(((16, 8), (16, 9), (16, 32), (16, 33), (24, 21), (24, 22), (25, 10), (32, 8), (32, 9))) == [0, 1, 1, 0, 1, 0, 0, 1, 0]
     assert tall(((16, 32), (19, 12), (19, 26), (24, 20), (24, 21), (32, 8)), 3, "true") == [1, 1, 0, 0, 1, 1]
+    assert tall(((16, 30), (16, 31), (17, 28)), 3, "true", "true") == [0, 1, 0]
     assert tall(((28, 5), (29, 5), (16, 9)), steps=256) == [0, 1, 1]  # more than 256 tiles of 256 steps
     assert tall(((16, 32), (17, 10), (20, 9), (32, 8), (17, 16)), 2, "true") == [0, 0, 1, 1, 0]
     # one round of the chip, as the queues deal the columns (33 to 63 columns in four, from 64 in eight)
