@@ -404,6 +404,16 @@ __device__ __forceinline__ Seg row16_inclusive_scan(Seg g)
     return g;
 }
 
+// Inclusive scan over lanes 0 to 7 (3 steps), of whatever they hold.
+template <int DOM>
+__device__ __forceinline__ Seg eighth_inclusive_scan(Seg g)
+{
+    g = seg_combine<DOM>(seg_dpp<0x111, 0xf, DOM>(g), g);
+    g = seg_combine<DOM>(seg_dpp<0x112, 0xf, DOM>(g), g);
+    g = seg_combine<DOM>(seg_dpp<0x114, 0xf, DOM>(g), g);
+    return g;
+}
+
 // Inclusive scan inside each half of the wave (5 steps): lanes 31 and 63 end up with the fold of lanes
 // 0..31 and 32..63, in lane order.
 template <int DOM>

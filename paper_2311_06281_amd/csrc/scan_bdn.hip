@@ -1191,6 +1191,11 @@ __device__ __forceinline__ void tiles_tile(const TileParams &p, const uint32_t t
     uint64_t have = 0;
     if (MULTI && w == 0) have = fetch_records();
 
+    // x_0 as well: a memory latency of its own where it is asked for when it is used.  (Rows of one tile ask then: without the
+    // first wave's hand-over, which keeps the workgroups that share a compute unit in step, they gain and lose: 1024 rows of 16384
+    // logarithms 41.1 and 38.4 us, but 512 signed ones 18.1 and 19.9, 800 rows of 10000 25.0 and 22.6, of 6000 12.4 and 13.6.)
+    float x0 = MULTI ? p.x0[p.x0_stride ? row : 0] : 0.0f;
+
     // global <-> lane traffic of each wave goes through its own LDS region (coalesced both ways)
     u32x4 *const region = stage + w * tile_stage_slots<VECIO, ITEMS, inputs_in_lds<DOM, LOG_OUT, MULTI, ITEMS>()>();
     const int64_t wstart = (int64_t)c * kTile + (int64_t)w * (64 * ITEMS); // first element of this wave's window
@@ -1210,7 +1215,7 @@ __device__ __forceinline__ void tiles_tile(const TileParams &p, const uint32_t t
         if (VECIO) clog_stage_span<InT, ITEMS>(arow - h + wstart, brow - h + wstart, sp, region, lane);
         else clog_stage_elems<InT, ITEMS>(arow + wstart, brow + wstart, p.n - wstart, region, lane);
         const OwnQuads<ITEMS> own{region + lane * (ITEMS / 2 + 1)};
-        const float x0 = p.x0[p.x0_stride ? row : 0];
+        x0 = p.x0[p.x0_stride ? row : 0];
         Lin g;
         int up;
         const bool in_range = wave_all(lin_summary<ITEMS>(own, g, up));
@@ -1301,27 +1306,30 @@ __device__ __forceinline__ void tiles_tile(const TileParams &p, const uint32_t t
     // summary of the waves before this one, and (wave 0) of the whole tile, in wave order
     Seg wave_excl = seg_identity<DOM>();
     Seg total = seg_identity<DOM>();
-    auto fold = [&](int j) {
-        Seg g2;
-        g2.A = lds_A[j];
-        g2.M = lds_M[j];
-        g2.sA = SIGNED ? (lds_S[j] << 31) : 0u;
-        g2.sM = SIGNED ? (lds_S[j] << 30) : 0u;
-        total = (j == 0) ? g2 : seg_combine<DOM>(total, g2);
-        if (j + 1 == w) wave_excl = total;
+    auto summary = [&](int j) {
+        return Seg{lds_A[j], lds_M[j], SIGNED ? (lds_S[j] << 31) : 0u, SIGNED ? (lds_S[j] << 30) : 0u};
     };
-    if (MULTI || nw == NW) { // all asked for at once
-#pragma unroll
-        for (int j = 0; j < NW; ++j) fold(j);
+    if (MULTI || nw == NW) {
+        // Eight lanes side by side: three combinations one after the other instead of seven, which every wave that waits for this tile
+        // waited for too.  One row of 300 steps to 2^26: 2^18 7.4 and 7.15 us, 2^20 9.4 and 9.2, 2^23 25.4 and 25.0, 2^26 148.8 and 148.4;
+        // signed 100000 steps 7.8 and 7.3, 300 rows of 4096 6.7 and 6.3, bf16 logarithms 33 10^6 steps 72.0 and 69.7.
+        const Seg part = eighth_inclusive_scan<DOM>(summary(lane & (NW - 1)));
+        if (w > 0) wave_excl = seg_readlane<DOM>(part, w - 1);
+        if (MULTI && w == 0) total = seg_readlane<DOM>(part, NW - 1);
     } else { // rows of one tile: nobody needs the last wave's
-        for (int j = 0; j + 1 < nw; ++j) fold(j);
+        for (int j = 0; j + 1 < nw; ++j) {
+            total = j == 0 ? summary(0) : seg_combine<DOM>(total, summary(j));
+            if (j + 1 == w) wave_excl = total;
+        }
     }
 
+    const Seg before = MULTI && w == 0 ? lane_excl : seg_combine<DOM>(wave_excl, lane_excl); // the lane's part of the tile
     if (w == 0) {
         State64 st;
         {
             float lx;
-            encode<DOM, LOG_IN>(p.x0[p.x0_stride ? row : 0], lx, st.s);
+            if (!MULTI) x0 = p.x0[p.x0_stride ? row : 0];
+            encode<DOM, LOG_IN>(x0, lx, st.s);
             st.lx = (double)lx;
         }
         p.tl.mark(tile, 3);
@@ -1393,7 +1401,7 @@ __device__ __forceinline__ void tiles_tile(const TileParams &p, const uint32_t t
     State st;
     st.lx = lds_startL;
     st.s = lds_startS;
-    st = seg_apply<DOM>(st, seg_combine<DOM>(wave_excl, lane_excl));
+    st = seg_apply<DOM>(st, before);
     if (VECIO)
         wave_emit_span<DOM, LOG_OUT, ITEMS>(orow + OW * (wstart - h), sp, region, lane, st, Av, Mv, sw, sm);
     else

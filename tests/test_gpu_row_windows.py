@@ -160,3 +160,15 @@ def test_complex_rows_on_up_to_sixteen_waves(gpu, n, offset, bf16):
     assert np.all(err[:3] <= 2.0 ** -23 * (1.0 + np.abs(ref[:3])))
     size = max(1.0, float(np.max(np.abs(ref[3]))) / np.log(2.0))
     assert np.max(err[3]) <= 5 * np.sqrt(n) * size * 2.0 ** -24 * np.log(2.0) + 2e-6
+
+
+# Rows of one tile on all eight waves (8, 16 and 32 steps per lane; a last wave with few steps, with one, with none), of several
+# half tiles, and so many rows that the tiles are whole ones: every wave begins with what the waves before it add up to.
+@pytest.mark.parametrize("mode", ["signed", "log_logout", "positive", "signed_clog"])
+@pytest.mark.parametrize("rows,n", [(2, 4096), (3, 3585), (1, 3583), (2, 8192), (1, 7169), (2, 16384), (1, 14337), (513, 12289), (2, 8192 * 2 + 1), (1, 8192 * 35), (140, 16400)])
+def test_sums_of_the_waves_of_a_tile(gpu, mode, rows, n):
+    rng = np.random.default_rng(rows + n)
+    a, b, x0 = cross._inputs(rng, (1, rows, n), "BDN", mode)
+    print(f"[waves] {mode} rows={rows} n={n}", flush=True)
+    got = cross._run(gpu, a, b, x0, "BDN", cross.MODES[mode], False, offset_elems=0)
+    cross._check(got, a, b, x0, "BDN", mode)
