@@ -28,6 +28,7 @@
 #include "scan_rules.hpp"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace hs {
 namespace {
@@ -121,14 +122,18 @@ __device__ __forceinline__ void unpack_signs(uint32_t s, Seg &g)
 // then the flag; the consumer polls the flag, then reads the data.  LDS operations of one wave are carried
 // out in order, so only the compiler has to be kept from moving them.
 // (The flags are pointed to as what they are, words of LDS: through generic pointers they became flat accesses, each of which waits
-// for all that the wave has in flight, its record and output stores included.  4 x 500 x 100 10.3 us so, 9.4 now.)
+// for all that the wave has in flight, its record and output stores included.  4 x 500 x 100 10.3 us so, 9.4 now.  The wide
+// tiles, bound by memory and seldom waiting for each other, are a little faster with the flat ones (why was not found out) and keep generic
+// pointers: 16 x 16384 x 2048 1038.1 us, by LDS instructions 1043.0, 32 x 8192 x 2048 1075.8 and 1083.3.)
 typedef __attribute__((address_space(3))) volatile uint32_t lds_flag_t;
-__device__ __forceinline__ void lds_signal(lds_flag_t *flag)
+template <typename Flag>
+__device__ __forceinline__ void lds_signal(Flag *flag)
 {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     *flag = 1u;
 }
-__device__ __forceinline__ bool lds_ready(lds_flag_t *flag)
+template <typename Flag>
+__device__ __forceinline__ bool lds_ready(Flag *flag)
 {
     const bool ready = __builtin_amdgcn_readfirstlane((int)*flag) != 0;
     asm volatile("" ::: "memory");
@@ -146,7 +151,8 @@ __device__ __forceinline__ void lds_await_all(lds_flag_t *flags, int count)
 {
     while (!lds_ready_all(flags, count)) __builtin_amdgcn_s_sleep(1);
 }
-__device__ __forceinline__ void lds_await(lds_flag_t *flag)
+template <typename Flag>
+__device__ __forceinline__ void lds_await(Flag *flag)
 {
     while (!lds_ready(flag)) __builtin_amdgcn_s_sleep(1);
     asm volatile("" ::: "memory");
@@ -279,8 +285,9 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     // The rows the workgroup reads and writes are runs of 256*CG contiguous bytes, requested by its CG
     // columns at about the same time, which is what the memory system wants to see.
     const int wc = w % CG, ts = w / CG;
-    lds_flag_t *flag_run = flags;              // [TS][CG]: the wave's summary is in LDS
-    lds_flag_t *flag_start = flags + TS * CG;  // [CG]: the column's start state is in LDS
+    using flag_t = std::conditional_t<CG == 1, lds_flag_t, volatile uint32_t>;
+    flag_t *flag_run = (flag_t *)flags;              // [TS][CG]: the wave's summary is in LDS
+    flag_t *flag_start = flag_run + TS * CG;  // [CG]: the column's start state is in LDS
     lds_flag_t *flag_part = flags + TS * CG + CG; // TREE: [2][TS]: the wave's summaries are in LDS,
     lds_flag_t *flag_sum = flag_part + 2 * G;     //   [2][NBL]: the sums of BL of them, [1]: the super-group's state, [NBL]: of BL waves, [1]: what lies between
 
