@@ -1309,18 +1309,31 @@ __device__ __forceinline__ void tiles_tile(const TileParams &p, const uint32_t t
     auto summary = [&](int j) {
         return Seg{lds_A[j], lds_M[j], SIGNED ? (lds_S[j] << 31) : 0u, SIGNED ? (lds_S[j] << 30) : 0u};
     };
+    auto fold = [&](int j) {
+        total = j == 0 ? summary(0) : seg_combine<DOM>(total, summary(j));
+        if (j + 1 == w) wave_excl = total;
+    };
     if (MULTI || nw == NW) {
+        static_assert(inputs_in_lds<DOM, LOG_OUT, MULTI, ITEMS>() || NW == 8, "eight lanes fold eight summaries");
         // Eight lanes side by side: three combinations one after the other instead of seven, which every wave that waits for this tile
         // waited for too.  One row of 300 steps to 2^26: 2^18 7.4 and 7.15 us, 2^20 9.4 and 9.2, 2^23 25.4 and 25.0, 2^26 148.8 and 148.4;
         // signed 100000 steps 7.8 and 7.3, 300 rows of 4096 6.7 and 6.3, bf16 logarithms 33 10^6 steps 72.0 and 69.7.
-        const Seg part = eighth_inclusive_scan<DOM>(summary(lane & (NW - 1)));
+        // That takes the waves in pairs, and lanes without a partner an empty one.  In wave order, as a sequence is evaluated, where the
+        // difference shows: a sum of logarithms that is +inf (one a_t = +inf) has no logarithm of zero added to it, and products,
+        // which two waves may take out of float32 where all that came before them is zero, are formed from the first wave on.
+        const Seg own = summary(lane & (NW - 1));
+        const Seg part = eighth_inclusive_scan<DOM>(own);
         if (w > 0) wave_excl = seg_readlane<DOM>(part, w - 1);
         if (MULTI && w == 0) total = seg_readlane<DOM>(part, NW - 1);
-    } else { // rows of one tile: nobody needs the last wave's
-        for (int j = 0; j + 1 < nw; ++j) {
-            total = j == 0 ? summary(0) : seg_combine<DOM>(total, summary(j));
-            if (j + 1 == w) wave_excl = total;
+        if (DOM == kLinear) { // all asked for at once
+#pragma unroll
+            for (int j = 0; j < NW; ++j) fold(j);
+        } else if (__builtin_expect(!wave_all(own.A < INFINITY), 0)) {
+#pragma unroll 1
+            for (int j = 0; j < NW; ++j) fold(j);
         }
+    } else { // rows of one tile: nobody needs the last wave's
+        for (int j = 0; j + 1 < nw; ++j) fold(j);
     }
 
     const Seg before = MULTI && w == 0 ? lane_excl : seg_combine<DOM>(wave_excl, lane_excl); // the lane's part of the tile

@@ -172,3 +172,23 @@ def test_sums_of_the_waves_of_a_tile(gpu, mode, rows, n):
     print(f"[waves] {mode} rows={rows} n={n}", flush=True)
     got = cross._run(gpu, a, b, x0, "BDN", cross.MODES[mode], False, offset_elems=0)
     cross._check(got, a, b, x0, "BDN", mode)
+
+
+# A wave whose sum of logarithms is +inf (its last a_t is), or whose product leaves float32 where that of half of its steps does
+# not: everything behind it is infinite, in the waves of its tile, which start from sums of waves, and in the tiles behind that one.
+# (Rows begin on 16 bytes, so that tiles do too.)
+@pytest.mark.parametrize("rows,n", [(2, 4096), (3, 3588), (2, 8192), (2, 16384), (1, 14337), (513, 14340), (2, 8192 * 2 + 4), (1, 8192 * 35), (140, 16400)])
+def test_behind_a_wave_that_leaves_float32_all_is_infinite(gpu, rows, n):
+    torch, hb = gpu
+    for mode in ("linear", "positive", "positive_logout", "signed"):
+        steps = hb.heinsen_tile_shape(1, rows, n, hb.HEINSEN_LAYOUT_BDN, hb.flags_from_names(cross.MODES[mode]))[1]
+        for wave in range(min(8, (n - 1) // (steps // 8))):
+            first, behind = wave * steps // 8, (wave + 1) * steps // 8
+            a, b = np.full((1, rows, n), 1.0 if mode == "linear" else 0.5, np.float32), np.full((1, rows, n), 0.5, np.float32)
+            if mode == "linear":
+                a[:, :, first:behind] = 2.0 ** (192 * 8 / steps)
+            else:
+                a[:, :, behind - 1] = np.inf
+            print(f"[to infinity] {mode} rows={rows} n={n} wave={wave}", flush=True)
+            got = cross._run(gpu, a, b, np.ones(rows, np.float32), "BDN", cross.MODES[mode], False)
+            assert np.all(got[:, :, behind:] == np.inf) and np.isfinite(got[:, :, :first]).all()
