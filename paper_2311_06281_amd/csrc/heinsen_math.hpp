@@ -168,6 +168,38 @@ __device__ __forceinline__ State64 seg_apply64(const State64 &x, const SEG &g)
     return r;
 }
 
+// Steps whose sum of logarithms is +inf or NaN (one a_t = +inf, or a NaN; linear domain: whose product leaves float32) have no
+// summary that is right for every state before them: 0 * inf is NaN, but whatever they add is added to it.  Their summary holds, in
+// place of what they contribute, the state behind them, and NaN in place of the sum: a state is replaced by it, and so is what a
+// summary before it contributes.  All other sums are finite or -inf, which add up in any order.
+template <int DOM>
+__device__ __forceinline__ bool seg_sums(float A)
+{
+    return (DOM == kLinear ? fabsf(A) : A) < INFINITY;
+}
+__device__ __forceinline__ Seg seg_of_state(const State64 &x)
+{
+    return Seg{__builtin_nanf(""), (float)x.lx, 0u, x.s};
+}
+template <int DOM, typename SEG>
+__device__ __forceinline__ Seg64 carry_append64(const Seg64 &g1, const SEG &g2)
+{
+    Seg64 r = seg_append64<DOM>(g1, g2); // A: NaN + or * anything is NaN
+    const bool state = g2.A != g2.A;
+    r.M = state ? (double)g2.M : r.M;
+    r.sM = state ? g2.sM : r.sM;
+    return r;
+}
+template <int DOM, typename SEG>
+__device__ __forceinline__ State64 carry_apply64(const State64 &x, const SEG &g)
+{
+    State64 r = seg_apply64<DOM>(x, g);
+    const bool state = g.A != g.A;
+    r.lx = state ? (double)g.M : r.lx;
+    r.s = state ? g.sM : r.s;
+    return r;
+}
+
 // ---- element encode / decode ---------------------------------------------------------------------
 
 __device__ __forceinline__ float widen(float v) { return v; }

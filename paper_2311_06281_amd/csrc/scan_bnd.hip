@@ -235,7 +235,8 @@ __device__ __forceinline__ void wave_lds_order()
 // No wave waits for more than it needs.  The first wave along time of each 64-channel column fetches the
 // carry records, forms the state at the start of the tile and hands it to the waves behind it through
 // LDS; a later wave waits only for the summaries of the waves before it in its own column; the last wave
-// along time publishes the tile's summary (and, closing a group, the state for the next group).  `flags`
+// along time publishes the tile's summary (and, closing a group, the state for the next group).  TREE: where some a_t is +inf or
+// NaN, or a product leaves float32, it first waits for the state at the start of the tile (see carry_append64).  `flags`
 // are words of LDS, as many as the kernel says, zero when the tile begins.
 template <int DOM, bool LOG_IN, bool LOG_OUT, typename InT, int T, int NW, int G, bool SB, bool DENSE, bool TREE, bool RUNS, int CG, int MEM>
 __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile, const uint32_t epoch, lds_flag_t *flags)
@@ -552,6 +553,8 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     //      time closes the tile: its fold with its own summary is the tile's -------------------------------
     Seg pre = seg_identity<DOM>(), total = seg_identity<DOM>();
     const bool closing = TS > 1 && ts == TS - 1; // wave-uniform
+    bool apart = false; // TREE: waves before this one have, in some channel, no summary for every state (see carry_append64),
+    bool late = false;  // closing wave: nor has the tile
     auto mine = [&]() -> Seg { // TREE: read back, registers are full
         if constexpr (!TREE) return run;
         Seg h;
@@ -561,21 +564,39 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
         if (SIGNED) unpack_signs(lds_S[ts][c], h);
         return h;
     };
+    auto get_run = [&](int j) -> Seg {
+        if (!TREE) lds_await(&flag_run[j * CG + wc]);
+        Seg h;
+        h.A = lds_A[j][c];
+        h.M = lds_M[j][c];
+        h.sA = h.sM = 0u;
+        if (SIGNED) unpack_signs(lds_S[j][c], h);
+        return h;
+    };
+    auto put_tile = [&]() { // closing wave
+        if (r < G - 1 && tile != p.drop_tile) {
+            rec_t *tp = p.agg + (size_t)tile * (2 * CH) + c;
+            seg_put<DOM>(tp, tp + CH, total, epoch);
+        }
+    };
+    auto keep_total = [&]() { // TREE: its slot among the waves' summaries is free
+        lds_A[TS - 1][c] = total.A;
+        lds_M[TS - 1][c] = total.M;
+        if (SIGNED) lds_S[TS - 1][c] = pack_signs(total);
+    };
     if (!first) {
-        auto get_run = [&](int j) -> Seg {
-            if (!TREE) lds_await(&flag_run[j * CG + wc]);
-            Seg h;
-            h.A = lds_A[j][c];
-            h.M = lds_M[j][c];
-            h.sA = h.sM = 0u;
-            if (SIGNED) unpack_signs(lds_S[j][c], h);
-            return h;
-        };
-        if constexpr (TREE) { // the waves before it in its block, which the block's last wave passes on, and the blocks before that
+        if constexpr (TREE && DOM == kLinear) {
+            // one after the other: products of waves that have nothing before them may leave float32 where those from the first on do not
+            lds_await_all(flag_run, ts);
+            pre = get_run(0);
+#pragma unroll 1
+            for (int j = 1; j < ts; ++j) pre = seg_combine<DOM>(pre, get_run(j));
+        } else if constexpr (TREE) { // the waves before it in its block, which the block's last wave passes on, and the blocks before that
             const int b0 = ts / BL;
             lds_await_all(&flag_run[b0 * BL], ts - b0 * BL);
+            if (ts > b0 * BL) pre = get_run(b0 * BL);
 #pragma unroll 1
-            for (int j = b0 * BL; j < ts; ++j) pre = seg_combine<DOM>(pre, get_run(j));
+            for (int j = b0 * BL + 1; j < ts; ++j) pre = seg_combine<DOM>(pre, get_run(j));
             if (ts % BL == BL - 1 && !closing) {
                 const Seg sum = seg_combine<DOM>(pre, mine());
                 lds_wavesA[b0][c] = sum.A;
@@ -583,18 +604,21 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
                 if (SIGNED) lds_wavesS[b0][c] = pack_signs(sum);
                 lds_signal(&flag_sum[2 * NBL + 1 + b0]);
             }
-            Seg before = seg_identity<DOM>();
-            lds_await_all(&flag_sum[2 * NBL + 1], b0);
-#pragma unroll 1
-            for (int j = 0; j < b0; ++j) {
+            auto get_waves = [&](int j) -> Seg {
                 Seg h;
                 h.A = lds_wavesA[j][c];
                 h.M = lds_wavesM[j][c];
                 h.sA = h.sM = 0u;
                 if (SIGNED) unpack_signs(lds_wavesS[j][c], h);
-                before = seg_combine<DOM>(before, h);
+                return h;
+            };
+            if (b0 > 0) {
+                lds_await_all(&flag_sum[2 * NBL + 1], b0);
+                Seg before = get_waves(0);
+#pragma unroll 1
+                for (int j = 1; j < b0; ++j) before = seg_combine<DOM>(before, get_waves(j));
+                pre = ts > b0 * BL ? seg_combine<DOM>(before, pre) : before;
             }
-            pre = seg_combine<DOM>(before, pre);
         } else {
 #pragma unroll
             for (int j = 0; j < TS - 1; ++j)
@@ -602,20 +626,15 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
         }
         if (closing && more) {
             total = seg_combine<DOM>(pre, mine());
-            if (r < G - 1 && tile != p.drop_tile) {
-                rec_t *tp = p.agg + (size_t)tile * (2 * CH) + c;
-                seg_put<DOM>(tp, tp + CH, total, epoch);
-            }
+            late = TREE && !wave_all(seg_sums<DOM>(total.A));
+            if (!late) put_tile();
         }
         if constexpr (TREE) {
+            apart = !wave_all(seg_sums<DOM>(pre.A));
             lds_preA[ts][c] = pre.A;
             lds_preM[ts][c] = pre.M;
             if (SIGNED) lds_preS[ts][c] = pack_signs(pre);
-            if (closing) { // its slot among the waves' summaries is free
-                lds_A[TS - 1][c] = total.A;
-                lds_M[TS - 1][c] = total.M;
-                if (SIGNED) lds_S[TS - 1][c] = pack_signs(total);
-            }
+            if (closing && !late) keep_total();
             asm volatile("" ::: "memory");
         }
     }
@@ -627,6 +646,18 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
         g2.sA = g2.sM = 0u;
         if (SIGNED) unpack_signs(lds_S[TS - 1][cv], g2);
         return g2;
+    };
+
+    auto get_pre = [&]() -> Seg {
+        if constexpr (!TREE) return pre;
+        Seg h{lds_preA[TREE ? ts : 0][c], lds_preM[TREE ? ts : 0][c], 0u, 0u};
+        if (SIGNED) unpack_signs(lds_preS[TREE ? ts : 0][c], h);
+        return h;
+    };
+    auto state_behind = [&](State64 x, int waves) -> State64 { // so many waves of the tile, one after the other
+#pragma unroll 1
+        for (int j = 0; j < waves; ++j) x = seg_apply64<DOM>(x, get_run(j));
+        return x;
     };
 
     State st;                // state at the wave's first step
@@ -671,6 +702,15 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
         const int gi_sums = SUM_GROUPS ? gi / BL : 0; // blocks of groups
         bool tile_sum = !(sums && bl + BL <= r), group_sum = !(sums && SUM_GROUPS && bl + BL <= gi);
         bool owes = closing && more && r == G - 1 && gi < G - 1; // the last tile of a group owes the later groups its sum
+        auto put_group = [&]() {
+            Seg64 sum = get64(lds_sumA[0][0], lds_sumM[0][0], lds_sumS[0][0]);
+#pragma unroll 1
+            for (int j = 1; j < NBL - 1; ++j) sum = carry_append64<DOM>(sum, get64(lds_sumA[0][j], lds_sumM[0][j], lds_sumS[0][j]));
+#pragma unroll 1
+            for (int j = G - BL; j < G - 1; ++j) sum = carry_append64<DOM>(sum, get_tile(j));
+            seg64_put<DOM>(p.agg + (size_t)tile * (2 * CH) + cv, p.state + ((size_t)g * p.ncols + col) * (2 * CH) + cv, CH,
+                           carry_append64<DOM>(sum, get_total()), epoch);
+        };
         uint32_t polls = 0;
         for (;;) {
             asm volatile("" : "+v"(cv));
@@ -684,7 +724,7 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
                 tile_sum = true;
                 Seg64 sum = seg64(get_tile(bl));
 #pragma unroll 1
-                for (int j = bl + 1; j < bl + BL; ++j) sum = seg_append64<DOM>(sum, get_tile(j));
+                for (int j = bl + 1; j < bl + BL; ++j) sum = carry_append64<DOM>(sum, get_tile(j));
                 put64(lds_sumA[0][bl / BL], lds_sumM[0][bl / BL], lds_sumS[0][bl / BL], sum);
                 lds_signal(&flag_sum[bl / BL]);
             }
@@ -692,21 +732,15 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
                 group_sum = true;
                 Seg64 sum = get64(lds_groupA[bl], lds_groupM[bl], lds_groupS[bl]);
 #pragma unroll 1
-                for (int j = bl + 1; j < bl + BL; ++j) sum = seg_append64<DOM>(sum, get64(lds_groupA[j], lds_groupM[j], lds_groupS[j]));
+                for (int j = bl + 1; j < bl + BL; ++j) sum = carry_append64<DOM>(sum, get64(lds_groupA[j], lds_groupM[j], lds_groupS[j]));
                 put64(lds_sumA[1][bl / BL], lds_sumM[1][bl / BL], lds_sumS[1][bl / BL], sum);
                 lds_signal(&flag_sum[NBL + bl / BL]);
             }
-            if (owes && lds_ready_all(flag_sum, NBL - 1) && lds_ready_all(&flag_part[G - BL], BL - 1)) {
+            if (owes && !late && lds_ready_all(flag_sum, NBL - 1) && lds_ready_all(&flag_part[G - BL], BL - 1)) {
                 owes = false;
-                Seg64 sum = get64(lds_sumA[0][0], lds_sumM[0][0], lds_sumS[0][0]);
-#pragma unroll 1
-                for (int j = 1; j < NBL - 1; ++j) sum = seg_append64<DOM>(sum, get64(lds_sumA[0][j], lds_sumM[0][j], lds_sumS[0][j]));
-#pragma unroll 1
-                for (int j = G - BL; j < G - 1; ++j) sum = seg_append64<DOM>(sum, get_tile(j));
-                seg64_put<DOM>(p.agg + (size_t)tile * (2 * CH) + cv, p.state + ((size_t)g * p.ncols + col) * (2 * CH) + cv, CH,
-                               seg_append64<DOM>(sum, get_total()), epoch);
+                put_group();
             }
-            if (!want_tile && !want_group && !want_state && tile_sum && group_sum && !owes) break;
+            if (!want_tile && !want_group && !want_state && tile_sum && group_sum && (!owes || late)) break;
             __builtin_amdgcn_s_sleep(1);
         }
         p.tl.mark(tile, 4);
@@ -738,7 +772,7 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
         // the state (one column of 400000 steps 89.7 and 75.9 us, of 1048576 206 and 168).
         if (SUM_GROUPS && ts == 1 && q > 0) {
             Seg64 sum{0.0, -INFINITY, 0u, 0u};
-            rest([&](const auto &part) { sum = seg_append64<DOM>(sum, part); });
+            rest([&](const auto &part) { sum = carry_append64<DOM>(sum, part); });
             put64(lds_restA, lds_restM, lds_restS, sum);
             lds_signal(flag_rest);
         }
@@ -747,15 +781,28 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
             else st64 = State64{lds_superL[c], lds_superS[c]};
             if (SUM_GROUPS && q > 0) {
                 lds_await(flag_rest);
-                st64 = seg_apply64<DOM>(st64, get64(lds_restA, lds_restM, lds_restS));
+                st64 = carry_apply64<DOM>(st64, get64(lds_restA, lds_restM, lds_restS));
             } else {
-                rest([&](const auto &part) { st64 = seg_apply64<DOM>(st64, part); });
+                rest([&](const auto &part) { st64 = carry_apply64<DOM>(st64, part); });
             }
             st.lx = (float)st64.lx;
             st.s = st64.s;
             lds_startL[c] = st64.lx;
             lds_startS[c] = st64.s;
             lds_signal(&flag_start[wc]);
+        }
+        if (late) {
+            lds_await(&flag_start[wc]);
+            const Seg sum = seg_combine<DOM>(get_pre(), get_run(TS - 1)), end = seg_of_state(state_behind(State64{lds_startL[c], lds_startS[c]}, TS));
+            const bool sums = seg_sums<DOM>(sum.A);
+            total = Seg{sums ? sum.A : end.A, sums ? sum.M : end.M, sums ? sum.sA : end.sA, sums ? sum.sM : end.sM};
+            keep_total();
+            if (owes) {
+                lds_await_all(flag_sum, NBL - 1);
+                lds_await_all(&flag_part[G - BL], BL - 1);
+                put_group();
+            }
+            put_tile();
         }
     } else if (first) {
         // ---- obtain the state at the start of the tile ------------------------------------------
@@ -816,15 +863,20 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
         if (closing && more && r == G - 1 && (!TREE || gi == G - 1)) {
             // last tile of a group (TREE: of a super-group): the state after this tile starts the next one
             rec_t *sp = (TREE ? p.agg + (size_t)tile * (2 * CH) : p.state + ((size_t)(q + 1) * p.ncols + col) * (2 * CH)) + c;
-            state64_put(sp, sp + CH, seg_apply64<DOM>(st64, get_total()), epoch, SIGNED);
+            state64_put(sp, sp + CH, TREE ? carry_apply64<DOM>(st64, get_total()) : seg_apply64<DOM>(st64, get_total()), epoch, SIGNED);
         }
         if constexpr (TREE) {
-            pre.A = lds_preA[ts][c];
-            pre.M = lds_preM[ts][c];
-            pre.sA = pre.sM = 0u;
-            if (SIGNED) unpack_signs(lds_preS[ts][c], pre);
+            pre = get_pre();
+            st = seg_apply<DOM>(st, pre);
+            if (__builtin_expect(apart, 0)) {
+                const State64 x = state_behind(st64, ts);
+                const bool sums = seg_sums<DOM>(pre.A);
+                st.lx = sums ? st.lx : (float)x.lx;
+                st.s = sums ? st.s : x.s;
+            }
+        } else {
+            st = seg_apply<DOM>(st, pre);
         }
-        st = seg_apply<DOM>(st, pre);
     }
 
     p.tl.mark(tile, 5);

@@ -98,6 +98,51 @@ def test_lost_summary_of_two_levels(gpu, shape, drop):
     assert np.array_equal(again.view(np.uint32), want.view(np.uint32))
 
 
+# Two carry levels, eight waves and tall tiles: behind one a_t = +inf every step of its channel is infinite, in the waves of its
+# tile, the tiles of its group and the groups behind, from x_0 = 0 and with a restart (a_t = 0) before it as well.  Each is in 32
+# steps (a lane's) of its own, with 32 steps at least before the infinite one.
+@pytest.mark.parametrize("mode", ["signed", "positive", "positive_logout", "log_logout"])
+@pytest.mark.parametrize("shape,steps", [((1, 1537, 64), 256), ((1, 256 * 18 + 5, 70), 256), ((9, 3000, 8), 256), ((12, 4096, 64), 256), ((2, 256 * 67, 64), 256),
+                                         ((1, 512 * 130 + 9, 48), 512), ((1, 512 * 259, 64), 512), ((8, 512 * 18 + 3, 64), 512), ((40, 3000, 64), 512)])
+def test_behind_an_infinite_coefficient_all_is_infinite(gpu, mode, shape, steps):
+    torch, hb = gpu
+    B, n, D = shape
+    assert hb.heinsen_tile_shape(B, D, n, hb.HEINSEN_LAYOUT_BND, hb.flags_from_names(cross.MODES[mode]))[1] == steps
+    rng = np.random.default_rng(sum(shape))
+    a, b = rng.uniform(0.4, 1.0, shape).astype(np.float32), rng.uniform(0.1, 1.0, shape).astype(np.float32)
+    x0 = np.where(rng.random(B * D) < 0.5, 0.0, 1.0).astype(np.float32)
+    at = rng.integers(32, n, (B, D))
+    at[0, :8] = 32 + np.arange(8) * (steps // 8)  # every wave of the first tile
+    restart = at // 32 * 32 - rng.integers(1, 2000, (B, D))
+    t = np.arange(n)[None, :, None]
+    a[t == restart[:, None]] = 0.0
+    a[t == at[:, None]] = np.inf
+    with np.errstate(divide="ignore"):
+        stored = [np.log(v) for v in (a, b, x0)] if mode == "log_logout" else (a, b, x0)
+    print(f"[to infinity] {mode} shape={shape}", flush=True)
+    got = cross._run(gpu, *stored, "BND", cross.MODES[mode], False)
+    assert np.array_equal(got == np.inf, np.broadcast_to(t >= at[:, None], shape)) and not np.isnan(got).any()
+
+
+# The same by growth, without logarithms: products of a few waves leave float32, and are zero in the tiles before that.
+@pytest.mark.parametrize("shape", [(1, 1537, 64), (1, 256 * 18 + 5, 70), (9, 3000, 8), (12, 4096, 64), (2, 256 * 67, 64)])
+def test_growth_without_logarithms_ends_in_infinity(gpu, shape):
+    B, n, D = shape
+    x0 = np.ones(B * D, np.float32)
+    t = np.arange(n)[None, :, None]
+    for grow in (2.1, 3.0, 5.0):
+        for begin in (0, 40, 300, 700, 1300):
+            a = np.broadcast_to(np.where(t < begin, 0.5, grow), shape).astype(np.float32)
+            b = np.full(shape, 0.5, np.float32)
+            print(f"[growth] shape={shape} {grow} from {begin} on", flush=True)
+            got = cross._run(gpu, a, b, x0, "BND", cross.MODES["linear"], False)
+            with np.errstate(over="ignore"):
+                ref = oracle.sequential(a, b, x0, layout=oracle.LAYOUT_BND)
+            assert np.all(got[ref > 3.5e38] == np.inf)
+            small = ref < 1e37
+            assert np.all(np.abs(got[small] - ref[small]) <= 1e-5 * ref[small])
+
+
 # Items of fewer than 32 channels, whose runs are dealt out through LDS: one wave's worth of steps more than the short
 # kernels take, tiles that end in the middle of a wave and of a vector, runs that begin on any element (odd n * D), the
 # last column with fewer items than the others, one item alone, one more item than a column, both numbers of items per
