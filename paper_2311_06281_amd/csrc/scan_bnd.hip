@@ -121,10 +121,11 @@ __device__ __forceinline__ void unpack_signs(uint32_t s, Seg &g)
 // Hand-over between the waves of a workgroup through LDS without a barrier: the producer writes its data,
 // then the flag; the consumer polls the flag, then reads the data.  LDS operations of one wave are carried
 // out in order, so only the compiler has to be kept from moving them.
-// (The flags are pointed to as what they are, words of LDS: through generic pointers they became flat accesses, each of which waits
-// for all that the wave has in flight, its record and output stores included.  4 x 500 x 100 10.3 us so, 9.4 now.  The wide
-// tiles, bound by memory and seldom waiting for each other, are a little faster with the flat ones (why was not found out) and keep generic
-// pointers: 16 x 16384 x 2048 1038.1 us, by LDS instructions 1043.0, 32 x 8192 x 2048 1075.8 and 1083.3.)
+// (Some flags are pointed to as what they are, words of LDS; through generic pointers they are flat accesses, each of which waits
+// for all that the wave has in flight, its record and output stores included.  As words of LDS in tiles whose scan stands behind
+// each way to load (EARLY: 4 x 500 x 100 10.4 and 9.4 us), in those of two carry levels, and in runs of bf16 (719 x 3461 x 9 49.0 and 48.3).
+// The others are faster with the flat ones: bf16 4 x 2816 x 1066 31.8 (as words of LDS 32.4), 2 x 1949 x 1170 15.6 (15.9), runs
+// of float32 700 x 8102 x 2 41.0 (42.1), 852 x 1620 x 4 18.7 (19.0); wide tiles and shared lines come out even.)
 typedef __attribute__((address_space(3))) volatile uint32_t lds_flag_t;
 template <typename Flag>
 __device__ __forceinline__ void lds_signal(Flag *flag)
@@ -135,6 +136,7 @@ __device__ __forceinline__ void lds_signal(Flag *flag)
 template <typename Flag>
 __device__ __forceinline__ bool lds_ready(Flag *flag)
 {
+    if constexpr (!std::is_same_v<Flag, lds_flag_t>) return *flag != 0u; // no word of LDS
     const bool ready = __builtin_amdgcn_readfirstlane((int)*flag) != 0;
     asm volatile("" ::: "memory");
     return ready;
@@ -286,7 +288,7 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     // The rows the workgroup reads and writes are runs of 256*CG contiguous bytes, requested by its CG
     // columns at about the same time, which is what the memory system wants to see.
     const int wc = w % CG, ts = w / CG;
-    using flag_t = std::conditional_t<CG == 1, lds_flag_t, volatile uint32_t>;
+    using flag_t = std::conditional_t<EARLY || TREE || (RUNS && sizeof(InT) == 2), lds_flag_t, volatile uint32_t>;
     flag_t *flag_run = (flag_t *)flags;              // [TS][CG]: the wave's summary is in LDS
     flag_t *flag_start = flag_run + TS * CG;  // [CG]: the column's start state is in LDS
     lds_flag_t *flag_part = flags + TS * CG + CG; // TREE: [2][TS]: the wave's summaries are in LDS,
@@ -333,10 +335,10 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     //      published, and the records then arrive ahead of the tile's own loads at no cost in latency ---
     const bool first = ts == 0; // wave-uniform
     const bool fetches = TREE || first;
-    struct Recs {
-        rec_t A[PT], M[PT], Q[4], S, S2;
+    struct Recs { // (what is not asked for is not set)
+        rec_t A[PT], M[PT], Q[4] = {}, S = 0, S2 = 0;
     };
-    Recs recs = {};
+    Recs recs;
     const int q = TREE ? g / G : g;   // TREE: super-group, and the group's place in it
     const int gi = TREE ? g % G : 0;
     const bool has_state = first && q > 0;
@@ -380,13 +382,13 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     };
     auto state_in = [&](const Recs &R) -> bool { return !has_state || (rec_ok(R.S, epoch) && rec_ok(R.S2, epoch)); };
     auto records_in = [&](const Recs &R) -> bool { // one carry level: all of this lane's
-        bool ok = state_in(R);
+        bool ok = true;
         if constexpr (!TREE) {
 #pragma unroll
             for (int j = 0; j < G - 1; ++j)
                 if (j < r) ok = ok && tile_in(R, j);
         }
-        return ok;
+        return ok && state_in(R);
     };
     auto wave_all = [](bool ok) -> bool { return __builtin_amdgcn_ballot_w64(!ok) == 0ull; };
     bool have_records = false;
@@ -421,9 +423,8 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
         }
     };
 
-    // ---- load the lane's T inputs, encode and scan them serially; Av/Mv become the per-element records (see stash).  Every way
-    //      to load has the scan behind it: with one scan behind them all the compiler, which cannot tell there what is still on
-    //      its way, would have the first step wait for the last input -----------------------------------------------
+    // ---- load the lane's T inputs, encode and scan them serially; Av/Mv become the per-element records (see stash).  EARLY:
+    //      every way to load has the scan behind it; otherwise it stands behind them all -----------------------------
     float Av[T], Mv[T];
     uint32_t sw = 0u, sm = 0u;
     Seg run;
@@ -533,6 +534,7 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
         }
     }
     if (!EARLY) {
+        if (!TREE && first) have_records = wave_all(records_in(recs)); // first look: answered while the tile's loads were in flight
         pass_on(recs, false);
         scan();
     }
@@ -547,7 +549,7 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
         lds_signal(&flag_run[ts * CG + wc]);
     }
     p.tl.mark(tile, 3);
-    if (!TREE && first) have_records = wave_all(records_in(recs)); // first look: answered ahead of the tile's loads
+    if (EARLY && !TREE && first) have_records = wave_all(records_in(recs));
 
     // ---- a later wave: the fold of the waves before it in its column, in wave order; the last one along
     //      time closes the tile: its fold with its own summary is the tile's -------------------------------
@@ -715,7 +717,7 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
         for (;;) {
             asm volatile("" : "+v"(cv));
             if (want_tile || want_group || want_state) {
-                Recs again = {};
+                Recs again;
                 issue_records(again);
                 if (++polls > p.spin_limit) note_wait_gave_up(p.header); // go on as if everything were in, with NaN for what is missing
                 pass_on(again, polls > p.spin_limit);
