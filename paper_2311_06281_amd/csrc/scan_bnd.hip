@@ -201,6 +201,7 @@ constexpr int run_rounds(int G) { return G > 4 ? 2 : 1; }
 constexpr int run_slots(int rounds) { return rounds == 1 ? 544 : 288; }
 
 constexpr int kTreeBlock = 4; // TREE: summaries that one wave adds up for the others (see bnd_tile)
+constexpr int kHalfTile = 8;  // TREE: waves of a tile that are folded in float32
 
 // Which item and which vector of its run the wave's vector g is.
 struct RunAt {
@@ -228,7 +229,8 @@ __device__ __forceinline__ void wave_lds_order()
 // summary of its group, and states are handed on only from one super-group of G groups to the next.  A
 // tile then reads up to G - 1 tile summaries, G - 1 group summaries and one state; each of its waves fetches
 // one of each level beside its own loads and passes it on through LDS, the last wave of every four adds up theirs, and
-// the first wave folds the sums.  Whatever is folded beyond a tile is folded in float64, as the chain of states is: some
+// the first wave folds the sums.  Whatever is folded beyond eight waves (256 steps) is folded in float64, as the chain of states is:
+// beyond a tile, and the two halves of a tile of sixteen waves, whose summary is rounded to float32 once more then.  That is some
 // 200 cycles each, which one after the other were half of what a tile waited.  Registers are full of the tile itself, so nothing
 // of this stays in them: records are looked at as soon as they are there and go to LDS, and addresses in LDS are formed anew in
 // every round of polling (kept, they pushed elements into scratch memory, whose loads wait for every store before them).  Before
@@ -251,12 +253,14 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     // and 13.2).  Not for bf16 (8 x 8192 x 1536 151.0 and 152.1), whose loads are half as long, where lines are shared (8 x 8000 x
     // 1501, logarithms, 252.5 and 254.5), for the wide tiles (16 x 16384 x 2048 1039 and 1042) and for runs, which leave no registers.
     constexpr bool EARLY = sizeof(InT) == 4 && !RUNS && CG == 1 && MEM != kShared;
+    constexpr bool TALL = TREE && TS > kHalfTile;
     constexpr int PT = TREE ? 1 : (G > 1 ? G - 1 : 1); // tile summaries a wave fetches
     static_assert(T <= 32, "one sign word per channel");
     static_assert(NW % CG == 0, "the waves form a CG x TS grid");
     static_assert(!DENSE || CG == 1, "dense columns are mapped one channel per lane");
     static_assert(!RUNS || (DENSE && NW > 1 && !(SIGNED && LOG_OUT)), "runs are of columns of whole items");
     static_assert(!TREE || (CG == 1 && G == TS && TS % kTreeBlock == 0), "every wave of a tile takes one summary of each level");
+    static_assert(!TREE || TS == kHalfTile || TS == 2 * kHalfTile, "a tile is one half or two");
     __shared__ float lds_A[TS][CH];
     __shared__ float lds_M[TS][CH];
     __shared__ uint32_t lds_S[SIGNED ? TS : 1][CH];
@@ -276,9 +280,9 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     __shared__ uint32_t lds_superS[TREE ? CH : 1];
     __shared__ double lds_restA[TREE ? CH : 1], lds_restM[TREE ? CH : 1]; // everything between there and the tile
     __shared__ uint32_t lds_restS[TREE ? CH : 1];
-    // the folds of BL waves
-    __shared__ float lds_wavesA[NBL][CH], lds_wavesM[NBL][CH];
-    __shared__ uint32_t lds_wavesS[NBL][CH];
+    // the fold of the first half's waves
+    __shared__ float lds_halfA[TALL ? CH : 1], lds_halfM[TALL ? CH : 1];
+    __shared__ uint32_t lds_halfS[TALL ? CH : 1];
 
     constexpr int ROUNDS = run_rounds(G);
     __shared__ u32x4 lds_runs[RUNS ? NW : 1][RUNS ? run_slots(ROUNDS) : 1];
@@ -292,7 +296,7 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     flag_t *flag_run = (flag_t *)flags;              // [TS][CG]: the wave's summary is in LDS
     flag_t *flag_start = flag_run + TS * CG;  // [CG]: the column's start state is in LDS
     lds_flag_t *flag_part = flags + TS * CG + CG; // TREE: [2][TS]: the wave's summaries are in LDS,
-    lds_flag_t *flag_sum = flag_part + 2 * G;     //   [2][NBL]: the sums of BL of them, [1]: the super-group's state, [NBL]: of BL waves, [1]: what lies between
+    lds_flag_t *flag_sum = flag_part + 2 * G;     //   [2][NBL]: the sums of BL of them, [1]: the super-group's state, [1]: what lies between, [1]: the first half's fold
 
     const int chunk = (int)(tile / (uint32_t)p.ncols);
     const int col = (int)(tile % (uint32_t)p.ncols);
@@ -551,8 +555,10 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     p.tl.mark(tile, 3);
     if (EARLY && !TREE && first) have_records = wave_all(records_in(recs));
 
-    // ---- a later wave: the fold of the waves before it in its column, in wave order; the last one along
-    //      time closes the tile: its fold with its own summary is the tile's -------------------------------
+    // ---- a later wave: the fold of the waves before it in its column, in wave order (tall tiles: in its half); the last one along
+    //      time closes the tile: its fold with its own summary is the tile's.  (TREE: one wave after the other as well.  From sums of
+    //      four and a tall tile as one, the fold rounds more often: 2 x 131072 x 96, relative rms error over gates 7.51e-8 instead
+    //      of 7.49e-8, with decays within 1e-2 of one 1.076e-7 and 1.068e-7; the time is the same, 66.2 and 66.1 us.) ----
     Seg pre = seg_identity<DOM>(), total = seg_identity<DOM>();
     const bool closing = TS > 1 && ts == TS - 1; // wave-uniform
     bool apart = false; // TREE: waves before this one have, in some channel, no summary for every state (see carry_append64),
@@ -586,40 +592,31 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
         lds_M[TS - 1][c] = total.M;
         if (SIGNED) lds_S[TS - 1][c] = pack_signs(total);
     };
+    const bool second = TALL && ts >= kHalfTile; // wave-uniform: a wave of the second half
+    auto get_half = [&]() -> Seg {
+        Seg h{lds_halfA[TALL ? c : 0], lds_halfM[TALL ? c : 0], 0u, 0u};
+        if (SIGNED) unpack_signs(lds_halfS[TALL ? c : 0], h);
+        return h;
+    };
+    lds_flag_t *flag_half = &flag_sum[2 * NBL + 2];
+    auto tile_of = [&](const Seg &half) -> Seg { // closing wave: the tile's summary, of its last half
+        if constexpr (!TALL) return half;
+        const Seg64 sum = seg_append64<DOM>(seg64(get_half()), half);
+        return Seg{(float)sum.A, (float)sum.M, sum.sA, sum.sM};
+    };
     if (!first) {
-        if constexpr (TREE && DOM == kLinear) {
-            // one after the other: products of waves that have nothing before them may leave float32 where those from the first on do not
-            lds_await_all(flag_run, ts);
-            pre = get_run(0);
+        if constexpr (TREE) {
+            const int from = second ? kHalfTile : 0;
+            lds_await_all(&flag_run[from], ts - from);
+            if (ts > from) pre = get_run(from);
 #pragma unroll 1
-            for (int j = 1; j < ts; ++j) pre = seg_combine<DOM>(pre, get_run(j));
-        } else if constexpr (TREE) { // the waves before it in its block, which the block's last wave passes on, and the blocks before that
-            const int b0 = ts / BL;
-            lds_await_all(&flag_run[b0 * BL], ts - b0 * BL);
-            if (ts > b0 * BL) pre = get_run(b0 * BL);
-#pragma unroll 1
-            for (int j = b0 * BL + 1; j < ts; ++j) pre = seg_combine<DOM>(pre, get_run(j));
-            if (ts % BL == BL - 1 && !closing) {
-                const Seg sum = seg_combine<DOM>(pre, mine());
-                lds_wavesA[b0][c] = sum.A;
-                lds_wavesM[b0][c] = sum.M;
-                if (SIGNED) lds_wavesS[b0][c] = pack_signs(sum);
-                lds_signal(&flag_sum[2 * NBL + 1 + b0]);
-            }
-            auto get_waves = [&](int j) -> Seg {
-                Seg h;
-                h.A = lds_wavesA[j][c];
-                h.M = lds_wavesM[j][c];
-                h.sA = h.sM = 0u;
-                if (SIGNED) unpack_signs(lds_wavesS[j][c], h);
-                return h;
-            };
-            if (b0 > 0) {
-                lds_await_all(&flag_sum[2 * NBL + 1], b0);
-                Seg before = get_waves(0);
-#pragma unroll 1
-                for (int j = 1; j < b0; ++j) before = seg_combine<DOM>(before, get_waves(j));
-                pre = ts > b0 * BL ? seg_combine<DOM>(before, pre) : before;
+            for (int j = from + 1; j < ts; ++j) pre = seg_combine<DOM>(pre, get_run(j));
+            if (TALL && ts == kHalfTile - 1) {
+                const Seg half = seg_combine<DOM>(pre, mine());
+                lds_halfA[c] = half.A;
+                lds_halfM[c] = half.M;
+                if (SIGNED) lds_halfS[c] = pack_signs(half);
+                lds_signal(flag_half);
             }
         } else {
 #pragma unroll
@@ -627,7 +624,9 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
                 if (j < ts) pre = (j == 0) ? get_run(j) : seg_combine<DOM>(pre, get_run(j));
         }
         if (closing && more) {
-            total = seg_combine<DOM>(pre, mine());
+            const Seg half = seg_combine<DOM>(pre, mine());
+            if (TALL) lds_await(flag_half);
+            total = tile_of(half);
             late = TREE && !wave_all(seg_sums<DOM>(total.A));
             if (!late) put_tile();
         }
@@ -769,7 +768,7 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
                 take(get_tile(j));
             }
         };
-        lds_flag_t *flag_rest = &flag_sum[2 * NBL + 1 + NBL];
+        lds_flag_t *flag_rest = &flag_sum[2 * NBL + 1];
         // Behind the first super-group the second wave adds it all up: a link of the chain of states is one step then, however late
         // the state (one column of 400000 steps 89.7 and 75.9 us, of 1048576 206 and 168).
         if (SUM_GROUPS && ts == 1 && q > 0) {
@@ -795,7 +794,7 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
         }
         if (late) {
             lds_await(&flag_start[wc]);
-            const Seg sum = seg_combine<DOM>(get_pre(), get_run(TS - 1)), end = seg_of_state(state_behind(State64{lds_startL[c], lds_startS[c]}, TS));
+            const Seg sum = tile_of(seg_combine<DOM>(get_pre(), get_run(TS - 1))), end = seg_of_state(state_behind(State64{lds_startL[c], lds_startS[c]}, TS));
             const bool sums = seg_sums<DOM>(sum.A);
             total = Seg{sums ? sum.A : end.A, sums ? sum.M : end.M, sums ? sum.sA : end.sA, sums ? sum.sM : end.sM};
             keep_total();
@@ -868,11 +867,21 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
             state64_put(sp, sp + CH, TREE ? carry_apply64<DOM>(st64, get_total()) : seg_apply64<DOM>(st64, get_total()), epoch, SIGNED);
         }
         if constexpr (TREE) {
+            bool sums = true;
+            if (second) {
+                lds_await(flag_half);
+                const Seg half = get_half();
+                sums = seg_sums<DOM>(half.A);
+                apart = apart || !wave_all(sums);
+                const State64 mid = seg_apply64<DOM>(st64, half);
+                st.lx = (float)mid.lx;
+                st.s = mid.s;
+            }
             pre = get_pre();
-            st = seg_apply<DOM>(st, pre);
+            if (!TALL || ts != kHalfTile) st = seg_apply<DOM>(st, pre);
             if (__builtin_expect(apart, 0)) {
                 const State64 x = state_behind(st64, ts);
-                const bool sums = seg_sums<DOM>(pre.A);
+                sums = sums && seg_sums<DOM>(pre.A);
                 st.lx = sums ? st.lx : (float)x.lx;
                 st.s = sums ? st.s : x.s;
             }
@@ -955,7 +964,7 @@ template <int DOM, bool LOG_IN, bool LOG_OUT, typename InT, int T, int NW, int G
 __global__ __launch_bounds__(NW * 64, MINW) void heinsen_scan_bnd(BndParams p)
 {
     __shared__ uint32_t s_tile, s_epoch, s_flag;
-    constexpr int NFLAGS = NW + CG + (TREE ? 2 * G + 3 * G / kTreeBlock + 2 : 0);
+    constexpr int NFLAGS = NW + CG + (TREE ? 2 * G + 2 * G / kTreeBlock + 3 : 0);
     __shared__ uint32_t s_flags[NFLAGS];
     const unsigned long long t_begin = p.tl.stamps != nullptr ? wall_clock64() : 0ull;
     uint32_t tile, epoch = 0u;

@@ -288,6 +288,54 @@ def test_summaries_of_many_tiles_keep_float64(gpu, columns):
     assert rms <= 1.25e-7, rms
 
 
+# The same where eight waves keep the sequence in 84 tiles, and in tall tiles, with 44 of them behind the first super-group.
+@pytest.mark.parametrize("shape,steps", [((1, 256 * 84, 192), 256), ((1, 512 * 300 + 17, 64), 512), ((2, 512 * 300 + 17, 64), 512)])
+def test_states_behind_a_super_group_keep_float64(gpu, shape, steps):
+    torch, hb = gpu
+    B, n, D = shape
+    flags = hb.flags_from_names(cross.MODES["log_logout"])
+    assert hb.heinsen_tile_shape(B, D, n, hb.HEINSEN_LAYOUT_BND, flags)[1] == steps
+    rng = np.random.default_rng(1)
+    a = np.exp(-1e-4 * rng.uniform(0.5, 1.5, shape)).astype(np.float32)
+    b = ((1 - a.astype(np.float64)) * rng.uniform(0.9, 1.1, shape)).astype(np.float32)
+    a, b, x0 = np.log(a), np.log(b), np.zeros(B * D, np.float32)
+    print(f"[float64] shape={shape}", flush=True)
+    got = cross._run(gpu, a, b, x0, "BND", cross.MODES["log_logout"], False)
+    behind = slice(64 * 256 if steps == 256 else 256 * 512, None)
+    err = got[:, behind].astype(np.float64) - oracle.sequential_log(a, b, x0, layout=oracle.LAYOUT_BND)[:, behind]
+    rms = float(np.sqrt(np.mean(err * err)))
+    print(f"[float64] shape={shape} rms {rms:.3g}", flush=True)
+    assert rms <= 1.25e-7, rms
+
+
+# Tall tiles, the second half of a tile: logarithms, no input.  Of every three tiles the first adds a small number e to log x, the second
+# takes a large one off and the third adds the large one again in its first half, in the same float32.  What its second half starts
+# from is the sum of the e.  Formed in float32, from a state at its start of about -1000, it would have few bits of e (2^-14 in the
+# base-2 logarithm, 4e-5).  Bound: e is rounded when it is converted to base 2, by at most 0.1 * 2^-23 each of up to 100
+# times (1.2e-6), and the sum, below 4, three times on its way out (7e-7).
+@pytest.mark.parametrize("shape", [(1, 512 * 300 + 17, 64), (8, 512 * 18, 64), (40, 512 * 45 + 3, 5)])
+def test_second_halves_of_tall_tiles_start_from_float64(gpu, shape):
+    torch, hb = gpu
+    B, n, D = shape
+    flags = hb.flags_from_names(cross.MODES["log_logout"])
+    assert hb.heinsen_tile_shape(B, D, n, hb.HEINSEN_LAYOUT_BND, flags)[1] == 512
+    rng = np.random.default_rng(n)
+    times = n // 1536
+    e, large = rng.uniform(-0.1, 0.1, (B, times, D)).astype(np.float32), rng.uniform(900, 1000, (B, times, D)).astype(np.float32)
+    a, b, x0 = np.zeros(shape, np.float32), np.full(shape, -np.inf, np.float32), np.zeros(B * D, np.float32)
+    at = np.arange(times)[None, :, None] * 1536 + rng.integers(0, 256, (3, B, times, D))
+    i, j = np.arange(B)[:, None, None], np.arange(D)[None, None, :]
+    a[i, at[0], j] = e
+    a[i, at[1] + 512, j] = -large
+    a[i, at[2] + 1024, j] = large
+    print(f"[halves] shape={shape}", flush=True)
+    got = cross._run(gpu, a, b, x0, "BND", cross.MODES["log_logout"], False)
+    last = got[:, :times * 1536].reshape(B, times, 1536, D)[:, :, 1280:].astype(np.float64)  # the second halves of the third tiles
+    want = np.cumsum(e.astype(np.float64), axis=1)[:, :, None]
+    assert np.abs(want).max() < 4
+    assert np.abs(last - want).max() <= 2e-6
+
+
 # a few steps: four channels per thread and one, the ends of a workgroup, the last length of the kernel and the next
 @pytest.mark.parametrize("mode", ["signed", "positive"])
 @pytest.mark.parametrize("bf16", [False, True])
