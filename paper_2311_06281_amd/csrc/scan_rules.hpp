@@ -62,14 +62,16 @@ constexpr int ticket_queues(int most, int64_t columns, bool wide)
 // nothing to load while its one workgroup waits.  So from half a round of the chip (below, a tile's own latency counts: 1 x
 // 16384 x 64 12.6 us with eight waves, 16.5 with sixteen) to three (eight and sixteen: one column of 131072 steps 35.8 and
 // 24.7, of 262144 57.7 and 47.2, 4 x 65536 51.9 and 45.6, 8 x 32768 51.4 and 44.7, 3 x 131072 70.9 and 67.6; four rounds, 4
-// x 131072, 90.0 and 91.2).  From 16 columns on a round counts the tiles as the queues deal them: 19 columns of 26 are 494,
+// x 131072, 90.0 and 91.2).  Runs in six to eight columns of few tiles, which are short enough not to wait for a chain of states,
+// want more of a round (eight columns of 17 18.2 and 19.6, float32 19.6 and 20.4, of 20 20.1 and 21.1, six of 23 18.6 and 19.4; six of 28 20.8
+// and 19.8, eight of 26 21.9 and 20.7; bf16 logarithms but for the one).  From 16 columns on a round counts the tiles as the queues deal them: 19 columns of 26 are 494,
 // but one of the two queues has 260 for the 256 places of two turns (302 x 12838 x 3 41.9 and 52.0; 50 columns of five, 13
 // in a queue, 23.0 and 28.1). One round: up to 32 columns always (16 x 8192 x 64 28.1 and 20.4, 32 x 4096 22.1 and 20.9),
 // more as soon as a column is long enough for its carries to cost something (36 columns of seven 20.3 and 18.5, 42 of four
 // 16.7 and 15.9, 48 of three 13.7 and 17.5; where lines are cut 34 of seven 23.5 and 21.0, 37 of four 18.1 and 19.4, bf16
 // 37 of five 16.2 and 16.9; runs 39 of five 20.9 and 19.7, 41 of four 15.7 and 17.5, bf16 37 of five 18.0 and 18.9).  Two
 // rounds: up to 24 columns (24 x 8192 x 64 36.4 and 36.1), and more only where the memory is not what they wait for.
-// Columns that cut lines, from one and a half rounds on: 6 x 3001 x 770 43.8 and 41.5, 4 x 7691 x 508 50.8 and 43.8, bf16 2
+// Columns that cut lines, from one and a half rounds on: 6 x 3001 x 770 47.8 and 43.5, 4 x 7691 x 508 50.8 and 43.8, bf16 2
 // x 3840 x 1945 40.1 and 34.7 (78 of four 27.2 and 29.5, bf16 72 of six 30.5 and 31.7).  Runs of up to 32 columns, bf16 16,
 // if they nearly fill both: 512 x 8192 x 4 47.6 and 42.9, 128 x 8192 x 16 46.0 and 41.9, bf16 256 x 15835 x 3 44.4 and 38.5
 // (24 of 20, 384 x 10203 x 3, 44.9 and 46.6, bf16 192 x 10203 x 5 35.0 and 37.3; more columns gain less and lose: 432 x
@@ -81,7 +83,7 @@ constexpr int ticket_queues(int most, int64_t columns, bool wide)
 constexpr bool tall_tiles(int64_t columns, int64_t chunks_of_256, int64_t channels, bool runs, bool bf16, int most_queues)
 {
     const int64_t chunks = (chunks_of_256 + 1) / 2, tiles = columns * chunks, places = 256;
-    if (columns < 16) return tiles > places / 2 && tiles <= 3 * places;
+    if (columns < 16) return tiles > places / 2 && tiles <= 3 * places && !(runs && columns <= 8 && chunks < 24);
     if (columns * chunks_of_256 <= places) return false;
     const int64_t queues = ticket_queues(most_queues, columns, false), dealt = (columns + queues - 1) / queues * queues * chunks;
     const bool cut_lines = !runs && channels % 32 != 0;

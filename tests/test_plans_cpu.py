@@ -133,3 +133,11 @@ def test_tall_tiles_are_for_few_columns_and_few_rounds(rules):
 ])
 def test_steps_of_a_tile(B, n, D, flags, steps):
     assert hb.heinsen_tile_shape(B, D, n, BND, flags)[1] == steps
+
+
+def test_few_short_runs_keep_tiles_of_eight_waves(rules):
+    # columns and tiles of 512 steps per column: as runs (float32, bf16) and not
+    sizes = ((8, 17), (8, 20), (7, 20), (6, 23), (8, 24), (6, 24), (5, 26), (4, 40), (9, 15), (12, 11), (15, 9))
+    for half in ("false", "true"):
+        assert rules([f"tall_tiles({c}, {2 * k}, 5, true, {half}, 8)" for c, k in sizes]) == [0] * 4 + [1] * 7
+        assert rules([f"tall_tiles({c}, {2 * k}, 64, false, {half}, 8)" for c, k in sizes]) == [1] * 11
