@@ -1316,7 +1316,7 @@ __device__ __forceinline__ void tiles_tile(const TileParams &p, const uint32_t t
     if (MULTI || nw == NW) {
         static_assert(inputs_in_lds<DOM, LOG_OUT, MULTI, ITEMS>() || NW == 8, "eight lanes fold eight summaries");
         // Eight lanes side by side: three combinations one after the other instead of seven, which every wave that waits for this tile
-        // waited for too.  One row of 300 steps to 2^26: 2^18 7.4 and 7.15 us, 2^20 9.4 and 9.2, 2^23 25.4 and 25.0, 2^26 148.8 and 148.4;
+        // waited for too.  One row of 300 steps to 2^26: 2^18 7.34 and 7.04 us, 2^20 9.36 and 9.08, 2^23 25.4 and 25.0, 2^26 148.6 and 147.4 (x_0 asked for early, above, included);
         // signed 100000 steps 7.8 and 7.3, 300 rows of 4096 6.7 and 6.3, bf16 logarithms 33 10^6 steps 72.0 and 69.7.
         // That takes the waves in pairs, and lanes without a partner an empty one.  In wave order, as a sequence is evaluated, where the
         // difference shows: a sum of logarithms that is +inf (one a_t = +inf) has no logarithm of zero added to it, and products,

@@ -1083,12 +1083,11 @@ struct BndPlan {
     size_t off_agg, off_state, records; // in records, relative to kRecordBase
 };
 
-// TREE: tiles per group and groups per super-group, and the number of columns below which it is used.
+// TREE, tiles of eight waves: tiles per group and groups per super-group, and the number of columns below which it is used.
 // Without it a link of the chain of group states takes 1.2-1.4 us and a group of four tiles is 786 KB per
 // column, 0.12 us of memory traffic: up to about 12 columns the chain is the slower of the two.  Measured with
-// and without: 3 columns of 131072 steps 75 and 176 us, 1 of 400000 109 and 479, 16 of 131072 283 and 279, 32 of
-// 32768 147 and 144 (the record loads).  Groups of 16 tiles instead of 8 cost registers (spills) and twice the
-// record loads: 106 us for the 3 columns.
+// and without, summaries folded one by one: 3 columns of 131072 steps 75 and 176 us (tall tiles, which they take, 66), 1 of 400000
+// 109 and 479 (in block sums 77), 16 of 131072 283 and 279, 32 of 32768 147 and 144 (the record loads).
 constexpr int kTreeGroup = 8;
 constexpr int kTreeBelow = 16;
 // Tall tiles (see tall_tiles): sixteen waves one after the other along time, and as many tiles per group and groups per

@@ -23,7 +23,7 @@ namespace hs {
 // 17000 137.2, 12 ns 138.0).
 //
 // That is for the tiles of which the chip holds kPacedTiles at a time, two workgroups per compute unit: real output moved
-// as vectors (114 to 128 registers).  Element by element (159 to 163 registers) and with complex output (178 to 208) a
+// as vectors (104 to 125 registers).  Element by element (149 to 161 registers) and with complex output (176 to 209) a
 // workgroup has its compute unit to itself; tickets 256 and up are then drawn in the middle of the launch, where a wait only
 // leaves the unit empty.  Without and with it: 200 rows of 40000 whose pointers are not alike 35.2 and 41.3 us, bf16 104.5
 // and 108.9, one row of 1.25 * 10^7 such steps 43.3 and 47.9; complex output, 200 x 40000, 46.2 and 50.5.
