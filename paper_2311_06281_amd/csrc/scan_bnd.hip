@@ -123,9 +123,10 @@ __device__ __forceinline__ void unpack_signs(uint32_t s, Seg &g)
 // out in order, so only the compiler has to be kept from moving them.
 // (Some flags are pointed to as what they are, words of LDS; through generic pointers they are flat accesses, each of which waits
 // for all that the wave has in flight, its record and output stores included.  As words of LDS in tiles whose scan stands behind
-// each way to load (EARLY: 4 x 500 x 100 10.4 and 9.4 us), in those of two carry levels, and in runs of bf16 (719 x 3461 x 9 49.0 and 48.3).
-// The others are faster with the flat ones: bf16 4 x 2816 x 1066 31.8 (as words of LDS 32.4), 2 x 1949 x 1170 15.6 (15.9), runs
-// of float32 700 x 8102 x 2 41.0 (42.1), 852 x 1620 x 4 18.7 (19.0); wide tiles and shared lines come out even.)
+// each way to load (EARLY: 4 x 500 x 100 10.4 and 9.4 us), in those of two carry levels, and for bf16 in runs (719 x 3461 x 9 49.0 and
+// 48.3) and whole lines (2 x 9728 x 1088 40.8 and 40.4, 32 x 8000 x 192 80.6 and 80.0, 16 x 1024 x 576 19.4 and 19.5).
+// The others are faster with the flat ones: bf16 that cuts lines 4 x 2816 x 1066 31.8 (as words of LDS 32.4), 2 x 1949 x 1170 15.6 (15.9),
+// runs of float32 700 x 8102 x 2 41.0 (42.1), 852 x 1620 x 4 18.7 (19.0); wide tiles and shared lines come out even.)
 typedef __attribute__((address_space(3))) volatile uint32_t lds_flag_t;
 template <typename Flag>
 __device__ __forceinline__ void lds_signal(Flag *flag)
@@ -292,7 +293,8 @@ __device__ __forceinline__ void bnd_tile(const BndParams &p, const uint32_t tile
     // The rows the workgroup reads and writes are runs of 256*CG contiguous bytes, requested by its CG
     // columns at about the same time, which is what the memory system wants to see.
     const int wc = w % CG, ts = w / CG;
-    using flag_t = std::conditional_t<EARLY || TREE || (RUNS && sizeof(InT) == 2), lds_flag_t, volatile uint32_t>;
+    constexpr bool HALVES = sizeof(InT) == 2 && CG == 1 && NW == 8 && (RUNS || MEM == kThrough || MEM == kStream); // runs, whole lines
+    using flag_t = std::conditional_t<EARLY || TREE || HALVES, lds_flag_t, volatile uint32_t>;
     flag_t *flag_run = (flag_t *)flags;              // [TS][CG]: the wave's summary is in LDS
     flag_t *flag_start = flag_run + TS * CG;  // [CG]: the column's start state is in LDS
     lds_flag_t *flag_part = flags + TS * CG + CG; // TREE: [2][TS]: the wave's summaries are in LDS,
